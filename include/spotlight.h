@@ -61,12 +61,13 @@ enum {
 
 /* Switches of a context, for spotlight_set_option. */
 enum {
-    /* 1 (default): a bulk spotlight_hash_keys call with bfloat16 weights evaluates the second hash
-     * layer on the matrix cores (same codes, see spotlight_hash_keys); 0: everything on the binary32
-     * fused-multiply-add chain. */
+    /* 1 (default): a bulk spotlight_hash_keys call (from 9, 17 or 32 rows per head on, by shape) runs on
+     * the matrix cores (same codes, see spotlight_hash_keys); 0: everything on the vector ALU's
+     * fused multiply-adds. */
     SPOTLIGHT_OPT_BULK_HASH_MATRIX_CORES = 0,
-    /* 1: the matrix-core bulk hash also evaluates EVERY output with the chain and records how far
-     * the two results are apart (spotlight_bulk_hash_audit_read).  Slow; for tests.  Default 0. */
+    /* 1: where the matrix-core bulk hash settles signs by a bound (bfloat16 weights), it also evaluates
+     * EVERY output with the chain and records how far the two results are apart
+     * (spotlight_bulk_hash_audit_read).  Slow; for tests.  Default 0. */
     SPOTLIGHT_OPT_BULK_HASH_AUDIT = 1,
     /* 1: spotlight_decode_step runs a short context (at most 65536 tokens, codes of at most 256
      * bits, at most 32 MB of codes in all) as ONE kernel launch, a workgroup per (batch, key-value
@@ -151,10 +152,11 @@ int spotlight_prepack_weights(spotlight_ctx *ctx, const spotlight_hash_weights *
  * prefill.  Eq. 5-6 (Eq. 4 if hidden == 0), then bit-packing: hash output c*W + j of a key lands
  * in word j, bit 31 - c (appendix "Bit-Packing CUDA Kernel").  sign(y) is the bit (y > 0).
  * The codes are those of IEEE binary32 arithmetic with one fused multiply-add chain per output
- * in increasing index order, so they do not depend on launch shape.  (With bfloat16 weights a
- * bulk call evaluates the second layer on the matrix cores and recomputes, with that chain, every
- * output whose sign the matrix-core result does not settle: same bits.
- * SPOTLIGHT_OPT_BULK_HASH_MATRIX_CORES = 0 keeps everything on the chain.)
+ * in increasing index order, so they do not depend on launch shape.  (A bulk call runs the chains on
+ * the binary32 matrix instructions, which are such chains; the last layer of bfloat16 weights goes
+ * through the bfloat16 instructions, and every output whose sign that result does not settle is
+ * recomputed with the chain: same bits.  SPOTLIGHT_OPT_BULK_HASH_MATRIX_CORES = 0 keeps everything
+ * on the vector ALU.)
  *
  *   K      [B, Hkv, Nmax, d]  kv_dtype   read rows t0 .. t0+n_new-1 of every head
  *   codes  [B, Hkv, Nmax, W]  uint32     those rows written, all others untouched
@@ -174,7 +176,8 @@ int spotlight_hash_keys(spotlight_ctx *ctx, const void *K, const spotlight_hash_
  *   wrong      outputs the bound did settle whose sign differs from the chain's; the method relies
  *              on this being 0
  *   max_ratio  largest |y_matrix - y_chain| / (||W2[j]|| ||h||) seen; the bound assumes it stays
- *              below eps = 1.01 (h (2^-24 + 1.01 2^-22) + 2^-17), returned in *eps
+ *              below eps = 1.01 (h (2^-24 + 1.01 2^-22) + 2^-17), returned in *eps (the linear
+ *              hash: R_j, x and d in place of W2[j], h and the hidden width)
  */
 int spotlight_bulk_hash_audit_read(spotlight_ctx *ctx, int64_t *outputs, int64_t *listed, int64_t *wrong,
                                    double *max_ratio, double *eps);

@@ -12,10 +12,15 @@
 // Phase 2: a wavefront owns two code words; lane l computes the hash output that belongs to bit
 //          (l & 31) of word 2p + (l >> 5), i.e. output (31 - (l & 31)) * W + word, so a wave-wide
 //          ballot of (y > 0) IS the pair of packed words.  No boolean tensor is ever stored.
+#include "hash_bulk.h"
 #include "hash_vec.h"
 
 namespace spotlight {
 using namespace hashdev;
+extern template int run_bulk_hash<float, float>(spotlight_ctx*, const HashArgs&, int, int);
+extern template int run_bulk_hash<float, bf16_raw>(spotlight_ctx*, const HashArgs&, int, int);
+extern template int run_bulk_hash<bf16_raw, float>(spotlight_ctx*, const HashArgs&, int, int);
+extern template int run_bulk_hash<bf16_raw, bf16_raw>(spotlight_ctx*, const HashArgs&, int, int);
 namespace {
 
 // TK consecutive floats from LDS (16-byte reads when TK is a multiple of 4)
@@ -145,303 +150,6 @@ __global__ __launch_bounds__(kThreads) void hash_kernel(HashArgs a)
     }
 }
 
-// ------------------------------------------------------------------------------------------
-// Bulk hashing with the second layer on the matrix cores.
-//
-// Phase 1 is the canonical binary32 chain above (the hidden activations feed a non-linear function,
-// so nothing but the defined arithmetic will do).  Phase 2, Y = H W2^T for a tile of 32 vectors, is
-// a dense contraction and runs as v_mfma_f32_32x32x16_bf16: W2 is bfloat16 as stored, and each
-// activation h is split on the fly into hi + lo (both bfloat16, |h - hi - lo| <= 2^-18 |h|), so
-// the products are exact and two accumulating MFMA passes give y to within
-//     |y_mfma - y_canonical| <= eps * sum_i |W2[j][i] h_i| <= eps * ||W2[j]|| * ||h||
-// with eps = 1.01 * (hidden * (2^-24 + 1.01 * 2^-22) + 2^-17):  hidden roundings of 2^-24 in the
-// canonical chain, at most 2 * hidden additions in the matrix core each assumed to err by at most
-// one unit in the last place of binary32 whatever their order, and the split residue (2^-18, taken
-// as 2^-17).  A fixed 1e-30 on top covers activations so small that a conversion flushes them.
-// The sign of y_mfma is therefore the canonical sign wherever |y_mfma| exceeds that bound; the few
-// outputs that do not (about 0.2 %) are recomputed with the canonical chain from the binary32
-// activations still in LDS.  The codes are identical to the all-binary32 kernel's, bit for bit.
-//
-// The 32 columns of an MFMA tile are the 32 outputs of ONE code word in bit order (column c is
-// output (31 - c) * W + word), so a wave ballot over an accumulator register is two packed words.
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef float f32x16_t __attribute__((ext_vector_type(16)));
-
-constexpr int kMfmaTile = 32;       // vectors per tile (rows of the MFMA)
-constexpr int kMfmaListCap = 1024;  // outputs of a tile that may go to the canonical recomputation
-
-struct MfmaLds {   // lives in the x tile's LDS once phase 1 is done with it
-    float part[8][kMfmaTile];
-    float hn[kMfmaTile];              // ||h_t||
-    uint32_t codes[kMfmaTile][16];
-    uint16_t list[kMfmaListCap];
-    uint32_t count;
-};
-static_assert(sizeof(MfmaLds) <= sizeof(float) * kHeadDim * kMfmaTile, "fits in the x tile");
-
-// hi / lo split of 8 activations into two MFMA operands: hi = bf16(h) and lo = bf16(h - hi), both
-// rounded to nearest by the packed conversion instruction; h - hi is exact.
-__device__ __forceinline__ void split8(const float (&h)[8], bf16x8_t& hi, bf16x8_t& lo)
-{
-    typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-    typedef float f32x2_t __attribute__((ext_vector_type(2)));
-    union { bf16x8_t v; uint32_t u[4]; } a, b;
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        const f32x2_t hv = {h[2 * p], h[2 * p + 1]};
-        const uint32_t hp = __builtin_bit_cast(uint32_t, __builtin_convertvector(hv, bf16x2_t));
-        const f32x2_t rv = {h[2 * p] - __uint_as_float(hp << 16), h[2 * p + 1] - __uint_as_float(hp & 0xffff0000u)};
-        a.u[p] = hp;
-        b.u[p] = __builtin_bit_cast(uint32_t, __builtin_convertvector(rv, bf16x2_t));
-    }
-    hi = a.v;
-    lo = b.v;
-}
-
-// ||W2[j]|| of every output row of every weight head, for the bound above.
-__global__ __launch_bounds__(kThreads) void w2_norm_kernel(const bf16_raw* __restrict__ w2, float* __restrict__ wnorm,
-                                                          int n_rows, int hidden)
-{
-    const int j = blockIdx.x * kThreads + threadIdx.x;
-    if (j >= n_rows) return;
-    float s = 0.0f;
-    for (int g = 0; g < hidden / 8; ++g) {
-        float wv[8];
-        load8(w2 + static_cast<int64_t>(j) * hidden + g * 8, wv);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) s = __builtin_fmaf(wv[e], wv[e], s);
-    }
-    wnorm[j] = __builtin_sqrtf(s);
-}
-
-// NBW: code words (MFMA column blocks) per wavefront = ceil(W / 4).
-// AUDIT: every output is also evaluated with the canonical chain and compared with the matrix
-// cores' value (distance in units of ||W2[j]|| ||h||, settled signs that disagree); the totals go to
-// a.audit.  The codes written are the same either way.
-template <typename XT, int NBW, bool AUDIT>
-__global__ __launch_bounds__(kThreads) void hash_mfma_kernel(HashArgs a, const float* __restrict__ wnorm, float eps,
-                                                            int tiles_per_group)
-{
-    using WT = bf16_raw;
-    constexpr int TK = kMfmaTile;
-    extern __shared__ __align__(16) float lds[];
-    float* xs = lds;                                   // [128][TK], later MfmaLds
-    float* hs = lds + kHeadDim * TK;                   // [hidden][TK]
-    MfmaLds& m = *reinterpret_cast<MfmaLds*>(xs);
-    float* hn = m.hn;
-    const float* wn = wnorm + static_cast<int64_t>(whead_of(a, blockIdx.y)) * a.L;   // ||W2[j]|| of this head
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int xhead = blockIdx.y;
-    const int whead = (xhead % a.heads_per_batch) / a.group;
-    const WT* w1 = static_cast<const WT*>(a.w1) + static_cast<int64_t>(whead) * a.hidden * kHeadDim;
-    const WT* b1 = static_cast<const WT*>(a.b1) + static_cast<int64_t>(whead) * a.hidden;
-    const WT* w2 = static_cast<const WT*>(a.w2) + static_cast<int64_t>(whead) * a.L * a.hidden;
-    const int n8 = a.hidden / 8;
-
-    uint32_t au_outputs = 0, au_listed = 0, au_wrong = 0;   // this lane's audit totals
-    float au_ratio = 0.0f;
-
-    const int64_t n_tiles = (a.n_rows + TK - 1) / TK;
-    const int64_t tile0 = static_cast<int64_t>(blockIdx.x) * tiles_per_group;
-    const int64_t tile1 = min(n_tiles, tile0 + tiles_per_group);
-    for (int64_t tile = tile0; tile < tile1; ++tile) {
-        const int64_t r0 = tile * TK;
-        const int rows = static_cast<int>(min(static_cast<int64_t>(TK), a.n_rows - r0));
-        __syncthreads();   // the previous tile is done with LDS
-
-        // ---- stage the x tile, transposed to [k][t], rows past the end as zeros
-        const XT* xbase = static_cast<const XT*>(a.x) + xhead * a.x_head_stride + (a.x_row0 + r0) * kHeadDim;
-        for (int e = tid; e < TK * (kHeadDim / 8); e += kThreads) {
-            const int t = e / (kHeadDim / 8), k8 = e % (kHeadDim / 8);
-            float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-            if (t < rows) load8(xbase + static_cast<int64_t>(t) * kHeadDim + k8 * 8, v);
-#pragma unroll
-            for (int j = 0; j < 8; ++j) xs[(k8 * 8 + j) * TK + t] = v[j];
-        }
-        __syncthreads();
-
-        // ---- phase 1 (canonical): hidden activations
-        for (int i = tid; i < a.hidden; i += kThreads) {
-            float acc[TK];
-            const float bias = load1(b1 + i);
-#pragma unroll
-            for (int t = 0; t < TK; ++t) acc[t] = bias;
-            dot_rows<WT, TK, 1>(w1 + static_cast<int64_t>(i) * kHeadDim, kHeadDim / 8, xs, TK, acc);
-#pragma unroll
-            for (int t = 0; t < TK; ++t) hs[i * TK + t] = silu(acc[t]);
-        }
-        __syncthreads();
-
-        // ---- norms of the activation rows; the x tile's LDS becomes scratch
-        {
-            const int t = tid & (TK - 1), part = tid / TK;   // 8 partial sums per vector
-            float s = 0.0f;
-            for (int i = part; i < a.hidden; i += kThreads / TK) s = __builtin_fmaf(hs[i * TK + t], hs[i * TK + t], s);
-            m.part[part][t] = s;
-            if (tid == 0) m.count = 0;
-        }
-        __syncthreads();
-        if (tid < TK) {
-            float s = 0.0f;
-#pragma unroll
-            for (int p8 = 0; p8 < 8; ++p8) s += m.part[p8][tid];
-            hn[tid] = __builtin_sqrtf(s);
-        }
-        __syncthreads();
-
-        // ---- phase 2 on the matrix cores: wave w owns code words w, w + 4, ...
-        const int c = lane & 31, half = lane >> 5;
-        f32x16_t acc[NBW];
-#pragma unroll
-        for (int nb = 0; nb < NBW; ++nb)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[nb][v] = 0.0f;
-        const WT* brow[NBW];
-#pragma unroll
-        for (int nb = 0; nb < NBW; ++nb) {
-            const int word = wave + 4 * nb;
-            const int j = word < a.W ? (31 - c) * a.W + word : 0;
-            brow[nb] = w2 + static_cast<int64_t>(j) * a.hidden + 8 * half;
-        }
-        const int n_ks = a.hidden / 16;
-        union BFrag { bf16x8_t v; uint4 u; };
-        BFrag bnext[NBW];
-#pragma unroll
-        for (int nb = 0; nb < NBW; ++nb) bnext[nb].u = *reinterpret_cast<const uint4*>(brow[nb]);
-        for (int ks = 0; ks < n_ks; ++ks) {
-            BFrag b[NBW];
-#pragma unroll
-            for (int nb = 0; nb < NBW; ++nb) b[nb] = bnext[nb];
-            if (ks + 1 < n_ks) {   // the next step's weights are requested before this step's arithmetic
-#pragma unroll
-                for (int nb = 0; nb < NBW; ++nb) bnext[nb].u = *reinterpret_cast<const uint4*>(brow[nb] + (ks + 1) * 16);
-            }
-            float h8[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) h8[e] = hs[(ks * 16 + 8 * half + e) * TK + c];
-            bf16x8_t ahi, alo;
-            split8(h8, ahi, alo);
-#pragma unroll
-            for (int nb = 0; nb < NBW; ++nb) {
-                acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ahi, b[nb].v, acc[nb], 0, 0, 0);
-                acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(alo, b[nb].v, acc[nb], 0, 0, 0);
-            }
-        }
-
-        if constexpr (AUDIT) {
-            // the canonical chain for each of this lane's outputs: its 16 vectors share the weight row
-#pragma unroll 1
-            for (int nb = 0; nb < NBW; ++nb) {
-                const int word = wave + 4 * nb;
-                if (word >= a.W) continue;
-                const int j = (31 - c) * a.W + word;
-                const WT* row = w2 + static_cast<int64_t>(j) * a.hidden;
-                float yc[16];
-#pragma unroll
-                for (int v = 0; v < 16; ++v) yc[v] = 0.0f;
-                for (int g = 0; g < n8; ++g) {
-                    float wv[8];
-                    load8(row + g * 8, wv);
-#pragma unroll
-                    for (int q = 0; q < 8; ++q)
-#pragma unroll
-                        for (int v = 0; v < 16; ++v)
-                            yc[v] = __builtin_fmaf(wv[q], hs[(g * 8 + q) * TK + (v / 4) * 8 + half * 4 + (v % 4)], yc[v]);
-                }
-                const float tcol = eps * wn[j];
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int t = (v / 4) * 8 + half * 4 + (v % 4);
-                    if (t >= rows) continue;
-                    const float y = acc[nb][v];
-                    const bool sure = __builtin_fabsf(y) > __builtin_fmaf(tcol, hn[t], 1e-30f);
-                    const float den = wn[j] * hn[t];
-                    const float diff = __builtin_fabsf(y - yc[v]);
-                    // a NaN or an infinity on either side is never settled and is not a distance
-                    const float ratio = (diff == 0.0f || !(diff < INFINITY)) ? 0.0f : (den > 0.0f ? diff / den : INFINITY);
-                    au_ratio = fmaxf(au_ratio, ratio);
-                    au_outputs += 1;
-                    au_listed += sure ? 0 : 1;
-                    au_wrong += (sure && ((y > 0.0f) != (yc[v] > 0.0f))) ? 1 : 0;
-                }
-            }
-        }
-
-        // ---- signs, ballot-pack, and the list of outputs too close to zero to trust
-#pragma unroll
-        for (int nb = 0; nb < NBW; ++nb) {
-            const int word = wave + 4 * nb;
-            if (word >= a.W) continue;   // uniform over the wavefront
-            const float tcol = eps * wn[(31 - c) * a.W + word];
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int t = (v / 4) * 8 + half * 4 + (v % 4);
-                const float y = acc[nb][v];
-                const float thr = __builtin_fmaf(tcol, hn[t], 1e-30f);
-                const bool sure = __builtin_fabsf(y) > thr;   // false for NaN
-                const unsigned long long pos = __ballot(y > 0.0f);
-                if (c == 0) m.codes[t][word] = half ? static_cast<uint32_t>(pos >> 32) : static_cast<uint32_t>(pos);
-                if (!sure) {
-                    const uint32_t at = atomicAdd(&m.count, 1u);
-                    if (at < static_cast<uint32_t>(kMfmaListCap))
-                        m.list[at] = static_cast<uint16_t>(t | (word << 5) | (c << 9));
-                }
-            }
-        }
-        __syncthreads();
-
-        // ---- canonical recomputation of the listed outputs (of every output if the list overflowed)
-        const uint32_t listed = m.count;
-        if (listed <= static_cast<uint32_t>(kMfmaListCap)) {
-            for (uint32_t e = tid; e < listed; e += kThreads) {
-                const int t = m.list[e] & 31, word = (m.list[e] >> 5) & 15, col = m.list[e] >> 9;
-                const WT* row = w2 + static_cast<int64_t>((31 - col) * a.W + word) * a.hidden;
-                float y = 0.0f;
-                for (int g = 0; g < n8; ++g) {
-                    float wv[8];
-                    load8(row + g * 8, wv);
-#pragma unroll
-                    for (int q = 0; q < 8; ++q) y = __builtin_fmaf(wv[q], hs[(g * 8 + q) * TK + t], y);
-                }
-                const uint32_t bit = 1u << col;
-                if (((m.codes[t][word] & bit) != 0) != (y > 0.0f)) atomicXor(&m.codes[t][word], bit);
-            }
-        } else {
-            for (int item = tid; item < TK * a.L; item += kThreads) {
-                const int t = item % TK, j = item / TK;
-                const WT* row = w2 + static_cast<int64_t>(j) * a.hidden;
-                float y = 0.0f;
-                for (int g = 0; g < n8; ++g) {
-                    float wv[8];
-                    load8(row + g * 8, wv);
-#pragma unroll
-                    for (int q = 0; q < 8; ++q) y = __builtin_fmaf(wv[q], hs[(g * 8 + q) * TK + t], y);
-                }
-                const int word = j % a.W, col = 31 - j / a.W;
-                const uint32_t bit = 1u << col;
-                if (((m.codes[t][word] & bit) != 0) != (y > 0.0f)) atomicXor(&m.codes[t][word], bit);
-            }
-        }
-        __syncthreads();
-
-        // ---- the tile's codes: rows * W consecutive words
-        uint32_t* cbase = a.codes + xhead * a.code_head_stride + (a.code_row0 + r0) * a.W;
-        for (int e = tid; e < rows * a.W; e += kThreads) cbase[e] = m.codes[e / a.W][e % a.W];
-    }
-    if constexpr (AUDIT) {
-        const uint32_t outputs = wave_sum(au_outputs), listed = wave_sum(au_listed), wrong = wave_sum(au_wrong);
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) au_ratio = fmaxf(au_ratio, __shfl_xor(au_ratio, off));
-        if (lane == 0) {
-            atomicAdd(&a.audit->outputs, static_cast<unsigned long long>(outputs));
-            if (listed) atomicAdd(&a.audit->listed, static_cast<unsigned long long>(listed));
-            if (wrong) atomicAdd(&a.audit->wrong, static_cast<unsigned long long>(wrong));
-            atomicMax(&a.audit->max_ratio_bits, __float_as_uint(au_ratio));   // non-negative floats order like their bits
-        }
-    }
-}
-
 // One vector per workgroup (the query of a head, or the key appended by a decode step), for hidden
 // widths that are multiples of 128 (or the linear hash).  Latency matters here, not throughput; the
 // work is hashdev::hash_one_vector (hash_vec.h).
@@ -555,48 +263,11 @@ int run_ks(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int stage)
     return run<XT, WT, TK, 1>(ctx, a, n_xheads, stage);
 }
 
-// Second layer on the matrix cores: bfloat16 weights, hidden a multiple of 16, at least one full tile.
-template <typename XT, int NBW>
-int run_mfma_nbw(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int stage, size_t lds, float* wnorm)
-{
-    auto kern = hash_mfma_kernel<XT, NBW, false>;
-    if (a.audit) kern = hash_mfma_kernel<XT, NBW, true>;
-    if (allow_dynamic_lds(ctx, reinterpret_cast<const void*>(kern), lds) != SPOTLIGHT_OK) return SPOTLIGHT_ERR_HIP;
-    const int64_t tiles = (a.n_rows + kMfmaTile - 1) / kMfmaTile;
-    // a workgroup takes a run of tiles of one head (the output-row norms are computed once per run),
-    // short enough that the grid still has a few thousand workgroups
-    int tpg = 8;
-    while (tpg > 1 && ((tiles + tpg - 1) / tpg) * n_xheads < 4096) tpg /= 2;
-    const double eps = bulk_hash_eps(a.hidden);   // error bound per unit of ||W2[j]|| * ||h||
-    dim3 grid(static_cast<unsigned>((tiles + tpg - 1) / tpg), static_cast<unsigned>(n_xheads));
-    const int n_out = a.n_wheads * a.L;
-    hipLaunchKernelGGL(w2_norm_kernel, dim3(static_cast<unsigned>((n_out + kThreads - 1) / kThreads)), dim3(kThreads), 0,
-                       ctx->stream, static_cast<const bf16_raw*>(a.w2), wnorm, n_out, a.hidden);   // microseconds: not timed
-    StageTimer timer(ctx, stage);
-    timer.launch(kern, grid, dim3(kThreads), lds, a, wnorm, static_cast<float>(eps), tpg);
-    return hip_rc(hipGetLastError());
-}
-
-inline size_t mfma_lds_bytes(int hidden) { return sizeof(float) * kMfmaTile * (kHeadDim + hidden); }
-
-template <typename XT>
-int run_mfma(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int stage, float* wnorm)
-{
-    const size_t lds = mfma_lds_bytes(a.hidden);
-    if (a.W <= 4) return run_mfma_nbw<XT, 1>(ctx, a, n_xheads, stage, lds, wnorm);
-    if (a.W <= 8) return run_mfma_nbw<XT, 2>(ctx, a, n_xheads, stage, lds, wnorm);
-    return run_mfma_nbw<XT, 4>(ctx, a, n_xheads, stage, lds, wnorm);
-}
-
 template <typename XT, typename WT>
 int run_tk(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int stage)
 {
     const size_t cap = static_cast<size_t>(ctx->max_lds);
-    if constexpr (sizeof(WT) == 2) {
-        if (a.n_rows >= kMfmaTile && a.hidden > 0 && a.hidden % 16 == 0 && a.W <= 16 &&
-            mfma_lds_bytes(a.hidden) <= cap && a.wnorm)
-            return run_mfma<XT>(ctx, a, n_xheads, stage, a.wnorm);
-    }
+    if (bulk_hash_applies(ctx, a, n_xheads, sizeof(XT))) return run_bulk_hash<XT, WT>(ctx, a, n_xheads, stage);
     // a single vector per head, hidden width a multiple of 128: the latency-oriented kernel
     if (a.n_rows == 1 && a.hidden % kHeadDim == 0) return run_vec<XT, WT>(ctx, a, n_xheads, nullptr, 0, stage);
     if (a.n_rows >= 32 && lds_bytes(32, a.hidden) <= cap) return run_ks<XT, WT, 32>(ctx, a, n_xheads, stage);

@@ -1,0 +1,1245 @@
+// Bulk hashing on the matrix cores (paper Sec. 3.2 Eq. 4-6): the code cache built after a prefill.
+//
+// The codes are defined by one binary32 chain per output (increasing index, one fused multiply-add
+// per term).  v_mfma_f32_32x32x2_f32 computes exactly that: an instruction adds the products of
+// two consecutive k to each of 32 x 32 accumulators, first the even k (lanes 0-31 of the operands),
+// then the odd k (lanes 32-63), each as one correctly rounded fused multiply-add with denormals
+// kept.  A sequence of these instructions is therefore the defined chain, bit for bit, at twice the
+// rate of the vector ALU's unpacked fused multiply-add (153 against 78.6 TFLOP/s measured / peak).
+// (tests/test_gpu_bulk_hash.py holds the builtin to the chain: wide exponents, denormal products,
+// overflow.)  Unlike the bfloat16 matrix instructions, which run beside the vector ALU, it does NOT
+// overlap with it: vector and binary32 matrix instructions of two wavefronts of one SIMD took the sum
+// of their times (481 + 306 -> 783 us; bfloat16: 518 + 301 -> 535 us).  So these kernels are bound by
+// matrix cycles PLUS vector cycles, and every vector instruction per output counts.
+//
+// A workgroup of NW wavefronts hashes a run of tiles of 32 vectors of one head.
+//
+// Layer 1 (rows = hidden units, columns = vectors): a wavefront owns blocks of 32 hidden units; its
+//   weights stay in registers for the whole run of tiles, so they are read once per run (they are
+//   a row per lane in memory: every load touches 32 cache lines, and re-reading them for every tile
+//   would keep the texture-address unit busier than the matrix cores).  The x tile sits in LDS as
+//   [k][vector], so the operand of a step is one conflict-free 4-byte LDS read.
+// Layer 2, exact (rows = vectors, columns = the 32 outputs of ONE code word in bit order, so that a
+//   ballot over an accumulator register is two packed words): the same instruction over the hidden
+//   activations, [unit][vector] in LDS.  Binary32 weights, 1024-bit codes, hidden widths that are no
+//   multiple of 16 or too large for the rest.
+// Layer 2, certified (bfloat16 weights): only the SIGN of an output is needed, so it runs on
+//   v_mfma_f32_32x32x16_bf16, 16 times the rate.  Each activation is split into hi + lo (both
+//   bfloat16, |h - hi - lo| <= 2^-18 |h|), so the products are exact and two accumulating passes give
+//   y to within
+//     |y_mfma - y_chain| <= eps * sum_i |W2[j][i] h_i| <= eps * ||W2[j]|| * ||h||
+//   with eps = 1.01 * (hidden * (2^-24 + 1.01 * 2^-22) + 2^-17):  hidden roundings of 2^-24 in the
+//   chain, at most 2 * hidden additions in the matrix core each assumed to err by at most one unit in
+//   the last place of binary32 whatever their order, and the split residue (2^-18, taken as 2^-17).
+//   A fixed 1e-30 on top covers activations so small that a conversion flushes them; a norm whose
+//   square underflows counts as infinite.  The sign of
+//   y_mfma is the chain's wherever |y_mfma| exceeds that bound; the few outputs that do not
+//   (0.1 - 0.8 %) are recomputed with the chain from the binary32 activations still in LDS.
+#pragma once
+#include "hash_vec.h"
+
+namespace spotlight {
+namespace bulk {
+using namespace hashdev;
+
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef float f32x16_t __attribute__((ext_vector_type(16)));
+
+constexpr int kTile = 32;       // vectors per tile
+// A norm from its square, for the bound: where the square is so small that its terms underflow, no bound
+// (infinity: nothing is settled).  Finite norms of both sides also keep every partial sum finite.
+__device__ __forceinline__ float norm_of(float s) { return s < 1e-30f ? INFINITY : __builtin_sqrtf(s); }
+
+constexpr int kListCap = 1024;  // outputs of a tile that may go to the recomputation
+
+struct Scratch {   // lives in the x tile's LDS once layer 1 is done with it
+    float part[16][kTile];
+    float hn[kTile];              // ||h_t||
+    uint32_t codes[kTile][16];
+    uint16_t list[kListCap];
+    uint32_t count;
+};
+static_assert(sizeof(Scratch) <= sizeof(float) * kHeadDim / 2 * kTile, "fits in the x tile");
+
+// hi / lo split of 8 activations into two MFMA operands: hi = bf16(h) and lo = bf16(h - hi), both
+// rounded to nearest by the packed conversion instruction; h - hi is exact.
+__device__ __forceinline__ void split8(const float (&h)[8], bf16x8_t& hi, bf16x8_t& lo)
+{
+    typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+    typedef float f32x2_t __attribute__((ext_vector_type(2)));
+    union { bf16x8_t v; uint32_t u[4]; } a, b;
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+        const f32x2_t hv = {h[2 * p], h[2 * p + 1]};
+        const uint32_t hp = __builtin_bit_cast(uint32_t, __builtin_convertvector(hv, bf16x2_t));
+        const f32x2_t rv = {h[2 * p] - __uint_as_float(hp << 16), h[2 * p + 1] - __uint_as_float(hp & 0xffff0000u)};
+        a.u[p] = hp;
+        b.u[p] = __builtin_bit_cast(uint32_t, __builtin_convertvector(rv, bf16x2_t));
+    }
+    hi = a.v;
+    lo = b.v;
+}
+
+// 4 consecutive weights in their stored form
+template <typename WT> struct Raw4;
+template <> struct Raw4<float> { float4 v; };
+template <> struct Raw4<bf16_raw> { uint2 v; };
+__device__ __forceinline__ void load_raw(const float* p, Raw4<float>& r) { r.v = *reinterpret_cast<const float4*>(p); }
+__device__ __forceinline__ void load_raw(const bf16_raw* p, Raw4<bf16_raw>& r) { r.v = *reinterpret_cast<const uint2*>(p); }
+__device__ __forceinline__ void expand(const Raw4<float>& r, float (&o)[4]) { o[0] = r.v.x; o[1] = r.v.y; o[2] = r.v.z; o[3] = r.v.w; }
+__device__ __forceinline__ void expand(const Raw4<bf16_raw>& r, float (&o)[4])
+{
+    o[0] = __uint_as_float(r.v.x << 16); o[1] = __uint_as_float(r.v.x & 0xffff0000u);
+    o[2] = __uint_as_float(r.v.y << 16); o[3] = __uint_as_float(r.v.y & 0xffff0000u);
+}
+
+// Turns 8 consecutive weights of a row, 4 in each half of the wavefront (lower half: k .. k+3, upper
+// half: k+4 .. k+7), into the operands of four consecutive steps (lower half: even k, upper: odd k).
+__device__ __forceinline__ void to_steps(float (&v)[4])
+{
+    float s[4];
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        // exchanges the upper half of the first with the lower half of the second
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[2 * p]), __float_as_uint(v[2 * p + 1]), false, false);
+        s[p] = __uint_as_float(r[0]);
+        s[p + 2] = __uint_as_float(r[1]);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = s[e];
+}
+
+// One lane's operands of the 64 steps of layer 1 for one block of 32 hidden units: bfloat16 weights
+// two steps to a register, binary32 weights one.
+template <typename WT> struct UnitBlock;
+template <> struct UnitBlock<bf16_raw> {
+    uint32_t w[32];
+    __device__ __forceinline__ void put(int g, const float (&v)[4])
+    {
+        w[2 * g] = (__float_as_uint(v[0]) >> 16) | __float_as_uint(v[1]);
+        w[2 * g + 1] = (__float_as_uint(v[2]) >> 16) | __float_as_uint(v[3]);
+    }
+    __device__ __forceinline__ float step(int s) const { return __uint_as_float((s & 1) ? w[s >> 1] & 0xffff0000u : w[s >> 1] << 16); }
+    // keeps the compiler from unpacking all steps once, in front of the loop over the tiles, into twice the registers
+    __device__ __forceinline__ void stay_packed()
+    {
+#pragma unroll
+        for (int i = 0; i < 32; ++i) asm volatile("" : "+v"(w[i]));
+    }
+};
+template <> struct UnitBlock<float> {
+    float w[64];
+    __device__ __forceinline__ void put(int g, const float (&v)[4])
+    {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w[4 * g + e] = v[e];
+    }
+    __device__ __forceinline__ float step(int s) const { return w[s]; }
+    __device__ __forceinline__ void stay_packed() {}
+};
+
+// The x tile in LDS, [step][vector]: bfloat16 vectors with both k of a step in one word (half the
+// room, so that one more workgroup fits a compute unit), binary32 vectors a word for each k.
+template <typename XT> struct XTile;
+template <> struct XTile<bf16_raw> {
+    static constexpr int kFloats = kHeadDim / 2 * kTile;
+    // elements 8 k8 .. 8 k8 + 7 of vector t
+    static __device__ __forceinline__ void put(float* xs, int k8, int t, const Raw8<bf16_raw>& r)
+    {
+        const uint32_t v[4] = {r.u.x, r.u.y, r.u.z, r.u.w};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) reinterpret_cast<uint32_t*>(xs)[(k8 * 4 + j) * kTile + t] = v[j];
+    }
+    // the lane's operand of step s: the even k in the lower half of the wavefront, the odd k in the upper
+    static __device__ __forceinline__ float step(const float* xs, int s, int lane)
+    {
+        const uint32_t v = reinterpret_cast<const uint32_t*>(xs)[s * kTile + (lane & 31)];
+        return __uint_as_float(__builtin_amdgcn_perm(v, v, lane < 32 ? 0x01000c0cu : 0x03020c0cu));
+    }
+};
+template <> struct XTile<float> {
+    static constexpr int kFloats = kHeadDim * kTile;
+    static __device__ __forceinline__ void put(float* xs, int k8, int t, const Raw8<float>& r)
+    {
+        float v[8];
+        expand(r, v);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) xs[(k8 * 8 + j) * kTile + t] = v[j];
+    }
+    template <typename R> static __device__ __forceinline__ void put_raw(float* xs, int k8, int t, const R& r)
+    {
+        float v[8];
+        expand(r, v);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) xs[(k8 * 8 + j) * kTile + t] = v[j];
+    }
+    static __device__ __forceinline__ float step(const float* xs, int s, int lane) { return xs[s * 64 + lane]; }
+};
+
+// ||W2[j]|| of every output row of every weight head, for the bound above: 16 lanes per row.
+template <int LPR>
+__global__ __launch_bounds__(kThreads) void row_norm_kernel(const bf16_raw* __restrict__ w2, float* __restrict__ wnorm, int n_rows, int n)
+{
+    const int j = (blockIdx.x * kThreads + threadIdx.x) / LPR, sub = threadIdx.x % LPR;
+    if (j >= n_rows) return;   // whole groups of LPR lanes
+    float s = 0.0f;
+    for (int g = sub; g < n / 8; g += LPR) {
+        float wv[8];
+        load8(w2 + static_cast<int64_t>(j) * n + g * 8, wv);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s = __builtin_fmaf(wv[e], wv[e], s);
+    }
+#pragma unroll
+    for (int off = 1; off < LPR; off <<= 1) s += __shfl_xor(s, off);
+    if (sub == 0) wnorm[j] = norm_of(s);
+}
+
+__host__ __device__ constexpr int hidden_padded(int hidden) { return (hidden + 31) / 32 * 32; }
+
+// Wavefronts per SIMD the register allocation must leave room for.  8 heads x 131072 vectors, 128 -> 512 ->
+// 256: four (a few spilled registers, outside the main loops) 3.25 ms, three 3.83 ms.
+constexpr int min_waves(int NW, int NBW) { return NBW == 1 && NW >= 8 ? 4 : 2; }
+
+// NW:    wavefronts per workgroup.
+// NUB:   blocks of 32 hidden units a wavefront owns, their weights in registers; 0: the linear hash;
+//        -1: any number, weights read again for every tile.
+// NBW:   code words per wavefront of the certified second layer; 0: exact second layer.
+// AUDIT: every output of the certified second layer is also evaluated with the chain and compared
+//        (distance in units of ||W2[j]|| ||h||, settled signs that disagree); totals go to a.audit.
+template <typename XT, typename WT, int NW, int NUB, int NBW, bool AUDIT>
+__global__ __launch_bounds__(NW * 64, min_waves(NW, NBW)) void hash_bulk_kernel(HashArgs a, float eps, int tiles_per_group)
+{
+    constexpr int TK = kTile, NT = NW * 64;
+    constexpr bool CERT = NBW > 0;
+    extern __shared__ __align__(16) float lds[];
+    float* xs = lds;                                   // the x tile, later Scratch
+    float* hs = lds + XTile<XT>::kFloats;              // [hidden, padded to 32][TK]
+    Scratch& m = *reinterpret_cast<Scratch*>(xs);
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int c = lane & 31, half = lane >> 5;
+    const int xhead = blockIdx.y;
+    const int whead = whead_of(a, xhead);
+    const WT* w1 = static_cast<const WT*>(a.w1) + static_cast<int64_t>(whead) * (a.hidden > 0 ? a.hidden : a.L) * kHeadDim;
+    const WT* b1 = static_cast<const WT*>(a.b1) + static_cast<int64_t>(whead) * a.hidden;
+    const int K2 = NUB == 0 ? kHeadDim : a.hidden;     // what layer 2 contracts over
+    const WT* w2 = NUB == 0 ? w1 : static_cast<const WT*>(a.w2) + static_cast<int64_t>(whead) * a.L * a.hidden;
+    const int nub = hidden_padded(a.hidden) / 32;
+
+    uint32_t au_outputs = 0, au_listed = 0, au_wrong = 0;   // this lane's audit totals
+    float au_ratio = 0.0f;
+
+    // Weights and biases of a block of hidden units; units past the end have zeros, i.e. activation 0.
+    auto load_block = [&](int ub, UnitBlock<WT>& u) {
+        const int unit = ub * 32 + c;
+        const WT* row = w1 + static_cast<int64_t>(min(unit, a.hidden - 1)) * kHeadDim + 4 * half;
+        Raw4<WT> raw[16];
+#pragma unroll
+        for (int g = 0; g < 16; ++g) load_raw(row + 8 * g, raw[g]);
+#pragma unroll
+        for (int g = 0; g < 16; ++g) {
+            float v[4];
+            expand(raw[g], v);
+            if (unit >= a.hidden) v[0] = v[1] = v[2] = v[3] = 0.0f;
+            to_steps(v);
+            u.put(g, v);
+        }
+    };
+    // accumulator register v of a block holds hidden unit 8 (v / 4) + 4 half + v % 4 of it
+    auto load_bias = [&](int ub, f32x16_t& acc) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int unit = ub * 32 + 8 * q + 4 * half;   // hidden is a multiple of 8: a group of four is whole
+            Raw4<WT> raw;
+            load_raw(b1 + min(unit, a.hidden - 4), raw);
+            float v[4];
+            expand(raw, v);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[4 * q + e] = unit < a.hidden ? v[e] : 0.0f;
+        }
+    };
+    float sumsq;
+    auto layer1 = [&](int ub, const UnitBlock<WT>& u) {
+        f32x16_t acc;
+        load_bias(ub, acc);
+#pragma unroll
+        for (int s = 0; s < kHeadDim / 2; ++s)
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(u.step(s), XTile<XT>::step(xs, s, lane), acc, 0, 0, 0);
+        float* h = hs + (ub * 32 + 4 * half) * TK + c;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const float hv = silu(acc[v]);
+            h[(8 * (v / 4) + v % 4) * TK] = hv;
+            if constexpr (CERT) sumsq = __builtin_fmaf(hv, hv, sumsq);
+            if (v % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // four at a time: sixteen side by side would spill
+        }
+    };
+    UnitBlock<WT> ublk[NUB > 0 ? NUB : 1];
+    if constexpr (NUB > 0) {
+#pragma unroll
+        for (int i = 0; i < NUB; ++i)
+            if (wave + NW * i < nub) load_block(wave + NW * i, ublk[i]);
+    }
+
+    const int64_t n_tiles = (a.n_rows + TK - 1) / TK;
+    const int64_t tile0 = static_cast<int64_t>(blockIdx.x) * tiles_per_group;
+    const int64_t tile1 = min(n_tiles, tile0 + tiles_per_group);
+
+    // the x tile of a tile, fetched ahead: thread e has 8 elements of vector e % 32
+    constexpr int XPT = TK * (kHeadDim / 8) >= NT ? TK * (kHeadDim / 8) / NT : 1;
+    const bool stages = tid < TK * (kHeadDim / 8);     // with 1024 threads only half of them
+    Raw8<XT> xr[XPT];
+    const XT* xhead_base = static_cast<const XT*>(a.x) + xhead * a.x_head_stride + a.x_row0 * kHeadDim;
+    auto fetch_x = [&](int64_t tile) {
+#pragma unroll
+        for (int i = 0; i < XPT; ++i) {
+            const int e = tid + i * NT, k8 = e / TK;
+            const int64_t row = min(tile * TK + e % TK, a.n_rows - 1);   // rows past the end: a stand-in, never stored
+            if (stages) load_raw(xhead_base + row * kHeadDim + k8 * 8, xr[i]);
+        }
+    };
+    fetch_x(tile0);
+    for (int64_t tile = tile0; tile < tile1; ++tile) {
+        const int64_t r0 = tile * TK;
+        const int rows = static_cast<int>(min(static_cast<int64_t>(TK), a.n_rows - r0));
+        __syncthreads();   // the previous tile is done with LDS
+#pragma unroll
+        for (int i = 0; i < XPT; ++i) {
+            const int e = tid + i * NT;
+            if (stages) XTile<XT>::put(xs, e / TK, e % TK, xr[i]);
+        }
+        __syncthreads();
+        if (tile + 1 < tile1) fetch_x(tile + 1);   // in flight during this tile
+
+        // ---- layer 1: hidden activations
+        sumsq = 0.0f;
+        if constexpr (NUB > 0) {
+#pragma unroll
+            for (int i = 0; i < NUB; ++i) {
+                ublk[i].stay_packed();
+                if (wave + NW * i < nub) layer1(wave + NW * i, ublk[i]);
+            }
+        } else if constexpr (NUB < 0) {
+            for (int ub = wave; ub < nub; ub += NW) {
+                load_block(ub, ublk[0]);
+                layer1(ub, ublk[0]);
+            }
+        }
+        if constexpr (NUB != 0) __syncthreads();
+
+        uint32_t* cbase = a.codes + xhead * a.code_head_stride + (a.code_row0 + r0) * a.W;
+        if constexpr (!CERT) {
+            // ---- layer 2, exact: one code word after another
+            auto act = [&](int s) { return NUB == 0 ? XTile<XT>::step(xs, s, lane) : hs[s * 64 + lane]; };
+            for (int word = wave; word < a.W; word += NW) {
+                const WT* row = w2 + static_cast<int64_t>((31 - c) * a.W + word) * K2 + 4 * half;
+                f32x16_t y;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) y[v] = 0.0f;
+                constexpr int PF = 8;   // groups of 8 weights on their way
+                Raw4<WT> nx[PF];
+                const int n8 = K2 / 8;
+#pragma unroll
+                for (int p = 0; p < PF; ++p) load_raw(row + 8 * min(p, n8 - 1), nx[p]);
+                for (int g0 = 0; g0 < n8; g0 += PF) {
+#pragma unroll
+                    for (int p = 0; p < PF; ++p) {
+                        if (g0 + p < n8) {
+                            float w[4];
+                            expand(nx[p], w);
+                            load_raw(row + 8 * min(g0 + p + PF, n8 - 1), nx[p]);
+                            to_steps(w);
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+                                y = __builtin_amdgcn_mfma_f32_32x32x2f32(act(4 * (g0 + p) + e), w[e], y, 0, 0, 0);
+                        }
+                    }
+                }
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int t = (v / 4) * 8 + half * 4 + (v % 4);
+                    const unsigned long long pos = __ballot(y[v] > 0.0f);
+                    if (c == 0 && t < rows) cbase[static_cast<int64_t>(t) * a.W + word] = half ? static_cast<uint32_t>(pos >> 32) : static_cast<uint32_t>(pos);
+                }
+            }
+        } else {
+            // ---- norms of the activation rows; the x tile's LDS becomes scratch
+            sumsq += __shfl_xor(sumsq, 32);
+            if (half == 0) m.part[wave][c] = sumsq;
+            if (tid == 0) m.count = 0;
+            __syncthreads();
+            if (tid < TK) {
+                float s = 0.0f;
+#pragma unroll
+                for (int p = 0; p < NW; ++p) s += m.part[p][tid];
+                m.hn[tid] = norm_of(s);
+            }
+
+            // ---- layer 2, certified: wave w owns code words w, w + NW, ...
+            f32x16_t acc[NBW];
+            const WT* brow[NBW];
+#pragma unroll
+            for (int nb = 0; nb < NBW; ++nb) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[nb][v] = 0.0f;
+                const int word = wave + NW * nb;
+                const int j = word < a.W ? (31 - c) * a.W + word : 0;
+                brow[nb] = w2 + static_cast<int64_t>(j) * K2 + 8 * half;
+            }
+            const int n_ks = K2 / 16;
+            union BFrag { bf16x8_t v; uint4 u; };
+            BFrag bnext[NBW];
+#pragma unroll
+            for (int nb = 0; nb < NBW; ++nb) bnext[nb].u = *reinterpret_cast<const uint4*>(brow[nb]);
+            for (int ks = 0; ks < n_ks; ++ks) {
+                BFrag b[NBW];
+#pragma unroll
+                for (int nb = 0; nb < NBW; ++nb) b[nb] = bnext[nb];
+                if (ks + 1 < n_ks) {   // the next step's weights are requested before this step's arithmetic
+#pragma unroll
+                    for (int nb = 0; nb < NBW; ++nb) bnext[nb].u = *reinterpret_cast<const uint4*>(brow[nb] + (ks + 1) * 16);
+                }
+                float h8[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) h8[e] = hs[(ks * 16 + 8 * half + e) * TK + c];
+                bf16x8_t ahi, alo;
+                split8(h8, ahi, alo);
+#pragma unroll
+                for (int nb = 0; nb < NBW; ++nb) {
+                    acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ahi, b[nb].v, acc[nb], 0, 0, 0);
+                    acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(alo, b[nb].v, acc[nb], 0, 0, 0);
+                }
+            }
+            __syncthreads();   // hn is there
+
+            const float* wn = a.wnorm + static_cast<int64_t>(whead) * a.L;   // ||W2[j]|| of this head
+            const int n8 = K2 / 8;
+            if constexpr (AUDIT) {
+                // the chain for each of this lane's outputs: its 16 vectors share the weight row
+#pragma unroll 1
+                for (int nb = 0; nb < NBW; ++nb) {
+                    const int word = wave + NW * nb;
+                    if (word >= a.W) continue;
+                    const int j = (31 - c) * a.W + word;
+                    const WT* row = w2 + static_cast<int64_t>(j) * K2;
+                    float yc[16];
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) yc[v] = 0.0f;
+                    for (int g = 0; g < n8; ++g) {
+                        float wv[8];
+                        load8(row + g * 8, wv);
+#pragma unroll
+                        for (int q = 0; q < 8; ++q)
+#pragma unroll
+                            for (int v = 0; v < 16; ++v)
+                                yc[v] = __builtin_fmaf(wv[q], hs[(g * 8 + q) * TK + (v / 4) * 8 + half * 4 + (v % 4)], yc[v]);
+                    }
+                    const float tcol = eps * wn[j];
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        const int t = (v / 4) * 8 + half * 4 + (v % 4);
+                        if (t >= rows) continue;
+                        const float y = acc[nb][v];
+                        const bool sure = __builtin_fabsf(y) > __builtin_fmaf(tcol, m.hn[t], 1e-30f);
+                        const float den = wn[j] * m.hn[t];
+                        const float diff = __builtin_fabsf(y - yc[v]);
+                        // a NaN or an infinity on either side is never settled and is not a distance
+                        const float ratio = (diff == 0.0f || !(diff < INFINITY)) ? 0.0f : (den > 0.0f ? diff / den : INFINITY);   // an infinite scale: 0
+                        au_ratio = fmaxf(au_ratio, ratio);
+                        au_outputs += 1;
+                        au_listed += sure ? 0 : 1;
+                        au_wrong += (sure && ((y > 0.0f) != (yc[v] > 0.0f))) ? 1 : 0;
+                    }
+                }
+            }
+
+            // ---- signs, ballot-pack, and the list of outputs too close to zero to trust
+#pragma unroll
+            for (int nb = 0; nb < NBW; ++nb) {
+                const int word = wave + NW * nb;
+                if (word >= a.W) continue;   // uniform over the wavefront
+                const float tcol = eps * wn[(31 - c) * a.W + word];
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int t = (v / 4) * 8 + half * 4 + (v % 4);
+                    const float y = acc[nb][v];
+                    const float thr = __builtin_fmaf(tcol, m.hn[t], 1e-30f);
+                    const bool sure = __builtin_fabsf(y) > thr;   // false for NaN
+                    const unsigned long long pos = __ballot(y > 0.0f);
+                    if (c == 0) m.codes[t][word] = half ? static_cast<uint32_t>(pos >> 32) : static_cast<uint32_t>(pos);
+                    if (!sure && t < rows) {
+                        const uint32_t at = atomicAdd(&m.count, 1u);
+                        if (at < static_cast<uint32_t>(kListCap))
+                            m.list[at] = static_cast<uint16_t>(t | (word << 5) | (c << 9));
+                    }
+                }
+            }
+            __syncthreads();
+
+            // ---- recomputation with the chain of the listed outputs (of every output if the list
+            // overflowed); a handful of threads with a long chain each, so the weights are fetched 32 at a time
+            auto chain = [&](int j, int t) {
+                constexpr int PF = 4;
+                const WT* row = w2 + static_cast<int64_t>(j) * K2;
+                float y = 0.0f;
+                for (int g0 = 0; g0 < n8; g0 += PF) {
+                    Raw8<WT> raw[PF];
+#pragma unroll
+                    for (int p = 0; p < PF; ++p) load_raw(row + 8 * min(g0 + p, n8 - 1), raw[p]);
+#pragma unroll
+                    for (int p = 0; p < PF; ++p) {
+                        if (g0 + p < n8) {
+                            float wv[8];
+                            expand(raw[p], wv);
+#pragma unroll
+                            for (int q = 0; q < 8; ++q) y = __builtin_fmaf(wv[q], hs[((g0 + p) * 8 + q) * TK + t], y);
+                        }
+                    }
+                }
+                return y;
+            };
+            auto settle = [&](int t, int word, int col) {
+                const uint32_t bit = 1u << col;
+                if (((m.codes[t][word] & bit) != 0) != (chain((31 - col) * a.W + word, t) > 0.0f)) atomicXor(&m.codes[t][word], bit);
+            };
+            const uint32_t listed = m.count;
+            if (listed <= static_cast<uint32_t>(kListCap)) {
+                for (uint32_t e = tid; e < listed; e += NT) settle(m.list[e] & 31, (m.list[e] >> 5) & 15, m.list[e] >> 9);
+            } else {
+                for (int item = tid; item < TK * a.L; item += NT) settle(item % TK, (item / TK) % a.W, 31 - (item / TK) / a.W);
+            }
+            __syncthreads();
+
+            // ---- the tile's codes: rows * W consecutive words
+            for (int e = tid; e < rows * a.W; e += NT) cbase[e] = m.codes[e / a.W][e % a.W];
+        }
+    }
+    if constexpr (AUDIT) {
+        const uint32_t outputs = wave_sum(au_outputs), listed = wave_sum(au_listed), wrong = wave_sum(au_wrong);
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) au_ratio = fmaxf(au_ratio, __shfl_xor(au_ratio, off));
+        if (lane == 0) {
+            atomicAdd(&a.audit->outputs, static_cast<unsigned long long>(outputs));
+            if (listed) atomicAdd(&a.audit->listed, static_cast<unsigned long long>(listed));
+            if (wrong) atomicAdd(&a.audit->wrong, static_cast<unsigned long long>(wrong));
+            atomicMax(&a.audit->max_ratio_bits, __float_as_uint(au_ratio));   // non-negative floats order like their bits
+        }
+    }
+}
+
+// ------------------------------------------------------------------------------------------------
+// The certified kernel for hidden widths up to 256 and codes up to 128 bits: everything the second layer
+// needs is laid out once per tile, and a wavefront finishes its own code word alone.
+//
+// Hidden unit and operand row are matched so that a lane's eight accumulators of layer 1 are eight
+// consecutive units.  The activations go to LDS three ways: binary32 by vector (for the recomputation),
+// and hi and lo exactly as the bfloat16 instruction reads them, so that the wavefronts share one split
+// instead of each splitting all activations for its own word.  Wavefront w owns code word w: it
+// contracts it, takes the signs and recomputes what the bound does not settle itself, with the weights
+// it holds, so a tile costs two barriers.  Two workgroups per compute unit (LDS and registers).
+// Measured, 32 heads x 131072 vectors, 128 -> 256 -> 128: 4.2 ms (131 TFLOP/s), against 6.25 ms with
+// layer 1 on the vector ALU.  A tile takes 19.7 K cycles of a SIMD: 8.2 K of binary32 matrix
+// instructions and 7.9 K of vector instructions (SiLU 4.0 K, recomputation 1.9 K, unpacking 1.0 K),
+// which do not overlap.  Tried and slower: a list of open outputs shared by the workgroup, one
+// wavefront taking all of it (4.55 ms: fewer instructions, but everybody waits for its chain); the
+// kernel below with three or four wavefronts per SIMD (4.6 and 5.0 ms); the contraction split over the
+// hidden units with sums through LDS float atomics (14.7 ms: those take about 4 cycles a lane).
+// hidden unit of operand row r of a block: bits 2 and 3 exchanged
+__device__ __forceinline__ int unit_of_row(int r) { return (r & 19) | ((r & 4) << 1) | ((r & 8) >> 1); }
+
+template <int NW> struct CertScratch {
+    float part[NW][kTile];            // sums of squares of the wavefronts' activations
+    float hn[NW][kTile];              // ||h_t||, a copy for each wavefront
+    uint32_t codes[NW][kTile];
+};
+
+constexpr int hs_stride(int hidden) { return hidden_padded(hidden) + 4; }   // words per vector: b128 accesses of 8 lanes miss each other
+
+// NUB: blocks of 32 hidden units a wavefront owns; WREG: steps of 16 units of layer 2.
+template <typename XT, int NW, int NUB, int WREG, bool AUDIT>
+__global__ __launch_bounds__(NW * 64, 2) void hash_cert_kernel(HashArgs a, float eps, int tiles_per_group)
+{
+    using WT = bf16_raw;
+    constexpr int TK = kTile, NT = NW * 64;
+    extern __shared__ __align__(16) float lds[];
+    float* xs = lds;                                                        // the x tile
+    const int stride = hs_stride(a.hidden), nub = hidden_padded(a.hidden) / 32;
+    float* hs = xs + XTile<XT>::kFloats;                                    // [TK][stride]
+    uint4* hilo = reinterpret_cast<uint4*>(hs + TK * stride);               // [2 nub steps of 16 units][hi, lo][64]
+    float* bias = reinterpret_cast<float*>(hilo + nub * 2 * 2 * 64);        // [hidden, padded to 32]
+    CertScratch<NW>& m = *reinterpret_cast<CertScratch<NW>*>(bias + nub * 32);
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c = lane & 31, half = lane >> 5;
+    const int xhead = blockIdx.y;
+    const int whead = whead_of(a, xhead);
+    const WT* w1 = static_cast<const WT*>(a.w1) + static_cast<int64_t>(whead) * a.hidden * kHeadDim;
+    const WT* b1 = static_cast<const WT*>(a.b1) + static_cast<int64_t>(whead) * a.hidden;
+    const WT* w2 = static_cast<const WT*>(a.w2) + static_cast<int64_t>(whead) * a.L * a.hidden;
+    const int n_mine = max(0, min(NUB, nub - wave * NUB));           // blocks of this wavefront
+    const int n_ks = a.hidden / 16;                                  // hidden is a multiple of 16
+
+    // ---- the weights of both layers, into registers by way of LDS: read by the wavefronts as they
+    // need them, a row per lane, every load touches 32 cache lines and the lines leave the cache
+    // before their other parts are asked for (a workgroup with a single tile took 43 us, most of it this).
+    // Rows are a multiple of 16 bytes, one chunk apart in LDS so that the rows of a wavefront miss each other.
+    auto stage = [&](const WT* src, int n_rows, int chunks) {
+        const uint4* from = reinterpret_cast<const uint4*>(src);
+        uint4* to = reinterpret_cast<uint4*>(lds);
+        constexpr int PF = 8;
+        const int n = n_rows * chunks;
+        for (int e0 = tid; e0 < n; e0 += NT * PF) {
+            uint4 v[PF];
+#pragma unroll
+            for (int p = 0; p < PF; ++p) v[p] = from[min(e0 + p * NT, n - 1)];
+#pragma unroll
+            for (int p = 0; p < PF; ++p) {
+                const int e = e0 + p * NT;
+                if (e < n) to[e / chunks * (chunks + 1) + e % chunks] = v[p];
+            }
+        }
+    };
+    const uint4* staged = reinterpret_cast<const uint4*>(lds);
+    stage(w1, a.hidden, kHeadDim / 8);
+    __syncthreads();
+    UnitBlock<WT> ublk[NUB];   // layer 1: a row of W1 per lane, turned into the operands of the 64 steps
+#pragma unroll
+    for (int i = 0; i < NUB; ++i) {
+        if (i >= n_mine) continue;
+        const int unit = (wave * NUB + i) * 32 + unit_of_row(c);
+        const uint4* row = staged + min(unit, a.hidden - 1) * (kHeadDim / 8 + 1) + half;
+#pragma unroll
+        for (int g = 0; g < 8; ++g) {   // k = 16 g .. + 7 in the lower half, 16 g + 8 .. + 15 in the upper
+            const uint4 w = unit < a.hidden ? row[2 * g] : make_uint4(0u, 0u, 0u, 0u);
+            const uint32_t d[4] = {w.x, w.y, w.z, w.w};
+            float s0[4], s1[4];         // steps 8 g .. + 3 and 8 g + 4 .. + 7
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {   // exchanges the upper half of the even k with the lower half of the odd k
+                const auto r = __builtin_amdgcn_permlane32_swap(d[p] << 16, d[p] & 0xffff0000u, false, false);
+                s0[p] = __uint_as_float(r[0]);
+                s1[p] = __uint_as_float(r[1]);
+            }
+            ublk[i].put(2 * g, s0);
+            ublk[i].put(2 * g + 1, s1);
+        }
+    }
+    __syncthreads();
+    stage(w2, a.L, a.hidden / 8);
+    __syncthreads();
+    uint4 wreg[WREG];          // layer 2: the wavefront's code word, 16 units a step, 8 of them per lane
+#pragma unroll
+    for (int ks = 0; ks < WREG; ++ks)
+        wreg[ks] = staged[((31 - c) * a.W + min(wave, a.W - 1)) * (a.hidden / 8 + 1) + min(ks, n_ks - 1) * 2 + half];
+    __syncthreads();
+    float norm = 0.0f;         // ||W2[j]|| of this lane's output
+#pragma unroll
+    for (int ks = 0; ks < WREG; ++ks) {
+        if (ks >= n_ks) continue;
+        const uint32_t d[4] = {wreg[ks].x, wreg[ks].y, wreg[ks].z, wreg[ks].w};
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            const float lo = __uint_as_float(d[p] << 16), hi = __uint_as_float(d[p] & 0xffff0000u);
+            norm = __builtin_fmaf(hi, hi, __builtin_fmaf(lo, lo, norm));
+        }
+    }
+    norm = norm_of(norm + __shfl_xor(norm, 32));
+    for (int i = tid; i < nub * 32; i += NT) bias[i] = i < a.hidden ? load1(b1 + i) : 0.0f;
+
+    uint32_t au_outputs = 0, au_listed = 0, au_wrong = 0;   // this lane's audit totals
+    float au_ratio = 0.0f;
+
+    const int64_t n_tiles = (a.n_rows + TK - 1) / TK;
+    const int64_t tile0 = static_cast<int64_t>(blockIdx.x) * tiles_per_group;
+    const int64_t tile1 = min(n_tiles, tile0 + tiles_per_group);
+
+    // the x tile of a tile, fetched ahead: thread e has 8 elements of vector e % 32
+    constexpr int XPT = TK * (kHeadDim / 8) / NT;
+    Raw8<XT> xr[XPT];
+    const XT* xhead_base = static_cast<const XT*>(a.x) + xhead * a.x_head_stride + a.x_row0 * kHeadDim;
+    auto fetch_x = [&](int64_t tile) {
+#pragma unroll
+        for (int i = 0; i < XPT; ++i) {
+            const int e = tid + i * NT;
+            const int64_t row = min(tile * TK + e % TK, a.n_rows - 1);   // rows past the end: a stand-in, never stored
+            load_raw(xhead_base + row * kHeadDim + (e / TK) * 8, xr[i]);
+        }
+    };
+    auto put_x = [&]() {
+#pragma unroll
+        for (int i = 0; i < XPT; ++i) {
+            const int e = tid + i * NT;
+            XTile<XT>::put(xs, e / TK, e % TK, xr[i]);
+        }
+    };
+    fetch_x(tile0);
+    put_x();
+    __syncthreads();
+    for (int64_t tile = tile0; tile < tile1; ++tile) {
+        const int64_t r0 = tile * TK;
+        const int rows = static_cast<int>(min(static_cast<int64_t>(TK), a.n_rows - r0));
+        if (tile + 1 < tile1) fetch_x(tile + 1);   // in flight during layer 1
+
+        // ---- layer 1.  The SiLU of a block runs in the shadow of the next block's matrix instructions.
+        f32x16_t h[NUB];
+        float sumsq = 0.0f;
+        auto activate = [&](int i, int v) {
+            h[i][v] = silu(h[i][v]);
+            sumsq = __builtin_fmaf(h[i][v], h[i][v], sumsq);
+        };
+        auto keep = [&](int i, int j) {   // accumulators 8 j .. 8 j + 7: units 16 j + 8 half .. + 7 of the block
+            float h8[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) h8[e] = h[i][8 * j + e];
+            const int ub = wave * NUB + i;
+            float4* f = reinterpret_cast<float4*>(hs + c * stride + ub * 32 + 16 * j + 8 * half);
+            f[0] = make_float4(h8[0], h8[1], h8[2], h8[3]);
+            f[1] = make_float4(h8[4], h8[5], h8[6], h8[7]);
+            bf16x8_t hi, lo;
+            split8(h8, hi, lo);
+            hilo[((ub * 2 + j) * 2 + 0) * 64 + lane] = __builtin_bit_cast(uint4, hi);
+            hilo[((ub * 2 + j) * 2 + 1) * 64 + lane] = __builtin_bit_cast(uint4, lo);
+        };
+#pragma unroll
+        for (int i = 0; i < NUB; ++i) {
+            ublk[i].stay_packed();
+            if (i >= n_mine) continue;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {   // accumulators 4 q .. 4 q + 3
+                const float4 f = *reinterpret_cast<const float4*>(bias + (wave * NUB + i) * 32 + 16 * (q / 2) + 8 * half + 4 * (q % 2));
+                h[i][4 * q] = f.x; h[i][4 * q + 1] = f.y; h[i][4 * q + 2] = f.z; h[i][4 * q + 3] = f.w;
+            }
+#pragma unroll
+            for (int s = 0; s < kHeadDim / 2; ++s) {
+                h[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(ublk[i].step(s), XTile<XT>::step(xs, s, lane), h[i], 0, 0, 0);
+                if (i > 0 && s % 4 == 3) activate(i - 1, s / 4);
+                if (i > 0 && s % 32 == 31) keep(i - 1, s / 32);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < NUB; ++i) {
+            if (i == n_mine - 1) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    activate(i, v);
+                    if (v % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // four at a time: sixteen side by side would spill
+                }
+                keep(i, 0);
+                keep(i, 1);
+            }
+        }
+        sumsq += __shfl_xor(sumsq, 32);
+        if (half == 0) m.part[wave][c] = sumsq;
+        __syncthreads();   // activations and norms are complete; the x tile is free
+        if (tile + 1 < tile1) put_x();
+
+        // ---- layer 2 of this wavefront's word
+        if (wave < a.W) {
+            float s = 0.0f;
+#pragma unroll
+            for (int p = 0; p < NW; ++p) s += m.part[p][c];
+            if (half == 0) m.hn[wave][c] = norm_of(s);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+
+            f32x16_t y;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) y[v] = 0.0f;
+#pragma unroll
+            for (int ks = 0; ks < WREG; ++ks) {
+                if (ks >= n_ks) continue;
+                const uint4 hi = hilo[(ks * 2 + 0) * 64 + lane], lo = hilo[(ks * 2 + 1) * 64 + lane];
+                y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, hi), __builtin_bit_cast(bf16x8_t, wreg[ks]), y, 0, 0, 0);
+                y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, lo), __builtin_bit_cast(bf16x8_t, wreg[ks]), y, 0, 0, 0);
+            }
+
+            float hn[16];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float4 f = *reinterpret_cast<const float4*>(&m.hn[wave][8 * q + 4 * half]);
+                hn[4 * q] = f.x; hn[4 * q + 1] = f.y; hn[4 * q + 2] = f.z; hn[4 * q + 3] = f.w;
+            }
+            {
+                const int word = wave;
+                const float tcol = eps * norm;
+
+                if constexpr (AUDIT) {   // the chain for each of this lane's outputs
+                    const WT* row = w2 + static_cast<int64_t>((31 - c) * a.W + word) * a.hidden;
+#pragma unroll 1
+                    for (int v = 0; v < 16; ++v) {
+                        const int t = (v / 4) * 8 + half * 4 + (v % 4);
+                        float yc = 0.0f, yv = 0.0f, hv = 0.0f;
+#pragma unroll
+                        for (int e = 0; e < 16; ++e) { yv = e == v ? y[e] : yv; hv = e == v ? hn[e] : hv; }
+                        for (int g = 0; g < a.hidden / 8; ++g) {
+                            float wv[8];
+                            load8(row + g * 8, wv);
+#pragma unroll
+                            for (int e = 0; e < 8; ++e) yc = __builtin_fmaf(wv[e], hs[t * stride + g * 8 + e], yc);
+                        }
+                        if (t >= rows) continue;
+                        const bool sure = __builtin_fabsf(yv) > __builtin_fmaf(tcol, hv, 1e-30f);
+                        const float den = norm * hv, diff = __builtin_fabsf(yv - yc);
+                        // a NaN or an infinity on either side is never settled and is not a distance
+                        const float ratio = (diff == 0.0f || !(diff < INFINITY)) ? 0.0f : (den > 0.0f ? diff / den : INFINITY);   // an infinite scale: 0
+                        au_ratio = fmaxf(au_ratio, ratio);
+                        au_outputs += 1;
+                        au_listed += sure ? 0 : 1;
+                        au_wrong += (sure && ((yv > 0.0f) != (yc > 0.0f))) ? 1 : 0;
+                    }
+                }
+
+                // ---- signs, packed by ballots; a lane notes which of its 16 outputs are too close to zero to trust
+                uint32_t open = 0;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int t = (v / 4) * 8 + half * 4 + (v % 4);
+                    const bool sure = __builtin_fabsf(y[v]) > __builtin_fmaf(tcol, hn[v], 1e-30f);   // false for NaN
+                    const unsigned long long pos = __ballot(y[v] > 0.0f);
+                    if (c == 0) m.codes[wave][t] = half ? static_cast<uint32_t>(pos >> 32) : static_cast<uint32_t>(pos);
+                    open |= sure ? 0u : 1u << v;
+                }
+                if (rows < TK) {   // rows past the end are copies of the last one: not to be recomputed over and over
+#pragma unroll
+                    for (int v = 0; v < 16; ++v)
+                        if ((v / 4) * 8 + half * 4 + (v % 4) >= rows) open &= ~(1u << v);
+                }
+                // ---- recomputation with the chain, a round for every lane's next open output (nearly always
+                // one round).  A lane's output row is the one it has the weights of: its own 8 of 16 units
+                // are here, the other 8 are in the other half.
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                while (__ballot(open != 0)) {
+                    const int v = open ? __builtin_ctz(open) : 0;
+                    const int t = (v / 4) * 8 + half * 4 + (v % 4);
+                    const float* hr = hs + t * stride;
+                    float yc = 0.0f;
+#pragma unroll
+                    for (int ks = 0; ks < WREG; ++ks) {
+                        if (ks >= n_ks) continue;
+                        const uint32_t own[4] = {wreg[ks].x, wreg[ks].y, wreg[ks].z, wreg[ks].w};
+                        uint32_t first[4], second[4];   // units 16 ks .. + 7 and 16 ks + 8 .. + 15, in both halves
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const auto r = __builtin_amdgcn_permlane32_swap(own[e], own[e], false, false);
+                            first[e] = r[0];
+                            second[e] = r[1];
+                        }
+#pragma unroll
+                        for (int p = 0; p < 4; ++p) {
+                            const float4 f = *reinterpret_cast<const float4*>(hr + ks * 16 + 4 * p);
+                            const uint32_t wa = p < 2 ? first[2 * p] : second[2 * p - 4], wb = p < 2 ? first[2 * p + 1] : second[2 * p - 3];
+                            yc = __builtin_fmaf(__uint_as_float(wa << 16), f.x, yc);
+                            yc = __builtin_fmaf(__uint_as_float(wa & 0xffff0000u), f.y, yc);
+                            yc = __builtin_fmaf(__uint_as_float(wb << 16), f.z, yc);
+                            yc = __builtin_fmaf(__uint_as_float(wb & 0xffff0000u), f.w, yc);
+                        }
+                    }
+                    if (open) {
+                        const uint32_t bit = 1u << c;
+                        if (((m.codes[wave][t] & bit) != 0) != (yc > 0.0f)) atomicXor(&m.codes[wave][t], bit);
+                        open &= open - 1;
+                    }
+                }
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                if (lane < rows) a.codes[xhead * a.code_head_stride + (a.code_row0 + r0 + lane) * a.W + word] = m.codes[wave][lane];
+            }
+        }
+        __syncthreads();   // LDS may be written again
+    }
+    if constexpr (AUDIT) {
+        const uint32_t outputs = wave_sum(au_outputs), listed = wave_sum(au_listed), wrong = wave_sum(au_wrong);
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) au_ratio = fmaxf(au_ratio, __shfl_xor(au_ratio, off));
+        if (lane == 0) {
+            atomicAdd(&a.audit->outputs, static_cast<unsigned long long>(outputs));
+            if (listed) atomicAdd(&a.audit->listed, static_cast<unsigned long long>(listed));
+            if (wrong) atomicAdd(&a.audit->wrong, static_cast<unsigned long long>(wrong));
+            atomicMax(&a.audit->max_ratio_bits, __float_as_uint(au_ratio));   // non-negative floats order like their bits
+        }
+    }
+}
+
+// ------------------------------------------------------------------------------------------------
+// The linear hash sign(xR) with bfloat16 weights, certified as above (eps with 128 in place of hidden).
+//
+// With nothing in front of it the contraction needs no binary32 matrix instruction at all: bfloat16
+// vectors enter the matrix cores as they are, binary32 ones as hi + lo.  A wavefront keeps the weights
+// of up to four code words in registers and streams tiles of 32 vectors from LDS, already in operand
+// order, double-buffered with one barrier a tile.  What is left is the vector work of the signs (about
+// six instructions for 64 outputs): 65536 x 8 vectors of 512 bits went from 983 us on the vector ALU
+// (728 us on the binary32 matrix instruction).
+constexpr int kLinearWords = 16;      // code words of a workgroup, four a wavefront
+constexpr int kLinearList = 256;      // open outputs of a wavefront and tile (of 32 x 128)
+constexpr int kLinearStage = 256;     // rows of R on their way into registers at a time
+
+template <typename XT> struct LinearLds {
+    static constexpr int kPasses = sizeof(XT) == 2 ? 1 : 2;     // hi, or hi and lo
+    uint4 x[2][kPasses][16 * kTile];                            // [chunk of 8 k][vector, exclusive-or with the chunk]
+    float hn[2][kTile];                                         // ||x_t||
+    uint32_t codes[2][kTile][kLinearWords];
+    uint16_t list[4][kLinearList];
+    uint4 pad;                                                  // the staging of R may run over the end of the rest
+};
+
+// Sum over the 16 lanes of a row, in every lane: rotations, no LDS.
+__device__ __forceinline__ float add_across_16(float x)
+{
+    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x128, 0xf, 0xf, true));  // row_ror:8
+    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x124, 0xf, 0xf, true));  // row_ror:4
+    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x122, 0xf, 0xf, true));  // row_ror:2
+    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x121, 0xf, 0xf, true));  // row_ror:1
+    return x;
+}
+
+// NB: code words of a wavefront
+template <typename XT, int NB, bool AUDIT>
+__global__ __launch_bounds__(kThreads, 2) void hash_linear_kernel(HashArgs a, float eps, int tiles_per_group)
+{
+    using WT = bf16_raw;
+    constexpr int TK = kTile, NT = kThreads, CH = kHeadDim / 8;
+    constexpr int PASSES = LinearLds<XT>::kPasses;
+    extern __shared__ __align__(16) float lds[];
+    LinearLds<XT>& m = *reinterpret_cast<LinearLds<XT>*>(lds);
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c = lane & 31, half = lane >> 5;
+    const int xhead = blockIdx.y;
+    const int whead = whead_of(a, xhead);
+    const int word0 = blockIdx.z * kLinearWords, n_words = min(kLinearWords, a.W - word0);
+    const WT* r = static_cast<const WT*>(a.w1) + static_cast<int64_t>(whead) * a.L * kHeadDim;
+    const XT* xbase = static_cast<const XT*>(a.x) + xhead * a.x_head_stride + a.x_row0 * kHeadDim;
+
+    // ---- R into registers by way of LDS (whole cache lines), kLinearStage rows at a time: word
+    // word0 + wave + 4 nb, the lane's output, 16 k a step and 8 of them per lane
+    uint4 wreg[NB][8];
+    for (int j0 = 0; j0 < a.L; j0 += kLinearStage) {
+        const uint4* from = reinterpret_cast<const uint4*>(r + static_cast<int64_t>(j0) * kHeadDim);
+        uint4* to = reinterpret_cast<uint4*>(lds);
+        const int rows = min(kLinearStage, a.L - j0), n = rows * CH;
+        for (int e0 = tid; e0 < n; e0 += NT * 8) {
+            uint4 v[8];
+#pragma unroll
+            for (int p = 0; p < 8; ++p) v[p] = from[min(e0 + p * NT, n - 1)];
+#pragma unroll
+            for (int p = 0; p < 8; ++p) {
+                const int e = e0 + p * NT;
+                if (e < n) to[e / CH * (CH + 1) + e % CH] = v[p];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            const int j = (31 - c) * a.W + word0 + min(wave + 4 * nb, n_words - 1) - j0;
+            if (j >= 0 && j < rows) {
+#pragma unroll
+                for (int ks = 0; ks < 8; ++ks) wreg[nb][ks] = reinterpret_cast<const uint4*>(lds)[j * (CH + 1) + 2 * ks + half];
+            }
+        }
+        __syncthreads();
+    }
+    float tcol[NB];   // eps ||R_j||
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        float s = 0.0f;
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) {
+            const uint32_t d[4] = {wreg[nb][ks].x, wreg[nb][ks].y, wreg[nb][ks].z, wreg[nb][ks].w};
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+                const float lo = __uint_as_float(d[p] << 16), hi = __uint_as_float(d[p] & 0xffff0000u);
+                s = __builtin_fmaf(hi, hi, __builtin_fmaf(lo, lo, s));
+            }
+        }
+        tcol[nb] = eps * norm_of(s + __shfl_xor(s, 32));
+    }
+
+    uint32_t au_outputs = 0, au_listed = 0, au_wrong = 0;   // this lane's audit totals
+    float au_ratio = 0.0f;
+
+    const int64_t n_tiles = (a.n_rows + TK - 1) / TK;
+    const int64_t tile0 = static_cast<int64_t>(blockIdx.x) * tiles_per_group;
+    const int64_t tile1 = min(n_tiles, tile0 + tiles_per_group);
+
+    // 16 neighbouring threads have one vector, 8 elements each
+    constexpr int XPT = TK * CH / NT;
+    Raw8<XT> xr[XPT];
+    auto fetch_x = [&](int64_t tile) {
+#pragma unroll
+        for (int i = 0; i < XPT; ++i) {
+            const int e = tid + i * NT;
+            const int64_t row = min(tile * TK + e / CH, a.n_rows - 1);   // rows past the end: a stand-in, never stored
+            load_raw(xbase + row * kHeadDim + (e % CH) * 8, xr[i]);
+        }
+    };
+    auto put_x = [&](int buf) {
+#pragma unroll
+        for (int i = 0; i < XPT; ++i) {
+            const int e = tid + i * NT, t = e / CH, k8 = e % CH, at = k8 * TK + (t ^ k8);
+            float v[8];
+            expand(xr[i], v);
+            if constexpr (PASSES == 1) {
+                m.x[buf][0][at] = xr[i].u;
+            } else {
+                bf16x8_t hi, lo;
+                split8(v, hi, lo);
+                m.x[buf][0][at] = __builtin_bit_cast(uint4, hi);
+                m.x[buf][PASSES - 1][at] = __builtin_bit_cast(uint4, lo);
+            }
+            float s = 0.0f;
+#pragma unroll
+            for (int q = 0; q < 8; ++q) s = __builtin_fmaf(v[q], v[q], s);
+            s = add_across_16(s);
+            if (k8 == 0) m.hn[buf][t] = norm_of(s);
+        }
+    };
+    // the chain of output row j for vector `row`, from the arrays as stored
+    auto chain = [&](int64_t row, int j) {
+        const XT* xp = xbase + row * kHeadDim;
+        const WT* rp = r + static_cast<int64_t>(j) * kHeadDim;
+        float y = 0.0f;
+#pragma unroll 1
+        for (int g0 = 0; g0 < CH; g0 += 4) {
+            Raw8<XT> xv[4];
+            Raw8<WT> wv[4];
+#pragma unroll
+            for (int p = 0; p < 4; ++p) { load_raw(xp + (g0 + p) * 8, xv[p]); load_raw(rp + (g0 + p) * 8, wv[p]); }
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+                float xf[8], wf[8];
+                expand(xv[p], xf);
+                expand(wv[p], wf);
+#pragma unroll
+                for (int q = 0; q < 8; ++q) y = __builtin_fmaf(wf[q], xf[q], y);
+            }
+        }
+        return y;
+    };
+
+    fetch_x(tile0);
+    put_x(0);
+    if (tile0 + 1 < tile1) fetch_x(tile0 + 1);
+    __syncthreads();
+    for (int64_t tile = tile0; tile < tile1; ++tile) {
+        const int buf = static_cast<int>(tile - tile0) & 1;
+        const int64_t r0 = tile * TK;
+        const int rows = static_cast<int>(min(static_cast<int64_t>(TK), a.n_rows - r0));
+        if (tile + 1 < tile1) put_x(buf ^ 1);
+        if (tile + 2 < tile1) fetch_x(tile + 2);
+
+        float hn[16];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const float4 f = *reinterpret_cast<const float4*>(&m.hn[buf][8 * q + 4 * half]);
+            hn[4 * q] = f.x; hn[4 * q + 1] = f.y; hn[4 * q + 2] = f.z; hn[4 * q + 3] = f.w;
+        }
+        // ---- signs, packed by ballots, and the wavefront's list of outputs too close to zero to trust
+        uint32_t listed = 0;
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            const int w = wave + 4 * nb;
+            if (w >= n_words) continue;   // uniform over the wavefront
+            f32x16_t y;                   // one word at a time: four side by side would spill, and the vector unit is what is busy
+#pragma unroll
+            for (int v = 0; v < 16; ++v) y[v] = 0.0f;
+#pragma unroll
+            for (int ks = 0; ks < 8; ++ks)
+#pragma unroll
+                for (int p = 0; p < PASSES; ++p) {
+                    const int k8 = 2 * ks + half;
+                    const uint4 x = m.x[buf][p][k8 * TK + (c ^ k8)];
+                    y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, x), __builtin_bit_cast(bf16x8_t, wreg[nb][ks]), y, 0, 0, 0);
+                }
+            if constexpr (AUDIT) {
+#pragma unroll 1
+                for (int v = 0; v < 16; ++v) {
+                    const int t = (v / 4) * 8 + half * 4 + (v % 4);
+                    if (t >= rows) continue;
+                    float yv = 0.0f, hv = 0.0f;
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) { yv = e == v ? y[e] : yv; hv = e == v ? hn[e] : hv; }
+                    const float yc = chain(r0 + t, (31 - c) * a.W + word0 + w);
+                    const bool sure = __builtin_fabsf(yv) > __builtin_fmaf(tcol[nb], hv, 1e-30f);
+                    const float den = tcol[nb] / eps * hv, diff = __builtin_fabsf(yv - yc);
+                    // a NaN or an infinity on either side is never settled and is not a distance
+                    const float ratio = (diff == 0.0f || !(diff < INFINITY)) ? 0.0f : (den > 0.0f ? diff / den : INFINITY);   // an infinite scale: 0
+                    au_ratio = fmaxf(au_ratio, ratio);
+                    au_outputs += 1;
+                    au_listed += sure ? 0 : 1;
+                    au_wrong += (sure && ((yv > 0.0f) != (yc > 0.0f))) ? 1 : 0;
+                }
+            }
+            unsigned long long any = 0;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int t = (v / 4) * 8 + half * 4 + (v % 4);
+                const unsigned long long pos = __ballot(y[v] > 0.0f);
+                any |= __ballot(!(__builtin_fabsf(y[v]) > __builtin_fmaf(tcol[nb], hn[v], 1e-30f)));   // NaN is never sure
+                if (c == 0) m.codes[buf][t][w] = half ? static_cast<uint32_t>(pos >> 32) : static_cast<uint32_t>(pos);
+            }
+            if (any) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int t = (v / 4) * 8 + half * 4 + (v % 4);
+                    const bool open = t < rows && !(__builtin_fabsf(y[v]) > __builtin_fmaf(tcol[nb], hn[v], 1e-30f));
+                    const unsigned long long o = __ballot(open);
+                    if (o) {
+                        const uint32_t at = listed + __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(o >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(o), 0u));
+                        if (open && at < static_cast<uint32_t>(kLinearList)) m.list[wave][at] = static_cast<uint16_t>(t | (c << 5) | (nb << 10));
+                        listed += static_cast<uint32_t>(__builtin_popcountll(o));
+                    }
+                }
+            }
+        }
+        // ---- recomputation with the chain, a lane each (of everything the wavefront has if the list overflowed)
+        if (listed) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            const bool all = listed > static_cast<uint32_t>(kLinearList);
+            const uint32_t n = all ? static_cast<uint32_t>(NB * TK * 32) : listed;
+            for (uint32_t e = lane; e < n; e += 64) {
+                const int entry = all ? static_cast<int>(e) : m.list[wave][e];
+                const int t = entry & 31, col = (entry >> 5) & 31, w = wave + 4 * (entry >> 10);
+                if (t >= rows || w >= n_words) continue;
+                const float yc = chain(r0 + t, (31 - col) * a.W + word0 + w);
+                const uint32_t bit = 1u << col;
+                if (((m.codes[buf][t][w] & bit) != 0) != (yc > 0.0f)) atomicXor(&m.codes[buf][t][w], bit);
+            }
+        }
+        __syncthreads();   // the tile's codes are final, the next tile's vectors are there
+        uint32_t* cbase = a.codes + xhead * a.code_head_stride + (a.code_row0 + r0) * a.W + word0;
+        for (int e = tid; e < rows * n_words; e += NT) cbase[static_cast<int64_t>(e / n_words) * a.W + e % n_words] = m.codes[buf][e / n_words][e % n_words];
+    }
+    if constexpr (AUDIT) {
+        const uint32_t outputs = wave_sum(au_outputs), listed = wave_sum(au_listed), wrong = wave_sum(au_wrong);
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) au_ratio = fmaxf(au_ratio, __shfl_xor(au_ratio, off));
+        if (lane == 0) {
+            atomicAdd(&a.audit->outputs, static_cast<unsigned long long>(outputs));
+            if (listed) atomicAdd(&a.audit->listed, static_cast<unsigned long long>(listed));
+            if (wrong) atomicAdd(&a.audit->wrong, static_cast<unsigned long long>(wrong));
+            atomicMax(&a.audit->max_ratio_bits, __float_as_uint(au_ratio));   // non-negative floats order like their bits
+        }
+    }
+}
+
+template <typename XT, typename WT, int NW, int NUB, int NBW, bool AUDIT>
+int launch(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int stage, size_t lds)
+{
+    auto kern = hash_bulk_kernel<XT, WT, NW, NUB, NBW, AUDIT>;
+    if (allow_dynamic_lds(ctx, reinterpret_cast<const void*>(kern), lds) != SPOTLIGHT_OK) return SPOTLIGHT_ERR_HIP;
+    const int64_t tiles = (a.n_rows + kTile - 1) / kTile;
+    // a workgroup takes a run of tiles of one head (the first layer's weights are fetched once per
+    // run), short enough that the grid still has a few thousand workgroups
+    int tpg = 16;
+    while (tpg > 1 && ((tiles + tpg - 1) / tpg) * n_xheads < 4096) tpg /= 2;
+    if constexpr (NBW > 0) {
+        constexpr int LPR = 16;
+        const int n_out = a.n_wheads * a.L;
+        hipLaunchKernelGGL(row_norm_kernel<LPR>, dim3(static_cast<unsigned>((n_out * LPR + kThreads - 1) / kThreads)), dim3(kThreads), 0,
+                           ctx->stream, static_cast<const bf16_raw*>(a.w2), a.wnorm, n_out, a.hidden);   // microseconds: not timed
+    }
+    dim3 grid(static_cast<unsigned>((tiles + tpg - 1) / tpg), static_cast<unsigned>(n_xheads));
+    StageTimer timer(ctx, stage);
+    timer.launch(kern, grid, dim3(NW * 64), lds, a, static_cast<float>(bulk_hash_eps(a.hidden)), tpg);
+    return hip_rc(hipGetLastError());
+}
+
+template <typename XT, int NW, int NUB, int WREG>
+int launch_word(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int stage)
+{
+    const size_t hp = hidden_padded(a.hidden);
+    const size_t work = sizeof(float) * (XTile<XT>::kFloats + kTile * hs_stride(a.hidden) + hp) + hp * kTile * 4 + sizeof(CertScratch<NW>);
+    const size_t stage1 = static_cast<size_t>(a.hidden) * (kHeadDim * 2 + 16), stage2 = static_cast<size_t>(a.L) * (a.hidden * 2 + 16);
+    const size_t lds = work > stage1 ? (work > stage2 ? work : stage2) : (stage1 > stage2 ? stage1 : stage2);
+    auto kern = hash_cert_kernel<XT, NW, NUB, WREG, false>;
+    if (a.audit) kern = hash_cert_kernel<XT, NW, NUB, WREG, true>;
+    if (allow_dynamic_lds(ctx, reinterpret_cast<const void*>(kern), lds) != SPOTLIGHT_OK) return SPOTLIGHT_ERR_HIP;
+    const int64_t tiles = (a.n_rows + kTile - 1) / kTile;
+    int tpg = 16;
+    while (tpg > 1 && ((tiles + tpg - 1) / tpg) * n_xheads < 2048) tpg /= 2;
+    dim3 grid(static_cast<unsigned>((tiles + tpg - 1) / tpg), static_cast<unsigned>(n_xheads));
+    StageTimer timer(ctx, stage);
+    timer.launch(kern, grid, dim3(NW * 64), lds, a, static_cast<float>(bulk_hash_eps(a.hidden)), tpg);
+    return hip_rc(hipGetLastError());
+}
+
+template <typename XT, int NB>
+int launch_linear(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int stage)
+{
+    const size_t work = sizeof(LinearLds<XT>), staged = static_cast<size_t>(a.L < kLinearStage ? a.L : kLinearStage) * (kHeadDim * 2 + 16);
+    const size_t lds = work > staged ? work : staged;
+    auto kern = hash_linear_kernel<XT, NB, false>;
+    if (a.audit) kern = hash_linear_kernel<XT, NB, true>;
+    if (allow_dynamic_lds(ctx, reinterpret_cast<const void*>(kern), lds) != SPOTLIGHT_OK) return SPOTLIGHT_ERR_HIP;
+    const int64_t tiles = (a.n_rows + kTile - 1) / kTile;
+    // a run of tiles pays for fetching R; the grid keeps two workgroups for every compute unit
+    const int groups = (a.W + kLinearWords - 1) / kLinearWords;
+    int tpg = 64;
+    while (tpg > 1 && ((tiles + tpg - 1) / tpg) * n_xheads * groups < 2 * ctx->n_cus) tpg /= 2;
+    dim3 grid(static_cast<unsigned>((tiles + tpg - 1) / tpg), static_cast<unsigned>(n_xheads), static_cast<unsigned>(groups));
+    StageTimer timer(ctx, stage);
+    timer.launch(kern, grid, dim3(kThreads), lds, a, static_cast<float>(bulk_hash_eps(kHeadDim)), tpg);
+    return hip_rc(hipGetLastError());
+}
+
+template <typename XT, int NW, int NUB, int NBW>
+int launch_cert(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int stage, size_t lds)
+{
+    if (a.audit) return launch<XT, bf16_raw, NW, NUB, NBW, true>(ctx, a, n_xheads, stage, lds);
+    return launch<XT, bf16_raw, NW, NUB, NBW, false>(ctx, a, n_xheads, stage, lds);
+}
+
+inline size_t lds_bytes(size_t x_size, int hidden) { return kTile * (x_size * kHeadDim + sizeof(float) * static_cast<size_t>(hidden_padded(hidden))); }
+
+}  // namespace bulk
+
+// Whether the matrix-core kernels serve this job: enough vectors, and the activations of a tile fit in
+// LDS (hidden widths up to 1152, or 1216 with bfloat16 vectors).
+inline bool bulk_hash_applies(const spotlight_ctx* ctx, const hashdev::HashArgs& a, int n_xheads, size_t x_size)
+{
+    // From how many vectors per head: below, the vector-ALU kernel's tiles of 8 do less work for padding.
+    // Measured for 8 / 512 heads of a 128 -> 256 -> 128 network: 8 rows 26 against 23 and 28 against 31 us,
+    // 9 rows 26 against 23 and 34 against 31 us, 17 rows 26 against 23 and 48 against 32 us; 128 -> 512 -> 256:
+    // 9 rows 53 against 48 and 70 against 75 us; linear, 512 bits: 31 rows 19 against 20 us, 100 rows 40 against 20 us.
+    const int min_rows = a.hidden == 0 ? bulk::kTile : n_xheads > ctx->n_cus ? 17 : 9;
+    return a.wnorm && a.n_rows >= min_rows && bulk::lds_bytes(x_size, a.hidden) <= static_cast<size_t>(ctx->max_lds);
+}
+
+template <typename XT, typename WT>
+int run_bulk_hash(spotlight_ctx* ctx, const hashdev::HashArgs& a, int n_xheads, int stage)
+{
+    using namespace bulk;
+    const size_t lds = lds_bytes(sizeof(XT), a.hidden);
+    const int nub = hidden_padded(a.hidden) / 32;
+    if constexpr (sizeof(WT) == 2) {
+        if (nub == 0) {
+            if (a.W <= 4) return launch_linear<XT, 1>(ctx, a, n_xheads, stage);
+            if (a.W <= 8) return launch_linear<XT, 2>(ctx, a, n_xheads, stage);
+            return launch_linear<XT, 4>(ctx, a, n_xheads, stage);
+        }
+        if (a.hidden % 16 == 0 && a.W <= 4 && nub <= 4) return launch_word<XT, 4, 1, 8>(ctx, a, n_xheads, stage);
+        if (a.hidden % 16 == 0 && a.W <= 4 && nub <= 8) return launch_word<XT, 4, 2, 16>(ctx, a, n_xheads, stage);
+        if (a.hidden % 16 == 0 && a.W <= 16 && nub <= 32) {
+            if (nub <= 4) {
+                if (a.W <= 8) return launch_cert<XT, 4, 1, 2>(ctx, a, n_xheads, stage, lds);
+                return launch_cert<XT, 4, 1, 4>(ctx, a, n_xheads, stage, lds);
+            }
+            if (nub <= 8) {
+                if (a.W <= 8) return launch_cert<XT, 4, 2, 2>(ctx, a, n_xheads, stage, lds);
+                return launch_cert<XT, 4, 2, 4>(ctx, a, n_xheads, stage, lds);
+            }
+            // wide hidden layers: eight wavefronts, because LDS holds only one or two workgroups
+            if (nub <= 16) {
+                if (a.W <= 8) return launch_cert<XT, 8, 2, 1>(ctx, a, n_xheads, stage, lds);
+                return launch_cert<XT, 8, 2, 2>(ctx, a, n_xheads, stage, lds);
+            }
+            return launch_cert<XT, 16, 2, 1>(ctx, a, n_xheads, stage, lds);
+        }
+    }
+    if constexpr (sizeof(WT) == 4) {
+        if (nub == 0) return launch<XT, WT, 4, 0, 0, false>(ctx, a, n_xheads, stage, lds);
+    }
+    if (nub <= 4) return launch<XT, WT, 4, 1, 0, false>(ctx, a, n_xheads, stage, lds);
+    if (nub <= 8) return launch<XT, WT, 4, 2, 0, false>(ctx, a, n_xheads, stage, lds);
+    if (nub <= 16) return launch<XT, WT, 8, 2, 0, false>(ctx, a, n_xheads, stage, lds);
+    return launch<XT, WT, 8, -1, 0, false>(ctx, a, n_xheads, stage, lds);
+}
+
+}  // namespace spotlight

@@ -55,8 +55,7 @@ __device__ __forceinline__ float load1(const bf16_raw* p) { return bf16_bits_to_
 
 __device__ __forceinline__ float silu_exp(float t)
 {
-    t = (t > -87.0f) ? t : -87.0f;  // NaN goes to -87 as well
-    t = (t < 88.0f) ? t : 88.0f;
+    t = __builtin_amdgcn_fmed3f(t, -87.0f, 88.0f);  // the clamp in one instruction; NaN goes to -87, as it does by comparisons
     const float n = __builtin_rintf(t * 0x1.715476p+0f);
     float r = __builtin_fmaf(n, -0x1.62e400p-1f, t);
     r = __builtin_fmaf(n, -0x1.7f7d1cp-20f, r);
@@ -68,8 +67,7 @@ __device__ __forceinline__ float silu_exp(float t)
     p = __builtin_fmaf(p, r, 0.5f);
     p = __builtin_fmaf(p, r, 1.0f);
     p = __builtin_fmaf(p, r, 1.0f);
-    const float s = __uint_as_float(static_cast<uint32_t>(static_cast<int>(n) + 127) << 23);
-    return p * s;
+    return __builtin_amdgcn_ldexpf(p, static_cast<int>(n));   // p * 2^n: exact, n in [-126, 127] (rounded once where denormal, as the product is)
 }
 
 __device__ __forceinline__ float silu(float a)
