@@ -417,6 +417,12 @@ __device__ __forceinline__ int ctz_m(uint32_t x) { return __builtin_ctz(x); }
 __device__ __forceinline__ int ctz_m(uint64_t x) { return __builtin_ctzll(x); }
 __device__ __forceinline__ uint32_t drop_highest(uint32_t x) { return x & ~(0x80000000u >> __builtin_clz(x)); }
 __device__ __forceinline__ uint64_t drop_highest(uint64_t x) { return x & ~(0x8000000000000000ull >> __builtin_clzll(x)); }
+// lane j's mask, in every lane
+__device__ __forceinline__ uint32_t broadcast_mask(uint32_t x, int j) { return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(x), j)); }
+__device__ __forceinline__ uint64_t broadcast_mask(uint64_t x, int j)
+{
+    return broadcast_mask(static_cast<uint32_t>(x), j) | static_cast<uint64_t>(broadcast_mask(static_cast<uint32_t>(x >> 32), j)) << 32;
+}
 // bits i of a 32-token bitmap word starting at token `first` with first + i < bound
 __device__ __forceinline__ uint32_t bits_below(uint32_t first, uint32_t bound)
 {
@@ -443,6 +449,7 @@ __global__ __launch_bounds__(THREADS) void select_kernel(
     static_assert(NW == 1 || NW == 2, "one or two wavefronts");
     static_assert(TOK == 32 || TOK == 64, "a thread's tokens fit one mask");
     using mask_t = typename TokenMask<TOK>::type;
+    constexpr uint32_t kManyTokens = 8;
     constexpr uint32_t kDenseOutput = 512;
     constexpr uint32_t kDenseChunk = 1024;
     __shared__ uint32_t s_T, s_r;
@@ -648,9 +655,21 @@ __global__ __launch_bounds__(THREADS) void select_kernel(
     }
     int32_t* op = out_idx + bh * k;
     if (n_sel <= kDenseOutput) {
-        // the usual case, a few dozen tokens per block: every thread writes its own
+        // the usual case, a few dozen tokens per block: every thread writes its own, unless it has many
+        // (a local window fills a thread's tokens whole): those are written by the wavefront, a lane
+        // a token.  16 x 32 heads, 128K tokens, local window of 64: one thread writing 64 tokens made
+        // the kernel take 34.5 us, this way 17.1 (16.8 with a window of one).
         pos += local;
         const int32_t tok0 = static_cast<int32_t>(t_begin) + tid * TOK;
+        for (unsigned long long many = __ballot(cnt > kManyTokens); many; many &= many - 1) {
+            const int j = __builtin_ctzll(many);
+            const mask_t mj = broadcast_mask(sel, j);
+            const uint32_t at = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(pos), j)) +
+                                popc_m(static_cast<mask_t>(mj & ((static_cast<mask_t>(1) << (lane % TOK)) - 1)));
+            if (lane < TOK && ((mj >> (lane % TOK)) & 1) && at < static_cast<uint32_t>(k))
+                op[at] = static_cast<int32_t>(t_begin) + (wave * 64 + j) * TOK + lane;
+            if (lane == j) sel = 0;
+        }
         while (sel) {
             const int bit = ctz_m(sel);
             sel &= sel - 1;
