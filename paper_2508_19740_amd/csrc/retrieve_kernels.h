@@ -5,14 +5,14 @@
 //
 //   score   one workgroup per (batch, key-value head, block of 4096 tokens) reads the packed key
 //           codes of its block, XORs them with the G query codes of the group and popcounts; the
-//           16 distances of each thread stay in registers.  The block counts them in an LDS
+//           distances of each thread (4, 8 or 16 keys) stay in registers.  The block counts them in an LDS
 //           histogram (replicated over lanes so that same-address atomics stay apart), turns it
 //           into a cumulative histogram and adds it to a running one that covers the blocks of
 //           the head the workgroup has counted so far (its "run" of consecutive blocks).  The
 //           running histogram is stored per block, and once per run added to the cumulative
 //           histogram of the head (integer atomics).  It then keeps a short list of CANDIDATES:
 //           the tokens up to a block-local distance bound chosen so that about twice the block's
-//           fair share of k qualifies (one sub-list per wavefront).  Nothing else is written per
+//           fair share of k qualifies (four sub-lists).  Nothing else is written per
 //           token.  Workgroups are persistent and fetch the next keys before finishing a block.
 //   select  one workgroup per (query head, block).  The head's cumulative histogram gives the
 //           exact threshold T with count(d < T) < k <= count(d <= T) and r = k - count(d < T),
@@ -46,9 +46,10 @@ namespace spotlight {
 namespace retrieve_detail {
 
 constexpr int kTPB = kTokensPerBlock;       // tokens per workgroup
-constexpr int kKPT = kTPB / kThreads;       // keys per thread (16)
 
-constexpr int kWaveCap = kCandCap / (kThreads / 64);  // entries of one wavefront's candidate sub-list (256)
+constexpr int kSubLists = 4;                // candidate sub-lists per block (one per wavefront of a 256-thread workgroup)
+constexpr int kWaveCap = kCandCap / kSubLists;        // entries of one sub-list (256)
+constexpr int kWideThreads = 1024;          // threads of a score workgroup where the grid is small
 constexpr int kWaveFull = 255;              // count value meaning "this sub-list overflowed"
 constexpr int kLongRun = 16;                // blocks per resident workgroup from which runs are cut short
 constexpr int kShortRun = 4;
@@ -59,7 +60,7 @@ constexpr int kShortRun = 4;
 constexpr int kBoundBits = 11;   // bins go up to 32 * 32 + 1
 struct BlockMeta {
     uint32_t bound_run;
-    uint8_t count[kThreads / 64];
+    uint8_t count[kSubLists];
 };
 static_assert(sizeof(BlockMeta) == 8, "workspace layout");
 
@@ -119,27 +120,44 @@ struct ScoreArgs {
 // heads per group: 4 waves measured 4 % faster than 3; 512-bit codes: 167 or 256 registers).
 constexpr int score_min_waves(int W, int G) { return (W == 8 && G == 4) ? 4 : (W == 16 && G <= 4) ? 3 : 1; }
 
+// Threads of a score workgroup.  The distances of a thread's keys stay in registers, a register for two
+// keys and each head, and the epilogue walks the heads one after another: with several heads per group
+// 256 threads of 16 keys need up to 256 registers (two wavefronts per SIMD) and a long chain per block.
+// 512 threads of 8 keys: groups of 8, 512 bits, 2 x 8 x 182867 tokens 97.8 -> 83 us; groups of 8, 128
+// bits, 16 x 8 x 37099 51 -> 47 us; groups of 4, 128 bits, 2 x 8 x 101906 16.7 -> 12.7 us; groups of 2,
+// 128 bits, 2 x 16 x 40338 10.2 -> 8.4 us.  Groups of 4 with 256 bits keep 256 (their registers just
+// fit four wavefronts: 115 us for 16 x 8 x 131072 against 124), as do groups of 2 otherwise (64 bits,
+// 303594 x 16: 14.7 against 17 us) and single heads, which stream keys two batches ahead.
+constexpr int score_threads(int W, int G) { return G >= 5 || (G >= 3 && W != 8) || (G == 2 && W == 4) ? 512 : kThreads; }
+
 // Persistent workgroups.  A task is one (batch * kv head, token block); a workgroup takes
 // tasks_per_group CONSECUTIVE tasks, which mostly belong to one head, and keeps that head's
 // cumulative histogram in LDS across them, so the (slow, device-wide) atomics into the head's
 // global histogram happen once per run of tasks instead of once per block.
-template <int W, int G, int R>
-__global__ __launch_bounds__(kThreads, score_min_waves(W, G)) void score_kernel(ScoreArgs a)
+//
+// T: threads of a workgroup (score_threads, or 1024 for small grids).
+template <int W, int G, int R, int T>
+__global__ __launch_bounds__(T, T == kThreads ? score_min_waves(W, G) : 4) void score_kernel(ScoreArgs a)
 {
+    constexpr int KPT = kTPB / T;          // keys per thread
+    constexpr int NREG = KPT / 2;          // registers of distances per head, two keys each
+    constexpr int WAVES = T / 64, WPL = WAVES / kSubLists;   // wavefronts, and how many share a candidate sub-list
     constexpr int L = W * 32;
     constexpr int BINS = L + 2;            // bin 0: forced tokens; bin d + 1: distance d
     constexpr int CH = (BINS + 63) / 64;   // bins per lane in the scan
     // lanes per key: 16 bytes per lane when the code is 16, 32, 64 or 128 bytes, else one lane per key
     constexpr int LPK = (W == 4 || W == 8 || W == 16 || W == 32) ? W / 4 : 1;
     constexpr int CWL = W / LPK;           // code words per lane
-    constexpr int SLOTS = kKPT * LPK;      // load instructions per thread and task
-    constexpr int KPS = kThreads / LPK;    // keys per slot
-    constexpr int KB = CWL <= 4 ? 4 : (CWL <= 8 ? 2 : 1);  // slots per batch of loads
+    constexpr int SLOTS = KPT * LPK;      // load instructions per thread and task
+    constexpr int KPS = T / LPK;           // keys per slot
+    constexpr int KBMAX = CWL <= 4 ? 4 : (CWL <= 8 ? 2 : 1);
+    constexpr int KB = KBMAX < SLOTS / 2 ? KBMAX : SLOTS / 2;   // slots per batch of loads
     __shared__ uint32_t hist[G * BINS * R];
     __shared__ uint32_t cum[G * BINS];     // this block's histogram, then its cumulative form
     __shared__ uint32_t gacc[G * BINS];    // cumulative histogram summed over this run of tasks
     __shared__ uint32_t s_thi[G];
-    __shared__ uint32_t escr[kThreads / 64][kKPT / 2][64];   // per-lane copy of one head's packed distances
+    __shared__ uint32_t s_listed[WPL > 1 ? G : 1][kSubLists];   // more wavefronts than sub-lists: the sub-lists' lengths so far
+    __shared__ uint32_t escr[WAVES][NREG][64];   // per-lane copy of one head's packed distances
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int rep = (tid / LPK) & (R - 1);   // the lanes of one key never record the same slot
@@ -147,8 +165,10 @@ __global__ __launch_bounds__(kThreads, score_min_waves(W, G)) void score_kernel(
     const uint32_t lane_off = static_cast<uint32_t>(tid) * (CWL * 4);
     const int sub = tid % LPK, kq = tid / LPK;   // part of the key this lane reads, key within a slot
 
-    for (int i = tid; i < G * BINS * R; i += kThreads) hist[i] = 0;
-    for (int i = tid; i < G * BINS; i += kThreads) gacc[i] = 0;
+    for (int i = tid; i < G * BINS * R; i += T) hist[i] = 0;
+    for (int i = tid; i < G * BINS; i += T) gacc[i] = 0;
+    if constexpr (WPL > 1)
+        for (int i = tid; i < G * kSubLists; i += T) s_listed[i / kSubLists][i % kSubLists] = 0;
     __syncthreads();
 
     const int task0 = blockIdx.x * a.tasks_per_group;
@@ -172,7 +192,7 @@ __global__ __launch_bounds__(kThreads, score_min_waves(W, G)) void score_kernel(
         for (int u = 0; u < KB; ++u) {
             const int sl = bt * KB + u;
             if (decltype(full)::value || sl * KPS + kq < n_blk)
-                load_key<CWL>(base + static_cast<size_t>(sl) * (kThreads * CWL * 4), lane_off, dst[u]);
+                load_key<CWL>(base + static_cast<size_t>(sl) * (T * CWL * 4), lane_off, dst[u]);
         }
     };
     if (AHEAD && task0 < task1) fetch(std::false_type{}, task0, 0, buf[0]);
@@ -208,7 +228,7 @@ __global__ __launch_bounds__(kThreads, score_min_waves(W, G)) void score_kernel(
         if (has_forced) {
             const char* blk_base = reinterpret_cast<const char*>(a.codes + (static_cast<int64_t>(bk) * a.Nmax + t_begin) * W);
             auto move_to_bin0 = [&](int lo, int hi) {   // fewer than KPS tokens: at most one per thread
-                for (int off = lo + tid; off < hi; off += kThreads) {
+                for (int off = lo + tid; off < hi; off += T) {
                     constexpr int CHUNK = W % 4 == 0 ? 4 : 1;   // words per load
                     uint32_t d[G];
 #pragma unroll
@@ -233,12 +253,12 @@ __global__ __launch_bounds__(kThreads, score_min_waves(W, G)) void score_kernel(
             move_to_bin0(local_off, min(n_blk, local_slot * KPS));
         }
 
-        // distances of the 16 keys this lane owns, two per register
-        uint32_t dv[G][kKPT / 2];
+        // distances of the keys this lane owns, two per register
+        uint32_t dv[G][NREG];
 #pragma unroll
         for (int g = 0; g < G; ++g)
 #pragma unroll
-            for (int i = 0; i < kKPT / 2; ++i) dv[g][i] = 0x7fff7fffu;   // absent keys: farther than any bound
+            for (int i = 0; i < NREG; ++i) dv[g][i] = 0x7fff7fffu;   // absent keys: farther than any bound
 
         // A "slot" is one load instruction of the workgroup: KPS = 256 / LPK keys, LPK adjacent lanes
         // per key, 16 bytes per lane (fully coalesced).  The partial distances of a key are added
@@ -293,14 +313,14 @@ __global__ __launch_bounds__(kThreads, score_min_waves(W, G)) void score_kernel(
         __syncthreads();
 
         // fold the replicas (rotated so that neighbouring threads hit different banks)
-        for (int i = tid; i < G * BINS; i += kThreads) {
+        for (int i = tid; i < G * BINS; i += T) {
             uint32_t s = 0;
 #pragma unroll
             for (int r = 0; r < R; ++r) s += hist[i * R + ((r + i) & (R - 1))];
             cum[i] = s;
         }
         __syncthreads();
-        for (int i = tid; i < G * BINS * R; i += kThreads) hist[i] = 0;  // ready for the next task
+        for (int i = tid; i < G * BINS * R; i += T) hist[i] = 0;  // ready for the next task
 
         // cumulative histogram per head (one wave per head), and the block-local candidate bound:
         // the first bin at which about twice the block's fair share of k (plus a little) is reached,
@@ -308,7 +328,7 @@ __global__ __launch_bounds__(kThreads, score_min_waves(W, G)) void score_kernel(
         // forced tokens by position and needs no candidates for them)
         const uint32_t want = static_cast<uint32_t>(min(static_cast<int64_t>(n_blk),
             (static_cast<int64_t>(n_blk) * a.k * 2 + a.n_tokens - 1) / a.n_tokens + 32));
-        for (int g = wave; g < G; g += kThreads / 64) {
+        for (int g = wave; g < G; g += WAVES) {
             uint32_t v[CH];
             uint32_t tot = 0;
 #pragma unroll
@@ -341,7 +361,7 @@ __global__ __launch_bounds__(kThreads, score_min_waves(W, G)) void score_kernel(
         // instead of summing over every block in front), and, at the end of a run, the same
         // numbers into the head's global histogram
         const bool flush = task + 1 == task1 || (task + 1) / a.nblk != bk;
-        for (int i = tid; i < G * BINS; i += kThreads) {
+        for (int i = tid; i < G * BINS; i += T) {
             const int g = i / BINS, bin = i % BINS;
             const uint32_t v = gacc[i];
             a.blockcum[((bh0 + g) * a.max_blocks + blk) * BINS + bin] = v;
@@ -351,50 +371,110 @@ __global__ __launch_bounds__(kThreads, score_min_waves(W, G)) void score_kernel(
             }
         }
 
-        // Candidate lists, one sub-list per wavefront, in any fixed order.  Few keys qualify (a few
+        // Candidate lists, a sub-list per wavefront (see below for wider workgroups), in any order.  Few keys qualify (a few
         // per cent), so the work is arranged per qualifying key, not per key: a packed 16-bit
         // subtraction per register marks the keys below the bound in a per-lane bit mask, a wave scan
         // of the mask populations gives every lane its place in the sub-list, and the lanes then
         // write their keys one per round (the longest mask of the wave sets the number of rounds).
         // The distance of the key a round picks comes back from a per-lane copy of the registers in
         // LDS, since registers cannot be indexed per lane.
+        //
+        // With more wavefronts than sub-lists, WPL of them share one: each adds its number to the
+        // sub-list's counter in LDS and continues where that stood (the order in a sub-list is free).
         typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
         typedef uint16_t __attribute__((may_alias)) u16_view;   // halves of the 32-bit words written below
-        static_assert(kKPT == 16, "the bit layout of the mask assumes eight registers of two keys");
+        static_assert(KPT <= 16 && KPT % 2 == 0, "the bit layout of the mask assumes at most eight registers of two keys");
+        if constexpr (WPL == 1) {
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-            const uint32_t thi = __builtin_amdgcn_readfirstlane(s_thi[g]);   // a bin: bound on distance + 1
-            const int64_t slot = (bh0 + g) * a.max_blocks + blk;
-            uint32_t* cl = a.cand + (slot * (kThreads / 64) + wave) * kWaveCap;
-            const u16x2 thi2 = __builtin_bit_cast(u16x2, thi | (thi << 16));
-            uint32_t q = 0;   // bit 7 - r: low key of register r qualifies; bit 23 - r: high key
+            for (int g = 0; g < G; ++g) {
+                const uint32_t thi = __builtin_amdgcn_readfirstlane(s_thi[g]);   // a bin: bound on distance + 1
+                const int64_t slot = (bh0 + g) * a.max_blocks + blk;
+                uint32_t* cl = a.cand + (slot * kSubLists + wave) * kWaveCap;
+                const u16x2 thi2 = __builtin_bit_cast(u16x2, thi | (thi << 16));
+                uint32_t q = 0;   // bit NREG - 1 - r: low key of register r qualifies; bit NREG + 15 - r: high key
 #pragma unroll
-            for (int r = 0; r < kKPT / 2; ++r) {
-                // d - thi in 16 bits: bit 15 set exactly when d < thi (d <= 0x7fff, thi <= L + 1)
-                const uint32_t t = __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2, dv[g][r]) - thi2);
-                q = (q << 1) | ((t >> 15) & 0x00010001u);
-                escr[wave][r][lane] = dv[g][r];
-            }
-            const uint32_t mine = popc(q);
-            const uint32_t incl = wave_inclusive_scan(mine);
-            const uint32_t total = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(incl), 63));
-            uint32_t at = incl - mine;
-            while (__ballot(q != 0)) {
-                if (q) {
-                    const int bit = __builtin_ctz(q);
-                    q &= q - 1;
-                    const int r = 7 - (bit & 15), half = bit >> 4;
-                    const uint32_t d = reinterpret_cast<const u16_view*>(&escr[wave][r][lane])[half];
-                    const int j = 2 * r + half;   // index among the keys this lane owns
-                    if (at < static_cast<uint32_t>(kWaveCap))
-                        cl[at] = (d << 16) + (0x10000u | static_cast<uint32_t>((j * LPK + sub) * KPS + kq));   // bin << 16 | offset
-                    ++at;
+                for (int r = 0; r < NREG; ++r) {
+                    // d - thi in 16 bits: bit 15 set exactly when d < thi (d <= 0x7fff, thi <= L + 1)
+                    const uint32_t t = __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2, dv[g][r]) - thi2);
+                    q = (q << 1) | ((t >> 15) & 0x00010001u);
+                    escr[wave][r][lane] = dv[g][r];
+                }
+                const uint32_t mine = popc(q);
+                const uint32_t incl = wave_inclusive_scan(mine);
+                const uint32_t total = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(incl), 63));
+                uint32_t at = incl - mine;
+                while (__ballot(q != 0)) {
+                    if (q) {
+                        const int bit = __builtin_ctz(q);
+                        q &= q - 1;
+                        const int r = NREG - 1 - (bit & 15), half = bit >> 4;
+                        const uint32_t d = reinterpret_cast<const u16_view*>(&escr[wave][r][lane])[half];
+                        const int j = 2 * r + half;   // index among the keys this lane owns
+                        if (at < static_cast<uint32_t>(kWaveCap))
+                            cl[at] = (d << 16) + (0x10000u | static_cast<uint32_t>((j * LPK + sub) * KPS + kq));   // bin << 16 | offset
+                        ++at;
+                    }
+                }
+                if (lane == 0) {
+                    BlockMeta* bm = a.blockmeta + slot;
+                    bm->count[wave] = total < static_cast<uint32_t>(kWaveFull) ? static_cast<uint8_t>(total) : static_cast<uint8_t>(kWaveFull);
+                    if (wave == 0) bm->bound_run = thi | (static_cast<uint32_t>(run_begin) << kBoundBits);
                 }
             }
-            if (lane == 0) {
-                BlockMeta* bm = a.blockmeta + slot;
-                bm->count[wave] = total < static_cast<uint32_t>(kWaveFull) ? static_cast<uint8_t>(total) : static_cast<uint8_t>(kWaveFull);
-                if (wave == 0) bm->bound_run = thi | (static_cast<uint32_t>(run_begin) << kBoundBits);
+        } else {
+            uint32_t qg[G], atg[G];
+            auto mark = [&](int g, uint32_t& at, uint32_t& total) {   // the mask of this lane, its place, the wavefront's number
+                const uint32_t thi = __builtin_amdgcn_readfirstlane(s_thi[g]);   // a bin: bound on distance + 1
+                const u16x2 thi2 = __builtin_bit_cast(u16x2, thi | (thi << 16));
+                uint32_t q = 0;   // bit NREG - 1 - r: low key of register r qualifies; bit NREG + 15 - r: high key
+#pragma unroll
+                for (int r = 0; r < NREG; ++r) {
+                    // d - thi in 16 bits: bit 15 set exactly when d < thi (d <= 0x7fff, thi <= L + 1)
+                    const uint32_t t = __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2, dv[g][r]) - thi2);
+                    q = (q << 1) | ((t >> 15) & 0x00010001u);
+                }
+                const uint32_t mine = popc(q);
+                const uint32_t incl = wave_inclusive_scan(mine);
+                total = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(incl), 63));
+                at = incl - mine;
+                return q;
+            };
+            auto emit = [&](int g, uint32_t q, uint32_t at) {
+                const int64_t slot = (bh0 + g) * a.max_blocks + blk;
+                uint32_t* cl = a.cand + (slot * kSubLists + wave / WPL) * kWaveCap;
+#pragma unroll
+                for (int r = 0; r < NREG; ++r) escr[wave][r][lane] = dv[g][r];
+                while (__ballot(q != 0)) {
+                    if (q) {
+                        const int bit = __builtin_ctz(q);
+                        q &= q - 1;
+                        const int r = NREG - 1 - (bit & 15), half = bit >> 4;
+                        const uint32_t d = reinterpret_cast<const u16_view*>(&escr[wave][r][lane])[half];
+                        const int j = 2 * r + half;   // index among the keys this lane owns
+                        if (at < static_cast<uint32_t>(kWaveCap))
+                            cl[at] = (d << 16) + (0x10000u | static_cast<uint32_t>((j * LPK + sub) * KPS + kq));   // bin << 16 | offset
+                        ++at;
+                    }
+                }
+            };
+            auto count_of = [](uint32_t total) { return total < static_cast<uint32_t>(kWaveFull) ? static_cast<uint8_t>(total) : static_cast<uint8_t>(kWaveFull); };
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                uint32_t total;
+                qg[g] = mark(g, atg[g], total);
+                uint32_t base = 0;
+                if (lane == 0) base = atomicAdd(&s_listed[g][wave / WPL], total);
+                atg[g] += static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(base)));
+            }
+#pragma unroll
+            for (int g = 0; g < G; ++g) emit(g, qg[g], atg[g]);
+            __syncthreads();   // the counters are final
+            for (int i = tid; i < G * kSubLists; i += T) {
+                const int g = i / kSubLists, l = i % kSubLists;
+                BlockMeta* bm = a.blockmeta + (bh0 + g) * a.max_blocks + blk;
+                bm->count[l] = count_of(s_listed[g][l]);
+                if (l == 0) bm->bound_run = s_thi[g] | (static_cast<uint32_t>(run_begin) << kBoundBits);
+                s_listed[g][l] = 0;   // for the next task: its barriers come before its additions
             }
         }
         // the next task's first barrier orders these reads of cum / s_thi / gacc before their reuse
@@ -441,7 +521,7 @@ __global__ __launch_bounds__(THREADS) void select_kernel(
 {
     constexpr int BINS = W * 32 + 2;   // bin 0: forced tokens; bin d + 1: distance d
     constexpr int NW = THREADS / 64;
-    constexpr int SUB = kThreads / 64;          // candidate sub-lists per block
+    constexpr int SUB = kSubLists;              // candidate sub-lists per block
     constexpr int PER = kWaveCap / THREADS;     // sub-list entries per thread
     constexpr int WORDS = kTPB / 32;            // bitmap words of a block
     constexpr int TOK = kTPB / THREADS;         // tokens owned by a thread
@@ -738,12 +818,13 @@ int launch_score_wg(spotlight_ctx* ctx, StageTimer& timer, const RetrieveArgs& a
                     : (G * BINS * 4 * 4 <= kCap && G * BINS * 4 * 4 + kRest <= 65536) ? 4
                     : (G * BINS * 2 * 4 <= kCap && G * BINS * 2 * 4 + kRest <= 65536) ? 2 : 1;
     static_assert(G * BINS * R * 4 + kRest <= 65536, "LDS of the score kernel");
-    auto kern = score_kernel<W, G, R>;
+    constexpr int T = score_threads(W, G);
+    auto kern = score_kernel<W, G, R, T>;
     // persistent grid: as many workgroups as the chip holds at once (a context has one code length
     // and one group size, hence one score kernel: asked once per context)
     if (ctx->score_resident == 0) {
         int per_cu = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, kThreads, 0) != hipSuccess || per_cu < 1)
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, T, 0) != hipSuccess || per_cu < 1)
             return SPOTLIGHT_ERR_HIP;
         ctx->score_resident = per_cu * ctx->n_cus;
     }
@@ -765,6 +846,15 @@ int launch_score_wg(spotlight_ctx* ctx, StageTimer& timer, const RetrieveArgs& a
     s.k = a.k;
     s.total_tasks = a.nblk * p.B * p.Hkv;
     s.tasks_per_group = (s.total_tasks + resident - 1) / resident;
+    // At most one block for every compute unit: what counts is the chain of one block, and 1024 threads
+    // of 4 keys shorten it (they cost the chip its second workgroup per compute unit, which such a
+    // grid has not got).  28 heads on 4, 100003 tokens: 16.2 -> 11 us; 32 heads on 4, 4724 tokens, 512
+    // bits: 40 -> 22 us; 32 heads, 32768 tokens: 6.8 -> 6.2 us; with twice as many blocks 512 threads do better.
+    if (s.total_tasks <= ctx->n_cus) {
+        *tasks_per_group = s.tasks_per_group = 1;
+        timer.launch(score_kernel<W, G, R, kWideThreads>, dim3(static_cast<unsigned>(s.total_tasks)), dim3(kWideThreads), 0, s);
+        return SPOTLIGHT_OK;
+    }
     // Long streams (gigabytes of codes): short runs, handed out by the hardware as workgroups
     // retire, instead of one long run per resident workgroup.  The workgroups in flight then read
     // one window of memory that moves through the cache in order, and uneven progress evens out
@@ -774,7 +864,7 @@ int launch_score_wg(spotlight_ctx* ctx, StageTimer& timer, const RetrieveArgs& a
     if (s.tasks_per_group >= kLongRun) s.tasks_per_group = kShortRun;
     *tasks_per_group = s.tasks_per_group;
     const int grid = (s.total_tasks + s.tasks_per_group - 1) / s.tasks_per_group;
-    timer.launch(kern, dim3(static_cast<unsigned>(grid)), dim3(kThreads), 0, s);
+    timer.launch(kern, dim3(static_cast<unsigned>(grid)), dim3(T), 0, s);
     return SPOTLIGHT_OK;
 }
 
