@@ -54,7 +54,8 @@ enum {
     SPOTLIGHT_STAGE_SCORE = 2,      /* Hamming distances, histograms, candidate lists            */
     SPOTLIGHT_STAGE_SELECT = 3,     /* threshold, offsets, ordered output of the selected tokens */
     SPOTLIGHT_STAGE_ATTEND = 4,     /* gather + softmax attention over a split of the rows       */
-    SPOTLIGHT_STAGE_MERGE = 5,      /* merge of the splits' partial results                      */
+    SPOTLIGHT_STAGE_MERGE = 5,      /* merge of the splits' partial results; where one workgroup has a
+                                       whole head it is part of ATTEND: counted, with no time of its own */
     SPOTLIGHT_STAGE_STEP_SMALL = 6, /* the whole decode step of a short context, as one kernel   */
     SPOTLIGHT_STAGE_COUNT = 7
 };
@@ -231,7 +232,8 @@ int spotlight_sparse_decode(spotlight_ctx *ctx, const void *q, const void *K, co
  *   codes    [B, Hkv, Nmax, W]  uint32     row n_tokens-1 is written, rows 0 .. n_tokens-1 are read
  *   out_idx  [B, Hq, k]         int32      selected token indices in increasing order
  *   out      [B, Hq, d]         float32
- * The call enqueues five kernels on the context's stream (one kernel for a short context under
+ * The call enqueues five kernels on the context's stream, or four with few rows per head (one kernel
+ * for a short context under
  * SPOTLIGHT_OPT_STEP_SINGLE_LAUNCH) and nothing else (no allocation, no memset, no copy), so it can
  * be captured into a HIP graph.
  * Errors: INVALID_ARG unless 1 <= n_tokens <= Nmax, 1 <= k <= min(n_tokens, max_topk),

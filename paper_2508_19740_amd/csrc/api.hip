@@ -74,6 +74,7 @@ StageTimer::StageTimer(spotlight_ctx* c, int stage) : ctx(c), rec(nullptr)
         c->n_events = c->n_rec + 1;
     }
     r->stage = stage;
+    r->whole = false;
     rec = r;
 }
 
@@ -434,6 +435,8 @@ int spotlight_profile_read(spotlight_ctx* ctx, int stage, double* total_ms, int6
         float ms = 0.0f;
         if (hipEventElapsedTime(&ms, ctx->recs[i].start, ctx->recs[i].stop) != hipSuccess) { rc = SPOTLIGHT_ERR_HIP; continue; }
         ctx->stage_ms[ctx->recs[i].stage] += ms;
+        // an attend kernel that has whole heads does its merge itself: recorded with it, without a time of its own
+        if (ctx->recs[i].stage == SPOTLIGHT_STAGE_ATTEND && ctx->recs[i].whole) ctx->stage_launches[SPOTLIGHT_STAGE_MERGE] += 1;
         ctx->stage_launches[ctx->recs[i].stage] += 1;
     }
     ctx->n_rec = 0;

@@ -16,22 +16,23 @@ namespace spotlight {
 using namespace rows;
 namespace {
 
-// RB rows per workgroup, RB / 4 per wavefront.
-template <typename T, int RB>
-__global__ __launch_bounds__(kThreads) void attend_kernel(
+// RB rows per workgroup of NT threads, shared out evenly over its wavefronts.
+template <typename T, int RB, int NT>
+__global__ __launch_bounds__(NT) void attend_kernel(
     const T* __restrict__ q, const T* __restrict__ K, const T* __restrict__ V, const int32_t* __restrict__ idx,
-    float2* __restrict__ part_ml, float* __restrict__ part_acc, int k, float scale, int64_t Nmax, int Hq, int Hkv,
+    float2* __restrict__ part_ml, float* __restrict__ part_acc, float* __restrict__ out, int k, float scale, int64_t Nmax, int Hq, int Hkv,
     int nsplit, int max_splits)
 {
     constexpr int LPR = RowTraits<T>::kLanesPerRow;   // lanes per row
     constexpr int E = RowTraits<T>::kElems;           // elements per lane
     constexpr int RPI = 64 / LPR;                     // rows per load instruction
-    constexpr int RPW = RB / 4;                       // rows per wave
+    constexpr int NW = NT / 64;
+    constexpr int RPW = RB / NW;                      // rows per wave
     constexpr int ITERS = RPW / RPI;
     static_assert(RPW % RPI == 0 && RPW <= 64, "row tiling");
 
-    __shared__ float s_m[4], s_l[4];
-    __shared__ float s_acc[4][kHeadDim];
+    __shared__ float s_m[NW], s_l[NW];
+    __shared__ float s_acc[NW][kHeadDim];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int split = blockIdx.x;
@@ -119,17 +120,23 @@ __global__ __launch_bounds__(kThreads) void attend_kernel(
     if (lane == 0) { s_m[wave] = m; s_l[wave] = l; }
     __syncthreads();
 
-    // merge the four waves; thread c < 128 owns output column c
+    // merge the waves; thread c < 128 owns output column c
     if (tid < kHeadDim) {
-        const float M = fmaxf(fmaxf(s_m[0], s_m[1]), fmaxf(s_m[2], s_m[3]));
+        float M = s_m[0];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) M = fmaxf(M, s_m[w]);
         float a = 0.0f, lsum = 0.0f;
         if (M > -INFINITY) {
 #pragma unroll
-            for (int w = 0; w < 4; ++w) {
+            for (int w = 0; w < NW; ++w) {
                 const float f = s_m[w] > -INFINITY ? __expf(s_m[w] - M) : 0.0f;
                 a = __builtin_fmaf(f, s_acc[w][tid], a);
                 lsum = __builtin_fmaf(f, s_l[w], lsum);
             }
+        }
+        if (nsplit == 1) {   // the whole head is here
+            out[bh * kHeadDim + tid] = lsum > 0.0f ? a / lsum : 0.0f;
+            return;
         }
         const int64_t pi = bh * max_splits + split;
         part_acc[pi * kHeadDim + tid] = a;
@@ -197,17 +204,21 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(const float2* __restric
     }
 }
 
-template <typename T, int RB>
+template <typename T, int RB, int NT = kThreads>
 void launch_rb(spotlight_ctx* ctx, StageTimer& timer, const void* q, const void* K, const void* V, const int32_t* idx,
-               int k, float scale, int nsplit)
+               int k, float scale, int nsplit, float* out)
 {
     const Plan& p = ctx->plan;
     dim3 grid(static_cast<unsigned>(nsplit), static_cast<unsigned>(p.B * p.Hq));
-    timer.launch(attend_kernel<T, RB>, grid, dim3(kThreads), 0, static_cast<const T*>(q), static_cast<const T*>(K),
+    timer.launch(attend_kernel<T, RB, NT>, grid, dim3(NT), 0, static_cast<const T*>(q), static_cast<const T*>(K),
                  static_cast<const T*>(V), idx, reinterpret_cast<float2*>(ctx->workspace + p.off_part_ml),
-                 reinterpret_cast<float*>(ctx->workspace + p.off_part_acc), k, scale, p.Nmax, p.Hq, p.Hkv, nsplit,
+                 reinterpret_cast<float*>(ctx->workspace + p.off_part_acc), out, k, scale, p.Nmax, p.Hq, p.Hkv, nsplit,
                  p.max_splits);
 }
+
+constexpr int kWholeThreads = 1024;   // threads of a workgroup that takes a whole head
+constexpr int kWholeRows = 512;       // rows it takes at most, and
+constexpr int kWholeHeads = 128;      // heads from which it takes that many
 
 template <typename T>
 int launch_t(spotlight_ctx* ctx, const void* q, const void* K, const void* V, const int32_t* idx, int k,
@@ -215,15 +226,30 @@ int launch_t(spotlight_ctx* ctx, const void* q, const void* K, const void* V, co
 {
     const Plan& p = ctx->plan;
     const int64_t heads = static_cast<int64_t>(p.B) * p.Hq;
+    // Few rows per head: one workgroup of 16 wavefronts takes the head whole and writes its output, and
+    // there is nothing to merge.  Against 256-thread splits and the merge kernel, bfloat16: 1 head, 20 /
+    // 128 / 256 / 512 rows 5.1 / 5.6 / 6.0 / 6.1 -> 3.9 / 3.9 / 4.5 / 6.7 us (one compute unit then reads
+    // all rows); 32 heads 5.5 / 6.8 / 7.2 / 8.3 -> 4.0 / 5.2 / 6.0 / 8.4 us; 128 heads 6.2 / 8.2 / 10.0 /
+    // 12.0 -> 4.7 / 5.8 / 7.0 / 9.8 us; 512 heads 7.9 / 12.1 / 17.0 / 28.3 -> 6.1 / 9.1 / 14.0 / 24.5 us.
+    // Binary32 rows are twice as long: 1 head, 128 / 256 / 512 rows 5.8 / 6.1 / 6.2 -> 4.2 / 5.8 / 10.3 us,
+    // 32 heads 6.9 / 7.7 / 9.1 -> 5.6 / 8.1 / 13.2 us, 128 heads 8.9 / 11.8 / 16.6 -> 6.5 / 9.6 / 15.7 us.
+    if (k <= (sizeof(T) == 2 ? 256 : 128) || (k <= kWholeRows && heads >= kWholeHeads)) {
+        StageTimer timer(ctx, SPOTLIGHT_STAGE_ATTEND);
+        if (timer.rec) timer.rec->whole = true;
+        if (k <= 128) launch_rb<T, 128, kWholeThreads>(ctx, timer, q, K, V, idx, k, scale, 1, out);
+        else if (k <= 256) launch_rb<T, 256, kWholeThreads>(ctx, timer, q, K, V, idx, k, scale, 1, out);
+        else launch_rb<T, 512, kWholeThreads>(ctx, timer, q, K, V, idx, k, scale, 1, out);
+        return hip_rc(hipGetLastError());
+    }
     // the largest row tile that still gives the chip about four workgroups per compute unit
     int RB = 128;
     while (RB > kAttendMinRows && heads * ((k + RB - 1) / RB) < 1024) RB >>= 1;
     const int nsplit = (k + RB - 1) / RB;
     {
         StageTimer timer(ctx, SPOTLIGHT_STAGE_ATTEND);
-        if (RB == 128) launch_rb<T, 128>(ctx, timer, q, K, V, idx, k, scale, nsplit);
-        else if (RB == 64) launch_rb<T, 64>(ctx, timer, q, K, V, idx, k, scale, nsplit);
-        else launch_rb<T, 32>(ctx, timer, q, K, V, idx, k, scale, nsplit);
+        if (RB == 128) launch_rb<T, 128>(ctx, timer, q, K, V, idx, k, scale, nsplit, out);
+        else if (RB == 64) launch_rb<T, 64>(ctx, timer, q, K, V, idx, k, scale, nsplit, out);
+        else launch_rb<T, 32>(ctx, timer, q, K, V, idx, k, scale, nsplit, out);
         if (hipGetLastError() != hipSuccess) return SPOTLIGHT_ERR_HIP;
     }
     StageTimer timer(ctx, SPOTLIGHT_STAGE_MERGE);

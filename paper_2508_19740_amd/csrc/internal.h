@@ -81,6 +81,7 @@ struct AuditRec {
 
 struct ProfileRec {
     int stage;
+    bool whole;   // an attend launch that leaves nothing to merge
     hipEvent_t start, stop;
 };
 
