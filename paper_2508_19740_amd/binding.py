@@ -85,6 +85,13 @@ class SpotlightError(RuntimeError):
         self.rc = rc
 
 
+def _raw_stream(index: int) -> int:
+    """The current stream's handle on a device: torch.cuda.current_stream(index).cuda_stream without the
+    Stream object (1.2 us a call)."""
+    get = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    return get(index) if get is not None else torch.cuda.current_stream(index).cuda_stream
+
+
 def _dtype_code(t: torch.dtype) -> int:
     if t == torch.float32:
         return F32
@@ -134,6 +141,14 @@ class Spotlight:
         if rc != OK:
             raise SpotlightError(rc, "spotlight_create")
         self._h = h
+        # what every call compares its tensors with
+        self._index = self.device.index if self.device.index is not None else torch.cuda.current_device()
+        self._q_shape, self._out_shape = (batch, n_q_heads, head_dim), (batch, n_q_heads, head_dim)
+        self._kv_shape, self._codes_shape = (batch, n_kv_heads, max_tokens, head_dim), (batch, n_kv_heads, max_tokens, self.W)
+        if hidden > 0:
+            self._w_shapes = ((n_kv_heads, hidden, head_dim), (n_kv_heads, hidden), (n_kv_heads, code_bits, hidden))
+        else:
+            self._w_shapes = ((n_kv_heads, code_bits, head_dim),)
 
     def close(self):
         if getattr(self, "_h", None):
@@ -148,21 +163,23 @@ class Spotlight:
 
     # ------------------------------------------------------------------ helpers
     def _chk(self, t: torch.Tensor, shape, dtype, name):
-        if t.device != self.device or not t.is_contiguous() or t.dtype != dtype or tuple(t.shape) != tuple(shape):
+        # a call makes nine of these checks, and a small step is bound by the host: the cheap comparison
+        # first (a shape compares with a tuple as it is), the rest only for the message
+        if t.dtype is not dtype or t.shape != shape or not t.is_contiguous() or t.device != self.device:
             raise ValueError(f"{name}: want contiguous {dtype} {tuple(shape)} on {self.device}, "
                              f"got {t.dtype} {tuple(t.shape)} on {t.device}")
         return t.data_ptr()
 
     def _weights(self, w1, b1, w2) -> HashWeights:
         if self.h > 0:
-            return HashWeights(self._chk(w1, (self.Hkv, self.h, self.d), self.weight_dtype, "w1"),
-                               self._chk(b1, (self.Hkv, self.h), self.weight_dtype, "b1"),
-                               self._chk(w2, (self.Hkv, self.L, self.h), self.weight_dtype, "w2"))
-        return HashWeights(self._chk(w1, (self.Hkv, self.L, self.d), self.weight_dtype, "w1"), None, None)
+            s = self._w_shapes
+            return HashWeights(self._chk(w1, s[0], self.weight_dtype, "w1"), self._chk(b1, s[1], self.weight_dtype, "b1"),
+                               self._chk(w2, s[2], self.weight_dtype, "w2"))
+        return HashWeights(self._chk(w1, self._w_shapes[0], self.weight_dtype, "w1"), None, None)
 
     def _sync_stream(self):
-        s = torch.cuda.current_stream(self.device).cuda_stream
-        if s != self.cfg.stream:
+        s = _raw_stream(self._index)
+        if s != (self.cfg.stream or 0):
             self.cfg.stream = s
             lib.spotlight_set_stream(self._h, s)
 
@@ -198,8 +215,8 @@ class Spotlight:
 
     def hash_keys(self, K, w1, b1, w2, t0: int, n_new: int, codes):
         self._sync_stream()
-        kp = self._chk(K, (self.B, self.Hkv, self.Nmax, self.d), self.kv_dtype, "K")
-        cp = self._chk(codes, (self.B, self.Hkv, self.Nmax, self.W), torch.int32, "codes")
+        kp = self._chk(K, self._kv_shape, self.kv_dtype, "K")
+        cp = self._chk(codes, self._codes_shape, torch.int32, "codes")
         w = self._weights(w1, b1, w2)
         rc = lib.spotlight_hash_keys(self._h, kp, C.byref(w), t0, n_new, cp)
         if rc != OK:
@@ -209,8 +226,8 @@ class Spotlight:
     def retrieve_topk(self, q, w1, b1, w2, codes, n_tokens: int, k: int, out_idx=None,
                       out_qcode=None, out_dist=None):
         self._sync_stream()
-        qp = self._chk(q, (self.B, self.Hq, self.d), self.kv_dtype, "q")
-        cp = self._chk(codes, (self.B, self.Hkv, self.Nmax, self.W), torch.int32, "codes")
+        qp = self._chk(q, self._q_shape, self.kv_dtype, "q")
+        cp = self._chk(codes, self._codes_shape, torch.int32, "codes")
         w = self._weights(w1, b1, w2)
         if not (isinstance(k, int) and isinstance(n_tokens, int)):
             raise TypeError("k and n_tokens are ints")
@@ -226,16 +243,16 @@ class Spotlight:
 
     def sparse_decode(self, q, K, V, idx, scale: Optional[float] = None, out=None):
         self._sync_stream()
-        qp = self._chk(q, (self.B, self.Hq, self.d), self.kv_dtype, "q")
-        kp = self._chk(K, (self.B, self.Hkv, self.Nmax, self.d), self.kv_dtype, "K")
-        vp = self._chk(V, (self.B, self.Hkv, self.Nmax, self.d), self.kv_dtype, "V")
+        qp = self._chk(q, self._q_shape, self.kv_dtype, "q")
+        kp = self._chk(K, self._kv_shape, self.kv_dtype, "K")
+        vp = self._chk(V, self._kv_shape, self.kv_dtype, "V")
         if idx.dim() != 3:
             raise ValueError("idx: want [B, Hq, k]")
         k = idx.shape[-1]
         ip = self._chk(idx, (self.B, self.Hq, k), torch.int32, "idx")
         if out is None:
             out = torch.empty(self.B, self.Hq, self.d, dtype=torch.float32, device=self.device)
-        op = self._chk(out, (self.B, self.Hq, self.d), torch.float32, "out")
+        op = self._chk(out, self._out_shape, torch.float32, "out")
         if scale is None:
             scale = 1.0 / math.sqrt(self.d)
         rc = lib.spotlight_sparse_decode(self._h, qp, kp, vp, ip, k, float(scale), op)
@@ -246,21 +263,21 @@ class Spotlight:
     def decode_step(self, q, K, V, w1, b1, w2, codes, n_tokens: int, k: int, n_sink: int = 0, n_local: int = 0,
                     scale: Optional[float] = None, out_idx=None, out=None):
         """Hash the key at row n_tokens-1 into codes, retrieve (first n_sink / last n_local tokens
-        forced), attend: one C call, five kernel launches.  Returns (idx, out)."""
+        forced), attend: one C call, four or five kernel launches.  Returns (idx, out)."""
         self._sync_stream()
-        qp = self._chk(q, (self.B, self.Hq, self.d), self.kv_dtype, "q")
-        kp = self._chk(K, (self.B, self.Hkv, self.Nmax, self.d), self.kv_dtype, "K")
-        vp = self._chk(V, (self.B, self.Hkv, self.Nmax, self.d), self.kv_dtype, "V")
-        cp = self._chk(codes, (self.B, self.Hkv, self.Nmax, self.W), torch.int32, "codes")
+        qp = self._chk(q, self._q_shape, self.kv_dtype, "q")
+        kp = self._chk(K, self._kv_shape, self.kv_dtype, "K")
+        vp = self._chk(V, self._kv_shape, self.kv_dtype, "V")
+        cp = self._chk(codes, self._codes_shape, torch.int32, "codes")
         w = self._weights(w1, b1, w2)
-        if not all(isinstance(v, int) for v in (k, n_tokens, n_sink, n_local)):
+        if not (isinstance(k, int) and isinstance(n_tokens, int) and isinstance(n_sink, int) and isinstance(n_local, int)):
             raise TypeError("k, n_tokens, n_sink and n_local are ints")
         if out_idx is None:
             out_idx = torch.empty(self.B, self.Hq, max(k, 0), dtype=torch.int32, device=self.device)
         ip = self._chk(out_idx, (self.B, self.Hq, k), torch.int32, "out_idx")
         if out is None:
             out = torch.empty(self.B, self.Hq, self.d, dtype=torch.float32, device=self.device)
-        op = self._chk(out, (self.B, self.Hq, self.d), torch.float32, "out")
+        op = self._chk(out, self._out_shape, torch.float32, "out")
         if scale is None:
             scale = 1.0 / math.sqrt(self.d)
         rc = lib.spotlight_decode_step(self._h, qp, kp, vp, C.byref(w), cp, n_tokens, k, n_sink, n_local,
