@@ -160,14 +160,14 @@ struct HashVecArgs {
     int n_first;
 };
 
-template <typename XT, typename WT, bool PACKED>
-__global__ __launch_bounds__(kThreads) void hash_vec_kernel(HashVecArgs jobs)
+template <typename XT, typename WT, bool PACKED, int T>
+__global__ __launch_bounds__(T) void hash_vec_kernel(HashVecArgs jobs)
 {
     extern __shared__ __align__(16) float act[];  // hidden activations, or x itself for the linear hash
     const bool second = static_cast<int>(blockIdx.x) >= jobs.n_first;   // uniform over the workgroup
     const HashArgs& a = jobs.job[second ? 1 : 0];
     const int xhead = static_cast<int>(blockIdx.x) - (second ? jobs.n_first : 0);
-    hash_one_vector<XT, WT, PACKED>(a, xhead, true, threadIdx.x, act, nullptr);
+    hash_one_vector<XT, WT, PACKED, T>(a, xhead, true, threadIdx.x, act, nullptr);
 }
 
 // One thread per group of 8 weights of the packed copies (layout: see hash_vec_kernel).
@@ -227,10 +227,21 @@ int run_vec(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, const HashArgs*
     jobs.n_first = n_xheads;
     const int grid = n_xheads + (b ? n_xheads_b : 0);
     const bool packed = a.pack_out && (a.hidden == 0 || a.pack_w1) && (!b || (b->pack_out == a.pack_out && b->pack_w1 == a.pack_w1));
-    auto kern = hash_vec_kernel<XT, WT, false>;
-    if (packed) kern = hash_vec_kernel<XT, WT, true>;
+    auto kern = packed ? hash_vec_kernel<XT, WT, true, kThreads> : hash_vec_kernel<XT, WT, false, kThreads>;
+    int threads = kThreads;
+    if constexpr (sizeof(WT) == 2) {
+        // Hidden layers of more than 512 units take 256 threads three rounds and more, and their code words
+        // two: with a compute unit for every vector, 512 threads shorten both.  128 -> 1024 -> 512: 40
+        // vectors 29.7 -> 18.8 us, 160 29.6 -> 19.4 us, 640 44.9 -> 52.2 us (weights from L2 bind it then).
+        // No gain at 512 units (11.8 against 11.6 us) or from the arrays as stored (41.7 against 42.4 us),
+        // and binary32 rows spill (39.9 against 52.2 us).
+        if (packed && a.hidden > 512 && grid <= ctx->n_cus) {
+            threads = 512;
+            kern = hash_vec_kernel<XT, WT, true, 512>;
+        }
+    }
     StageTimer timer(ctx, stage);
-    timer.launch(kern, dim3(static_cast<unsigned>(grid)), dim3(kThreads), lds, jobs);
+    timer.launch(kern, dim3(static_cast<unsigned>(grid)), dim3(static_cast<unsigned>(threads)), lds, jobs);
     return hip_rc(hipGetLastError());
 }
 

@@ -1,4 +1,4 @@
-// Device code shared by the kernels that hash ONE vector per group of 256 threads (the query of a
+// Device code shared by the kernels that hash ONE vector per group of 256 (or 512) threads (the query of a
 // head, or the key appended by a decode step): hash_vec_kernel in hash.hip and the single-launch
 // decode step in step_small.hip.  Same arithmetic as every other hash kernel: one binary32
 // accumulator per output, fused multiply-adds in increasing index order (paper Sec. 3.2 Eq. 4-6,
@@ -99,7 +99,9 @@ struct HashArgs {
 __device__ __forceinline__ int whead_of(const HashArgs& a, int xhead) { return (xhead % a.heads_per_batch) / a.group; }
 
 
-// Hashes the vector of x-head `xhead` of job `a` with the 256 threads tid = 0 .. 255 of one group.
+constexpr int kPackRows = 256;   // rows of the first layer side by side in the packed copy
+
+// Hashes the vector of x-head `xhead` of job `a` with the GT threads tid = 0 .. GT - 1 of one group.
 // EVERY thread of the workgroup must call it (it contains one workgroup barrier); groups with
 // live == false only take part in the barrier.  `act` is LDS for the hidden activations of this
 // group (max(hidden, 128) floats).  The packed code words go to a.codes and, if lds_code is set,
@@ -120,12 +122,11 @@ __device__ __forceinline__ int whead_of(const HashArgs& a, int xhead) { return (
 //   output matrix: [weight head][pair][run][g][lane][8]        = Wout[o(pair, lane)][128 run + 8g ...]
 // with o(pair, lane) = (31 - lane % 32) * W + 2 pair + lane / 32, the output that lands in bit
 // lane % 32 of word 2 pair + lane / 32 (zeros where that word does not exist).
-template <typename XT, typename WT, bool PACKED>
+template <typename XT, typename WT, bool PACKED, int GT = kPackRows>
 __device__ __forceinline__ void hash_one_vector(const HashArgs& a, int xhead, bool live, int tid, float* act,
                                                 uint32_t* lds_code)
 {
     constexpr int G16 = kHeadDim / 8;             // groups of 8 in a run of 128 weights
-    constexpr int GT = 256;                       // threads of a group
 
     const int lane = tid & 63, wave = tid >> 6;
     const int whead = (xhead % a.heads_per_batch) / a.group;
@@ -160,7 +161,7 @@ __device__ __forceinline__ void hash_one_vector(const HashArgs& a, int xhead, bo
                 for (int g = 0; g < G16; ++g) {
                     if constexpr (PACKED)
                         load_raw(static_cast<const WT*>(a.pack_w1) +
-                                     (((static_cast<int64_t>(whead) * ((a.hidden + GT - 1) / GT) + i / GT) * G16 + g) * GT + tid) * 8,
+                                     (((static_cast<int64_t>(whead) * ((a.hidden + kPackRows - 1) / kPackRows) + i / kPackRows) * G16 + g) * kPackRows + i % kPackRows) * 8,
                                  w1r[g]);
                     else
                         load_raw(w1 + static_cast<int64_t>(i) * kHeadDim + g * 8, w1r[g]);
