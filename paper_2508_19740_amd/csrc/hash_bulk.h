@@ -80,6 +80,15 @@ __device__ __forceinline__ void split8(const float (&h)[8], bf16x8_t& hi, bf16x8
     lo = b.v;
 }
 
+// the hi part of the split alone
+__device__ __forceinline__ uint4 round8(const float4& f0, const float4& f1)
+{
+    typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+    typedef float f32x2_t __attribute__((ext_vector_type(2)));
+    const auto two = [](float x, float y) { return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_t{x, y}, bf16x2_t)); };
+    return make_uint4(two(f0.x, f0.y), two(f0.z, f0.w), two(f1.x, f1.y), two(f1.z, f1.w));
+}
+
 // 4 consecutive weights in their stored form
 template <typename WT> struct Raw4;
 template <> struct Raw4<float> { float4 v; };
@@ -555,6 +564,12 @@ template <int NW> struct CertScratch {
 
 constexpr int hs_stride(int hidden) { return hidden_padded(hidden) + 4; }   // words per vector: b128 accesses of 8 lanes miss each other
 
+// Operands of a step of 16 units kept in LDS: hi and lo, or with the x tile in binary32 and up to 256 units
+// lo alone, so that two workgroups fit into a compute unit; hi is then taken from the activations again
+// (four conversions a step).  128 -> 256 -> 128 with both kept and with lo: 512 heads x 18 binary32 vectors
+// 46.8 and 31.9 us, 256 x 70 70 and 49.7 us, 8 x 30000 361 and 306 us.
+template <typename XT, int NUB> constexpr int kept_operands() { return sizeof(XT) == 4 && NUB > 1 ? 1 : 2; }
+
 // NUB: blocks of 32 hidden units a wavefront owns; WREG: steps of 16 units of layer 2.
 template <typename XT, int NW, int NUB, int WREG, bool AUDIT>
 __global__ __launch_bounds__(NW * 64, 2) void hash_cert_kernel(HashArgs a, float eps, int tiles_per_group)
@@ -565,8 +580,9 @@ __global__ __launch_bounds__(NW * 64, 2) void hash_cert_kernel(HashArgs a, float
     float* xs = lds;                                                        // the x tile
     const int stride = hs_stride(a.hidden), nub = hidden_padded(a.hidden) / 32;
     float* hs = xs + XTile<XT>::kFloats;                                    // [TK][stride]
-    uint4* hilo = reinterpret_cast<uint4*>(hs + TK * stride);               // [2 nub steps of 16 units][hi, lo][64]
-    float* bias = reinterpret_cast<float*>(hilo + nub * 2 * 2 * 64);        // [hidden, padded to 32]
+    constexpr int KEPT = kept_operands<XT, NUB>();
+    uint4* hilo = reinterpret_cast<uint4*>(hs + TK * stride);               // [2 nub steps of 16 units][hi, lo or lo][64]
+    float* bias = reinterpret_cast<float*>(hilo + nub * 2 * KEPT * 64);     // [hidden, padded to 32]
     CertScratch<NW>& m = *reinterpret_cast<CertScratch<NW>*>(bias + nub * 32);
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -696,8 +712,8 @@ __global__ __launch_bounds__(NW * 64, 2) void hash_cert_kernel(HashArgs a, float
             f[1] = make_float4(h8[4], h8[5], h8[6], h8[7]);
             bf16x8_t hi, lo;
             split8(h8, hi, lo);
-            hilo[((ub * 2 + j) * 2 + 0) * 64 + lane] = __builtin_bit_cast(uint4, hi);
-            hilo[((ub * 2 + j) * 2 + 1) * 64 + lane] = __builtin_bit_cast(uint4, lo);
+            if constexpr (KEPT == 2) hilo[((ub * 2 + j) * 2 + 0) * 64 + lane] = __builtin_bit_cast(uint4, hi);
+            hilo[((ub * 2 + j) * KEPT + KEPT - 1) * 64 + lane] = __builtin_bit_cast(uint4, lo);
         };
 #pragma unroll
         for (int i = 0; i < NUB; ++i) {
@@ -746,7 +762,13 @@ __global__ __launch_bounds__(NW * 64, 2) void hash_cert_kernel(HashArgs a, float
 #pragma unroll
             for (int ks = 0; ks < WREG; ++ks) {
                 if (ks >= n_ks) continue;
-                const uint4 hi = hilo[(ks * 2 + 0) * 64 + lane], lo = hilo[(ks * 2 + 1) * 64 + lane];
+                uint4 hi, lo = hilo[(ks * KEPT + KEPT - 1) * 64 + lane];
+                if constexpr (KEPT == 2) {
+                    hi = hilo[ks * 2 * 64 + lane];
+                } else {
+                    const float4* f = reinterpret_cast<const float4*>(hs + c * stride + ks * 16 + 8 * half);
+                    hi = round8(f[0], f[1]);
+                }
                 y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, hi), __builtin_bit_cast(bf16x8_t, wreg[ks]), y, 0, 0, 0);
                 y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, lo), __builtin_bit_cast(bf16x8_t, wreg[ks]), y, 0, 0, 0);
             }
@@ -1119,16 +1141,58 @@ __global__ __launch_bounds__(kThreads, 2) void hash_linear_kernel(HashArgs a, fl
     }
 }
 
+// A workgroup takes a run of up to 16 tiles of one head; the weights are fetched once per run.
+
+// The longest run, halved until the grid has `least` workgroups.
+inline int short_runs(int64_t tiles, int n_xheads, int least)
+{
+    int run = 16;
+    while (run > 1 && ((tiles + run - 1) / run) * n_xheads < least) run /= 2;
+    return run;
+}
+
+// Workgroups on a compute unit at a time: `by_registers`, or what LDS holds.
+inline int resident(const spotlight_ctx* ctx, int by_registers, size_t lds)
+{
+    int per_cu = by_registers;
+    while (per_cu > 1 && per_cu * lds > static_cast<size_t>(ctx->max_lds)) --per_cu;
+    return per_cu;
+}
+
+// The run for which the last generation of workgroups is not nearly empty: least is generations x (tiles +
+// what the weights take, about a third of a tile).  The workgroups of a compute unit share its matrix cores:
+// a last generation of no more than one for each counts two thirds.  8 heads, the longest run with 512 or
+// 1024 workgroups and this one: 4000 / 8000 / 30000 vectors 128 -> 256 -> 128 60, 92, 299 and 51, 87, 276 us;
+// 128 -> 512 -> 256 141, 266, 868 and 130, 233, 815 us; 128 -> 1024 -> 512 433, 846, 2922 and 395, 759, 2770 us.
+inline int whole_generations(int64_t tiles, int n_xheads, int n_cus, int per_cu)
+{
+    const int64_t slots = static_cast<int64_t>(n_cus) * per_cu;
+    int best = 1;
+    int64_t best_cost = INT64_MAX;
+    for (int run = 1; run <= 16; ++run) {
+        const int64_t groups = (tiles + run - 1) / run * n_xheads, last = groups % slots;
+        const int64_t thirds = groups / slots * 3 + (last == 0 ? 0 : last <= n_cus && per_cu > 1 ? 2 : 3);
+        if (thirds * (3 * run + 1) < best_cost) {
+            best = run;
+            best_cost = thirds * (3 * run + 1);
+        }
+    }
+    return best;
+}
+
 template <typename XT, typename WT, int NW, int NUB, int NBW, bool AUDIT>
 int launch(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int stage, size_t lds)
 {
     auto kern = hash_bulk_kernel<XT, WT, NW, NUB, NBW, AUDIT>;
     if (allow_dynamic_lds(ctx, reinterpret_cast<const void*>(kern), lds) != SPOTLIGHT_OK) return SPOTLIGHT_ERR_HIP;
     const int64_t tiles = (a.n_rows + kTile - 1) / kTile;
-    // a workgroup takes a run of tiles of one head (the first layer's weights are fetched once per
-    // run), short enough that the grid still has a few thousand workgroups
-    int tpg = 16;
-    while (tpg > 1 && ((tiles + tpg - 1) / tpg) * n_xheads < 4096) tpg /= 2;
+    // nothing is fetched once a run without a first layer or with weights read again for every tile (linear
+    // binary32, 4 x 20000 vectors: 124 us with at least 4096 workgroups, 137 with 1024; 8 x 8000, binary32, 128 ->
+    // 1024 -> 512: 959 us with short runs, 994 with whole generations); narrow layers have little to fetch, and more
+    // workgroups share a compute unit
+    constexpr int kShort = NUB == 0 ? 4096 : NUB < 0 || (NUB == 1 && NW == 4) ? 1024 : 0;
+    const int tpg = kShort ? short_runs(tiles, n_xheads, kShort)
+                           : whole_generations(tiles, n_xheads, ctx->n_cus, resident(ctx, 4 * min_waves(NW, NBW) / NW, lds));
     if constexpr (NBW > 0) {
         constexpr int LPR = 16;
         const int n_out = a.n_wheads * a.L;
@@ -1145,15 +1209,16 @@ template <typename XT, int NW, int NUB, int WREG>
 int launch_word(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int stage)
 {
     const size_t hp = hidden_padded(a.hidden);
-    const size_t work = sizeof(float) * (XTile<XT>::kFloats + kTile * hs_stride(a.hidden) + hp) + hp * kTile * 4 + sizeof(CertScratch<NW>);
+    const size_t work = sizeof(float) * (XTile<XT>::kFloats + kTile * hs_stride(a.hidden) + hp) + hp * kTile * 2 * kept_operands<XT, NUB>() + sizeof(CertScratch<NW>);
     const size_t stage1 = static_cast<size_t>(a.hidden) * (kHeadDim * 2 + 16), stage2 = static_cast<size_t>(a.L) * (a.hidden * 2 + 16);
     const size_t lds = work > stage1 ? (work > stage2 ? work : stage2) : (stage1 > stage2 ? stage1 : stage2);
     auto kern = hash_cert_kernel<XT, NW, NUB, WREG, false>;
     if (a.audit) kern = hash_cert_kernel<XT, NW, NUB, WREG, true>;
     if (allow_dynamic_lds(ctx, reinterpret_cast<const void*>(kern), lds) != SPOTLIGHT_OK) return SPOTLIGHT_ERR_HIP;
     const int64_t tiles = (a.n_rows + kTile - 1) / kTile;
-    int tpg = 16;
-    while (tpg > 1 && ((tiles + tpg - 1) / tpg) * n_xheads < 2048) tpg /= 2;
+    // narrow layers have less to fetch per run, and more workgroups share a compute unit (8 x 65536, 128 -> 128
+    // -> 64: 257 us with at least 2048, 267 with 1024)
+    const int tpg = NUB == 1 ? short_runs(tiles, n_xheads, 2048) : whole_generations(tiles, n_xheads, ctx->n_cus, resident(ctx, 2, lds));
     dim3 grid(static_cast<unsigned>((tiles + tpg - 1) / tpg), static_cast<unsigned>(n_xheads));
     StageTimer timer(ctx, stage);
     timer.launch(kern, grid, dim3(NW * 64), lds, a, static_cast<float>(bulk_hash_eps(a.hidden)), tpg);
@@ -1199,6 +1264,10 @@ inline bool bulk_hash_applies(const spotlight_ctx* ctx, const hashdev::HashArgs&
     // 9 rows 26 against 23 and 34 against 31 us, 17 rows 26 against 23 and 48 against 32 us; 128 -> 512 -> 256:
     // 9 rows 53 against 48 and 70 against 75 us; linear, 512 bits: 31 rows 19 against 20 us, 100 rows 40 against 20 us.
     const int min_rows = a.hidden == 0 ? bulk::kTile : n_xheads > ctx->n_cus ? 17 : 9;
+    // Codes of one or two words with a wide hidden layer: while every tile of 8 has a compute unit of its own
+    // that kernel is the faster one, its lanes sharing the sums.  8 heads x 20 vectors, 64 bits: hidden 256 19.2
+    // against 22.1 us, 512 34 against 46 us; hidden 128 17 against 14 us; 512 heads x 18, 256 -> 64: 45 against 31 us.
+    if (a.hidden > 128 && a.W <= 2 && a.n_rows < bulk::kTile && n_xheads * ((a.n_rows + 7) / 8) <= ctx->n_cus) return false;
     return a.wnorm && a.n_rows >= min_rows && bulk::lds_bytes(x_size, a.hidden) <= static_cast<size_t>(ctx->max_lds);
 }
 
@@ -1237,6 +1306,12 @@ int run_bulk_hash(spotlight_ctx* ctx, const hashdev::HashArgs& a, int n_xheads, 
         if (nub == 0) return launch<XT, WT, 4, 0, 0, false>(ctx, a, n_xheads, stage, lds);
     }
     if (nub <= 4) return launch<XT, WT, 4, 1, 0, false>(ctx, a, n_xheads, stage, lds);
+    // Eight wavefronts where four have more than a code word each, and where no compute unit gets a second tile:
+    // the tile is done sooner (8 heads x 20 binary32 vectors, 128 -> 256 -> 256: 25.6 against 30.8 us; 128 bits:
+    // 21.2 against 22.8; 8 x 65536, 256 bits: 1251 against 1276).  Otherwise the four hide each other's waits
+    // better (4 x 4 x 10000, 32 bits: 276 against 304 us).
+    const int64_t tiles = (a.n_rows + kTile - 1) / kTile * n_xheads;
+    if (nub > 4 && nub <= 8 && (a.W > 4 || tiles <= ctx->n_cus)) return launch<XT, WT, 8, 1, 0, false>(ctx, a, n_xheads, stage, lds);
     if (nub <= 8) return launch<XT, WT, 4, 2, 0, false>(ctx, a, n_xheads, stage, lds);
     if (nub <= 16) return launch<XT, WT, 8, 2, 0, false>(ctx, a, n_xheads, stage, lds);
     return launch<XT, WT, 8, -1, 0, false>(ctx, a, n_xheads, stage, lds);

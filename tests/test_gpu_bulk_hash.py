@@ -82,6 +82,21 @@ def test_many_heads_of_few_rows():
 
 
 @pytest.mark.parametrize("kv", ["bf16", "f32"])
+@pytest.mark.parametrize("bits,hidden", [(128, 256), (32, 136), (64, 200)])
+def test_two_blocks_a_wavefront_with_more_tiles_than_compute_units(bits, hidden, kv):
+    _both(10, 30, 33, 1, 36, bits, hidden, kv, "f32")
+    _both(10, 30, 33, 1, 36, bits, hidden, kv, "bf16")
+
+
+@pytest.mark.parametrize("rows", [31, 32])
+@pytest.mark.parametrize("bits,hidden", [(64, 256), (32, 160), (64, 512), (96, 256)])
+def test_short_codes_of_few_rows(rows, bits, hidden):
+    """Up to 64 bits behind a wide hidden layer: few rows stay with the tiles of 8."""
+    _both(1, 2, rows, 3, 40, bits, hidden, "bf16", "bf16")
+    _both(1, 2, rows, 3, 40, bits, hidden, "f32", "f32")
+
+
+@pytest.mark.parametrize("kv", ["bf16", "f32"])
 @pytest.mark.parametrize("bits,hidden", [(128, 0), (512, 0), (128, 256), (256, 512)])
 def test_audit(bits, hidden, kv):
     """The audited call writes the same codes, counts every output of every row, and finds none settled wrongly."""
