@@ -377,7 +377,7 @@ int check_step_args(const spotlight_ctx* ctx, const void* q, const void* K, cons
     return SPOTLIGHT_OK;
 }
 
-// The decode step of spotlight_decode_step and spotlight_decode_step_noalloc: argument checks, then five launches.
+// The decode step of spotlight_decode_step and spotlight_decode_step_noalloc: argument checks, then four or five launches.
 int decode_step(spotlight_ctx* ctx, const void* q, const void* K, const void* V, const spotlight_hash_weights* w,
                 uint32_t* codes, int64_t n_tokens, int32_t k, int32_t n_sink, int32_t n_local, float scale,
                 int32_t* out_idx, float* out)
