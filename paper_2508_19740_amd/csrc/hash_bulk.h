@@ -102,6 +102,13 @@ __device__ __forceinline__ void expand(const Raw4<bf16_raw>& r, float (&o)[4])
     o[2] = __uint_as_float(r.v.y << 16); o[3] = __uint_as_float(r.v.y & 0xffff0000u);
 }
 
+// 4 consecutive biases, one element at a time: b1 may start at any element (a slice of one flat parameter
+// buffer), where the calls ask W1 and W2 for 16 bytes.
+template <typename WT> __host__ __device__ inline void load_bias4(const WT* p, float (&o)[4])
+{
+    for (int e = 0; e < 4; ++e) o[e] = load1(p + e);
+}
+
 // Turns 8 consecutive weights of a row, 4 in each half of the wavefront (lower half: k .. k+3, upper
 // half: k+4 .. k+7), into the operands of four consecutive steps (lower half: even k, upper: odd k).
 __device__ __forceinline__ void to_steps(float (&v)[4])
@@ -259,10 +266,8 @@ __global__ __launch_bounds__(NW * 64, min_waves(NW, NBW)) void hash_bulk_kernel(
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int unit = ub * 32 + 8 * q + 4 * half;   // hidden is a multiple of 8: a group of four is whole
-            Raw4<WT> raw;
-            load_raw(b1 + min(unit, a.hidden - 4), raw);
             float v[4];
-            expand(raw, v);
+            load_bias4(b1 + min(unit, a.hidden - 4), v);
 #pragma unroll
             for (int e = 0; e < 4; ++e) acc[4 * q + e] = unit < a.hidden ? v[e] : 0.0f;
         }

@@ -11,8 +11,6 @@ namespace hashdev {
 
 struct bf16_raw { uint16_t v; };
 
-__device__ __forceinline__ float bf16_bits_to_f32(uint32_t hi16) { return __uint_as_float(hi16 << 16); }
-
 // load 8 consecutive elements starting at p (16-byte aligned for bf16, 32-byte for f32) as floats
 __device__ __forceinline__ void load8(const float* p, float (&o)[8])
 {
@@ -50,8 +48,8 @@ __device__ __forceinline__ void expand(const Raw8<bf16_raw>& r, float (&o)[8])
     o[4] = __uint_as_float(r.u.z << 16); o[5] = __uint_as_float(r.u.z & 0xffff0000u);
     o[6] = __uint_as_float(r.u.w << 16); o[7] = __uint_as_float(r.u.w & 0xffff0000u);
 }
-__device__ __forceinline__ float load1(const float* p) { return *p; }
-__device__ __forceinline__ float load1(const bf16_raw* p) { return bf16_bits_to_f32(p->v); }
+__host__ __device__ inline float load1(const float* p) { return *p; }
+__host__ __device__ inline float load1(const bf16_raw* p) { return __builtin_bit_cast(float, static_cast<uint32_t>(p->v) << 16); }
 
 __device__ __forceinline__ float silu_exp(float t)
 {

@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 DT = {"f32": torch.float32, "bf16": torch.bfloat16}
 
 
-def _both(B, H, rows, t0, cap, bits, hidden, kv, w, stress=False, seed=3):
+def _both(B, H, rows, t0, cap, bits, hidden, kv, w, stress=False, seed=3, b1_at=0):
     import paper_2508_19740_amd as sp
     g = torch.Generator().manual_seed(seed + rows + bits + hidden)
     K = torch.randn(B, H, cap, 128, generator=g)
@@ -35,6 +35,10 @@ def _both(B, H, rows, t0, cap, bits, hidden, kv, w, stress=False, seed=3):
     ws = [t.to(DT[w]).contiguous() for t in ws] + ([None, None] if not hidden else [])
     dev = torch.device("cuda:0")
     Kd, wd = K.to(dev), [None if t is None else t.to(dev) for t in ws]
+    if b1_at:   # a slice of a larger buffer that starts at this element
+        flat = torch.zeros(b1_at + ws[1].numel(), dtype=DT[w], device=dev)
+        wd[1] = flat[b1_at:].view(ws[1].shape).copy_(wd[1])
+        assert wd[1].data_ptr() % 16 != 0 and wd[1].is_contiguous()
     ctx = sp.Spotlight(B, H, H, bits, hidden, cap, 1, kv_dtype=DT[kv], weight_dtype=DT[w], device=dev)
     try:
         got = torch.full((B, H, cap, bits // 32), 77, dtype=torch.int32, device=dev)
@@ -62,6 +66,14 @@ def _both(B, H, rows, t0, cap, bits, hidden, kv, w, stress=False, seed=3):
 ])
 def test_every_instantiation(bits, hidden, kv, w):
     _both(1, 2, 33, 3, 40, bits, hidden, kv, w)
+
+
+@pytest.mark.parametrize("kv", ["bf16", "f32"])
+@pytest.mark.parametrize("w", ["bf16", "f32"])
+@pytest.mark.parametrize("bits,hidden", [(128, 256), (256, 128), (256, 512), (128, 264), (512, 1024), (64, 1112)])
+def test_biases_at_any_element(bits, hidden, kv, w):
+    """W1 and W2 are 16-byte aligned, b1 need not be."""
+    _both(1, 2, 33, 3, 40, bits, hidden, kv, w, b1_at=1)
 
 
 @pytest.mark.parametrize("rows", [8, 9, 16, 17, 31, 32, 63, 64, 65, 511, 513, 2049])
