@@ -31,9 +31,9 @@
 //   with eps = 1.01 * (hidden * (2^-24 + 1.01 * 2^-22) + 2^-17):  hidden roundings of 2^-24 in the
 //   chain, at most 2 * hidden additions in the matrix core each assumed to err by at most one unit in
 //   the last place of binary32 whatever their order, and the split residue (2^-18, taken as 2^-17).
-//   A fixed 1e-30 on top covers activations so small that a conversion flushes them; a norm whose
-//   square underflows counts as infinite.  The sign of
-//   y_mfma is the chain's wherever |y_mfma| exceeds that bound; the few outputs that do not
+//   Norms below 1e-12 count as infinite: the bound is then never below 1e-29, and what a conversion or the
+//   matrix core flushes (1.2e-38 a term) is far inside its factor of 1.01.  The sign of
+//   y_mfma is the chain's wherever |y_mfma| reaches that bound; the few outputs that do not
 //   (0.1 - 0.8 %) are recomputed with the chain from the binary32 activations still in LDS.
 #pragma once
 #include "hash_vec.h"
@@ -46,9 +46,26 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
 constexpr int kTile = 32;       // vectors per tile
-// A norm from its square, for the bound: where the square is so small that its terms underflow, no bound
+// A norm from its square, for the bound: where the square is so small that its terms may underflow, no bound
 // (infinity: nothing is settled).  Finite norms of both sides also keep every partial sum finite.
-__device__ __forceinline__ float norm_of(float s) { return s < 1e-30f ? INFINITY : __builtin_sqrtf(s); }
+//
+// A vector of zeros (padding in front of a prompt) has y = 0 exactly, or NaN beside a weight that is no number:
+// bit 0 either way, nothing to recompute.  So has an output row of zeros (a code filled up to whole words).  The
+// square is 0 exactly where all elements are zeros (kTinySquare stands for one that underflowed): norm and
+// bound are then 0, and y = 0 is settled.  Keys of zeros, with all their outputs sent to the chain and settled:
+// 512 heads x 313, linear, 512 bits, 4991 and 78 us; 64 heads x 30, 128 -> 512 -> 256, 222 and 39 us.
+constexpr float kTinySquare = 1e-37f;
+__device__ __forceinline__ float square_of(float s, uint32_t bits) { return s == 0.0f && bits != 0 ? kTinySquare : s; }   // bits: of the elements
+__device__ __forceinline__ float norm_of(float s) { return s < 1e-24f ? (s == 0.0f ? 0.0f : INFINITY) : __builtin_sqrtf(s); }
+// false where either side is NaN, or one norm is infinite and the other 0
+__device__ __forceinline__ bool settled(float y, float tcol, float hn) { return __builtin_fabsf(y) >= tcol * hn; }
+__device__ __forceinline__ uint32_t magnitude_bits(const uint4& bf16x8) { return (bf16x8.x | bf16x8.y | bf16x8.z | bf16x8.w) & 0x7fff7fffu; }
+__device__ __forceinline__ uint32_t magnitude_bits(const float4& f)
+{
+    return (__float_as_uint(f.x) | __float_as_uint(f.y) | __float_as_uint(f.z) | __float_as_uint(f.w)) & 0x7fffffffu;
+}
+__device__ __forceinline__ uint32_t magnitude_bits(const Raw8<bf16_raw>& r) { return magnitude_bits(r.u); }
+__device__ __forceinline__ uint32_t magnitude_bits(const Raw8<float>& r) { return magnitude_bits(r.a) | magnitude_bits(r.b); }
 
 constexpr int kListCap = 1024;  // outputs of a tile that may go to the recomputation
 
@@ -199,12 +216,17 @@ __global__ __launch_bounds__(kThreads) void row_norm_kernel(const bf16_raw* __re
     const int j = (blockIdx.x * kThreads + threadIdx.x) / LPR, sub = threadIdx.x % LPR;
     if (j >= n_rows) return;   // whole groups of LPR lanes
     float s = 0.0f;
+    uint32_t bits = 0;
     for (int g = sub; g < n / 8; g += LPR) {
+        Raw8<bf16_raw> raw;
+        load_raw(w2 + static_cast<int64_t>(j) * n + g * 8, raw);
         float wv[8];
-        load8(w2 + static_cast<int64_t>(j) * n + g * 8, wv);
+        expand(raw, wv);
+        bits |= magnitude_bits(raw);
 #pragma unroll
         for (int e = 0; e < 8; ++e) s = __builtin_fmaf(wv[e], wv[e], s);
     }
+    s = square_of(s, bits);
 #pragma unroll
     for (int off = 1; off < LPR; off <<= 1) s += __shfl_xor(s, off);
     if (sub == 0) wnorm[j] = norm_of(s);
@@ -379,6 +401,13 @@ __global__ __launch_bounds__(NW * 64, min_waves(NW, NBW)) void hash_bulk_kernel(
         } else {
             // ---- norms of the activation rows; the x tile's LDS becomes scratch
             sumsq += __shfl_xor(sumsq, 32);
+            if (__ballot(sumsq == 0.0f)) {   // zeros, or did their squares underflow?  (This lane's own activations, read back.)
+                uint32_t bits = 0;
+                for (int ub = wave; ub < nub; ub += NW)
+                    for (int v = 0; v < 16; ++v) bits |= __float_as_uint(hs[(ub * 32 + 4 * half + 8 * (v / 4) + v % 4) * TK + c]) << 1;
+                bits |= __shfl_xor(bits, 32);
+                sumsq = square_of(sumsq, bits);
+            }
             if (half == 0) m.part[wave][c] = sumsq;
             if (tid == 0) m.count = 0;
             __syncthreads();
@@ -454,7 +483,7 @@ __global__ __launch_bounds__(NW * 64, min_waves(NW, NBW)) void hash_bulk_kernel(
                         const int t = (v / 4) * 8 + half * 4 + (v % 4);
                         if (t >= rows) continue;
                         const float y = acc[nb][v];
-                        const bool sure = __builtin_fabsf(y) > __builtin_fmaf(tcol, m.hn[t], 1e-30f);
+                        const bool sure = settled(y, tcol, m.hn[t]);
                         const float den = wn[j] * m.hn[t];
                         const float diff = __builtin_fabsf(y - yc[v]);
                         // a NaN or an infinity on either side is never settled and is not a distance
@@ -477,8 +506,7 @@ __global__ __launch_bounds__(NW * 64, min_waves(NW, NBW)) void hash_bulk_kernel(
                 for (int v = 0; v < 16; ++v) {
                     const int t = (v / 4) * 8 + half * 4 + (v % 4);
                     const float y = acc[nb][v];
-                    const float thr = __builtin_fmaf(tcol, m.hn[t], 1e-30f);
-                    const bool sure = __builtin_fabsf(y) > thr;   // false for NaN
+                    const bool sure = settled(y, tcol, m.hn[t]);
                     const unsigned long long pos = __ballot(y > 0.0f);
                     if (c == 0) m.codes[t][word] = half ? static_cast<uint32_t>(pos >> 32) : static_cast<uint32_t>(pos);
                     if (!sure && t < rows) {
@@ -653,9 +681,11 @@ __global__ __launch_bounds__(NW * 64, 2) void hash_cert_kernel(HashArgs a, float
         wreg[ks] = staged[((31 - c) * a.W + min(wave, a.W - 1)) * (a.hidden / 8 + 1) + min(ks, n_ks - 1) * 2 + half];
     __syncthreads();
     float norm = 0.0f;         // ||W2[j]|| of this lane's output
+    uint32_t bits = 0;
 #pragma unroll
     for (int ks = 0; ks < WREG; ++ks) {
         if (ks >= n_ks) continue;
+        bits |= magnitude_bits(wreg[ks]);
         const uint32_t d[4] = {wreg[ks].x, wreg[ks].y, wreg[ks].z, wreg[ks].w};
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
@@ -663,6 +693,7 @@ __global__ __launch_bounds__(NW * 64, 2) void hash_cert_kernel(HashArgs a, float
             norm = __builtin_fmaf(hi, hi, __builtin_fmaf(lo, lo, norm));
         }
     }
+    norm = square_of(norm, bits);
     norm = norm_of(norm + __shfl_xor(norm, 32));
     for (int i = tid; i < nub * 32; i += NT) bias[i] = i < a.hidden ? load1(b1 + i) : 0.0f;
 
@@ -749,6 +780,14 @@ __global__ __launch_bounds__(NW * 64, 2) void hash_cert_kernel(HashArgs a, float
             }
         }
         sumsq += __shfl_xor(sumsq, 32);
+        if (__ballot(sumsq == 0.0f)) {   // zeros, or did their squares underflow?  (This lane's own activations, read back.)
+            uint32_t bits = 0;
+            for (int i = 0; i < n_mine; ++i)
+                for (int q = 0; q < 4; ++q)
+                    bits |= magnitude_bits(*reinterpret_cast<const float4*>(hs + c * stride + (wave * NUB + i) * 32 + 16 * (q / 2) + 8 * half + 4 * (q % 2)));
+            bits |= __shfl_xor(bits, 32);
+            sumsq = square_of(sumsq, bits);
+        }
         if (half == 0) m.part[wave][c] = sumsq;
         __syncthreads();   // activations and norms are complete; the x tile is free
         if (tile + 1 < tile1) put_x();
@@ -803,7 +842,7 @@ __global__ __launch_bounds__(NW * 64, 2) void hash_cert_kernel(HashArgs a, float
                             for (int e = 0; e < 8; ++e) yc = __builtin_fmaf(wv[e], hs[t * stride + g * 8 + e], yc);
                         }
                         if (t >= rows) continue;
-                        const bool sure = __builtin_fabsf(yv) > __builtin_fmaf(tcol, hv, 1e-30f);
+                        const bool sure = settled(yv, tcol, hv);
                         const float den = norm * hv, diff = __builtin_fabsf(yv - yc);
                         // a NaN or an infinity on either side is never settled and is not a distance
                         const float ratio = (diff == 0.0f || !(diff < INFINITY)) ? 0.0f : (den > 0.0f ? diff / den : INFINITY);   // an infinite scale: 0
@@ -819,7 +858,7 @@ __global__ __launch_bounds__(NW * 64, 2) void hash_cert_kernel(HashArgs a, float
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
                     const int t = (v / 4) * 8 + half * 4 + (v % 4);
-                    const bool sure = __builtin_fabsf(y[v]) > __builtin_fmaf(tcol, hn[v], 1e-30f);   // false for NaN
+                    const bool sure = settled(y[v], tcol, hn[v]);
                     const unsigned long long pos = __ballot(y[v] > 0.0f);
                     if (c == 0) m.codes[wave][t] = half ? static_cast<uint32_t>(pos >> 32) : static_cast<uint32_t>(pos);
                     open |= sure ? 0u : 1u << v;
@@ -966,8 +1005,10 @@ __global__ __launch_bounds__(kThreads, 2) void hash_linear_kernel(HashArgs a, fl
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
         float s = 0.0f;
+        uint32_t bits = 0;
 #pragma unroll
         for (int ks = 0; ks < 8; ++ks) {
+            bits |= magnitude_bits(wreg[nb][ks]);
             const uint32_t d[4] = {wreg[nb][ks].x, wreg[nb][ks].y, wreg[nb][ks].z, wreg[nb][ks].w};
 #pragma unroll
             for (int p = 0; p < 4; ++p) {
@@ -975,6 +1016,7 @@ __global__ __launch_bounds__(kThreads, 2) void hash_linear_kernel(HashArgs a, fl
                 s = __builtin_fmaf(hi, hi, __builtin_fmaf(lo, lo, s));
             }
         }
+        s = square_of(s, bits);
         tcol[nb] = eps * norm_of(s + __shfl_xor(s, 32));
     }
 
@@ -1014,6 +1056,10 @@ __global__ __launch_bounds__(kThreads, 2) void hash_linear_kernel(HashArgs a, fl
 #pragma unroll
             for (int q = 0; q < 8; ++q) s = __builtin_fmaf(v[q], v[q], s);
             s = add_across_16(s);
+            if (__ballot(s == 0.0f)) {   // zeros, or did their squares underflow?
+                const unsigned long long some = __ballot(magnitude_bits(xr[i]) != 0) >> (lane & 48);
+                s = square_of(s, static_cast<uint32_t>(some) & 0xffffu);
+            }
             if (k8 == 0) m.hn[buf][t] = norm_of(s);
         }
     };
@@ -1083,7 +1129,7 @@ __global__ __launch_bounds__(kThreads, 2) void hash_linear_kernel(HashArgs a, fl
 #pragma unroll
                     for (int e = 0; e < 16; ++e) { yv = e == v ? y[e] : yv; hv = e == v ? hn[e] : hv; }
                     const float yc = chain(r0 + t, (31 - c) * a.W + word0 + w);
-                    const bool sure = __builtin_fabsf(yv) > __builtin_fmaf(tcol[nb], hv, 1e-30f);
+                    const bool sure = settled(yv, tcol[nb], hv);
                     const float den = tcol[nb] / eps * hv, diff = __builtin_fabsf(yv - yc);
                     // a NaN or an infinity on either side is never settled and is not a distance
                     const float ratio = (diff == 0.0f || !(diff < INFINITY)) ? 0.0f : (den > 0.0f ? diff / den : INFINITY);   // an infinite scale: 0
@@ -1098,14 +1144,14 @@ __global__ __launch_bounds__(kThreads, 2) void hash_linear_kernel(HashArgs a, fl
             for (int v = 0; v < 16; ++v) {
                 const int t = (v / 4) * 8 + half * 4 + (v % 4);
                 const unsigned long long pos = __ballot(y[v] > 0.0f);
-                any |= __ballot(!(__builtin_fabsf(y[v]) > __builtin_fmaf(tcol[nb], hn[v], 1e-30f)));   // NaN is never sure
+                any |= __ballot(!settled(y[v], tcol[nb], hn[v]));
                 if (c == 0) m.codes[buf][t][w] = half ? static_cast<uint32_t>(pos >> 32) : static_cast<uint32_t>(pos);
             }
             if (any) {
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
                     const int t = (v / 4) * 8 + half * 4 + (v % 4);
-                    const bool open = t < rows && !(__builtin_fabsf(y[v]) > __builtin_fmaf(tcol[nb], hn[v], 1e-30f));
+                    const bool open = t < rows && !settled(y[v], tcol[nb], hn[v]);
                     const unsigned long long o = __ballot(open);
                     if (o) {
                         const uint32_t at = listed + __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(o >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(o), 0u));

@@ -133,6 +133,42 @@ def test_audit(bits, hidden, kv):
         ctx.close()
 
 
+@pytest.mark.parametrize("kv", ["bf16", "f32"])
+@pytest.mark.parametrize("bits,hidden", [(128, 0), (512, 0), (128, 256), (96, 112), (256, 512), (352, 48), (512, 1024)])
+def test_zeros_are_settled(bits, hidden, kv):
+    """A vector of zeros (padding; b1 = 0) and an output row of zeros (a code filled up) are settled as they
+    stand: none of their outputs is recomputed, alone or together.  A vector whose squares underflow is not
+    zeros: all its outputs are."""
+    import paper_2508_19740_amd as sp
+    g = torch.Generator().manual_seed(bits + hidden)
+    dev = torch.device("cuda:0")
+    n = 300
+    x = torch.randn(1, 2, n, 128, generator=g)
+    ws = [0.05 * torch.randn(2, *s, generator=g) for s in (((hidden, 128), (hidden,), (bits, hidden)) if hidden else ((bits, 128),))]
+    if hidden:
+        ws[1].zero_()
+    ws[-1][:, 5:bits:3] = -0.0
+    zero = torch.zeros_like(x)
+    zero[:, :, ::2] = -0.0
+    tiny = torch.zeros_like(x)
+    tiny[..., 77] = 1e-30
+    live = torch.count_nonzero(ws[-1][0].abs().sum(-1)).item()              # outputs of a head that are not zero rows
+    wd = [t.bfloat16().to(dev) for t in ws] + ([None, None] if not hidden else [])
+    ctx = sp.Spotlight(1, 2, 2, bits, hidden, n, 1, kv_dtype=DT[kv], weight_dtype=torch.bfloat16, device=dev)
+    try:
+        ctx.set_option(sp.OPT_BULK_HASH_AUDIT, 1)
+        for keys, least, most in ((zero, 0, 0), (x, 0, 2 * n * live // 50), (tiny, 2 * n * bits, 2 * n * bits)):
+            got = torch.full((1, 2, n, bits // 32), -1, dtype=torch.int32, device=dev)
+            ctx.hash_keys(keys.to(DT[kv]).to(dev), *wd, 0, n, got)
+            au = ctx.bulk_hash_audit_read()
+            assert au["outputs"] == 2 * n * bits and au["wrong"] == 0 and least <= au["listed"] <= most, au
+            want = torch.zeros(1, 2, n, bits // 32, dtype=torch.int32)
+            oracle.hash_keys(keys.to(DT[kv]), *[t.bfloat16() for t in ws], *([None, None] if not hidden else []), bits, 0, n, want)
+            assert torch.equal(got.cpu(), want)
+    finally:
+        ctx.close()
+
+
 @pytest.mark.parametrize("bits,hidden,kv,w", [(128, 256, "f32", "f32"), (64, 128, "bf16", "bf16"), (128, 256, "bf16", "bf16"), (512, 0, "f32", "f32"),
                                               (512, 0, "bf16", "bf16"), (128, 0, "f32", "bf16"), (256, 512, "f32", "bf16")])
 def test_extreme_values(bits, hidden, kv, w):
