@@ -49,7 +49,6 @@ constexpr int kTPB = kTokensPerBlock;       // tokens per workgroup
 
 constexpr int kSubLists = 4;                // candidate sub-lists per block (one per wavefront of a 256-thread workgroup)
 constexpr int kWaveCap = kCandCap / kSubLists;        // entries of one sub-list (256)
-constexpr int kWideThreads = 1024;          // threads of a score workgroup where the grid is small
 constexpr int kWaveFull = 255;              // count value meaning "this sub-list overflowed"
 constexpr int kLongRun = 16;                // blocks per resident workgroup from which runs are cut short
 constexpr int kShortRun = 4;
@@ -115,29 +114,60 @@ struct ScoreArgs {
     int Hkv, nblk, max_blocks, k, total_tasks, tasks_per_group;
 };
 
-// Wavefronts per SIMD the register allocation must leave room for.  Without the hint the allocator
+// Lanes that share a key: 16 bytes per lane when the code is 16, 32, 64 or 128 bytes, else one lane per key.
+constexpr int lanes_per_key(int W) { return (W == 4 || W == 8 || W == 16 || W == 32) ? W / 4 : 1; }
+// Single heads and pairs stream keys one batch of loads ahead, in two register buffers.
+constexpr bool loads_ahead(int G) { return G <= 2; }
+// Load instructions per batch with T threads.
+constexpr int load_batch(int W, int T)
+{
+    const int cwl = W / lanes_per_key(W), slots = kTPB / T * lanes_per_key(W), most = cwl <= 4 ? 4 : cwl <= 8 ? 2 : 1;
+    return most < slots / 2 ? most : slots / 2;
+}
+
+// Threads of a score workgroup.  The distances of a thread's keys stay in registers, two keys to a register and
+// head, beside the query codes and the keys on their way; the epilogue walks the heads one after another.  More
+// threads hold fewer keys each and hide each other's epilogues, fewer threads leave more registers and more blocks
+// per compute unit.  All pairs of W and G were timed with every width at 24 to 3840 blocks; 256 compute units:
+//
+//  * Up to one block per compute unit the chain of a block is what counts: 1024 threads, where their state leaves
+//    them within 128 registers, else 512 threads with 256.  28 heads on 4, 128 bits, 25 blocks each: 16.2 -> 11 us;
+//    32 heads on 4, 512 bits, 24 blocks: 39 -> 23 us; groups of 8, 416 bits, 240 blocks: 31 us with 256 threads, 82
+//    with 1024 (141 spilled registers), 26 with 512.
+//  * Up to two, 512 threads of 128 registers where the state fits them: one generation, four wavefronts a SIMD.
+//    Groups of 4, 128 bits, 384 blocks: 14.1 -> 11.4 us.
+//  * More: 256 threads while three such workgroups fit a compute unit (168 registers), 512 where the group is too
+//    large for that (kWideFrom) and the state fits.  32-bit codes, groups of 3, 768 blocks: 8.8 us with 256 threads,
+//    12 with 512; 256 bits, groups of 6: 33 and 42; groups of 8, 128 bits, 1536 blocks: 54 and 48.  480 bits, groups
+//    of 8: 143 and 648 (224 spilled registers).
+//
+// The state: distances, query codes and words of keys on their way (with a second buffer, and what moves between
+// the two, three times), and three words of a key in temporaries.  The limits are where spills start to cost more
+// than the width gains.
+constexpr int score_state(int W, int G, int T)
+{
+    const int cwl = W / lanes_per_key(W);
+    return G * (kTPB / T / 2 + cwl) + ((loads_ahead(G) ? 3 : 1) * load_batch(W, T) + 3) * cwl;
+}
+constexpr bool fits_1024(int W, int G) { return score_state(W, G, 1024) <= 106; }
+constexpr bool fits_512(int W, int G) { return score_state(W, G, 512) <= 116; }
+// The group size from which 256 threads need more than 168 registers, per code word count (the compiler's figures).
+constexpr int kWideFrom[33] = {0, 9, 7, 5, 4, 5, 4, 4, 7, 4, 4, 4, 3, 9, 9, 9, 5, 9, 9, 9, 9, 9, 9, 9, 9, 9, 9, 9, 9, 9, 9, 9, 9};
+constexpr int score_threads(int W, int G) { return G >= kWideFrom[W] && fits_512(W, G) ? 512 : kThreads; }
+
+// Wavefronts per SIMD the register allocation of 256 threads must leave room for.  Without the hint the allocator
 // lands on either side of an occupancy step depending on unrelated code (256-bit codes with four
 // heads per group: 4 waves measured 4 % faster than 3; 512-bit codes: 167 or 256 registers).
 constexpr int score_min_waves(int W, int G) { return (W == 8 && G == 4) ? 4 : (W == 16 && G <= 4) ? 3 : 1; }
-
-// Threads of a score workgroup.  The distances of a thread's keys stay in registers, a register for two
-// keys and each head, and the epilogue walks the heads one after another: with several heads per group
-// 256 threads of 16 keys need up to 256 registers (two wavefronts per SIMD) and a long chain per block.
-// 512 threads of 8 keys: groups of 8, 512 bits, 2 x 8 x 182867 tokens 97.8 -> 83 us; groups of 8, 128
-// bits, 16 x 8 x 37099 51 -> 47 us; groups of 4, 128 bits, 2 x 8 x 101906 16.7 -> 12.7 us; groups of 2,
-// 128 bits, 2 x 16 x 40338 10.2 -> 8.4 us.  Groups of 4 with 256 bits keep 256 (their registers just
-// fit four wavefronts: 115 us for 16 x 8 x 131072 against 124), as do groups of 2 otherwise (64 bits,
-// 303594 x 16: 14.7 against 17 us) and single heads, which stream keys two batches ahead.
-constexpr int score_threads(int W, int G) { return G >= 5 || (G >= 3 && W != 8) || (G == 2 && W == 4) ? 512 : kThreads; }
 
 // Persistent workgroups.  A task is one (batch * kv head, token block); a workgroup takes
 // tasks_per_group CONSECUTIVE tasks, which mostly belong to one head, and keeps that head's
 // cumulative histogram in LDS across them, so the (slow, device-wide) atomics into the head's
 // global histogram happen once per run of tasks instead of once per block.
 //
-// T: threads of a workgroup (score_threads, or 1024 for small grids).
-template <int W, int G, int R, int T>
-__global__ __launch_bounds__(T, T == kThreads ? score_min_waves(W, G) : 4) void score_kernel(ScoreArgs a)
+// T: threads of a workgroup, OCC: wavefronts per SIMD that its registers must allow.
+template <int W, int G, int R, int T, int OCC>
+__global__ __launch_bounds__(T, OCC) void score_kernel(ScoreArgs a)
 {
     constexpr int KPT = kTPB / T;          // keys per thread
     constexpr int NREG = KPT / 2;          // registers of distances per head, two keys each
@@ -145,13 +175,11 @@ __global__ __launch_bounds__(T, T == kThreads ? score_min_waves(W, G) : 4) void 
     constexpr int L = W * 32;
     constexpr int BINS = L + 2;            // bin 0: forced tokens; bin d + 1: distance d
     constexpr int CH = (BINS + 63) / 64;   // bins per lane in the scan
-    // lanes per key: 16 bytes per lane when the code is 16, 32, 64 or 128 bytes, else one lane per key
-    constexpr int LPK = (W == 4 || W == 8 || W == 16 || W == 32) ? W / 4 : 1;
+    constexpr int LPK = lanes_per_key(W);
     constexpr int CWL = W / LPK;           // code words per lane
-    constexpr int SLOTS = KPT * LPK;      // load instructions per thread and task
+    constexpr int SLOTS = KPT * LPK;       // load instructions per thread and task
     constexpr int KPS = T / LPK;           // keys per slot
-    constexpr int KBMAX = CWL <= 4 ? 4 : (CWL <= 8 ? 2 : 1);
-    constexpr int KB = KBMAX < SLOTS / 2 ? KBMAX : SLOTS / 2;   // slots per batch of loads
+    constexpr int KB = load_batch(W, T);   // slots per batch of loads
     __shared__ uint32_t hist[G * BINS * R];
     __shared__ uint32_t cum[G * BINS];     // this block's histogram, then its cumulative form
     __shared__ uint32_t gacc[G * BINS];    // cumulative histogram summed over this run of tasks
@@ -180,7 +208,7 @@ __global__ __launch_bounds__(T, T == kThreads ? score_min_waves(W, G) : 4) void 
     // Groups of four or eight heads keep too many distances in registers for a second buffer (it
     // measured slower): they load each batch right before using it.
     constexpr int NB = SLOTS / KB;
-    constexpr bool AHEAD = G <= 2;
+    constexpr bool AHEAD = loads_ahead(G);
     static_assert(NB % 2 == 0, "the first batch of every task lands in buf[0]");
     uint32_t buf[AHEAD ? 2 : 1][KB][CWL];
     auto fetch = [&](auto full, int t, int bt, uint32_t (&dst)[KB][CWL]) {
@@ -260,10 +288,10 @@ __global__ __launch_bounds__(T, T == kThreads ? score_min_waves(W, G) : 4) void 
 #pragma unroll
             for (int i = 0; i < NREG; ++i) dv[g][i] = 0x7fff7fffu;   // absent keys: farther than any bound
 
-        // A "slot" is one load instruction of the workgroup: KPS = 256 / LPK keys, LPK adjacent lanes
+        // A "slot" is one load instruction of the workgroup: KPS = T / LPK keys, LPK adjacent lanes
         // per key, 16 bytes per lane (fully coalesced).  The partial distances of a key are added
         // across its LPK lanes; lane `sub` of the key keeps the slots with s % LPK == sub, so every
-        // lane ends up owning 16 keys: key j of a lane is slot j * LPK + sub, token offset
+        // lane ends up owning KPT keys: key j of a lane is slot j * LPK + sub, token offset
         // (j * LPK + sub) * KPS + kq.
         auto score_block = [&](auto full) {
 #pragma unroll
@@ -819,9 +847,9 @@ int launch_score_wg(spotlight_ctx* ctx, StageTimer& timer, const RetrieveArgs& a
                     : (G * BINS * 2 * 4 <= kCap && G * BINS * 2 * 4 + kRest <= 65536) ? 2 : 1;
     static_assert(G * BINS * R * 4 + kRest <= 65536, "LDS of the score kernel");
     constexpr int T = score_threads(W, G);
-    auto kern = score_kernel<W, G, R, T>;
+    auto kern = score_kernel<W, G, R, T, T == kThreads ? score_min_waves(W, G) : 4>;
     // persistent grid: as many workgroups as the chip holds at once (a context has one code length
-    // and one group size, hence one score kernel: asked once per context)
+    // and one group size, hence one such kernel: asked once per context)
     if (ctx->score_resident == 0) {
         int per_cu = 0;
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, T, 0) != hipSuccess || per_cu < 1)
@@ -846,15 +874,18 @@ int launch_score_wg(spotlight_ctx* ctx, StageTimer& timer, const RetrieveArgs& a
     s.k = a.k;
     s.total_tasks = a.nblk * p.B * p.Hkv;
     s.tasks_per_group = (s.total_tasks + resident - 1) / resident;
-    // At most one block for every compute unit: what counts is the chain of one block, and 1024 threads
-    // of 4 keys shorten it (they cost the chip its second workgroup per compute unit, which such a
-    // grid has not got).  28 heads on 4, 100003 tokens: 16.2 -> 11 us; 32 heads on 4, 4724 tokens, 512
-    // bits: 40 -> 22 us; 32 heads, 32768 tokens: 6.8 -> 6.2 us; with twice as many blocks 512 threads do better.
-    if (s.total_tasks <= ctx->n_cus) {
+    // a workgroup for every block
+    auto single = [&](auto k, int threads) {
         *tasks_per_group = s.tasks_per_group = 1;
-        timer.launch(score_kernel<W, G, R, kWideThreads>, dim3(static_cast<unsigned>(s.total_tasks)), dim3(kWideThreads), 0, s);
+        timer.launch(k, dim3(static_cast<unsigned>(s.total_tasks)), dim3(static_cast<unsigned>(threads)), 0, s);
         return SPOTLIGHT_OK;
+    };
+    if (s.total_tasks <= ctx->n_cus) {
+        if constexpr (fits_1024(W, G)) return single(score_kernel<W, G, R, 1024, 4>, 1024);
+        else return single(score_kernel<W, G, R, 512, 2>, 512);
     }
+    if constexpr (G >= 2 && fits_512(W, G))
+        if (s.total_tasks <= 2 * ctx->n_cus) return single(score_kernel<W, G, R, 512, 4>, 512);
     // Long streams (gigabytes of codes): short runs, handed out by the hardware as workgroups
     // retire, instead of one long run per resident workgroup.  The workgroups in flight then read
     // one window of memory that moves through the cache in order, and uneven progress evens out

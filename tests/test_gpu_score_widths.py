@@ -66,3 +66,15 @@ def test_sub_lists_that_overflow(G, k):
 @pytest.mark.parametrize("B", [1, 300])
 def test_windows_that_fill_a_threads_tokens(B, n_sink, n_local):
     _check(B, 8 if B > 1 else 1, 4, 4096 + 640, 64, 400, n_sink, n_local, heads=2)   # both select widths
+
+
+# the code lengths and groups on either side of every line of the rule that gives a score workgroup its threads
+# and registers: 1024 threads or 512 with 256 registers up to a block per compute unit, 512 with 128 up to two,
+# 512 or 256 above
+@pytest.mark.parametrize("Hkv,B", [(5, 4), (25, 6), (28, 10)])     # 40, 300 and 560 blocks
+@pytest.mark.parametrize("bits,G", [(32, 3), (64, 6), (64, 7), (128, 3), (128, 4), (160, 4), (192, 8), (224, 7), (224, 8), (256, 6), (256, 7),
+                                    (288, 6), (288, 7), (320, 5), (320, 6), (352, 3), (352, 4), (352, 5), (384, 2), (384, 3), (416, 1), (416, 2),
+                                    (416, 3), (416, 8), (448, 1), (448, 2), (448, 8), (480, 1), (480, 2), (480, 3), (480, 8), (512, 4),
+                                    (512, 5), (512, 8), (1024, 1), (1024, 2)])
+def test_widths_by_registers(bits, G, Hkv, B):
+    _check(B, Hkv, G, 4096 + 50, bits, 60, 2, 3, heads=2)
