@@ -66,6 +66,15 @@ __device__ __forceinline__ uint32_t magnitude_bits(const float4& f)
 }
 __device__ __forceinline__ uint32_t magnitude_bits(const Raw8<bf16_raw>& r) { return magnitude_bits(r.u); }
 __device__ __forceinline__ uint32_t magnitude_bits(const Raw8<float>& r) { return magnitude_bits(r.a) | magnitude_bits(r.b); }
+__device__ __forceinline__ uint32_t magnitude_bits(const bf16_raw* row, int n)   // of n weights in memory
+{
+    uint32_t bits = 0;
+#pragma unroll 1
+    for (int i = 0; i < n; i += 8) bits |= magnitude_bits(*reinterpret_cast<const uint4*>(row + i));
+    return bits;
+}
+// whether a lane has the condition; what follows is seldom run and kept out of the way
+__device__ __forceinline__ bool rare(bool condition) { return __builtin_expect(__ballot(condition) != 0, 0); }
 
 constexpr int kListCap = 1024;  // outputs of a tile that may go to the recomputation
 
@@ -681,11 +690,9 @@ __global__ __launch_bounds__(NW * 64, 2) void hash_cert_kernel(HashArgs a, float
         wreg[ks] = staged[((31 - c) * a.W + min(wave, a.W - 1)) * (a.hidden / 8 + 1) + min(ks, n_ks - 1) * 2 + half];
     __syncthreads();
     float norm = 0.0f;         // ||W2[j]|| of this lane's output
-    uint32_t bits = 0;
 #pragma unroll
     for (int ks = 0; ks < WREG; ++ks) {
         if (ks >= n_ks) continue;
-        bits |= magnitude_bits(wreg[ks]);
         const uint32_t d[4] = {wreg[ks].x, wreg[ks].y, wreg[ks].z, wreg[ks].w};
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
@@ -693,8 +700,10 @@ __global__ __launch_bounds__(NW * 64, 2) void hash_cert_kernel(HashArgs a, float
             norm = __builtin_fmaf(hi, hi, __builtin_fmaf(lo, lo, norm));
         }
     }
-    norm = square_of(norm, bits);
-    norm = norm_of(norm + __shfl_xor(norm, 32));
+    norm += __shfl_xor(norm, 32);
+    if (rare(norm == 0.0f))   // a row of zeros, or did its squares underflow?
+        norm = square_of(norm, magnitude_bits(w2 + static_cast<int64_t>((31 - c) * a.W + min(wave, a.W - 1)) * a.hidden, a.hidden));
+    norm = norm_of(norm);
     for (int i = tid; i < nub * 32; i += NT) bias[i] = i < a.hidden ? load1(b1 + i) : 0.0f;
 
     uint32_t au_outputs = 0, au_listed = 0, au_wrong = 0;   // this lane's audit totals
@@ -780,8 +789,9 @@ __global__ __launch_bounds__(NW * 64, 2) void hash_cert_kernel(HashArgs a, float
             }
         }
         sumsq += __shfl_xor(sumsq, 32);
-        if (__ballot(sumsq == 0.0f)) {   // zeros, or did their squares underflow?  (This lane's own activations, read back.)
+        if (rare(sumsq == 0.0f)) {   // zeros, or did their squares underflow?  (This lane's own activations, read back.)
             uint32_t bits = 0;
+#pragma unroll 1
             for (int i = 0; i < n_mine; ++i)
                 for (int q = 0; q < 4; ++q)
                     bits |= magnitude_bits(*reinterpret_cast<const float4*>(hs + c * stride + (wave * NUB + i) * 32 + 16 * (q / 2) + 8 * half + 4 * (q % 2)));
@@ -1005,10 +1015,8 @@ __global__ __launch_bounds__(kThreads, 2) void hash_linear_kernel(HashArgs a, fl
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
         float s = 0.0f;
-        uint32_t bits = 0;
 #pragma unroll
         for (int ks = 0; ks < 8; ++ks) {
-            bits |= magnitude_bits(wreg[nb][ks]);
             const uint32_t d[4] = {wreg[nb][ks].x, wreg[nb][ks].y, wreg[nb][ks].z, wreg[nb][ks].w};
 #pragma unroll
             for (int p = 0; p < 4; ++p) {
@@ -1016,8 +1024,10 @@ __global__ __launch_bounds__(kThreads, 2) void hash_linear_kernel(HashArgs a, fl
                 s = __builtin_fmaf(hi, hi, __builtin_fmaf(lo, lo, s));
             }
         }
-        s = square_of(s, bits);
-        tcol[nb] = eps * norm_of(s + __shfl_xor(s, 32));
+        s += __shfl_xor(s, 32);
+        if (rare(s == 0.0f))   // a row of zeros, or did its squares underflow?
+            s = square_of(s, magnitude_bits(r + static_cast<int64_t>((31 - c) * a.W + word0 + min(wave + 4 * nb, n_words - 1)) * kHeadDim, kHeadDim));
+        tcol[nb] = eps * norm_of(s);
     }
 
     uint32_t au_outputs = 0, au_listed = 0, au_wrong = 0;   // this lane's audit totals
@@ -1039,6 +1049,8 @@ __global__ __launch_bounds__(kThreads, 2) void hash_linear_kernel(HashArgs a, fl
         }
     };
     auto put_x = [&](int buf) {
+        float s[XPT];
+        bool none = false;
 #pragma unroll
         for (int i = 0; i < XPT; ++i) {
             const int e = tid + i * NT, t = e / CH, k8 = e % CH, at = k8 * TK + (t ^ k8);
@@ -1052,15 +1064,24 @@ __global__ __launch_bounds__(kThreads, 2) void hash_linear_kernel(HashArgs a, fl
                 m.x[buf][0][at] = __builtin_bit_cast(uint4, hi);
                 m.x[buf][PASSES - 1][at] = __builtin_bit_cast(uint4, lo);
             }
-            float s = 0.0f;
+            s[i] = 0.0f;
 #pragma unroll
-            for (int q = 0; q < 8; ++q) s = __builtin_fmaf(v[q], v[q], s);
-            s = add_across_16(s);
-            if (__ballot(s == 0.0f)) {   // zeros, or did their squares underflow?
-                const unsigned long long some = __ballot(magnitude_bits(xr[i]) != 0) >> (lane & 48);
-                s = square_of(s, static_cast<uint32_t>(some) & 0xffffu);
-            }
-            if (k8 == 0) m.hn[buf][t] = norm_of(s);
+            for (int q = 0; q < 8; ++q) s[i] = __builtin_fmaf(v[q], v[q], s[i]);
+            s[i] = add_across_16(s[i]);
+            none = none || s[i] == 0.0f;
+        }
+        // zeros, or did their squares underflow?  (Both sums first: a branch behind each costs a launch of single tiles
+        // 1 us.  Looked at only where outputs turn out to be open, which is in nearly every tile: 263 -> 301 us for
+        // 8 x 65536 vectors of 512 bits, this way 267.)
+        if (rare(none)) {
+#pragma unroll
+            for (int i = 0; i < XPT; ++i)
+                s[i] = square_of(s[i], static_cast<uint32_t>(__ballot(magnitude_bits(xr[i]) != 0) >> (lane & 48)) & 0xffffu);
+        }
+#pragma unroll
+        for (int i = 0; i < XPT; ++i) {
+            const int e = tid + i * NT;
+            if (e % CH == 0) m.hn[buf][e / CH] = norm_of(s[i]);
         }
     };
     // the chain of output row j for vector `row`, from the arrays as stored
