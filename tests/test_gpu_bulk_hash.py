@@ -87,6 +87,13 @@ def test_runs_of_several_tiles():
     _both(2, 32, 16 * 32 * 6 + 1, 0, 16 * 32 * 6 + 1, 96, 0, "f32", "bf16")
 
 
+@pytest.mark.parametrize("bits,hidden,w", [(96, 64, "f32"), (64, 64, "bf16"), (96, 0, "bf16")])
+@pytest.mark.parametrize("rows", [90, 600])
+def test_runs_that_do_not_divide(rows, bits, hidden, w):
+    """512 heads of 3 and of 19 tiles: runs of one, and of ten and nine."""
+    _both(16, 32, rows, 0, rows, bits, hidden, "bf16", w)
+
+
 def test_many_heads_of_few_rows():
     """More heads than compute units: the row count from which the matrix cores take over is another."""
     _both(10, 30, 16, 1, 20, 64, 128, "bf16", "bf16")
