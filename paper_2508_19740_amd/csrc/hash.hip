@@ -278,7 +278,7 @@ template <typename XT, typename WT>
 int run_tk(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int stage)
 {
     const size_t cap = static_cast<size_t>(ctx->max_lds);
-    if (bulk_hash_applies(ctx, a, n_xheads, sizeof(XT))) return run_bulk_hash<XT, WT>(ctx, a, n_xheads, stage);
+    if (bulk_hash_applies(ctx, a, n_xheads, sizeof(XT), sizeof(WT))) return run_bulk_hash<XT, WT>(ctx, a, n_xheads, stage);
     // a single vector per head, hidden width a multiple of 128: the latency-oriented kernel
     if (a.n_rows == 1 && a.hidden % kHeadDim == 0) return run_vec<XT, WT>(ctx, a, n_xheads, nullptr, 0, stage);
     if (a.n_rows >= 32 && lds_bytes(32, a.hidden) <= cap) return run_ks<XT, WT, 32>(ctx, a, n_xheads, stage);

@@ -1340,7 +1340,7 @@ inline size_t lds_bytes(size_t x_size, int hidden) { return kTile * (x_size * kH
 
 // Whether the matrix-core kernels serve this job: enough vectors, and the activations of a tile fit in
 // LDS (hidden widths up to 1152, or 1216 with bfloat16 vectors).
-inline bool bulk_hash_applies(const spotlight_ctx* ctx, const hashdev::HashArgs& a, int n_xheads, size_t x_size)
+inline bool bulk_hash_applies(const spotlight_ctx* ctx, const hashdev::HashArgs& a, int n_xheads, size_t x_size, size_t w_size)
 {
     // From how many vectors per head: below, the vector-ALU kernel's tiles of 8 do less work for padding.
     // Measured for 8 / 512 heads of a 128 -> 256 -> 128 network: 8 rows 26 against 23 and 28 against 31 us,
@@ -1350,7 +1350,21 @@ inline bool bulk_hash_applies(const spotlight_ctx* ctx, const hashdev::HashArgs&
     // Codes of one or two words with a wide hidden layer: while every tile of 8 has a compute unit of its own
     // that kernel is the faster one, its lanes sharing the sums.  8 heads x 20 vectors, 64 bits: hidden 256 19.2
     // against 22.1 us, 512 34 against 46 us; hidden 128 17 against 14 us; 512 heads x 18, 256 -> 64: 45 against 31 us.
-    if (a.hidden > 128 && a.W <= 2 && a.n_rows < bulk::kTile && n_xheads * ((a.n_rows + 7) / 8) <= ctx->n_cus) return false;
+    const bool few = a.n_rows < bulk::kTile && n_xheads * ((a.n_rows + 7) / 8) <= ctx->n_cus;
+    if (few && a.hidden > 128 && a.W <= 2) return false;
+    // Likewise long codes behind a narrow layer of binary32 weights, whose words a wavefront takes one after another.
+    // 8 heads x 17: 128 -> 64 -> 512 18.2 against 19.5 us, 1024 bits 25.7 against 31; 384 bits 18.4 against 16.3.
+    if (few && w_size == 4 && a.hidden <= 128 && a.W >= 16) return false;
+    // One word of bfloat16 weights has one wavefront of eight or sixteen at work in layer 2: up to three tiles of 8 are
+    // the faster ones on any grid.  512 heads x 17, 32 bits: hidden 512 68 against 73 us, 1024 172 against 184;
+    // hidden 256 40 against 28; binary32 weights 100 against 73.
+    if (w_size == 2 && a.hidden > 256 && a.hidden <= 1024 && a.W == 1 && a.n_rows <= 24) return false;
+    // Exact words, one or more for every hidden unit, on grids of more than two tiles for every compute unit: their
+    // loads and signs are all there is, and the vector-ALU kernel spreads those over all its lanes.  512 heads x 600,
+    // 128 -> 16 -> 1024: 345 against 500 us; 512 bits, binary32 249 against 298; 256 bits 206 against 202; 8 heads x
+    // 300, 1024 bits 39 against 21.
+    const bool exact = w_size == 4 || a.hidden % 16 != 0 || a.W > 16;
+    if (exact && a.hidden > 0 && a.W >= a.hidden && (a.n_rows + bulk::kTile - 1) / bulk::kTile * n_xheads > 2 * ctx->n_cus) return false;
     return a.wnorm && a.n_rows >= min_rows && bulk::lds_bytes(x_size, a.hidden) <= static_cast<size_t>(ctx->max_lds);
 }
 

@@ -1,4 +1,5 @@
-"""Host rules of the bulk hash, compiled for the CPU: how the tiles of a head are shared out over workgroups."""
+"""Host rules of the bulk hash, compiled for the CPU: how the tiles of a head are shared out over workgroups, and
+which calls stay with the vector-ALU kernels because those are faster there."""
 import os
 import subprocess
 
@@ -40,6 +41,31 @@ int main()
 }
 """
 
+ROUTES = r"""
+#include <stdio.h>
+#include <string.h>
+#include "hash_bulk.h"
+using namespace spotlight;
+int main(int argc, char** argv)
+{
+    int heads, rows, bits, hidden, x_size, w_size;
+    while (scanf("%d %d %d %d %d %d", &heads, &rows, &bits, &hidden, &x_size, &w_size) == 6) {
+        spotlight_ctx ctx;
+        memset(&ctx, 0, sizeof(ctx));
+        ctx.n_cus = 256;
+        ctx.max_lds = 160 * 1024;
+        hashdev::HashArgs a;
+        memset(&a, 0, sizeof(a));
+        float scratch;
+        a.wnorm = &scratch;
+        a.n_rows = rows; a.hidden = hidden; a.L = bits; a.W = bits / 32;
+        printf("%d\n", bulk_hash_applies(&ctx, a, heads, x_size, w_size) ? 1 : 0);
+    }
+    return 0;
+}
+"""
+
+
 def _program(tmp_path, text, name):
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     if not os.path.exists(hipcc):
@@ -54,3 +80,27 @@ def _program(tmp_path, text, name):
 def test_runs_are_even(tmp_path):
     run = subprocess.run([_program(tmp_path, RUNS, "runs")], capture_output=True, text=True)
     assert run.returncode == 0, run.stdout
+
+
+def test_routes(tmp_path):
+    """(heads, rows, bits, hidden, weight bytes) -> whether the matrix-core kernels take the call."""
+    routes = {
+        (8, 8, 128, 256, 2): 0, (8, 9, 128, 256, 2): 1, (512, 16, 128, 256, 2): 0, (512, 17, 128, 256, 2): 1,
+        (8, 31, 512, 0, 2): 0, (8, 32, 512, 0, 2): 1,
+        (8, 31, 64, 256, 2): 0, (8, 31, 96, 256, 2): 1, (8, 32, 64, 256, 2): 1, (512, 18, 64, 256, 2): 1, (8, 20, 64, 128, 2): 1,
+        # long codes behind a narrow layer of binary32 weights, few vectors
+        (8, 17, 512, 64, 4): 0, (8, 17, 1024, 128, 4): 0, (8, 17, 384, 64, 4): 1, (8, 17, 512, 136, 4): 1, (8, 32, 512, 64, 4): 1,
+        (8, 17, 512, 64, 2): 1, (512, 17, 512, 64, 4): 1,
+        # one word behind a wide layer of bfloat16 weights
+        (512, 24, 32, 512, 2): 0, (512, 25, 32, 512, 2): 1, (512, 24, 32, 256, 2): 1, (512, 24, 32, 512, 4): 1, (512, 24, 64, 512, 2): 1,
+        (512, 24, 32, 1152, 2): 1,
+        # a word or more for every hidden unit, on large grids
+        (512, 90, 512, 16, 4): 0, (512, 90, 1024, 16, 2): 0, (512, 90, 384, 16, 4): 1, (512, 90, 512, 16, 2): 1, (512, 32, 1024, 16, 4): 1,
+        (8, 300, 1024, 16, 4): 1, (8, 4000, 1024, 16, 4): 0, (512, 90, 1024, 64, 4): 1,
+        # what LDS holds
+        (8, 64, 128, 1152, 4): 1, (8, 64, 128, 1224, 4): 0,
+    }
+    text = "\n".join(f"{h} {r} {b} {n} 2 {w}" for h, r, b, n, w in routes)
+    run = subprocess.run([_program(tmp_path, ROUTES, "routes")], input=text, capture_output=True, text=True, check=True)
+    got = dict(zip(routes, map(int, run.stdout.split())))
+    assert got == routes

@@ -94,6 +94,12 @@ def test_runs_that_do_not_divide(rows, bits, hidden, w):
     _both(16, 32, rows, 0, rows, bits, hidden, "bf16", w)
 
 
+@pytest.mark.parametrize("B,rows,bits,hidden,w", [(1, 31, 512, 64, "f32"), (1, 32, 512, 64, "f32"), (10, 24, 32, 264, "bf16"), (10, 25, 32, 264, "bf16"),
+                                                  (10, 65, 512, 16, "f32"), (10, 65, 480, 16, "f32"), (10, 65, 1024, 24, "bf16")])
+def test_calls_of_either_kernel(B, rows, bits, hidden, w):
+    _both(B, 30 if B > 1 else 3, rows, 2, rows + 5, bits, hidden, "bf16", w)
+
+
 def test_many_heads_of_few_rows():
     """More heads than compute units: the row count from which the matrix cores take over is another."""
     _both(10, 30, 16, 1, 20, 64, 128, "bf16", "bf16")
