@@ -137,9 +137,10 @@ constexpr int load_batch(int W, int T)
 //  * Up to two, 512 threads of 128 registers where the state fits them: one generation, four wavefronts a SIMD.
 //    Groups of 4, 128 bits, 384 blocks: 14.1 -> 11.4 us.
 //  * More: 256 threads while three such workgroups fit a compute unit (168 registers), 512 where the group is too
-//    large for that (kWideFrom) and the state fits.  32-bit codes, groups of 3, 768 blocks: 8.8 us with 256 threads,
-//    12 with 512; 256 bits, groups of 6: 33 and 42; groups of 8, 128 bits, 1536 blocks: 54 and 48.  480 bits, groups
-//    of 8: 143 and 648 (224 spilled registers).
+//    large for that (kWideFrom) and the state fits.  Groups of 8, 128 bits, 1536 blocks: 54 and 48 us; 480 bits: 143 and
+//    648 (224 spilled registers).  Between the two generations of workgroups decide (wide_runs): 96 bits, groups
+//    of 4, 1024 blocks, two of either width, 24.5 us with 256 threads, 20 with 512; 256 bits, groups of 6, 768
+//    blocks, one and two: 33 and 42.
 //
 // The state: distances, query codes and words of keys on their way (with a second buffer, and what moves between
 // the two, three times), and three words of a key in temporaries.  The limits are where spills start to cost more
@@ -153,6 +154,13 @@ constexpr bool fits_1024(int W, int G) { return score_state(W, G, 1024) <= 106; 
 constexpr bool fits_512(int W, int G) { return score_state(W, G, 512) <= 116; }
 // The group size from which 256 threads need more than 168 registers, per code word count (the compiler's figures).
 constexpr int kWideFrom[33] = {0, 9, 7, 5, 4, 5, 4, 4, 7, 4, 4, 4, 3, 9, 9, 9, 5, 9, 9, 9, 9, 9, 9, 9, 9, 9, 9, 9, 9, 9, 9, 9, 9};
+// Whether `runs` generations of 512 threads take less time than `narrow` of 256, measured: no more of them for codes
+// of two lanes, four to three for codes of one, three to two for codes of four (pairs of heads of those excepted:
+// 102 us with 256 threads, 114 with 512, 2048 blocks).
+constexpr bool wide_runs(int W, int runs, int narrow)
+{
+    return lanes_per_key(W) == 1 ? 3 * runs <= 4 * narrow : lanes_per_key(W) == 2 ? runs <= narrow : 2 * runs <= 3 * narrow;
+}
 constexpr int score_threads(int W, int G) { return G >= kWideFrom[W] && fits_512(W, G) ? 512 : kThreads; }
 
 // Wavefronts per SIMD the register allocation of 256 threads must leave room for.  Without the hint the allocator
@@ -874,18 +882,21 @@ int launch_score_wg(spotlight_ctx* ctx, StageTimer& timer, const RetrieveArgs& a
     s.k = a.k;
     s.total_tasks = a.nblk * p.B * p.Hkv;
     s.tasks_per_group = (s.total_tasks + resident - 1) / resident;
-    // a workgroup for every block
-    auto single = [&](auto k, int threads) {
+    if (s.total_tasks <= ctx->n_cus) {   // a workgroup for every block
+        constexpr int TS = fits_1024(W, G) ? 1024 : 512;
         *tasks_per_group = s.tasks_per_group = 1;
-        timer.launch(k, dim3(static_cast<unsigned>(s.total_tasks)), dim3(static_cast<unsigned>(threads)), 0, s);
+        timer.launch(score_kernel<W, G, R, TS, TS == 1024 ? 4 : 2>, dim3(static_cast<unsigned>(s.total_tasks)), dim3(TS), 0, s);
         return SPOTLIGHT_OK;
-    };
-    if (s.total_tasks <= ctx->n_cus) {
-        if constexpr (fits_1024(W, G)) return single(score_kernel<W, G, R, 1024, 4>, 1024);
-        else return single(score_kernel<W, G, R, 512, 2>, 512);
     }
-    if constexpr (G >= 2 && fits_512(W, G))
-        if (s.total_tasks <= 2 * ctx->n_cus) return single(score_kernel<W, G, R, 512, 4>, 512);
+    int threads = T;
+    if constexpr (T == kThreads && G >= 2 && fits_512(W, G)) {
+        const int runs = (s.total_tasks + 2 * ctx->n_cus - 1) / (2 * ctx->n_cus);
+        if (runs == 1 || ((G > 2 || lanes_per_key(W) == 1) && resident >= 3 * ctx->n_cus && wide_runs(W, runs, s.tasks_per_group))) {
+            threads = 512;
+            kern = score_kernel<W, G, R, 512, 4>;
+            s.tasks_per_group = runs;
+        }
+    }
     // Long streams (gigabytes of codes): short runs, handed out by the hardware as workgroups
     // retire, instead of one long run per resident workgroup.  The workgroups in flight then read
     // one window of memory that moves through the cache in order, and uneven progress evens out
@@ -895,7 +906,7 @@ int launch_score_wg(spotlight_ctx* ctx, StageTimer& timer, const RetrieveArgs& a
     if (s.tasks_per_group >= kLongRun) s.tasks_per_group = kShortRun;
     *tasks_per_group = s.tasks_per_group;
     const int grid = (s.total_tasks + s.tasks_per_group - 1) / s.tasks_per_group;
-    timer.launch(kern, dim3(static_cast<unsigned>(grid)), dim3(T), 0, s);
+    timer.launch(kern, dim3(static_cast<unsigned>(grid)), dim3(static_cast<unsigned>(threads)), 0, s);
     return SPOTLIGHT_OK;
 }
 

@@ -69,9 +69,9 @@ def test_windows_that_fill_a_threads_tokens(B, n_sink, n_local):
 
 
 # the code lengths and groups on either side of every line of the rule that gives a score workgroup its threads
-# and registers: 1024 threads or 512 with 256 registers up to a block per compute unit, 512 with 128 up to two,
-# 512 or 256 above
-@pytest.mark.parametrize("Hkv,B", [(5, 4), (25, 6), (28, 10)])     # 40, 300 and 560 blocks
+# and registers: 1024 threads or 512 with 256 registers up to a block per compute unit, 512 with 128 up to two, by
+# generations above (two of either width between three and four blocks; four and three from six on)
+@pytest.mark.parametrize("Hkv,B", [(5, 4), (25, 6), (28, 10), (40, 11), (40, 20)])     # 40, 300, 560, 880 and 1600 blocks
 @pytest.mark.parametrize("bits,G", [(32, 3), (64, 6), (64, 7), (128, 3), (128, 4), (160, 4), (192, 8), (224, 7), (224, 8), (256, 6), (256, 7),
                                     (288, 6), (288, 7), (320, 5), (320, 6), (352, 3), (352, 4), (352, 5), (384, 2), (384, 3), (416, 1), (416, 2),
                                     (416, 3), (416, 8), (448, 1), (448, 2), (448, 8), (480, 1), (480, 2), (480, 3), (480, 8), (512, 4),
