@@ -689,21 +689,6 @@ __global__ __launch_bounds__(NW * 64, 2) void hash_cert_kernel(HashArgs a, float
     for (int ks = 0; ks < WREG; ++ks)
         wreg[ks] = staged[((31 - c) * a.W + min(wave, a.W - 1)) * (a.hidden / 8 + 1) + min(ks, n_ks - 1) * 2 + half];
     __syncthreads();
-    float norm = 0.0f;         // ||W2[j]|| of this lane's output
-#pragma unroll
-    for (int ks = 0; ks < WREG; ++ks) {
-        if (ks >= n_ks) continue;
-        const uint32_t d[4] = {wreg[ks].x, wreg[ks].y, wreg[ks].z, wreg[ks].w};
-#pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            const float lo = __uint_as_float(d[p] << 16), hi = __uint_as_float(d[p] & 0xffff0000u);
-            norm = __builtin_fmaf(hi, hi, __builtin_fmaf(lo, lo, norm));
-        }
-    }
-    norm += __shfl_xor(norm, 32);
-    if (rare(norm == 0.0f))   // a row of zeros, or did its squares underflow?
-        norm = square_of(norm, magnitude_bits(w2 + static_cast<int64_t>((31 - c) * a.W + min(wave, a.W - 1)) * a.hidden, a.hidden));
-    norm = norm_of(norm);
     for (int i = tid; i < nub * 32; i += NT) bias[i] = i < a.hidden ? load1(b1 + i) : 0.0f;
 
     uint32_t au_outputs = 0, au_listed = 0, au_wrong = 0;   // this lane's audit totals
@@ -733,6 +718,21 @@ __global__ __launch_bounds__(NW * 64, 2) void hash_cert_kernel(HashArgs a, float
         }
     };
     fetch_x(tile0);
+    float norm = 0.0f;         // ||W2[j]|| of this lane's output
+#pragma unroll
+    for (int ks = 0; ks < WREG; ++ks) {
+        if (ks >= n_ks) continue;
+        const uint32_t d[4] = {wreg[ks].x, wreg[ks].y, wreg[ks].z, wreg[ks].w};
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            const float lo = __uint_as_float(d[p] << 16), hi = __uint_as_float(d[p] & 0xffff0000u);
+            norm = __builtin_fmaf(hi, hi, __builtin_fmaf(lo, lo, norm));
+        }
+    }
+    norm += __shfl_xor(norm, 32);
+    if (rare(norm == 0.0f))   // a row of zeros, or did its squares underflow?
+        norm = square_of(norm, magnitude_bits(w2 + static_cast<int64_t>((31 - c) * a.W + min(wave, a.W - 1)) * a.hidden, a.hidden));
+    norm = norm_of(norm);
     put_x();
     __syncthreads();
     for (int64_t tile = tile0; tile < tile1; ++tile) {
@@ -1011,25 +1011,6 @@ __global__ __launch_bounds__(kThreads, 2) void hash_linear_kernel(HashArgs a, fl
         }
         __syncthreads();
     }
-    float tcol[NB];   // eps ||R_j||
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-        float s = 0.0f;
-#pragma unroll
-        for (int ks = 0; ks < 8; ++ks) {
-            const uint32_t d[4] = {wreg[nb][ks].x, wreg[nb][ks].y, wreg[nb][ks].z, wreg[nb][ks].w};
-#pragma unroll
-            for (int p = 0; p < 4; ++p) {
-                const float lo = __uint_as_float(d[p] << 16), hi = __uint_as_float(d[p] & 0xffff0000u);
-                s = __builtin_fmaf(hi, hi, __builtin_fmaf(lo, lo, s));
-            }
-        }
-        s += __shfl_xor(s, 32);
-        if (rare(s == 0.0f))   // a row of zeros, or did its squares underflow?
-            s = square_of(s, magnitude_bits(r + static_cast<int64_t>((31 - c) * a.W + word0 + min(wave + 4 * nb, n_words - 1)) * kHeadDim, kHeadDim));
-        tcol[nb] = eps * norm_of(s);
-    }
-
     uint32_t au_outputs = 0, au_listed = 0, au_wrong = 0;   // this lane's audit totals
     float au_ratio = 0.0f;
 
@@ -1108,6 +1089,24 @@ __global__ __launch_bounds__(kThreads, 2) void hash_linear_kernel(HashArgs a, fl
     };
 
     fetch_x(tile0);
+    float tcol[NB];   // eps ||R_j||
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        float s = 0.0f;
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) {
+            const uint32_t d[4] = {wreg[nb][ks].x, wreg[nb][ks].y, wreg[nb][ks].z, wreg[nb][ks].w};
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+                const float lo = __uint_as_float(d[p] << 16), hi = __uint_as_float(d[p] & 0xffff0000u);
+                s = __builtin_fmaf(hi, hi, __builtin_fmaf(lo, lo, s));
+            }
+        }
+        s += __shfl_xor(s, 32);
+        if (rare(s == 0.0f))   // a row of zeros, or did its squares underflow?
+            s = square_of(s, magnitude_bits(r + static_cast<int64_t>((31 - c) * a.W + word0 + min(wave + 4 * nb, n_words - 1)) * kHeadDim, kHeadDim));
+        tcol[nb] = eps * norm_of(s);
+    }
     put_x(0);
     if (tile0 + 1 < tile1) fetch_x(tile0 + 1);
     __syncthreads();
