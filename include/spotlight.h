@@ -272,7 +272,8 @@ int spotlight_decode_step_noalloc(const spotlight_config *cfg, const void *q, co
  * Stage timing for benchmarks.  While enabled, every kernel launch carries two HIP events that are
  * stamped when the kernel starts and when it ends.  spotlight_profile_read waits for the stream,
  * adds the elapsed times of the launches recorded since the last read to the per-stage totals and
- * returns the totals for `stage` (milliseconds, number of launches).  Do not capture into a HIP
+ * returns the totals for `stage` (milliseconds, number of launches; an ATTEND launch that has whole heads
+ * adds one to MERGE as well, so that both stages count the calls).  Do not capture into a HIP
  * graph while it is enabled.  spotlight_profile_enable(ctx, 0) stops recording
  * and clears the totals.  At most 8192 launches are recorded between two reads; later ones are
  * not timed.

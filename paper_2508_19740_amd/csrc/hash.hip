@@ -179,16 +179,16 @@ __global__ __launch_bounds__(kThreads) void pack_weights_kernel(const WT* __rest
     constexpr int G16 = kHeadDim / 8;
     const int W = L / 32, npairs = (W + 1) / 2;
     const int act_dim = hidden > 0 ? hidden : kHeadDim, n16 = act_dim / kHeadDim;
-    const int nib = (hidden + kThreads - 1) / kThreads;   // 0 for the linear hash: no first layer
-    const int64_t groups1 = static_cast<int64_t>(n_wheads) * nib * G16 * kThreads;
+    const int nib = (hidden + kPackRows - 1) / kPackRows;   // 0 for the linear hash: no first layer
+    const int64_t groups1 = static_cast<int64_t>(n_wheads) * nib * G16 * kPackRows;
     const int64_t groups2 = static_cast<int64_t>(n_wheads) * npairs * n16 * G16 * 64;
     const int64_t x = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
     const WT* src = nullptr;
     WT* dst;
     if (x < groups1) {
-        const int t = static_cast<int>(x % kThreads), g = static_cast<int>((x / kThreads) % G16);
-        const int ib = static_cast<int>((x / (kThreads * G16)) % nib), whead = static_cast<int>(x / (static_cast<int64_t>(kThreads) * G16 * nib));
-        const int row = ib * kThreads + t;
+        const int t = static_cast<int>(x % kPackRows), g = static_cast<int>((x / kPackRows) % G16);
+        const int ib = static_cast<int>((x / (kPackRows * G16)) % nib), whead = static_cast<int>(x / (static_cast<int64_t>(kPackRows) * G16 * nib));
+        const int row = ib * kPackRows + t;
         if (row < hidden) src = w1 + (static_cast<int64_t>(whead) * hidden + row) * kHeadDim + g * 8;
         dst = pack_w1 + x * 8;
     } else if (x < groups1 + groups2) {
@@ -322,7 +322,7 @@ void pack_sizes(int hidden, int L, size_t* w1_elems, size_t* out_elems)
     if (hidden % kHeadDim != 0) return;   // the single-vector kernel takes hidden widths that are multiples of 128 (or 0)
     const int W = L / 32, npairs = (W + 1) / 2;
     const int act_dim = hidden > 0 ? hidden : kHeadDim;
-    *w1_elems = static_cast<size_t>((hidden + kThreads - 1) / kThreads) * kThreads * kHeadDim;
+    *w1_elems = static_cast<size_t>((hidden + kPackRows - 1) / kPackRows) * kPackRows * kHeadDim;
     *out_elems = static_cast<size_t>(npairs) * 64 * act_dim;
 }
 

@@ -208,13 +208,6 @@ template <> struct XTile<float> {
 #pragma unroll
         for (int j = 0; j < 8; ++j) xs[(k8 * 8 + j) * kTile + t] = v[j];
     }
-    template <typename R> static __device__ __forceinline__ void put_raw(float* xs, int k8, int t, const R& r)
-    {
-        float v[8];
-        expand(r, v);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) xs[(k8 * 8 + j) * kTile + t] = v[j];
-    }
     static __device__ __forceinline__ float step(const float* xs, int s, int lane) { return xs[s * 64 + lane]; }
 };
 
@@ -244,7 +237,7 @@ __global__ __launch_bounds__(kThreads) void row_norm_kernel(const bf16_raw* __re
 __host__ __device__ constexpr int hidden_padded(int hidden) { return (hidden + 31) / 32 * 32; }
 
 // Wavefronts per SIMD the register allocation must leave room for.  8 heads x 131072 vectors, 128 -> 512 ->
-// 256: four (a few spilled registers, outside the main loops) 3.25 ms, three 3.83 ms.
+// 256: four (128 registers and 38 spilled; 51 with binary32 vectors) 3.32 ms, three 3.83 ms.
 constexpr int min_waves(int NW, int NBW) { return NBW == 1 && NW >= 8 ? 4 : 2; }
 
 // NW:    wavefronts per workgroup.
@@ -588,10 +581,10 @@ __global__ __launch_bounds__(NW * 64, min_waves(NW, NBW)) void hash_bulk_kernel(
 // instead of each splitting all activations for its own word.  Wavefront w owns code word w: it
 // contracts it, takes the signs and recomputes what the bound does not settle itself, with the weights
 // it holds, so a tile costs two barriers.  Two workgroups per compute unit (LDS and registers).
-// Measured, 32 heads x 131072 vectors, 128 -> 256 -> 128: 4.2 ms (131 TFLOP/s), against 6.25 ms with
-// layer 1 on the vector ALU.  A tile takes 19.7 K cycles of a SIMD: 8.2 K of binary32 matrix
-// instructions and 7.9 K of vector instructions (SiLU 4.0 K, recomputation 1.9 K, unpacking 1.0 K),
-// which do not overlap.  Tried and slower: a list of open outputs shared by the workgroup, one
+// Measured, 32 heads x 131072 vectors, 128 -> 256 -> 128: 4.28 ms (128 TFLOP/s), against 6.25 ms with
+// layer 1 on the vector ALU.  A tile takes 19.8 K cycles of a SIMD (counters): 8.2 K of binary32 and 1.0 K of
+// bfloat16 matrix instructions and 8.1 K of vector instructions (by count SiLU 4.0 K, recomputation 1.9 K,
+// unpacking 1.0 K), of which only the bfloat16 ones overlap with others.  Tried and slower: a list of open outputs shared by the workgroup, one
 // wavefront taking all of it (4.55 ms: fewer instructions, but everybody waits for its chain); the
 // kernel below with three or four wavefronts per SIMD (4.6 and 5.0 ms); the contraction split over the
 // hidden units with sums through LDS float atomics (14.7 ms: those take about 4 cycles a lane).
@@ -940,8 +933,10 @@ __global__ __launch_bounds__(NW * 64, 2) void hash_cert_kernel(HashArgs a, float
 // vectors enter the matrix cores as they are, binary32 ones as hi + lo.  A wavefront keeps the weights
 // of up to four code words in registers and streams tiles of 32 vectors from LDS, already in operand
 // order, double-buffered with one barrier a tile.  What is left is the vector work of the signs (about
-// six instructions for 64 outputs): 65536 x 8 vectors of 512 bits went from 983 us on the vector ALU
-// (728 us on the binary32 matrix instruction).
+// six instructions for 64 outputs) and waits: 65536 x 8 vectors of 512 bits went from 983 us on the vector ALU
+// (728 us on the binary32 matrix instruction) to 270 us; 39 % of the cycles issue vector instructions, 10 %
+// are matrix instructions.  With four words a wavefront 50 registers are spilled (66 with binary32 vectors); a
+// recomputation that holds half as many operands spills 48 and is slower (284 us).
 constexpr int kLinearWords = 16;      // code words of a workgroup, four a wavefront
 constexpr int kLinearList = 256;      // open outputs of a wavefront and tile (of 32 x 128)
 constexpr int kLinearStage = 256;     // rows of R on their way into registers at a time
@@ -1129,7 +1124,7 @@ __global__ __launch_bounds__(kThreads, 2) void hash_linear_kernel(HashArgs a, fl
         for (int nb = 0; nb < NB; ++nb) {
             const int w = wave + 4 * nb;
             if (w >= n_words) continue;   // uniform over the wavefront
-            f32x16_t y;                   // one word at a time: four side by side would spill, and the vector unit is what is busy
+            f32x16_t y;                   // one word at a time: registers are short as it is, and the vector unit is what is busy
 #pragma unroll
             for (int v = 0; v < 16; ++v) y[v] = 0.0f;
 #pragma unroll

@@ -12,7 +12,7 @@
 namespace spotlight {
 
 constexpr int kHeadDim = 128;
-constexpr int kThreads = 256;       // 4 wavefronts of 64 lanes per workgroup (all kernels but the single-launch step)
+constexpr int kThreads = 256;       // 4 wavefronts of 64 lanes: the workgroup of most kernels
 constexpr int kMaxGroup = 8;        // query heads per key-value head
 constexpr int kAttendMinRows = 32;  // smallest number of gathered rows one workgroup takes
 constexpr int kTokensPerBlock = 4096;  // tokens one score / select workgroup covers
