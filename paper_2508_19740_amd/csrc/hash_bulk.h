@@ -782,15 +782,6 @@ __global__ __launch_bounds__(NW * 64, 2) void hash_cert_kernel(HashArgs a, float
             }
         }
         sumsq += __shfl_xor(sumsq, 32);
-        if (rare(sumsq == 0.0f)) {   // zeros, or did their squares underflow?  (This lane's own activations, read back.)
-            uint32_t bits = 0;
-#pragma unroll 1
-            for (int i = 0; i < n_mine; ++i)
-                for (int q = 0; q < 4; ++q)
-                    bits |= magnitude_bits(*reinterpret_cast<const float4*>(hs + c * stride + (wave * NUB + i) * 32 + 16 * (q / 2) + 8 * half + 4 * (q % 2)));
-            bits |= __shfl_xor(bits, 32);
-            sumsq = square_of(sumsq, bits);
-        }
         if (half == 0) m.part[wave][c] = sumsq;
         __syncthreads();   // activations and norms are complete; the x tile is free
         if (tile + 1 < tile1) put_x();
@@ -800,6 +791,12 @@ __global__ __launch_bounds__(NW * 64, 2) void hash_cert_kernel(HashArgs a, float
             float s = 0.0f;
 #pragma unroll
             for (int p = 0; p < NW; ++p) s += m.part[p][c];
+            if (rare(s == 0.0f)) {   // zeros, or did their squares underflow?
+                uint32_t bits = 0;
+#pragma unroll 1
+                for (int i = 4 * half; i < a.hidden; i += 8) bits |= magnitude_bits(*reinterpret_cast<const float4*>(hs + c * stride + i));
+                s = square_of(s, bits | __shfl_xor(bits, 32));
+            }
             if (half == 0) m.hn[wave][c] = norm_of(s);
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 
