@@ -1,7 +1,9 @@
 """GPU parity over every supported (code length, heads per group) pair (17 code lengths x groups of 1 to 8): each pair is its own
 instantiation of the score and select kernels (lanes per key, histogram replicas, batch sizes and
 register budgets all depend on it), so each one runs the one-call decode step against the oracle:
-appended code, index arrays (with and without forced tokens) bit-exact, attention within 2e-3."""
+appended code, index arrays (with and without forced tokens) bit-exact, attention within 2e-3.
+These grids are small; the widths that a score workgroup has on larger ones run for every pair in
+test_gpu_score_widths.py."""
 import pytest
 import torch
 

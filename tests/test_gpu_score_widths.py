@@ -78,3 +78,9 @@ def test_windows_that_fill_a_threads_tokens(B, n_sink, n_local):
                                     (512, 5), (512, 8), (1024, 1), (1024, 2)])
 def test_widths_by_registers(bits, G, Hkv, B):
     _check(B, Hkv, G, 4096 + 50, bits, 60, 2, 3, heads=2)
+
+
+@pytest.mark.parametrize("B", [6, 12])     # 300 and 600 blocks: the widths above a block per compute unit
+@pytest.mark.parametrize("words,G", [(w, g) for w in list(range(1, 17)) + [32] for g in range(1, 9) if not (w == 32 and g > 2)])
+def test_every_pair_on_larger_grids(words, G, B):
+    _check(B, 25, G, 4096 + 9 + words, words * 32, 50, 1, 2, heads=1)
