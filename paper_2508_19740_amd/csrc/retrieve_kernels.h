@@ -139,8 +139,8 @@ constexpr int load_batch(int W, int T)
 //  * More: 256 threads while three such workgroups fit a compute unit (168 registers), 512 where the group is too
 //    large for that (kWideFrom) and the state fits.  Groups of 8, 128 bits, 1536 blocks: 54 and 48 us; 480 bits: 143 and
 //    648 (224 spilled registers).  Between the two generations of workgroups decide (wide_runs): 96 bits, groups
-//    of 4, 1024 blocks, two of either width, 24.5 us with 256 threads, 20 with 512; 256 bits, groups of 6, 768
-//    blocks, one and two: 33 and 42.
+//    of 4, 1024 blocks, two of either width, 24.9 us with 256 threads, 20 with 512; 256 bits, groups of 6, 768
+//    blocks, one and two: 31.5 and 39.
 //
 // The state: distances, query codes and words of keys on their way (with a second buffer, and what moves between
 // the two, three times), and three words of a key in temporaries.  The limits are where spills start to cost more
