@@ -152,7 +152,8 @@ constexpr int score_state(int W, int G, int T)
 }
 constexpr bool fits_1024(int W, int G) { return score_state(W, G, 1024) <= 106; }
 constexpr bool fits_512(int W, int G) { return score_state(W, G, 512) <= 116; }
-// The group size from which 256 threads need more than 168 registers, per code word count (the compiler's figures).
+// The group size from which 256 threads need more than 168 registers, per code word count (the compiler's figures);
+// 9: none, or 512 gain nothing there (416 - 480 bits, 512 against 256 threads at 1536 blocks 1.02 - 1.05 of the time).
 constexpr int kWideFrom[33] = {0, 9, 7, 5, 4, 5, 4, 4, 7, 4, 4, 4, 3, 9, 9, 9, 5, 9, 9, 9, 9, 9, 9, 9, 9, 9, 9, 9, 9, 9, 9, 9, 9};
 // Whether `runs` generations of 512 threads take less time than `narrow` of 256, measured: no more of them for codes
 // of two lanes, four to three for codes of one, three to two for codes of four (pairs of heads of those excepted:
