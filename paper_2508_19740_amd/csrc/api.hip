@@ -59,6 +59,8 @@ int make_plan(const spotlight_config* c, Plan* p)
     const size_t welem = p->w_dtype == SPOTLIGHT_BF16 ? 2 : 4;
     p->off_pack_w1 = off;   off = align_up(off + static_cast<size_t>(p->Hkv) * p->pack_w1_elems * welem, 256);
     p->off_pack_out = off;  off = align_up(off + static_cast<size_t>(p->Hkv) * p->pack_out_elems * welem, 256);
+    p->off_scales = off;    off = align_up(off + static_cast<size_t>(p->Hkv) * (1 + p->W) * 16, 256);
+    p->off_open = off;      off = align_up(off + static_cast<size_t>(p->B) * p->Hkv * ((p->Nmax + 31) / 32) * 4, 256);
     p->off_audit = off;     off = align_up(off + sizeof(AuditRec), 256);
     p->total_bytes = off;
     return SPOTLIGHT_OK;
@@ -75,6 +77,7 @@ StageTimer::StageTimer(spotlight_ctx* c, int stage) : ctx(c), rec(nullptr)
     }
     r->stage = stage;
     r->whole = false;
+    r->more = false;
     rec = r;
 }
 
@@ -267,6 +270,9 @@ static HashLaunch key_job(const spotlight_ctx* ctx, const void* K, const spotlig
     h.zero_words = 0;
     h.wnorm = ctx->opt[SPOTLIGHT_OPT_BULK_HASH_MATRIX_CORES] ? reinterpret_cast<float*>(ctx->workspace + p.off_wnorm) : nullptr;
     h.audit = ctx->opt[SPOTLIGHT_OPT_BULK_HASH_AUDIT] ? reinterpret_cast<AuditRec*>(ctx->workspace + p.off_audit) : nullptr;
+    h.scales = h.wnorm ? ctx->workspace + p.off_scales : nullptr;
+    h.open = h.wnorm ? reinterpret_cast<uint32_t*>(ctx->workspace + p.off_open) : nullptr;
+    h.open_stride = (p.Nmax + 31) / 32;
     attach_packed(ctx, w, &h);
     return h;
 }
@@ -298,6 +304,9 @@ static HashLaunch query_job(const spotlight_ctx* ctx, const void* q, const spotl
     h.zero_words = p.L + 2;
     h.wnorm = nullptr;
     h.audit = nullptr;
+    h.scales = nullptr;
+    h.open = nullptr;
+    h.open_stride = 0;
     attach_packed(ctx, w, &h);
     return h;
 }
@@ -437,7 +446,7 @@ int spotlight_profile_read(spotlight_ctx* ctx, int stage, double* total_ms, int6
         ctx->stage_ms[ctx->recs[i].stage] += ms;
         // an attend kernel that has whole heads does its merge itself: recorded with it, without a time of its own
         if (ctx->recs[i].stage == SPOTLIGHT_STAGE_ATTEND && ctx->recs[i].whole) ctx->stage_launches[SPOTLIGHT_STAGE_MERGE] += 1;
-        ctx->stage_launches[ctx->recs[i].stage] += 1;
+        ctx->stage_launches[ctx->recs[i].stage] += ctx->recs[i].more ? 0 : 1;
     }
     ctx->n_rec = 0;
     if (total_ms) *total_ms = ctx->stage_ms[stage];

@@ -278,7 +278,14 @@ template <typename XT, typename WT>
 int run_tk(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int stage)
 {
     const size_t cap = static_cast<size_t>(ctx->max_lds);
-    if (bulk_hash_applies(ctx, a, n_xheads, sizeof(XT), sizeof(WT))) return run_bulk_hash<XT, WT>(ctx, a, n_xheads, stage);
+    if constexpr (sizeof(XT) == 2 && sizeof(WT) == 2) {
+        if (screened_hash_applies(ctx, a, n_xheads)) return run_screened_hash(ctx, a, n_xheads, stage);
+    }
+    if (bulk_hash_applies(ctx, a, n_xheads, sizeof(XT), sizeof(WT))) {
+        HashArgs all = a;
+        all.open = nullptr;   // no first pass has written it
+        return run_bulk_hash<XT, WT>(ctx, all, n_xheads, stage);
+    }
     // a single vector per head, hidden width a multiple of 128: the latency-oriented kernel
     if (a.n_rows == 1 && a.hidden % kHeadDim == 0) return run_vec<XT, WT>(ctx, a, n_xheads, nullptr, 0, stage);
     if (a.n_rows >= 32 && lds_bytes(32, a.hidden) <= cap) return run_ks<XT, WT, 32>(ctx, a, n_xheads, stage);
@@ -313,6 +320,9 @@ HashArgs make_hash_args(const HashLaunch& h)
     a.audit = h.audit;
     a.pack_w1 = h.pack_w1;
     a.pack_out = h.pack_out;
+    a.scales = h.scales;
+    a.open = h.open;
+    a.open_stride = h.open_stride;
     return a;
 }
 

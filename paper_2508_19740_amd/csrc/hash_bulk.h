@@ -115,6 +115,16 @@ __device__ __forceinline__ uint4 round8(const float4& f0, const float4& f1)
     return make_uint4(two(f0.x, f0.y), two(f0.z, f0.w), two(f1.x, f1.y), two(f1.z, f1.w));
 }
 
+// Sum over the 16 lanes of a row, in every lane: rotations, no LDS.
+__device__ __forceinline__ float add_across_16(float x)
+{
+    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x128, 0xf, 0xf, true));  // row_ror:8
+    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x124, 0xf, 0xf, true));  // row_ror:4
+    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x122, 0xf, 0xf, true));  // row_ror:2
+    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x121, 0xf, 0xf, true));  // row_ror:1
+    return x;
+}
+
 // 4 consecutive weights in their stored form
 template <typename WT> struct Raw4;
 template <> struct Raw4<float> { float4 v; };
@@ -236,6 +246,64 @@ __global__ __launch_bounds__(kThreads) void row_norm_kernel(const bf16_raw* __re
 
 __host__ __device__ constexpr int hidden_padded(int hidden) { return (hidden + 31) / 32 * 32; }
 
+// The rows of a workgroup's range that a first pass left open (hash_screen.h), compacted a span at a time, so that the
+// kernels below hash tiles of 32 of those alone: what does not fill a tile waits for the next span.
+constexpr int kOpenSpan = 2048;       // rows: a word of the bitmap for each lane of a wavefront
+struct OpenRows {
+    uint16_t row[kOpenSpan + kTile];  // behind the first row of the range
+    int count;
+};
+
+// The walk of a workgroup over its range.
+struct OpenWalk {
+    OpenRows& list;
+    const uint32_t* open;             // the range's words of the bitmap
+    int n_words, next;                // words of the range, the first one not in the list yet
+    int count, tiles;                 // rows in the list, whole tiles of it to be hashed now
+
+    // Whether the range has an open row at all; every thread of the workgroup calls it.
+    __device__ __forceinline__ bool any(int tid, int n_threads) const
+    {
+        if (tid == 0) list.count = 0;
+        __syncthreads();
+        for (int i = tid; i < n_words; i += n_threads)
+            if (open[i] != 0) list.count = 1;
+        __syncthreads();
+        return list.count != 0;
+    }
+    // Fills the list up to the next tiles; false: there are none left.  Every thread of the workgroup calls it.
+    __device__ __forceinline__ bool advance(int wave, int lane)
+    {
+        if (next >= n_words) return false;
+        do {
+            __syncthreads();   // the tiles before are done with the list
+            if (wave == 0) {
+                const int rest = count - tiles * kTile;   // fewer than a tile
+                const uint16_t r = list.row[tiles * kTile + min(lane, kTile - 1)];
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                if (lane < rest) list.row[lane] = r;
+                uint32_t bits = next + lane < n_words ? open[next + lane] : 0u;
+                const uint32_t mine = static_cast<uint32_t>(__builtin_popcount(bits)), upto = wave_inclusive_scan(mine);
+                for (int at = rest + static_cast<int>(upto - mine); bits != 0; bits &= bits - 1, ++at)
+                    list.row[at] = static_cast<uint16_t>((next + lane) * 32 + __builtin_ctz(bits));
+                if (lane == 63) list.count = rest + static_cast<int>(upto);
+            }
+            __syncthreads();
+            count = list.count;
+            next += kOpenSpan / 32;
+            tiles = next < n_words ? count / kTile : (count + kTile - 1) / kTile;
+        } while (tiles == 0 && next < n_words);
+        return tiles > 0;
+    }
+};
+
+// Outputs of a word that a first pass settled and the chain contradicts.
+__device__ __forceinline__ uint32_t settled_wrong(const HashArgs& a, int xhead, int64_t row, uint32_t before, uint32_t now)
+{
+    if (!a.open || (a.open[xhead * a.open_stride + row / 32] >> (row % 32)) & 1u) return 0;
+    return static_cast<uint32_t>(__builtin_popcount(before ^ now));
+}
+
 // Wavefronts per SIMD the register allocation must leave room for.  8 heads x 131072 vectors, 128 -> 512 ->
 // 256: four (128 registers and 38 spilled; 51 with binary32 vectors) 3.32 ms, three 3.83 ms.
 constexpr int min_waves(int NW, int NBW) { return NBW == 1 && NW >= 8 ? 4 : 2; }
@@ -246,8 +314,9 @@ constexpr int min_waves(int NW, int NBW) { return NBW == 1 && NW >= 8 ? 4 : 2; }
 // NBW:   code words per wavefront of the certified second layer; 0: exact second layer.
 // AUDIT: every output of the certified second layer is also evaluated with the chain and compared
 //        (distance in units of ||W2[j]|| ||h||, settled signs that disagree); totals go to a.audit.
-template <typename XT, typename WT, int NW, int NUB, int NBW, bool AUDIT>
-__global__ __launch_bounds__(NW * 64, min_waves(NW, NBW)) void hash_bulk_kernel(HashArgs a, float eps, int tiles_per_group)
+// OPEN:  only the rows a first pass left open, of the workgroup's range of tiles.
+template <typename XT, typename WT, int NW, int NUB, int NBW, bool AUDIT, bool OPEN = false>
+__global__ __launch_bounds__(NW * 64, min_waves(NW, NBW)) void hash_bulk_kernel(HashArgs a, float eps, int tiles_per_group, int open_at)
 {
     constexpr int TK = kTile, NT = NW * 64;
     constexpr bool CERT = NBW > 0;
@@ -265,6 +334,20 @@ __global__ __launch_bounds__(NW * 64, min_waves(NW, NBW)) void hash_bulk_kernel(
     const int K2 = NUB == 0 ? kHeadDim : a.hidden;     // what layer 2 contracts over
     const WT* w2 = NUB == 0 ? w1 : static_cast<const WT*>(a.w2) + static_cast<int64_t>(whead) * a.L * a.hidden;
     const int nub = hidden_padded(a.hidden) / 32;
+
+    const int64_t n_tiles = (a.n_rows + TK - 1) / TK;
+    const int64_t first = static_cast<int64_t>(blockIdx.x) * tiles_per_group;   // of the workgroup's tiles
+    int64_t tile0 = first, tile1 = min(n_tiles, first + tiles_per_group);
+    OpenWalk walk{*reinterpret_cast<OpenRows*>(reinterpret_cast<char*>(lds) + open_at), OPEN ? a.open + xhead * a.open_stride + first : nullptr,
+                  static_cast<int>(tile1 - tile0), 0, 0, 0};
+    if constexpr (OPEN) {
+        if (!walk.any(tid, NT)) return;
+        (void)walk.advance(wave, lane);
+        tile0 = 0;
+        tile1 = walk.tiles;
+    }
+    auto n_items = [&]() { return OPEN ? static_cast<int64_t>(walk.count) : a.n_rows; };
+    auto row_of = [&](int64_t item) { return OPEN ? first * TK + walk.list.row[item] : item; };
 
     uint32_t au_outputs = 0, au_listed = 0, au_wrong = 0;   // this lane's audit totals
     float au_ratio = 0.0f;
@@ -319,10 +402,6 @@ __global__ __launch_bounds__(NW * 64, min_waves(NW, NBW)) void hash_bulk_kernel(
             if (wave + NW * i < nub) load_block(wave + NW * i, ublk[i]);
     }
 
-    const int64_t n_tiles = (a.n_rows + TK - 1) / TK;
-    const int64_t tile0 = static_cast<int64_t>(blockIdx.x) * tiles_per_group;
-    const int64_t tile1 = min(n_tiles, tile0 + tiles_per_group);
-
     // the x tile of a tile, fetched ahead: thread e has 8 elements of vector e % 32
     constexpr int XPT = TK * (kHeadDim / 8) >= NT ? TK * (kHeadDim / 8) / NT : 1;
     const bool stages = tid < TK * (kHeadDim / 8);     // with 1024 threads only half of them
@@ -332,14 +411,16 @@ __global__ __launch_bounds__(NW * 64, min_waves(NW, NBW)) void hash_bulk_kernel(
 #pragma unroll
         for (int i = 0; i < XPT; ++i) {
             const int e = tid + i * NT, k8 = e / TK;
-            const int64_t row = min(tile * TK + e % TK, a.n_rows - 1);   // rows past the end: a stand-in, never stored
+            const int64_t row = row_of(min(tile * TK + e % TK, n_items() - 1));   // rows past the end: a stand-in, never stored
             if (stages) load_raw(xhead_base + row * kHeadDim + k8 * 8, xr[i]);
         }
     };
+    bool more = true;
+    while (more) {
     fetch_x(tile0);
     for (int64_t tile = tile0; tile < tile1; ++tile) {
         const int64_t r0 = tile * TK;
-        const int rows = static_cast<int>(min(static_cast<int64_t>(TK), a.n_rows - r0));
+        const int rows = static_cast<int>(min(static_cast<int64_t>(TK), n_items() - r0));
         __syncthreads();   // the previous tile is done with LDS
 #pragma unroll
         for (int i = 0; i < XPT; ++i) {
@@ -555,8 +636,19 @@ __global__ __launch_bounds__(NW * 64, min_waves(NW, NBW)) void hash_bulk_kernel(
             __syncthreads();
 
             // ---- the tile's codes: rows * W consecutive words
-            for (int e = tid; e < rows * a.W; e += NT) cbase[e] = m.codes[e / a.W][e % a.W];
+            if constexpr (OPEN) {
+                uint32_t* chead = a.codes + xhead * a.code_head_stride + a.code_row0 * a.W;
+                for (int e = tid; e < rows * a.W; e += NT) chead[row_of(r0 + e / a.W) * a.W + e % a.W] = m.codes[e / a.W][e % a.W];
+            } else {
+                for (int e = tid; e < rows * a.W; e += NT) {
+                    if constexpr (AUDIT) au_wrong += settled_wrong(a, xhead, r0 + e / a.W, cbase[e], m.codes[e / a.W][e % a.W]);
+                    cbase[e] = m.codes[e / a.W][e % a.W];
+                }
+            }
         }
+    }
+    more = OPEN && walk.advance(wave, lane);
+    tile1 = OPEN ? walk.tiles : tile1;
     }
     if constexpr (AUDIT) {
         const uint32_t outputs = wave_sum(au_outputs), listed = wave_sum(au_listed), wrong = wave_sum(au_wrong);
@@ -606,8 +698,8 @@ constexpr int hs_stride(int hidden) { return hidden_padded(hidden) + 4; }   // w
 template <typename XT, int NUB> constexpr int kept_operands() { return sizeof(XT) == 4 && NUB > 1 ? 1 : 2; }
 
 // NUB: blocks of 32 hidden units a wavefront owns; WREG: steps of 16 units of layer 2.
-template <typename XT, int NW, int NUB, int WREG, bool AUDIT>
-__global__ __launch_bounds__(NW * 64, 2) void hash_cert_kernel(HashArgs a, float eps, int tiles_per_group)
+template <typename XT, int NW, int NUB, int WREG, bool AUDIT, bool OPEN = false>
+__global__ __launch_bounds__(NW * 64, 2) void hash_cert_kernel(HashArgs a, float eps, int tiles_per_group, int open_at)
 {
     using WT = bf16_raw;
     constexpr int TK = kTile, NT = NW * 64;
@@ -629,6 +721,20 @@ __global__ __launch_bounds__(NW * 64, 2) void hash_cert_kernel(HashArgs a, float
     const WT* w2 = static_cast<const WT*>(a.w2) + static_cast<int64_t>(whead) * a.L * a.hidden;
     const int n_mine = max(0, min(NUB, nub - wave * NUB));           // blocks of this wavefront
     const int n_ks = a.hidden / 16;                                  // hidden is a multiple of 16
+
+    const int64_t n_tiles = (a.n_rows + TK - 1) / TK;
+    const int64_t first = static_cast<int64_t>(blockIdx.x) * tiles_per_group;   // of the workgroup's tiles
+    int64_t tile0 = first, tile1 = min(n_tiles, first + tiles_per_group);
+    OpenWalk walk{*reinterpret_cast<OpenRows*>(reinterpret_cast<char*>(lds) + open_at), OPEN ? a.open + xhead * a.open_stride + first : nullptr,
+                  static_cast<int>(tile1 - tile0), 0, 0, 0};
+    if constexpr (OPEN) {
+        if (!walk.any(tid, NT)) return;
+        (void)walk.advance(wave, lane);
+        tile0 = 0;
+        tile1 = walk.tiles;
+    }
+    auto n_items = [&]() { return OPEN ? static_cast<int64_t>(walk.count) : a.n_rows; };
+    auto row_of = [&](int64_t item) { return OPEN ? first * TK + walk.list.row[item] : item; };
 
     // ---- the weights of both layers, into registers by way of LDS: read by the wavefronts as they
     // need them, a row per lane, every load touches 32 cache lines and the lines leave the cache
@@ -687,10 +793,6 @@ __global__ __launch_bounds__(NW * 64, 2) void hash_cert_kernel(HashArgs a, float
     uint32_t au_outputs = 0, au_listed = 0, au_wrong = 0;   // this lane's audit totals
     float au_ratio = 0.0f;
 
-    const int64_t n_tiles = (a.n_rows + TK - 1) / TK;
-    const int64_t tile0 = static_cast<int64_t>(blockIdx.x) * tiles_per_group;
-    const int64_t tile1 = min(n_tiles, tile0 + tiles_per_group);
-
     // the x tile of a tile, fetched ahead: thread e has 8 elements of vector e % 32
     constexpr int XPT = TK * (kHeadDim / 8) / NT;
     Raw8<XT> xr[XPT];
@@ -699,7 +801,7 @@ __global__ __launch_bounds__(NW * 64, 2) void hash_cert_kernel(HashArgs a, float
 #pragma unroll
         for (int i = 0; i < XPT; ++i) {
             const int e = tid + i * NT;
-            const int64_t row = min(tile * TK + e % TK, a.n_rows - 1);   // rows past the end: a stand-in, never stored
+            const int64_t row = row_of(min(tile * TK + e % TK, n_items() - 1));   // rows past the end: a stand-in, never stored
             load_raw(xhead_base + row * kHeadDim + (e / TK) * 8, xr[i]);
         }
     };
@@ -726,11 +828,13 @@ __global__ __launch_bounds__(NW * 64, 2) void hash_cert_kernel(HashArgs a, float
     if (rare(norm == 0.0f))   // a row of zeros, or did its squares underflow?
         norm = square_of(norm, magnitude_bits(w2 + static_cast<int64_t>((31 - c) * a.W + min(wave, a.W - 1)) * a.hidden, a.hidden));
     norm = norm_of(norm);
+    bool more = true;
+    while (more) {
     put_x();
     __syncthreads();
     for (int64_t tile = tile0; tile < tile1; ++tile) {
         const int64_t r0 = tile * TK;
-        const int rows = static_cast<int>(min(static_cast<int64_t>(TK), a.n_rows - r0));
+        const int rows = static_cast<int>(min(static_cast<int64_t>(TK), n_items() - r0));
         if (tile + 1 < tile1) fetch_x(tile + 1);   // in flight during layer 1
 
         // ---- layer 1.  The SiLU of a block runs in the shadow of the next block's matrix instructions.
@@ -905,10 +1009,20 @@ __global__ __launch_bounds__(NW * 64, 2) void hash_cert_kernel(HashArgs a, float
                     }
                 }
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                if (lane < rows) a.codes[xhead * a.code_head_stride + (a.code_row0 + r0 + lane) * a.W + word] = m.codes[wave][lane];
+                if (lane < rows) {
+                    uint32_t* to = a.codes + xhead * a.code_head_stride + (a.code_row0 + row_of(r0 + lane)) * a.W + word;
+                    if constexpr (AUDIT) au_wrong += settled_wrong(a, xhead, r0 + lane, *to, m.codes[wave][lane]);
+                    *to = m.codes[wave][lane];
+                }
             }
         }
         __syncthreads();   // LDS may be written again
+    }
+    more = OPEN && walk.advance(wave, lane);
+    if (more) {
+        tile1 = walk.tiles;
+        fetch_x(0);
+    }
     }
     if constexpr (AUDIT) {
         const uint32_t outputs = wave_sum(au_outputs), listed = wave_sum(au_listed), wrong = wave_sum(au_wrong);
@@ -946,16 +1060,6 @@ template <typename XT> struct LinearLds {
     uint16_t list[4][kLinearList];
     uint4 pad;                                                  // the staging of R may run over the end of the rest
 };
-
-// Sum over the 16 lanes of a row, in every lane: rotations, no LDS.
-__device__ __forceinline__ float add_across_16(float x)
-{
-    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x128, 0xf, 0xf, true));  // row_ror:8
-    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x124, 0xf, 0xf, true));  // row_ror:4
-    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x122, 0xf, 0xf, true));  // row_ror:2
-    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x121, 0xf, 0xf, true));  // row_ror:1
-    return x;
-}
 
 // NB: code words of a wavefront
 template <typename XT, int NB, bool AUDIT>
@@ -1276,17 +1380,24 @@ int launch(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int stage, size_
     }
     dim3 grid(static_cast<unsigned>((tiles + tpg - 1) / tpg), static_cast<unsigned>(n_xheads));
     StageTimer timer(ctx, stage);
-    timer.launch(kern, grid, dim3(NW * 64), lds, a, static_cast<float>(bulk_hash_eps(a.hidden)), tpg);
+    timer.launch(kern, grid, dim3(NW * 64), lds, a, static_cast<float>(bulk_hash_eps(a.hidden)), tpg, 0);
     return hip_rc(hipGetLastError());
+}
+
+// LDS of hash_cert_kernel: what a tile takes, or the weights on their way into the registers
+template <typename XT, int NW, int NUB>
+size_t word_lds(const HashArgs& a)
+{
+    const size_t hp = hidden_padded(a.hidden);
+    const size_t work = sizeof(float) * (XTile<XT>::kFloats + kTile * hs_stride(a.hidden) + hp) + hp * kTile * 2 * kept_operands<XT, NUB>() + sizeof(CertScratch<NW>);
+    const size_t stage1 = static_cast<size_t>(a.hidden) * (kHeadDim * 2 + 16), stage2 = static_cast<size_t>(a.L) * (a.hidden * 2 + 16);
+    return work > stage1 ? (work > stage2 ? work : stage2) : (stage1 > stage2 ? stage1 : stage2);
 }
 
 template <typename XT, int NW, int NUB, int WREG>
 int launch_word(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int stage)
 {
-    const size_t hp = hidden_padded(a.hidden);
-    const size_t work = sizeof(float) * (XTile<XT>::kFloats + kTile * hs_stride(a.hidden) + hp) + hp * kTile * 2 * kept_operands<XT, NUB>() + sizeof(CertScratch<NW>);
-    const size_t stage1 = static_cast<size_t>(a.hidden) * (kHeadDim * 2 + 16), stage2 = static_cast<size_t>(a.L) * (a.hidden * 2 + 16);
-    const size_t lds = work > stage1 ? (work > stage2 ? work : stage2) : (stage1 > stage2 ? stage1 : stage2);
+    const size_t lds = word_lds<XT, NW, NUB>(a);
     auto kern = hash_cert_kernel<XT, NW, NUB, WREG, false>;
     if (a.audit) kern = hash_cert_kernel<XT, NW, NUB, WREG, true>;
     if (allow_dynamic_lds(ctx, reinterpret_cast<const void*>(kern), lds) != SPOTLIGHT_OK) return SPOTLIGHT_ERR_HIP;
@@ -1296,7 +1407,7 @@ int launch_word(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int stage)
     const int tpg = NUB == 1 ? short_runs(tiles, n_xheads, 2048) : whole_generations(tiles, n_xheads, ctx->n_cus, resident(ctx, 2, lds));
     dim3 grid(static_cast<unsigned>((tiles + tpg - 1) / tpg), static_cast<unsigned>(n_xheads));
     StageTimer timer(ctx, stage);
-    timer.launch(kern, grid, dim3(NW * 64), lds, a, static_cast<float>(bulk_hash_eps(a.hidden)), tpg);
+    timer.launch(kern, grid, dim3(NW * 64), lds, a, static_cast<float>(bulk_hash_eps(a.hidden)), tpg, 0);
     return hip_rc(hipGetLastError());
 }
 
@@ -1323,6 +1434,50 @@ int launch_cert(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int stage, 
 {
     if (a.audit) return launch<XT, bf16_raw, NW, NUB, NBW, true>(ctx, a, n_xheads, stage, lds);
     return launch<XT, bf16_raw, NW, NUB, NBW, false>(ctx, a, n_xheads, stage, lds);
+}
+
+// Tiles of a workgroup's range where only the rows left open are hashed: two workgroups for every slot, so that
+// ranges with more open rows than others even out; rows of the list are 16-bit offsets.
+inline int open_range(int64_t tiles, int n_xheads, int slots)
+{
+    const int64_t per = (tiles * n_xheads + 2 * slots - 1) / (2 * slots);
+    return static_cast<int>(per < 16 ? 16 : per > 2048 ? 2048 : per);
+}
+
+inline size_t align16(size_t bytes) { return (bytes + 15) / 16 * 16; }
+
+template <int NW, int NUB, int NBW>
+int launch_open(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int stage, size_t work)
+{
+    using T = bf16_raw;
+    const size_t open_at = align16(work), lds = open_at + sizeof(OpenRows);
+    auto kern = hash_bulk_kernel<T, T, NW, NUB, NBW, false, true>;
+    if (allow_dynamic_lds(ctx, reinterpret_cast<const void*>(kern), lds) != SPOTLIGHT_OK) return SPOTLIGHT_ERR_HIP;
+    const int64_t tiles = (a.n_rows + kTile - 1) / kTile;
+    const int range = open_range(tiles, n_xheads, ctx->n_cus * resident(ctx, 4 * min_waves(NW, NBW) / NW, lds));
+    constexpr int LPR = 16;
+    const int n_out = a.n_wheads * a.L;
+    hipLaunchKernelGGL(row_norm_kernel<LPR>, dim3(static_cast<unsigned>((n_out * LPR + kThreads - 1) / kThreads)), dim3(kThreads), 0,
+                       ctx->stream, static_cast<const T*>(a.w2), a.wnorm, n_out, a.hidden);   // microseconds: not timed
+    dim3 grid(static_cast<unsigned>((tiles + range - 1) / range), static_cast<unsigned>(n_xheads));
+    StageTimer timer(ctx, stage);
+    timer.launch(kern, grid, dim3(NW * 64), lds, a, static_cast<float>(bulk_hash_eps(a.hidden)), range, static_cast<int>(open_at));
+    return hip_rc(hipGetLastError());
+}
+
+template <int NW, int NUB, int WREG>
+int launch_word_open(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int stage)
+{
+    using T = bf16_raw;
+    const size_t open_at = align16(word_lds<T, NW, NUB>(a)), lds = open_at + sizeof(OpenRows);
+    auto kern = hash_cert_kernel<T, NW, NUB, WREG, false, true>;
+    if (allow_dynamic_lds(ctx, reinterpret_cast<const void*>(kern), lds) != SPOTLIGHT_OK) return SPOTLIGHT_ERR_HIP;
+    const int64_t tiles = (a.n_rows + kTile - 1) / kTile;
+    const int range = open_range(tiles, n_xheads, ctx->n_cus * resident(ctx, 2, lds));
+    dim3 grid(static_cast<unsigned>((tiles + range - 1) / range), static_cast<unsigned>(n_xheads));
+    StageTimer timer(ctx, stage);
+    timer.launch(kern, grid, dim3(NW * 64), lds, a, static_cast<float>(bulk_hash_eps(a.hidden)), range, static_cast<int>(open_at));
+    return hip_rc(hipGetLastError());
 }
 
 inline size_t lds_bytes(size_t x_size, int hidden) { return kTile * (x_size * kHeadDim + sizeof(float) * static_cast<size_t>(hidden_padded(hidden))); }
@@ -1358,6 +1513,25 @@ inline bool bulk_hash_applies(const spotlight_ctx* ctx, const hashdev::HashArgs&
     if (exact && a.hidden > 0 && a.W >= a.hidden && (a.n_rows + bulk::kTile - 1) / bulk::kTile * n_xheads > 2 * ctx->n_cus) return false;
     return a.wnorm && a.n_rows >= min_rows && bulk::lds_bytes(x_size, a.hidden) <= static_cast<size_t>(ctx->max_lds);
 }
+
+// The rows a first pass left open (a.open), with the chain: bfloat16 vectors and weights, hidden a multiple of 16
+// up to 1024, codes up to 256 bits.
+inline int run_open_hash(spotlight_ctx* ctx, const hashdev::HashArgs& a, int n_xheads, int stage)
+{
+    using namespace bulk;
+    const size_t lds = lds_bytes(2, a.hidden);
+    const int nub = hidden_padded(a.hidden) / 32;
+    if (a.W <= 4 && nub <= 4) return launch_word_open<4, 1, 8>(ctx, a, n_xheads, stage);
+    if (a.W <= 4 && nub <= 8) return launch_word_open<4, 2, 16>(ctx, a, n_xheads, stage);
+    if (nub <= 4) return launch_open<4, 1, 2>(ctx, a, n_xheads, stage, lds);
+    if (nub <= 8) return launch_open<4, 2, 2>(ctx, a, n_xheads, stage, lds);
+    if (nub <= 16) return launch_open<8, 2, 1>(ctx, a, n_xheads, stage, lds);
+    return launch_open<16, 2, 1>(ctx, a, n_xheads, stage, lds);
+}
+
+// Bulk hashing in two passes (hash_screen.h); declared here for the dispatch in hash.hip.
+bool screened_hash_applies(const spotlight_ctx* ctx, const hashdev::HashArgs& a, int n_xheads);
+int run_screened_hash(spotlight_ctx* ctx, const hashdev::HashArgs& a, int n_xheads, int stage);
 
 template <typename XT, typename WT>
 int run_bulk_hash(spotlight_ctx* ctx, const hashdev::HashArgs& a, int n_xheads, int stage)

@@ -1,0 +1,496 @@
+// Bulk hashing, first pass: most keys are settled by bfloat16 matrix instructions alone.
+//
+// Bulk hashing with the defined binary32 chain in layer 1 (hash_bulk.h) is bound by the binary32 matrix
+// instruction (153 TFLOP/s) plus the vector instructions beside it.  A code only holds SIGNS, so this pass
+// evaluates the whole network on v_mfma_f32_32x32x16_bf16 (products of bfloat16 vectors and weights are exact
+// there, only the sums round differently) with the hardware's exponential, and keeps a bound on the distance of
+// every output from the defined chain's.  A key all of whose outputs are further from zero than that bound has
+// its code; the others (about 8 % of random keys at 128 -> 256 -> 128) are marked in a bitmap, and the kernels of
+// hash_bulk.h hash those alone afterwards, with the chain.  The codes are the same bit for bit.
+//
+// The bound, in units of u = 2^-24.  One instruction adds its 16 products to c as two groups of eight,
+// consecutive in k; a group's result r is within u (10 max|p| + 2 |c| + |r|) of the exact sum: nine terms and the sum of the
+// products are cut at 2^-24 of the largest, then r is rounded (tests/test_gpu_hash_screen.py holds the
+// instruction to it: 0.38 of that at most over wide exponents, cancellation and ties).
+//   layer 1: chain and matrix core round partial sums S_k of the same products.  With S known at k = 0 (b1), 32,
+//     64, 96 and 128, |S_k| is at most the nearest of them plus the products between, so that
+//       |a - a'| <= u (24 |b1| + 44 (|S_32| + |S_64| + |S_96|) + 20 |a'| + sum_j t_j |w_j x_j|),
+//     t_j <= 32 (first_layer_charge).  sum_j t_j |w_j x_j| <= ||t w_i|| ||x||.
+//   SiLU: |silu'(a)| <= min(1.1, 0.5 + 0.5 |a|); its two evaluations (the fixed routine, and a * rcp(1 + exp2))
+//     are within 12 u |h| + 2 u |a| of each other for equal a.
+//   Over all hidden units of a key that is, as norms, ||h - h'|| <= dh (see below).
+//   layer 2: h' enters as hi + lo (128 u |h'|); chain and matrix core round partial sums again, charged to the nearer
+//     end: |y - y'| <= u ||s w_j|| (||h'|| + dh) + ||w_j|| dh + (hidden + 16) u |y'|, s_i = second_layer_charge.
+// Norms carry an absolute 1e-12, far more than any conversion or flushed term; a bound that is not a number or
+// not small against the range of binary32 settles nothing.
+#pragma once
+#include "hash_bulk.h"
+
+namespace spotlight {
+namespace screen {
+using namespace hashdev;
+using bulk::bf16x8_t;
+using bulk::f32x16_t;
+
+constexpr int kWaves = 8;             // wavefronts of a workgroup
+constexpr int kWords = 8;             // code words at most
+constexpr double kU = 0x1p-24;
+
+// How often the product of index j (0 ..) of a row's `n` counts in the bounds above.
+__host__ __device__ inline float first_layer_charge(int j)
+{
+    const int k = j % 32;   // between two known sums: the chain rounds up to 16 sums with it, the matrix core up to 2
+    const int chain = k < 16 ? 16 - k : k - 16, groups = k < 8 ? 6 : k < 16 ? 3 : k < 24 ? 0 : 3;
+    return static_cast<float>(chain + groups + 10);
+}
+__host__ __device__ inline float second_layer_charge(int i, int n)
+{
+    const int chain = i < n / 2 ? n / 2 - i : i - n / 2 + 1;
+    return 1.75f * chain + 12.0f + 11.0f + 128.0f;  // 12 per 16 units from the groups' sums; the cut products; the split
+}
+
+// What the bound needs to know of a weight head, in front of its n_words word records.
+struct LayerScale {
+    float t1;         // sqrt(sum_i ||t W1_i||^2)
+    float t1_max;     // max_i ||t W1_i||
+    float b1;         // ||b1||
+    uint32_t no_bias; // b1 is all zeros
+};
+struct WordScale {
+    float s2;         // max_j u ||s W2_j|| over the outputs of the word
+    float w2;         // max_j ||W2_j||
+    uint32_t zeros;   // bit c: output c * W + word has a row of zeros (y = 0, bit 0)
+    uint32_t pad;
+};
+static_assert(sizeof(LayerScale) == 16 && sizeof(WordScale) == 16, "one record is 16 bytes");
+
+constexpr float kSlack = 1e-12f;
+
+// grid (weight heads, 1 + words): block 0 the first layer, block 1 + w code word w.
+__global__ __launch_bounds__(kThreads) void scales_kernel(const bf16_raw* __restrict__ w1, const bf16_raw* __restrict__ b1,
+                                                          const bf16_raw* __restrict__ w2, char* __restrict__ out, int hidden, int L)
+{
+    __shared__ float sums[kThreads / 64][3];
+    __shared__ uint32_t bits[kThreads / 64];
+    const int W = L / 32, whead = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    char* rec = out + static_cast<int64_t>(whead) * (1 + W) * 16;
+    float a = 0.0f, b = 0.0f, c = 0.0f;
+    uint32_t any = 0;
+    if (blockIdx.y == 0) {   // 16 lanes a row
+        const bf16_raw* base = w1 + static_cast<int64_t>(whead) * hidden * kHeadDim;
+        for (int i0 = 0; i0 < hidden; i0 += kThreads / 16) {
+            const int i = i0 + tid / 16;
+            float s = 0.0f;
+            if (i < hidden) {
+                float v[8];
+                load8(base + static_cast<int64_t>(i) * kHeadDim + tid % 16 * 8, v);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const float t = first_layer_charge(tid % 16 * 8 + e) * v[e];
+                    s = __builtin_fmaf(t, t, s);
+                }
+            }
+            s = bulk::add_across_16(s);
+            a += s;                                     // 16 times, once in each lane of the row
+            b = s > b || s != s ? s : b;
+        }
+        a *= 1.0f / 16.0f;
+        for (int i = tid; i < hidden; i += kThreads) {
+            const float v = load1(b1 + static_cast<int64_t>(whead) * hidden + i);
+            c = __builtin_fmaf(v, v, c);
+            any |= __float_as_uint(v) << 1;
+        }
+    } else {                 // 8 lanes a row
+        const int word = blockIdx.y - 1, r = tid / 8;
+        const bf16_raw* row = w2 + (static_cast<int64_t>(whead) * L + r * W + word) * hidden;
+        for (int g = tid % 8; g < hidden / 8; g += 8) {
+            float v[8];
+            load8(row + g * 8, v);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const float s = second_layer_charge(g * 8 + e, hidden) * v[e];
+                a = __builtin_fmaf(s, s, a);
+                b = __builtin_fmaf(v[e], v[e], b);
+                any |= __float_as_uint(v[e]) << 1;
+            }
+        }
+#pragma unroll
+        for (int off = 1; off < 8; off <<= 1) {
+            a += __shfl_xor(a, off);
+            b += __shfl_xor(b, off);
+            any |= __shfl_xor(any, off);
+        }
+    }
+    // over the workgroup: sums of a and c and the largest b (layer 1), the largest a and b (a word); a NaN stays
+#pragma unroll
+    for (int off = 8; off < 64; off <<= 1) {
+        const float a2 = __shfl_xor(a, off), b2 = __shfl_xor(b, off);
+        b = b2 > b || b2 != b2 ? b2 : b;
+        a = blockIdx.y == 0 ? a + a2 : a2 > a || a2 != a2 ? a2 : a;
+    }
+    if (blockIdx.y == 0) {
+#pragma unroll
+        for (int off = 1; off < 8; off <<= 1) a += __shfl_xor(a, off);
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) { c += __shfl_xor(c, off); any |= __shfl_xor(any, off); }
+    } else {
+        // lane 8 r of a wavefront has row 8 wave + r of the word
+        const unsigned long long z = __ballot(any == 0);
+        any = 0;
+#pragma unroll
+        for (int r = 0; r < 8; ++r) any |= static_cast<uint32_t>((z >> (8 * r)) & 1) << (8 * wave + r);
+    }
+    if (lane == 0) { sums[wave][0] = a; sums[wave][1] = b; sums[wave][2] = c; bits[wave] = any; }
+    __syncthreads();
+    if (tid != 0) return;
+    for (int w = 1; w < kThreads / 64; ++w) {
+        const float a2 = sums[w][0], b2 = sums[w][1];
+        b = b2 > b || b2 != b2 ? b2 : b;
+        a = blockIdx.y == 0 ? a + a2 : a2 > a || a2 != a2 ? a2 : a;
+        c += sums[w][2];
+        any |= bits[w];
+    }
+    if (blockIdx.y == 0) {
+        LayerScale s;
+        s.t1 = 1.001f * __builtin_sqrtf(a) + kSlack;
+        s.t1_max = 1.001f * __builtin_sqrtf(b) + kSlack;
+        s.b1 = 1.001f * __builtin_sqrtf(c) + kSlack;
+        s.no_bias = any == 0;
+        *reinterpret_cast<LayerScale*>(rec) = s;
+    } else {
+        WordScale s;
+        s.s2 = static_cast<float>(1.001 * kU) * (__builtin_sqrtf(a) + static_cast<float>(hidden) * kSlack);
+        s.w2 = 1.001f * __builtin_sqrtf(b) + kSlack;
+        s.zeros = any;
+        s.pad = 0;
+        reinterpret_cast<WordScale*>(rec)[blockIdx.y] = s;
+    }
+}
+
+// h = a / (1 + exp(-a)) with the hardware's exponential and reciprocal
+__device__ __forceinline__ float fast_silu(float a)
+{
+    return a * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(a * -0x1.715476p+0f));
+}
+
+// the value of lane l + 32 in lane l and the other way round
+__device__ __forceinline__ uint32_t other_half(uint32_t v)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);   // the lower half's value in all lanes, the upper half's
+    return (threadIdx.x & 32) ? r[0] : r[1];
+}
+__device__ __forceinline__ float add_halves(float v)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// The hi / lo split of bulk::split8, each h - hi in one instruction: h - 1 * hi[0] - 0 * hi[1] (exact; where hi[1] is no
+// number the key is not settled).
+__device__ __forceinline__ void split8(const float (&h)[8], bf16x8_t& hi, bf16x8_t& lo)
+{
+    typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+    typedef float f32x2_t __attribute__((ext_vector_type(2)));
+    union { bf16x8_t v; bf16x2_t p[4]; } a, b;
+    // {-1, 0} and {0, -1}, in registers: as a literal of the instruction the first is taken for the second
+    uint32_t minus_first = 0x0000bf80u, minus_second = 0xbf800000u;
+    asm("" : "+s"(minus_first), "+s"(minus_second));
+    const bf16x2_t first = __builtin_bit_cast(bf16x2_t, minus_first), second = __builtin_bit_cast(bf16x2_t, minus_second);
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+        a.p[p] = __builtin_convertvector(f32x2_t{h[2 * p], h[2 * p + 1]}, bf16x2_t);
+        b.p[p] = __builtin_convertvector(f32x2_t{__builtin_amdgcn_fdot2_f32_bf16(a.p[p], first, h[2 * p], false),
+                                                 __builtin_amdgcn_fdot2_f32_bf16(a.p[p], second, h[2 * p + 1], false)}, bf16x2_t);
+    }
+    hi = a.v;
+    lo = b.v;
+}
+
+// A wavefront takes tiles of 32 keys alone.  Layer 1 (rows = hidden units of a block of 32, columns = keys) leaves eight
+// consecutive units of a key in eight accumulators of a lane, which is how layer 2 (rows = the outputs of a code word,
+// columns = keys) reads them: activations stay in the registers of their wavefront.  The weights of both layers are in
+// LDS as the instruction reads them, 16 bytes a lane: all of them (RESIDENT), fetched once per workgroup, or a block of 32
+// hidden units at a time, double-buffered, for eight tiles at once.
+// Lane c + 32 half has outputs 16 half .. 16 half + 15 (in bit order, highest first) of a word of key c, so a code is
+// shifted together in the lane from the signs.
+template <int WM, bool RESIDENT>
+__global__ __launch_bounds__(kWaves * 64, 2) void hash_screen_kernel(HashArgs a, const char* __restrict__ scales, int rounds)
+{
+    constexpr int NT = kWaves * 64, TK = bulk::kTile;
+    extern __shared__ __align__(16) float lds[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c = lane & 31, half = lane >> 5;
+    const int xhead = blockIdx.y;
+    const int whead = whead_of(a, xhead);
+    const bf16_raw* w1 = static_cast<const bf16_raw*>(a.w1) + static_cast<int64_t>(whead) * a.hidden * kHeadDim;
+    const bf16_raw* b1 = static_cast<const bf16_raw*>(a.b1) + static_cast<int64_t>(whead) * a.hidden;
+    const bf16_raw* w2 = static_cast<const bf16_raw*>(a.w2) + static_cast<int64_t>(whead) * a.L * a.hidden;
+    const LayerScale* ls = reinterpret_cast<const LayerScale*>(scales + static_cast<int64_t>(whead) * (1 + a.W) * 16);
+    const WordScale* ws = reinterpret_cast<const WordScale*>(ls) + 1;
+    const int nub = bulk::hidden_padded(a.hidden) / 32, W = a.W;
+    constexpr int frags = 8 + 2 * WM;                        // operands of a block of hidden units, 64 x 16 bytes each
+    float* bias = lds;                                       // [hidden, padded to 32]
+    uint4* frag = reinterpret_cast<uint4*>(bias + nub * 32); // [blocks, or 2][frags][64]
+
+    // operand f of block ub: 0 .. 7 a step of 16 k of layer 1, then [half of the block][word] of layer 2
+    auto operand = [&](int ub, int f) {
+        uint4 v = make_uint4(0u, 0u, 0u, 0u);
+        if (f < 8) {
+            const int unit = ub * 32 + bulk::unit_of_row(c);
+            if (unit < a.hidden) v = *reinterpret_cast<const uint4*>(w1 + static_cast<int64_t>(unit) * kHeadDim + (2 * f + half) * 8);
+        } else {
+            const int ks = (f - 8) / WM, word = (f - 8) % WM, unit = ub * 32 + ks * 16 + half * 8;
+            const int j = ((c >> 3) * 4 + (c & 3) + 16 * ((c >> 2) & 1)) * W + word;
+            if (unit < a.hidden && word < W) v = *reinterpret_cast<const uint4*>(w2 + static_cast<int64_t>(j) * a.hidden + unit);
+        }
+        return v;
+    };
+    for (int i = tid; i < nub * 32; i += NT) bias[i] = i < a.hidden ? load1(b1 + i) : 0.0f;
+    if constexpr (RESIDENT) {
+        const int n = nub * frags;
+        for (int f0 = wave; f0 < n; f0 += kWaves * 8) {
+            uint4 v[8];
+#pragma unroll
+            for (int p = 0; p < 8; ++p) { const int f = min(f0 + p * kWaves, n - 1); v[p] = operand(f / frags, f % frags); }
+#pragma unroll
+            for (int p = 0; p < 8; ++p) { const int f = f0 + p * kWaves; if (f < n) frag[f * 64 + lane] = v[p]; }
+        }
+    }
+    constexpr int ST = (8 + 2 * WM + kWaves - 1) / kWaves;   // operands a wavefront brings for the next block
+    uint4 stage[ST];
+    auto fetch = [&](int ub) {
+#pragma unroll
+        for (int p = 0; p < ST; ++p) { const int f = wave + p * kWaves; if (f < frags) stage[p] = operand(ub, f); }
+    };
+    auto keep = [&](int buf) {
+#pragma unroll
+        for (int p = 0; p < ST; ++p) { const int f = wave + p * kWaves; if (f < frags) frag[(buf * frags + f) * 64 + lane] = stage[p]; }
+    };
+    if constexpr (!RESIDENT) { fetch(0); keep(0); }
+
+    const bf16_raw* xbase = static_cast<const bf16_raw*>(a.x) + xhead * a.x_head_stride + a.x_row0 * kHeadDim;
+    const int64_t n_tiles = (a.n_rows + TK - 1) / TK, tile0 = static_cast<int64_t>(blockIdx.x) * rounds * kWaves;
+    uint4 x[8];
+    auto fetch_x = [&](int64_t tile) {
+        const int64_t row = min(tile * TK + c, a.n_rows - 1);   // rows past the end: a stand-in, never stored
+#pragma unroll
+        for (int s = 0; s < 8; ++s) x[s] = *reinterpret_cast<const uint4*>(xbase + row * kHeadDim + (2 * s + half) * 8);
+    };
+    fetch_x(tile0 + wave);
+    const float t1 = ls->t1, t1_max = ls->t1_max, bn = ls->b1;
+    const bool no_bias = ls->no_bias != 0;
+    __syncthreads();
+    int buf = 0;
+    for (int round = 0; round < rounds; ++round) {
+        const int64_t tile = tile0 + round * kWaves + wave;
+        if constexpr (RESIDENT) { if (tile >= n_tiles) break; }   // (otherwise every wavefront meets the barriers)
+        // ---- ||x||
+        float xx = 0.0f;
+        typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            const uint32_t d[4] = {x[s].x, x[s].y, x[s].z, x[s].w};
+#pragma unroll
+            for (int p = 0; p < 4; ++p) xx = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, d[p]), __builtin_bit_cast(bf16x2_t, d[p]), xx, false);
+        }
+        xx = add_halves(xx);
+        bool nothing = false;   // the key and b1 are zeros: so is every output, and the code
+        if (bulk::rare(xx == 0.0f && no_bias)) {
+            uint32_t bits = 0;
+#pragma unroll
+            for (int s = 0; s < 8; ++s) bits |= bulk::magnitude_bits(x[s]);
+            nothing = no_bias && (bits | other_half(bits)) == 0;
+        }
+        const float xn = 1.001f * __builtin_amdgcn_sqrtf(xx) + kSlack;
+
+        f32x16_t y[WM];
+#pragma unroll
+        for (int w = 0; w < WM; ++w) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) y[w][v] = 0.0f;
+            if (w < W) {
+                const uint32_t z = ws[w].zeros;   // rows of zeros: far from zero, and negative
+                if (z) {
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) y[w][v] = (z >> (v + 16 * half)) & 1 ? -1e30f : 0.0f;
+                }
+            }
+        }
+        float ca = 0.0f, aa = 0.0f, hh = 0.0f;   // sums of squares of S_32, S_64 and S_96, of a', of h'
+        auto layer1 = [&](int ub, const uint4* op, f32x16_t& h) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float4 f = *reinterpret_cast<const float4*>(bias + ub * 32 + 16 * (q / 2) + 8 * half + 4 * (q % 2));
+                h[4 * q] = f.x; h[4 * q + 1] = f.y; h[4 * q + 2] = f.z; h[4 * q + 3] = f.w;
+            }
+#pragma unroll
+            for (int s = 0; s < 8; ++s) {
+                h = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, op[s * 64]), __builtin_bit_cast(bf16x8_t, x[s]), h, 0, 0, 0);
+                if (s == 1 || s == 3 || s == 5) {
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) ca = __builtin_fmaf(h[v], h[v], ca);
+                }
+            }
+        };
+        auto layer2 = [&](const uint4* op, const f32x16_t& h) {
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                float h8[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const float av = h[8 * j + e], hv = fast_silu(av);
+                    aa = __builtin_fmaf(av, av, aa);
+                    hh = __builtin_fmaf(hv, hv, hh);
+                    h8[e] = hv;
+                }
+                bf16x8_t hi, lo;
+                // (the sum first, so that the split may overwrite h8)
+                asm volatile("" : "+v"(hh), "+v"(h8[0]), "+v"(h8[1]), "+v"(h8[2]), "+v"(h8[3]), "+v"(h8[4]), "+v"(h8[5]), "+v"(h8[6]), "+v"(h8[7]));
+                split8(h8, hi, lo);
+#pragma unroll
+                for (int w = 0; w < WM; ++w) {
+                    const bf16x8_t b = __builtin_bit_cast(bf16x8_t, op[(8 + j * WM + w) * 64]);
+                    y[w] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, hi, y[w], 0, 0, 0);
+                    y[w] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, lo, y[w], 0, 0, 0);
+                }
+            }
+        };
+        if constexpr (RESIDENT) {
+            f32x16_t h;
+            layer1(0, frag + lane, h);
+#pragma unroll 1
+            for (int ub = 0; ub + 1 < nub; ++ub) {
+                f32x16_t next;
+                layer1(ub + 1, frag + (ub + 1) * frags * 64 + lane, next);
+                layer2(frag + ub * frags * 64 + lane, h);
+                h = next;
+            }
+            fetch_x(min(tile + kWaves, n_tiles - 1));   // the next tile's, in flight during the rest
+            layer2(frag + (nub - 1) * frags * 64 + lane, h);
+        } else {
+#pragma unroll 1
+            for (int ub = 0; ub < nub; ++ub) {
+                fetch(ub + 1 < nub ? ub + 1 : 0);
+                const uint4* op = frag + buf * frags * 64 + lane;
+                f32x16_t h;
+                layer1(ub, op, h);
+                if (ub == nub - 1) fetch_x(min(tile + kWaves, n_tiles - 1));   // the next tile's, in flight during the rest
+                layer2(op, h);
+                buf ^= 1;
+                keep(buf);
+                __syncthreads();
+            }
+        }
+        // ---- the bound of this key
+        ca = add_halves(ca);
+        aa = add_halves(aa);
+        hh = add_halves(hh);
+        constexpr float u = static_cast<float>(1.02 * kU);
+        const float an = 1.001f * __builtin_amdgcn_sqrtf(aa) + kSlack, hn = 1.001f * __builtin_amdgcn_sqrtf(hh) + kSlack;
+        const float sums = 24.0f * bn + 76.3f * (1.001f * __builtin_amdgcn_sqrtf(ca) + kSlack) + 20.0f * an;   // 44 sqrt(3) for the three of them
+        const float da = u * (t1 * xn + sums);                                                         // >= ||a - a'||
+        const float slope = 0.5f * t1 + 0.5f * t1_max * (an + da), steepest = 1.1f * t1;
+        const float dh = u * ((slope < steepest ? slope : steepest) * xn + 1.1f * sums + 12.0f * hn + 2.0f * an);
+        // ---- signs and the distance of the nearest output from zero
+        uint32_t code[WM];
+        bool sure = true;
+#pragma unroll
+        for (int w = 0; w < WM; ++w) {
+            if (w >= W) continue;
+            uint32_t s = 0;
+            float nearest = INFINITY;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                s = __builtin_amdgcn_alignbit(s, __float_as_uint(y[w][v]), 31);
+                nearest = fminf(nearest, __builtin_fabsf(y[w][v]));
+            }
+            const float bound = 1.002f * (ws[w].s2 * (hn + dh) + ws[w].w2 * dh);
+            sure = sure && nearest >= bound && bound < 1e25f;
+            code[w] = ~s & 0xffffu;   // a settled output is no zero
+        }
+        uint32_t open = sure || nothing ? 0u : 1u;
+        open |= other_half(open);
+        const bool mine = half == 0 && tile * TK + c < a.n_rows;
+        const uint32_t marked = static_cast<uint32_t>(__ballot(mine && open != 0));
+#pragma unroll
+        for (int w = 0; w < WM; ++w) {
+            if (w >= W) continue;
+            code[w] = (code[w] << 16) | other_half(code[w]);
+            if (nothing) code[w] = 0;
+        }
+        if (mine) {
+            uint32_t* to = a.codes + xhead * a.code_head_stride + (a.code_row0 + tile * TK + c) * W;
+#pragma unroll
+            for (int w = 0; w < WM; ++w)
+                if (w < W) to[w] = code[w];
+        }
+        if (lane == 0 && tile < n_tiles) a.open[xhead * a.open_stride + tile] = marked;
+    }
+}
+
+inline size_t lds_bytes(int hidden, int words, bool resident)
+{
+    const size_t nub = bulk::hidden_padded(hidden) / 32, frags = 8 + 2 * static_cast<size_t>(words);
+    return nub * 32 * sizeof(float) + (resident ? nub : 2) * frags * 64 * sizeof(uint4);
+}
+
+// Rounds of eight tiles a workgroup takes, one workgroup on a compute unit at a time: the fewest rounds in turn, the
+// weights counted as one.
+inline int rounds_of(int64_t all_rounds, int n_xheads, int n_cus)
+{
+    int64_t best = all_rounds, best_cost = INT64_MAX;
+    const int64_t most = 4 * static_cast<int64_t>(n_cus) / n_xheads + 1;   // workgroups of a head
+    for (int64_t groups = 1; groups <= most && groups <= all_rounds; ++groups) {
+        const int64_t rounds = (all_rounds + groups - 1) / groups, used = (all_rounds + rounds - 1) / rounds;
+        const int64_t cost = (used * n_xheads + n_cus - 1) / n_cus * (rounds + 1);
+        if (cost < best_cost) { best = rounds; best_cost = cost; }
+    }
+    return static_cast<int>(best);
+}
+
+template <int WM, bool RESIDENT>
+int launch_kernel(spotlight_ctx* ctx, const HashArgs& a, const char* scales, int n_xheads, int stage)
+{
+    const size_t lds = lds_bytes(a.hidden, WM, RESIDENT);
+    auto kern = hash_screen_kernel<WM, RESIDENT>;
+    if (allow_dynamic_lds(ctx, reinterpret_cast<const void*>(kern), lds) != SPOTLIGHT_OK) return SPOTLIGHT_ERR_HIP;
+    const int64_t all_rounds = (a.n_rows + bulk::kTile * kWaves - 1) / (bulk::kTile * kWaves);
+    const int rounds = rounds_of(all_rounds, n_xheads, ctx->n_cus);
+    dim3 grid(static_cast<unsigned>((all_rounds + rounds - 1) / rounds), static_cast<unsigned>(n_xheads));
+    StageTimer timer(ctx, stage);
+    if (timer.rec) timer.rec->more = true;
+    timer.launch(kern, grid, dim3(kWaves * 64), lds, a, scales, rounds);
+    return hip_rc(hipGetLastError());
+}
+
+template <int WM>
+int launch_words(spotlight_ctx* ctx, const HashArgs& a, const char* scales, int n_xheads, int stage)
+{
+    if (lds_bytes(a.hidden, WM, true) <= static_cast<size_t>(ctx->max_lds)) return launch_kernel<WM, true>(ctx, a, scales, n_xheads, stage);
+    return launch_kernel<WM, false>(ctx, a, scales, n_xheads, stage);
+}
+
+// Whether two passes serve this job (bfloat16 vectors and weights): a network that the kernels of the second one take,
+// and enough tiles, since a workgroup of each pass fetches the weights and a tile of open rows is hashed by few wavefronts
+// of the chip.  One pass against two, 131072 vectors in all, 1 to 512 heads: 64 -> 32 62 - 64 and 30 - 33 us, 256 -> 128
+// 154 and 86 - 97 us, 512 -> 256 437 - 464 and 326 - 388 us; 65536: 39 and 26, 84 - 87 and 83 - 85, 230 - 240 and 282 -
+// 310 us; heads of 64 vectors fill half a round.
+inline bool applies(const spotlight_ctx* ctx, const HashArgs& a, int n_xheads)
+{
+    if (!a.open || !a.wnorm || a.hidden <= 0 || a.hidden % 16 != 0 || a.hidden > 1024 || a.W > kWords) return false;
+    const int64_t tiles = (a.n_rows + bulk::kTile - 1) / bulk::kTile * n_xheads;
+    return a.n_rows >= bulk::kTile * kWaves && tiles >= (a.hidden <= 128 ? 8 : 16) * static_cast<int64_t>(ctx->n_cus);
+}
+
+inline int launch(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int stage)
+{
+    char* scales = static_cast<char*>(a.scales);
+    hipLaunchKernelGGL(scales_kernel, dim3(static_cast<unsigned>(a.n_wheads), static_cast<unsigned>(1 + a.W)), dim3(kThreads), 0, ctx->stream,
+                       static_cast<const bf16_raw*>(a.w1), static_cast<const bf16_raw*>(a.b1), static_cast<const bf16_raw*>(a.w2), scales, a.hidden, a.L);
+    if (a.W <= 2) return launch_words<2>(ctx, a, scales, n_xheads, stage);
+    if (a.W <= 4) return launch_words<4>(ctx, a, scales, n_xheads, stage);
+    return launch_words<8>(ctx, a, scales, n_xheads, stage);
+}
+
+}  // namespace screen
+}  // namespace spotlight

@@ -1,0 +1,18 @@
+// Bulk hashing in two passes: hash_screen.h settles most keys, hash_bulk.h hashes the others with the chain.
+#include "hash_screen.h"
+
+namespace spotlight {
+using namespace hashdev;
+extern template int run_bulk_hash<bf16_raw, bf16_raw>(spotlight_ctx*, const HashArgs&, int, int);
+
+bool screened_hash_applies(const spotlight_ctx* ctx, const HashArgs& a, int n_xheads) { return screen::applies(ctx, a, n_xheads); }
+
+int run_screened_hash(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int stage)
+{
+    const int rc = screen::launch(ctx, a, n_xheads, stage);
+    if (rc != SPOTLIGHT_OK) return rc;
+    // audited: every row with the chain, which also counts what the first pass settled wrongly
+    return a.audit ? run_bulk_hash<bf16_raw, bf16_raw>(ctx, a, n_xheads, stage) : run_open_hash(ctx, a, n_xheads, stage);
+}
+
+}  // namespace spotlight

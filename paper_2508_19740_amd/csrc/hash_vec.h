@@ -92,6 +92,9 @@ struct HashArgs {
     AuditRec* audit;   // totals of the audited matrix-core path, or null
     const void* pack_w1;   // packed copies for the single-vector kernel, or null
     const void* pack_out;
+    void* scales;      // scratch of the first pass of bulk hashing (hash_screen.h), or null
+    uint32_t* open;
+    int64_t open_stride;
 };
 
 __device__ __forceinline__ int whead_of(const HashArgs& a, int xhead) { return (xhead % a.heads_per_batch) / a.group; }

@@ -39,6 +39,8 @@ struct Plan {
     size_t off_pack_w1;    // first hash layer in the single-vector kernel's read order (pack_w1_elems per kv head)
     size_t off_pack_out;   // output matrix of the hash (W2, or R of the linear hash) in that order
     size_t pack_w1_elems, pack_out_elems;   // elements per kv head; both 0 if the hash shape has no such copy
+    size_t off_scales;     // [Hkv][1 + W][16 bytes] norms of the weights for the first pass of bulk hashing (hash_screen.h)
+    size_t off_open;       // [B*Hkv][ceil(Nmax / 32)] rows that pass left open, a bit each
     size_t off_audit;      // AuditRec of the bulk hash (SPOTLIGHT_OPT_BULK_HASH_AUDIT)
     size_t total_bytes;
 };
@@ -82,6 +84,7 @@ struct AuditRec {
 struct ProfileRec {
     int stage;
     bool whole;   // an attend launch that leaves nothing to merge
+    bool more;    // a call's first launch of two: its time counts, the call is counted with the second
     hipEvent_t start, stop;
 };
 
@@ -158,6 +161,9 @@ struct HashLaunch {
     AuditRec* audit;          // set: the matrix-core path also checks every output against the chain
     const void* pack_w1;      // packed copies of the weights (see launch_pack_weights), or null
     const void* pack_out;
+    void* scales;             // scratch of the first pass of bulk hashing, or null: norms of the weights,
+    uint32_t* open;           // and a bit for each row it leaves open, open_stride words per x-head
+    int64_t open_stride;
 };
 int launch_hash(spotlight_ctx* ctx, const HashLaunch& a, int stage);
 // Elements per weight head of the packed copies the single-vector hash kernel can read (0: none).
