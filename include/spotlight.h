@@ -177,8 +177,8 @@ int spotlight_hash_keys(spotlight_ctx *ctx, const void *K, const spotlight_hash_
  *   wrong      outputs the bound did settle whose sign differs from the chain's; the method relies
  *              on this being 0
  *   max_ratio  largest |y_matrix - y_chain| / (||W2[j]|| ||h||) seen; the bound assumes it stays
- *              below eps = 1.01 (h (2^-24 + 1.01 2^-22) + 2^-17), returned in *eps (the linear
- *              hash: R_j, x and d in place of W2[j], h and the hidden width)
+ *              below eps = 1.01 2^-24 (0.875 h + 23 + 128), returned in *eps (the linear hash: R_j, x
+ *              and d in place of W2[j], h and the hidden width, and no 128 for bfloat16 vectors)
  */
 int spotlight_bulk_hash_audit_read(spotlight_ctx *ctx, int64_t *outputs, int64_t *listed, int64_t *wrong,
                                    double *max_ratio, double *eps);

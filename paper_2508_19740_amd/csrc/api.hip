@@ -223,7 +223,7 @@ int spotlight_bulk_hash_audit_read(spotlight_ctx* ctx, int64_t* outputs, int64_t
         memcpy(&f, &rec.max_ratio_bits, sizeof(f));
         *max_ratio = f;
     }
-    if (eps) *eps = bulk_hash_eps(ctx->plan.hidden > 0 ? ctx->plan.hidden : kHeadDim);
+    if (eps) *eps = bulk_hash_eps(ctx->plan.hidden > 0 ? ctx->plan.hidden : kHeadDim, ctx->plan.hidden > 0 || ctx->plan.kv_dtype == SPOTLIGHT_F32);
     return SPOTLIGHT_OK;
 }
 

@@ -180,10 +180,11 @@ int launch_retrieve(spotlight_ctx* ctx, const uint32_t* codes, int64_t n_tokens,
 int launch_attend(spotlight_ctx* ctx, const void* q, const void* K, const void* V,
                   const int32_t* idx, int k, float scale, float* out);
 
-// Error bound of the matrix-core second hash layer per unit of ||W2[j]|| * ||h||: `hidden` roundings
-// of 2^-24 in the binary32 chain, at most 2 * hidden additions in the matrix core each taken to err
-// by at most one unit in the last place, and the residue of the hi/lo split (2^-18, taken as 2^-17).
-inline double bulk_hash_eps(int hidden) { return 1.01 * (hidden * (0x1p-24 + 1.01 * 0x1p-22) + 0x1p-17); }
+// Error bound of the matrix-core last hash layer per unit of ||W2[j]|| * ||h||, n terms long (hash_bulk.h): the rounding of
+// partial sums, which are at most as large as the terms before them or as the result and the terms behind them,
+// by the binary32 chain (n / 2) and between the groups of eight that the matrix core adds (three times n / 8 groups, of hi and
+// of lo); the ten cut terms of a group, and what rounding up leaves; the residue of the hi/lo split of the activations.
+inline double bulk_hash_eps(int n, bool split) { return 1.01 * 0x1p-24 * (0.875 * n + 23 + (split ? 128 : 0)); }
 
 // Raises a kernel's dynamic LDS limit (once per kernel and context).
 int allow_dynamic_lds(spotlight_ctx* ctx, const void* kernel, size_t bytes);
