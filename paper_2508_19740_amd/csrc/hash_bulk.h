@@ -249,35 +249,62 @@ __global__ __launch_bounds__(kThreads) void row_norm_kernel(const bf16_raw* __re
 
 __host__ __device__ constexpr int hidden_padded(int hidden) { return (hidden + 31) / 32 * 32; }
 
-// The rows of a workgroup's range that a first pass left open (hash_screen.h), compacted a span at a time, so that the
-// kernels below hash tiles of 32 of those alone: what does not fill a tile waits for the next span.
+// The rows that a first pass left open (hash_screen.h), compacted a span at a time, so that the kernels below hash
+// tiles of 32 of those alone: what does not fill a tile waits for the next span.  A segment of a head's rows is shared out
+// over `parts` workgroups, the same number of tiles of open rows each, as far as they divide: every one of them counts the
+// segment's rows first, a few words a thread.  (A range of rows for each, two for every slot of the chip, had a
+// tile that was not full in every range and waited for the ranges with the most: 32 heads x 131072, 128 -> 256 -> 128, 9 % open,
+// 557 us; this way 527.)
+constexpr int kOpenSegment = 65536;   // rows: offsets in 16 bits
 constexpr int kOpenSpan = 2048;       // rows: a word of the bitmap for each lane of a wavefront
 struct OpenRows {
-    uint16_t row[kOpenSpan + kTile];  // behind the first row of the range
-    int count;
+    uint16_t row[kOpenSpan + kTile];  // in the segment
+    int count, left;                  // rows in the list, rows of the share not in the list yet
+    int sums[16];
 };
 
-// The walk of a workgroup over its range.
 struct OpenWalk {
     OpenRows& list;
-    const uint32_t* open;             // the range's words of the bitmap
-    int n_words, next;                // words of the range, the first one not in the list yet
-    int count, tiles;                 // rows in the list, whole tiles of it to be hashed now
+    const uint32_t* open;             // the segment's words of the bitmap
+    int n_words, next, skip;          // words of the segment, the next to be looked at, open rows there that belong to the shares before
+    int count, left, tiles;           // as above; whole tiles of the list to be hashed now
 
-    // Whether the range has an open row at all; every thread of the workgroup calls it.
-    __device__ __forceinline__ bool any(int tid, int n_threads) const
+    // Finds the share; false: it is empty.  Every thread of the workgroup calls it.
+    __device__ __forceinline__ bool begin(int part, int parts, int tid, int n_threads)
     {
-        if (tid == 0) list.count = 0;
+        const int lane = tid & 63, wave = tid >> 6, per = (n_words + n_threads - 1) / n_threads;   // 64 words at most
+        uint32_t mine = 0;
+        for (int i = 0; i < per; ++i) {
+            const int at = tid * per + i;
+            if (at < n_words) mine += static_cast<uint32_t>(__builtin_popcount(open[at]));
+        }
+        const int upto = static_cast<int>(wave_inclusive_scan(mine));
+        if (lane == 63) list.sums[wave] = upto;
         __syncthreads();
-        for (int i = tid; i < n_words; i += n_threads)
-            if (open[i] != 0) list.count = 1;
+        int before = upto - static_cast<int>(mine), total = 0;
+        for (int w = 0; w < n_threads / 64; ++w) {
+            before += w < wave ? list.sums[w] : 0;
+            total += list.sums[w];
+        }
+        const int all = (total + kTile - 1) / kTile;
+        const int from = static_cast<int>(static_cast<int64_t>(all) * part / parts) * kTile;
+        const int to = min(total, static_cast<int>(static_cast<int64_t>(all) * (part + 1) / parts) * kTile);
+        if (from >= to) return false;
+        if (before <= from && from < before + static_cast<int>(mine)) {
+            list.count = tid * per;
+            list.left = from - before;
+        }
         __syncthreads();
-        return list.count != 0;
+        next = list.count;
+        skip = list.left;
+        count = tiles = 0;
+        left = to - from;
+        return true;
     }
     // Fills the list up to the next tiles; false: there are none left.  Every thread of the workgroup calls it.
     __device__ __forceinline__ bool advance(int wave, int lane)
     {
-        if (next >= n_words) return false;
+        if (left == 0) return false;
         do {
             __syncthreads();   // the tiles before are done with the list
             if (wave == 0) {
@@ -286,17 +313,23 @@ struct OpenWalk {
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
                 if (lane < rest) list.row[lane] = r;
                 uint32_t bits = next + lane < n_words ? open[next + lane] : 0u;
-                const uint32_t mine = static_cast<uint32_t>(__builtin_popcount(bits)), upto = wave_inclusive_scan(mine);
-                for (int at = rest + static_cast<int>(upto - mine); bits != 0; bits &= bits - 1, ++at)
-                    list.row[at] = static_cast<uint16_t>((next + lane) * 32 + __builtin_ctz(bits));
-                if (lane == 63) list.count = rest + static_cast<int>(upto);
+                const int mine = __builtin_popcount(bits), upto = static_cast<int>(wave_inclusive_scan(static_cast<uint32_t>(mine)));
+                for (int at = upto - mine - skip; bits != 0; bits &= bits - 1, ++at)
+                    if (at >= 0 && at < left) list.row[rest + at] = static_cast<uint16_t>((next + lane) * 32 + __builtin_ctz(bits));
+                if (lane == 63) {
+                    const int added = min(left, upto - skip);
+                    list.count = rest + added;
+                    list.left = left - added;
+                }
             }
             __syncthreads();
             count = list.count;
+            left = list.left;
             next += kOpenSpan / 32;
-            tiles = next < n_words ? count / kTile : (count + kTile - 1) / kTile;
-        } while (tiles == 0 && next < n_words);
-        return tiles > 0;
+            skip = 0;
+            tiles = left > 0 ? count / kTile : (count + kTile - 1) / kTile;
+        } while (tiles == 0);
+        return true;
     }
 };
 
@@ -339,12 +372,13 @@ __global__ __launch_bounds__(NW * 64, min_waves(NW, NBW)) void hash_bulk_kernel(
     const int nub = hidden_padded(a.hidden) / 32;
 
     const int64_t n_tiles = (a.n_rows + TK - 1) / TK;
-    const int64_t first = static_cast<int64_t>(blockIdx.x) * tiles_per_group;   // of the workgroup's tiles
-    int64_t tile0 = first, tile1 = min(n_tiles, first + tiles_per_group);
+    // OPEN: tiles_per_group workgroups share a segment of the rows
+    const int64_t first = OPEN ? static_cast<int64_t>(blockIdx.x / tiles_per_group) * (kOpenSegment / TK) : static_cast<int64_t>(blockIdx.x) * tiles_per_group;
+    int64_t tile0 = first, tile1 = min(n_tiles, first + (OPEN ? kOpenSegment / TK : tiles_per_group));
     OpenWalk walk{*reinterpret_cast<OpenRows*>(reinterpret_cast<char*>(lds) + open_at), OPEN ? a.open + xhead * a.open_stride + first : nullptr,
-                  static_cast<int>(tile1 - tile0), 0, 0, 0};
+                  static_cast<int>(tile1 - tile0), 0, 0, 0, 0, 0};
     if constexpr (OPEN) {
-        if (!walk.any(tid, NT)) return;
+        if (!walk.begin(static_cast<int>(blockIdx.x % tiles_per_group), tiles_per_group, tid, NT)) return;
         (void)walk.advance(wave, lane);
         tile0 = 0;
         tile1 = walk.tiles;
@@ -726,12 +760,13 @@ __global__ __launch_bounds__(NW * 64, 2) void hash_cert_kernel(HashArgs a, float
     const int n_ks = a.hidden / 16;                                  // hidden is a multiple of 16
 
     const int64_t n_tiles = (a.n_rows + TK - 1) / TK;
-    const int64_t first = static_cast<int64_t>(blockIdx.x) * tiles_per_group;   // of the workgroup's tiles
-    int64_t tile0 = first, tile1 = min(n_tiles, first + tiles_per_group);
+    // OPEN: tiles_per_group workgroups share a segment of the rows
+    const int64_t first = OPEN ? static_cast<int64_t>(blockIdx.x / tiles_per_group) * (kOpenSegment / TK) : static_cast<int64_t>(blockIdx.x) * tiles_per_group;
+    int64_t tile0 = first, tile1 = min(n_tiles, first + (OPEN ? kOpenSegment / TK : tiles_per_group));
     OpenWalk walk{*reinterpret_cast<OpenRows*>(reinterpret_cast<char*>(lds) + open_at), OPEN ? a.open + xhead * a.open_stride + first : nullptr,
-                  static_cast<int>(tile1 - tile0), 0, 0, 0};
+                  static_cast<int>(tile1 - tile0), 0, 0, 0, 0, 0};
     if constexpr (OPEN) {
-        if (!walk.any(tid, NT)) return;
+        if (!walk.begin(static_cast<int>(blockIdx.x % tiles_per_group), tiles_per_group, tid, NT)) return;
         (void)walk.advance(wave, lane);
         tile0 = 0;
         tile1 = walk.tiles;
@@ -1439,12 +1474,17 @@ int launch_cert(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int stage, 
     return launch<XT, bf16_raw, NW, NUB, NBW, false>(ctx, a, n_xheads, stage, lds);
 }
 
-// Tiles of a workgroup's range where only the rows left open are hashed: two workgroups for every slot, so that
-// ranges with more open rows than others even out; rows of the list are 16-bit offsets.
-inline int open_range(int64_t tiles, int n_xheads, int slots)
+// Workgroups that share a segment of open rows: the chip is filled, and not by a last generation that is nearly empty;
+// each fetches the weights (a thirtieth of a segment's tiles).
+inline int open_parts(int64_t segments, int slots)
 {
-    const int64_t per = (tiles * n_xheads + 2 * slots - 1) / (2 * slots);
-    return static_cast<int>(per < 16 ? 16 : per > 2048 ? 2048 : per);
+    int best = 1;
+    double best_cost = 1e30;
+    for (int parts = 1; parts <= 64; ++parts) {
+        const double cost = static_cast<double>((segments * parts + slots - 1) / slots) * (1.0 / parts + 0.03);
+        if (cost < best_cost) { best = parts; best_cost = cost; }
+    }
+    return best;
 }
 
 inline size_t align16(size_t bytes) { return (bytes + 15) / 16 * 16; }
@@ -1456,15 +1496,15 @@ int launch_open(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int stage, 
     const size_t open_at = align16(work), lds = open_at + sizeof(OpenRows);
     auto kern = hash_bulk_kernel<T, T, NW, NUB, NBW, false, true>;
     if (allow_dynamic_lds(ctx, reinterpret_cast<const void*>(kern), lds) != SPOTLIGHT_OK) return SPOTLIGHT_ERR_HIP;
-    const int64_t tiles = (a.n_rows + kTile - 1) / kTile;
-    const int range = open_range(tiles, n_xheads, ctx->n_cus * resident(ctx, 4 * min_waves(NW, NBW) / NW, lds));
+    const int64_t segments = (a.n_rows + kOpenSegment - 1) / kOpenSegment;
+    const int parts = open_parts(segments * n_xheads, ctx->n_cus * resident(ctx, 4 * min_waves(NW, NBW) / NW, lds));
     constexpr int LPR = 16;
     const int n_out = a.n_wheads * a.L;
     hipLaunchKernelGGL(row_norm_kernel<LPR>, dim3(static_cast<unsigned>((n_out * LPR + kThreads - 1) / kThreads)), dim3(kThreads), 0,
                        ctx->stream, static_cast<const T*>(a.w2), a.wnorm, n_out, a.hidden);   // microseconds: not timed
-    dim3 grid(static_cast<unsigned>((tiles + range - 1) / range), static_cast<unsigned>(n_xheads));
+    dim3 grid(static_cast<unsigned>(segments * parts), static_cast<unsigned>(n_xheads));
     StageTimer timer(ctx, stage);
-    timer.launch(kern, grid, dim3(NW * 64), lds, a, static_cast<float>(bulk_hash_eps(a.hidden, true)), range, static_cast<int>(open_at));
+    timer.launch(kern, grid, dim3(NW * 64), lds, a, static_cast<float>(bulk_hash_eps(a.hidden, true)), parts, static_cast<int>(open_at));
     return hip_rc(hipGetLastError());
 }
 
@@ -1475,11 +1515,11 @@ int launch_word_open(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int st
     const size_t open_at = align16(word_lds<T, NW, NUB>(a)), lds = open_at + sizeof(OpenRows);
     auto kern = hash_cert_kernel<T, NW, NUB, WREG, false, true>;
     if (allow_dynamic_lds(ctx, reinterpret_cast<const void*>(kern), lds) != SPOTLIGHT_OK) return SPOTLIGHT_ERR_HIP;
-    const int64_t tiles = (a.n_rows + kTile - 1) / kTile;
-    const int range = open_range(tiles, n_xheads, ctx->n_cus * resident(ctx, 2, lds));
-    dim3 grid(static_cast<unsigned>((tiles + range - 1) / range), static_cast<unsigned>(n_xheads));
+    const int64_t segments = (a.n_rows + kOpenSegment - 1) / kOpenSegment;
+    const int parts = open_parts(segments * n_xheads, ctx->n_cus * resident(ctx, 2, lds));
+    dim3 grid(static_cast<unsigned>(segments * parts), static_cast<unsigned>(n_xheads));
     StageTimer timer(ctx, stage);
-    timer.launch(kern, grid, dim3(NW * 64), lds, a, static_cast<float>(bulk_hash_eps(a.hidden, true)), range, static_cast<int>(open_at));
+    timer.launch(kern, grid, dim3(NW * 64), lds, a, static_cast<float>(bulk_hash_eps(a.hidden, true)), parts, static_cast<int>(open_at));
     return hip_rc(hipGetLastError());
 }
 
