@@ -56,10 +56,12 @@ int make_plan(const spotlight_config* c, Plan* p)
     p->off_part_acc = off;  off = align_up(off + BH * p->max_splits * static_cast<size_t>(kHeadDim) * 4, 256);
     p->off_wnorm = off;     off = align_up(off + static_cast<size_t>(p->Hkv) * p->L * 4, 256);
     pack_sizes(p->hidden, p->L, &p->pack_w1_elems, &p->pack_out_elems);
+    const bool bf16 = p->w_dtype == SPOTLIGHT_BF16 && p->kv_dtype == SPOTLIGHT_BF16;
     const size_t welem = p->w_dtype == SPOTLIGHT_BF16 ? 2 : 4;
     p->off_pack_w1 = off;   off = align_up(off + static_cast<size_t>(p->Hkv) * p->pack_w1_elems * welem, 256);
     p->off_pack_out = off;  off = align_up(off + static_cast<size_t>(p->Hkv) * p->pack_out_elems * welem, 256);
     p->off_scales = off;    off = align_up(off + static_cast<size_t>(p->Hkv) * (1 + p->W) * 16, 256);
+    p->off_operands = off;  off = align_up(off + (bf16 ? static_cast<size_t>(p->Hkv) * screen_operand_bytes(p->hidden, p->W) : 0), 256);
     p->off_open = off;      off = align_up(off + static_cast<size_t>(p->B) * p->Hkv * ((p->Nmax + 31) / 32) * 4, 256);
     p->off_audit = off;     off = align_up(off + sizeof(AuditRec), 256);
     p->total_bytes = off;
@@ -271,6 +273,7 @@ static HashLaunch key_job(const spotlight_ctx* ctx, const void* K, const spotlig
     h.wnorm = ctx->opt[SPOTLIGHT_OPT_BULK_HASH_MATRIX_CORES] ? reinterpret_cast<float*>(ctx->workspace + p.off_wnorm) : nullptr;
     h.audit = ctx->opt[SPOTLIGHT_OPT_BULK_HASH_AUDIT] ? reinterpret_cast<AuditRec*>(ctx->workspace + p.off_audit) : nullptr;
     h.scales = h.wnorm ? ctx->workspace + p.off_scales : nullptr;
+    h.operands = h.wnorm ? ctx->workspace + p.off_operands : nullptr;
     h.open = h.wnorm ? reinterpret_cast<uint32_t*>(ctx->workspace + p.off_open) : nullptr;
     h.open_stride = (p.Nmax + 31) / 32;
     attach_packed(ctx, w, &h);
@@ -305,6 +308,7 @@ static HashLaunch query_job(const spotlight_ctx* ctx, const void* q, const spotl
     h.wnorm = nullptr;
     h.audit = nullptr;
     h.scales = nullptr;
+    h.operands = nullptr;
     h.open = nullptr;
     h.open_stride = 0;
     attach_packed(ctx, w, &h);

@@ -321,6 +321,7 @@ HashArgs make_hash_args(const HashLaunch& h)
     a.pack_w1 = h.pack_w1;
     a.pack_out = h.pack_out;
     a.scales = h.scales;
+    a.operands = h.operands;
     a.open = h.open;
     a.open_stride = h.open_stride;
     return a;

@@ -66,13 +66,50 @@ static_assert(sizeof(LayerScale) == 16 && sizeof(WordScale) == 16, "one record i
 
 constexpr float kSlack = 1e-12f;
 
-// grid (weight heads, 1 + words): block 0 the first layer, block 1 + w code word w.
+// Blocks of 32 hidden units; at least two, so that the kernel below always has a next one.
+__host__ __device__ inline int blocks_of(int hidden) { return hidden > 32 ? (hidden + 31) / 32 : 2; }
+// Operands of a block, 64 x 16 bytes each: 8 steps of 16 k of layer 1, then [half of the block][code word] of layer 2.
+__host__ __device__ constexpr int operands_of(int words) { return 8 + 2 * words; }
+// Code words the kernel below is compiled for.
+__host__ __device__ inline int words_for(int W) { return W <= 2 ? 2 : W <= 4 ? 4 : 8; }
+constexpr int kPerBlock = 32;         // operands a workgroup of the next kernel lays out
+
+// Lane l's part of operand f of block ub: eight weights of one row, zeros past the end.  Rows of layer 1 are
+// in the order that leaves a lane of the result eight consecutive units; of layer 2, in the order of a word's bits.
+__device__ __forceinline__ uint4 operand(const bf16_raw* w1, const bf16_raw* w2, int hidden, int W, int words, int ub, int f, int l)
+{
+    const int c = l & 31, half = l >> 5;
+    if (f < 8) {
+        const int unit = ub * 32 + bulk::unit_of_row(c);
+        if (unit < hidden) return *reinterpret_cast<const uint4*>(w1 + static_cast<int64_t>(unit) * kHeadDim + (2 * f + half) * 8);
+    } else {
+        const int ks = (f - 8) / words, word = (f - 8) % words, unit = ub * 32 + ks * 16 + half * 8;
+        const int j = ((c >> 3) * 4 + (c & 3) + 16 * ((c >> 2) & 1)) * W + word;
+        if (unit < hidden && word < W) return *reinterpret_cast<const uint4*>(w2 + static_cast<int64_t>(j) * hidden + unit);
+    }
+    return make_uint4(0u, 0u, 0u, 0u);
+}
+
+// What the first pass needs of the weights.  grid (weight heads, 1 + words + ...): block 0 the norms of the first layer, block
+// 1 + w those of code word w; the others lay out the operands for kernels that read them again for every eight tiles (from
+// the arrays as stored, a row per lane, each 16-byte load touches 64 cache lines).
 __global__ __launch_bounds__(kThreads) void scales_kernel(const bf16_raw* __restrict__ w1, const bf16_raw* __restrict__ b1,
-                                                          const bf16_raw* __restrict__ w2, char* __restrict__ out, int hidden, int L)
+                                                          const bf16_raw* __restrict__ w2, char* __restrict__ out,
+                                                          uint4* __restrict__ operands, int hidden, int L)
 {
     __shared__ float sums[kThreads / 64][3];
     __shared__ uint32_t bits[kThreads / 64];
     const int W = L / 32, whead = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (static_cast<int>(blockIdx.y) > W) {
+        const int words = words_for(W), per = operands_of(words), n = blocks_of(hidden) * per;
+        w1 += static_cast<int64_t>(whead) * hidden * kHeadDim;
+        w2 += static_cast<int64_t>(whead) * L * hidden;
+        for (int e = wave; e < kPerBlock; e += kThreads / 64) {
+            const int at = (static_cast<int>(blockIdx.y) - 1 - W) * kPerBlock + e;
+            if (at < n) operands[(static_cast<int64_t>(whead) * n + at) * 64 + lane] = operand(w1, w2, hidden, W, words, at / per, at % per, lane);
+        }
+        return;
+    }
     char* rec = out + static_cast<int64_t>(whead) * (1 + W) * 16;
     float a = 0.0f, b = 0.0f, c = 0.0f;
     uint32_t any = 0;
@@ -209,64 +246,28 @@ __device__ __forceinline__ void split8(const float (&h)[8], bf16x8_t& hi, bf16x8
 // A wavefront takes tiles of 32 keys alone.  Layer 1 (rows = hidden units of a block of 32, columns = keys) leaves eight
 // consecutive units of a key in eight accumulators of a lane, which is how layer 2 (rows = the outputs of a code word,
 // columns = keys) reads them: activations stay in the registers of their wavefront.  The weights of both layers are in
-// LDS as the instruction reads them, 16 bytes a lane: all of them (RESIDENT), fetched once per workgroup, or a block of 32
-// hidden units at a time, double-buffered, for eight tiles at once.
+// LDS as the instruction reads them, 16 bytes a lane: all of them (RESIDENT), fetched once per workgroup, or one step's at
+// a time, double-buffered, for eight tiles at once.
+// A step is layer 1 of a block (of the next tile's first after a tile's last), beside the activations and layer 2 of the
+// block before: matrix and vector instructions that do not wait for each other.
 // Lane c + 32 half has outputs 16 half .. 16 half + 15 (in bit order, highest first) of a word of key c, so a code is
 // shifted together in the lane from the signs.
 template <int WM, bool RESIDENT>
-__global__ __launch_bounds__(kWaves * 64, 2) void hash_screen_kernel(HashArgs a, const char* __restrict__ scales, int rounds)
+__global__ __launch_bounds__(kWaves * 64, 2) void hash_screen_kernel(HashArgs a, const char* __restrict__ scales, const uint4* __restrict__ operands, int rounds)
 {
-    constexpr int NT = kWaves * 64, TK = bulk::kTile;
+    constexpr int NT = kWaves * 64, TK = bulk::kTile, OPS = operands_of(WM);
     extern __shared__ __align__(16) float lds[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = lane & 31, half = lane >> 5;
     const int xhead = blockIdx.y;
     const int whead = whead_of(a, xhead);
-    const bf16_raw* w1 = static_cast<const bf16_raw*>(a.w1) + static_cast<int64_t>(whead) * a.hidden * kHeadDim;
     const bf16_raw* b1 = static_cast<const bf16_raw*>(a.b1) + static_cast<int64_t>(whead) * a.hidden;
-    const bf16_raw* w2 = static_cast<const bf16_raw*>(a.w2) + static_cast<int64_t>(whead) * a.L * a.hidden;
     const LayerScale* ls = reinterpret_cast<const LayerScale*>(scales + static_cast<int64_t>(whead) * (1 + a.W) * 16);
     const WordScale* ws = reinterpret_cast<const WordScale*>(ls) + 1;
-    const int nub = bulk::hidden_padded(a.hidden) / 32, W = a.W;
-    constexpr int frags = 8 + 2 * WM;                        // operands of a block of hidden units, 64 x 16 bytes each
-    float* bias = lds;                                       // [hidden, padded to 32]
-    uint4* frag = reinterpret_cast<uint4*>(bias + nub * 32); // [blocks, or 2][frags][64]
-
-    // operand f of block ub: 0 .. 7 a step of 16 k of layer 1, then [half of the block][word] of layer 2
-    auto operand = [&](int ub, int f) {
-        uint4 v = make_uint4(0u, 0u, 0u, 0u);
-        if (f < 8) {
-            const int unit = ub * 32 + bulk::unit_of_row(c);
-            if (unit < a.hidden) v = *reinterpret_cast<const uint4*>(w1 + static_cast<int64_t>(unit) * kHeadDim + (2 * f + half) * 8);
-        } else {
-            const int ks = (f - 8) / WM, word = (f - 8) % WM, unit = ub * 32 + ks * 16 + half * 8;
-            const int j = ((c >> 3) * 4 + (c & 3) + 16 * ((c >> 2) & 1)) * W + word;
-            if (unit < a.hidden && word < W) v = *reinterpret_cast<const uint4*>(w2 + static_cast<int64_t>(j) * a.hidden + unit);
-        }
-        return v;
-    };
-    for (int i = tid; i < nub * 32; i += NT) bias[i] = i < a.hidden ? load1(b1 + i) : 0.0f;
-    if constexpr (RESIDENT) {
-        const int n = nub * frags;
-        for (int f0 = wave; f0 < n; f0 += kWaves * 8) {
-            uint4 v[8];
-#pragma unroll
-            for (int p = 0; p < 8; ++p) { const int f = min(f0 + p * kWaves, n - 1); v[p] = operand(f / frags, f % frags); }
-#pragma unroll
-            for (int p = 0; p < 8; ++p) { const int f = f0 + p * kWaves; if (f < n) frag[f * 64 + lane] = v[p]; }
-        }
-    }
-    constexpr int ST = (8 + 2 * WM + kWaves - 1) / kWaves;   // operands a wavefront brings for the next block
-    uint4 stage[ST];
-    auto fetch = [&](int ub) {
-#pragma unroll
-        for (int p = 0; p < ST; ++p) { const int f = wave + p * kWaves; if (f < frags) stage[p] = operand(ub, f); }
-    };
-    auto keep = [&](int buf) {
-#pragma unroll
-        for (int p = 0; p < ST; ++p) { const int f = wave + p * kWaves; if (f < frags) frag[(buf * frags + f) * 64 + lane] = stage[p]; }
-    };
-    if constexpr (!RESIDENT) { fetch(0); keep(0); }
+    const int nub = blocks_of(a.hidden), W = a.W;
+    const uint4* from = operands + static_cast<int64_t>(whead) * nub * OPS * 64;
+    float* bias = lds;                                       // [blocks][32]
+    uint4* ops = reinterpret_cast<uint4*>(bias + nub * 32);  // [blocks, or two buffers][OPS][64]
 
     const bf16_raw* xbase = static_cast<const bf16_raw*>(a.x) + xhead * a.x_head_stride + a.x_row0 * kHeadDim;
     const int64_t n_tiles = (a.n_rows + TK - 1) / TK, tile0 = static_cast<int64_t>(blockIdx.x) * rounds * kWaves;
@@ -277,14 +278,48 @@ __global__ __launch_bounds__(kWaves * 64, 2) void hash_screen_kernel(HashArgs a,
         for (int s = 0; s < 8; ++s) x[s] = *reinterpret_cast<const uint4*>(xbase + row * kHeadDim + (2 * s + half) * 8);
     };
     fetch_x(tile0 + wave);
+    for (int i = tid; i < nub * 32; i += NT) bias[i] = i < a.hidden ? load1(b1 + i) : 0.0f;
+    // operand f of a step: layer 1 of the block behind `ub`, layer 2 of `ub`
+    auto bring = [&](int ub, int buf) {
+        const int behind = ub + 1 < nub ? ub + 1 : 0;
+#pragma unroll
+        for (int p = 0; p < (OPS + kWaves - 1) / kWaves; ++p) {
+            const int f = wave + p * kWaves;
+            if (f < OPS)
+                __builtin_amdgcn_global_load_lds(
+                    reinterpret_cast<const __attribute__((address_space(1))) uint32_t*>(reinterpret_cast<uintptr_t>(from + ((f < 8 ? behind : ub) * OPS + f) * 64 + lane)),
+                    reinterpret_cast<__attribute__((address_space(3))) uint32_t*>(static_cast<uint32_t>(reinterpret_cast<uintptr_t>(ops + (buf * OPS + f) * 64))), 16, 0, 0);
+        }
+    };
+    // what this wavefront has asked for is there (also in LDS), then everybody's
+    auto arrive = [&]() {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+    };
+    if constexpr (RESIDENT) {
+        const bf16_raw* w1 = static_cast<const bf16_raw*>(a.w1) + static_cast<int64_t>(whead) * a.hidden * kHeadDim;
+        const bf16_raw* w2 = static_cast<const bf16_raw*>(a.w2) + static_cast<int64_t>(whead) * a.L * a.hidden;
+        const int n = nub * OPS;
+        for (int f0 = wave; f0 < n; f0 += kWaves * 8) {
+            uint4 v[8];
+#pragma unroll
+            for (int p = 0; p < 8; ++p) { const int f = min(f0 + p * kWaves, n - 1); v[p] = operand(w1, w2, a.hidden, W, WM, f / OPS, f % OPS, lane); }
+#pragma unroll
+            for (int p = 0; p < 8; ++p) { const int f = f0 + p * kWaves; if (f < n) ops[f * 64 + lane] = v[p]; }
+        }
+    } else {
+        bring(nub - 1, 1);   // layer 1 of block 0
+        bring(0, 0);
+    }
     const float t1 = ls->t1, t1_max = ls->t1_max, bn = ls->b1;
     const bool no_bias = ls->no_bias != 0;
-    __syncthreads();
-    int buf = 0;
-    for (int round = 0; round < rounds; ++round) {
-        const int64_t tile = tile0 + round * kWaves + wave;
-        if constexpr (RESIDENT) { if (tile >= n_tiles) break; }   // (otherwise every wavefront meets the barriers)
-        // ---- ||x||
+    arrive();
+
+    f32x16_t y[WM], h;
+    float xn, ca, aa, hh;    // ||x||; sums of squares of S_32, S_64 and S_96, of a', of h'
+    bool nothing;            // the key and b1 are zeros: so is every output, and the code
+    // a new tile: its norm, and outputs of 0 (rows of zeros: far from zero, and negative)
+    auto start = [&]() {
         float xx = 0.0f;
         typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 #pragma unroll
@@ -294,94 +329,74 @@ __global__ __launch_bounds__(kWaves * 64, 2) void hash_screen_kernel(HashArgs a,
             for (int p = 0; p < 4; ++p) xx = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, d[p]), __builtin_bit_cast(bf16x2_t, d[p]), xx, false);
         }
         xx = add_halves(xx);
-        bool nothing = false;   // the key and b1 are zeros: so is every output, and the code
+        nothing = false;
         if (bulk::rare(xx == 0.0f && no_bias)) {
             uint32_t bits = 0;
 #pragma unroll
             for (int s = 0; s < 8; ++s) bits |= bulk::magnitude_bits(x[s]);
             nothing = no_bias && (bits | other_half(bits)) == 0;
         }
-        const float xn = 1.001f * __builtin_amdgcn_sqrtf(xx) + kSlack;
-
-        f32x16_t y[WM];
+        xn = 1.001f * __builtin_amdgcn_sqrtf(xx) + kSlack;
+    };
+    auto clear = [&]() {
+        aa = hh = 0.0f;
 #pragma unroll
         for (int w = 0; w < WM; ++w) {
 #pragma unroll
             for (int v = 0; v < 16; ++v) y[w][v] = 0.0f;
             if (w < W) {
-                const uint32_t z = ws[w].zeros;   // rows of zeros: far from zero, and negative
+                const uint32_t z = ws[w].zeros;
                 if (z) {
 #pragma unroll
                     for (int v = 0; v < 16; ++v) y[w][v] = (z >> (v + 16 * half)) & 1 ? -1e30f : 0.0f;
                 }
             }
         }
-        float ca = 0.0f, aa = 0.0f, hh = 0.0f;   // sums of squares of S_32, S_64 and S_96, of a', of h'
-        auto layer1 = [&](int ub, const uint4* op, f32x16_t& h) {
+    };
+    // layer 1 of block ub; the sum of squares of its sums on the way
+    auto layer1 = [&](int ub, const uint4* op, f32x16_t& acc) {
+        float sum = 0.0f;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const float4 f = *reinterpret_cast<const float4*>(bias + ub * 32 + 16 * (q / 2) + 8 * half + 4 * (q % 2));
-                h[4 * q] = f.x; h[4 * q + 1] = f.y; h[4 * q + 2] = f.z; h[4 * q + 3] = f.w;
-            }
+        for (int q = 0; q < 4; ++q) {
+            const float4 f = *reinterpret_cast<const float4*>(bias + ub * 32 + 16 * (q / 2) + 8 * half + 4 * (q % 2));
+            acc[4 * q] = f.x; acc[4 * q + 1] = f.y; acc[4 * q + 2] = f.z; acc[4 * q + 3] = f.w;
+        }
 #pragma unroll
-            for (int s = 0; s < 8; ++s) {
-                h = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, op[s * 64]), __builtin_bit_cast(bf16x8_t, x[s]), h, 0, 0, 0);
-                if (s == 1 || s == 3 || s == 5) {
+        for (int s = 0; s < 8; ++s) {
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, op[s * 64]), __builtin_bit_cast(bf16x8_t, x[s]), acc, 0, 0, 0);
+            if (s == 1 || s == 3 || s == 5) {
 #pragma unroll
-                    for (int v = 0; v < 16; ++v) ca = __builtin_fmaf(h[v], h[v], ca);
-                }
-            }
-        };
-        auto layer2 = [&](const uint4* op, const f32x16_t& h) {
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                float h8[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const float av = h[8 * j + e], hv = fast_silu(av);
-                    aa = __builtin_fmaf(av, av, aa);
-                    hh = __builtin_fmaf(hv, hv, hh);
-                    h8[e] = hv;
-                }
-                bf16x8_t hi, lo;
-                // (the sum first, so that the split may overwrite h8)
-                asm volatile("" : "+v"(hh), "+v"(h8[0]), "+v"(h8[1]), "+v"(h8[2]), "+v"(h8[3]), "+v"(h8[4]), "+v"(h8[5]), "+v"(h8[6]), "+v"(h8[7]));
-                split8(h8, hi, lo);
-#pragma unroll
-                for (int w = 0; w < WM; ++w) {
-                    const bf16x8_t b = __builtin_bit_cast(bf16x8_t, op[(8 + j * WM + w) * 64]);
-                    y[w] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, hi, y[w], 0, 0, 0);
-                    y[w] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, lo, y[w], 0, 0, 0);
-                }
-            }
-        };
-        if constexpr (RESIDENT) {
-            f32x16_t h;
-            layer1(0, frag + lane, h);
-#pragma unroll 1
-            for (int ub = 0; ub + 1 < nub; ++ub) {
-                f32x16_t next;
-                layer1(ub + 1, frag + (ub + 1) * frags * 64 + lane, next);
-                layer2(frag + ub * frags * 64 + lane, h);
-                h = next;
-            }
-            fetch_x(min(tile + kWaves, n_tiles - 1));   // the next tile's, in flight during the rest
-            layer2(frag + (nub - 1) * frags * 64 + lane, h);
-        } else {
-#pragma unroll 1
-            for (int ub = 0; ub < nub; ++ub) {
-                fetch(ub + 1 < nub ? ub + 1 : 0);
-                const uint4* op = frag + buf * frags * 64 + lane;
-                f32x16_t h;
-                layer1(ub, op, h);
-                if (ub == nub - 1) fetch_x(min(tile + kWaves, n_tiles - 1));   // the next tile's, in flight during the rest
-                layer2(op, h);
-                buf ^= 1;
-                keep(buf);
-                __syncthreads();
+                for (int v = 0; v < 16; ++v) sum = __builtin_fmaf(acc[v], acc[v], sum);
             }
         }
-        // ---- the bound of this key
+        return sum;
+    };
+    // the activations of a block, and its part of the outputs
+    auto layer2 = [&](const uint4* op) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            float h8[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const float av = h[8 * j + e], hv = fast_silu(av);
+                aa = __builtin_fmaf(av, av, aa);
+                hh = __builtin_fmaf(hv, hv, hh);
+                h8[e] = hv;
+            }
+            bf16x8_t hi, lo;
+            // (the sum first, so that the split may overwrite h8)
+            asm volatile("" : "+v"(hh), "+v"(h8[0]), "+v"(h8[1]), "+v"(h8[2]), "+v"(h8[3]), "+v"(h8[4]), "+v"(h8[5]), "+v"(h8[6]), "+v"(h8[7]));
+            split8(h8, hi, lo);
+#pragma unroll
+            for (int w = 0; w < WM; ++w) {
+                const bf16x8_t b = __builtin_bit_cast(bf16x8_t, op[(8 + j * WM + w) * 64]);
+                y[w] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, hi, y[w], 0, 0, 0);
+                y[w] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, lo, y[w], 0, 0, 0);
+            }
+        }
+    };
+    // the tile's bound, codes and open keys
+    auto finish = [&](int64_t tile) {
         ca = add_halves(ca);
         aa = add_halves(aa);
         hh = add_halves(hh);
@@ -391,7 +406,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void hash_screen_kernel(HashArgs a,
         const float da = u * (t1 * xn + sums);                                                         // >= ||a - a'||
         const float slope = 0.5f * t1 + 0.5f * t1_max * (an + da), steepest = 1.1f * t1;
         const float dh = u * ((slope < steepest ? slope : steepest) * xn + 1.1f * sums + 12.0f * hn + 2.0f * an);
-        // ---- signs and the distance of the nearest output from zero
+        // signs, and the distance of the nearest output from zero
         uint32_t code[WM];
         bool sure = true;
 #pragma unroll
@@ -425,14 +440,60 @@ __global__ __launch_bounds__(kWaves * 64, 2) void hash_screen_kernel(HashArgs a,
                 if (w < W) to[w] = code[w];
         }
         if (lane == 0 && tile < n_tiles) a.open[xhead * a.open_stride + tile] = marked;
+    };
+
+    // operands of a step: layer 1 of the block behind `ub`, layer 2 of `ub`
+    int buf = 0;
+    auto first_ops = [&](int ub) { return ops + (RESIDENT ? (ub + 1 < nub ? ub + 1 : 0) : buf) * OPS * 64 + lane; };
+    auto second_ops = [&](int ub) { return ops + (RESIDENT ? ub : buf) * OPS * 64 + lane; };
+    auto next_step = [&]() {
+        if constexpr (!RESIDENT) {
+            arrive();
+            buf ^= 1;
+        }
+    };
+    start();
+    clear();
+    ca = layer1(0, RESIDENT ? ops + lane : ops + OPS * 64 + lane, h);
+    if constexpr (!RESIDENT) __syncthreads();   // before step 0 brings step 1's operands over these
+    for (int round = 0; round < rounds; ++round) {
+        const int64_t tile = tile0 + round * kWaves + wave;
+        if constexpr (RESIDENT) { if (tile >= n_tiles) break; }   // (otherwise every wavefront meets the barriers)
+        f32x16_t next;
+#pragma unroll 1
+        for (int ub = 0; ub < nub - 2; ++ub) {
+            if constexpr (!RESIDENT) bring(ub + 1, buf ^ 1);
+            ca += layer1(ub + 1, first_ops(ub), next);
+            layer2(second_ops(ub));
+            h = next;
+            next_step();
+        }
+        if constexpr (!RESIDENT) bring(nub - 1, buf ^ 1);
+        ca += layer1(nub - 1, first_ops(nub - 2), next);
+        fetch_x(min(tile + kWaves, n_tiles - 1));   // the next tile's, in flight during the rest of this step
+        layer2(second_ops(nub - 2));
+        h = next;
+        next_step();
+        if constexpr (!RESIDENT) bring(0, buf ^ 1);
+        const float ca_next = layer1(0, first_ops(nub - 1), next);
+        layer2(second_ops(nub - 1));
+        h = next;
+        finish(tile);
+        start();
+        clear();
+        ca = ca_next;
+        next_step();
     }
 }
 
 inline size_t lds_bytes(int hidden, int words, bool resident)
 {
-    const size_t nub = bulk::hidden_padded(hidden) / 32, frags = 8 + 2 * static_cast<size_t>(words);
-    return nub * 32 * sizeof(float) + (resident ? nub : 2) * frags * 64 * sizeof(uint4);
+    const size_t nub = blocks_of(hidden);
+    return nub * 32 * sizeof(float) + (resident ? nub : 2) * operands_of(words) * 64 * sizeof(uint4);
 }
+
+// Whether a workgroup's LDS (160 KB) holds the operands of all blocks.
+inline bool resident(int hidden, int W) { return lds_bytes(hidden, words_for(W), true) <= 160 * 1024; }
 
 // Rounds of eight tiles a workgroup takes, one workgroup on a compute unit at a time: the fewest rounds in turn, the
 // weights counted as one.
@@ -459,16 +520,19 @@ int launch_kernel(spotlight_ctx* ctx, const HashArgs& a, const char* scales, int
     dim3 grid(static_cast<unsigned>((all_rounds + rounds - 1) / rounds), static_cast<unsigned>(n_xheads));
     StageTimer timer(ctx, stage);
     if (timer.rec) timer.rec->more = true;
-    timer.launch(kern, grid, dim3(kWaves * 64), lds, a, scales, rounds);
+    timer.launch(kern, grid, dim3(kWaves * 64), lds, a, scales, static_cast<const uint4*>(a.operands), rounds);
     return hip_rc(hipGetLastError());
 }
 
 template <int WM>
 int launch_words(spotlight_ctx* ctx, const HashArgs& a, const char* scales, int n_xheads, int stage)
 {
-    if (lds_bytes(a.hidden, WM, true) <= static_cast<size_t>(ctx->max_lds)) return launch_kernel<WM, true>(ctx, a, scales, n_xheads, stage);
+    if (resident(a.hidden, a.W)) return launch_kernel<WM, true>(ctx, a, scales, n_xheads, stage);
     return launch_kernel<WM, false>(ctx, a, scales, n_xheads, stage);
 }
+
+// Networks that the kernels of both passes take.
+inline bool serves(int hidden, int W) { return hidden > 0 && hidden % 16 == 0 && hidden <= 1024 && W <= kWords; }
 
 // Whether two passes serve this job (bfloat16 vectors and weights): a network that the kernels of the second one take,
 // and enough tiles, since a workgroup of each pass fetches the weights and a tile of open rows is hashed by few wavefronts
@@ -477,7 +541,7 @@ int launch_words(spotlight_ctx* ctx, const HashArgs& a, const char* scales, int 
 // 310 us; heads of 64 vectors fill half a round.
 inline bool applies(const spotlight_ctx* ctx, const HashArgs& a, int n_xheads)
 {
-    if (!a.open || !a.wnorm || a.hidden <= 0 || a.hidden % 16 != 0 || a.hidden > 1024 || a.W > kWords) return false;
+    if (!a.open || !a.wnorm || !serves(a.hidden, a.W) || ctx->max_lds < 160 * 1024) return false;
     const int64_t tiles = (a.n_rows + bulk::kTile - 1) / bulk::kTile * n_xheads;
     return a.n_rows >= bulk::kTile * kWaves && tiles >= (a.hidden <= 128 ? 8 : 16) * static_cast<int64_t>(ctx->n_cus);
 }
@@ -485,8 +549,10 @@ inline bool applies(const spotlight_ctx* ctx, const HashArgs& a, int n_xheads)
 inline int launch(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int stage)
 {
     char* scales = static_cast<char*>(a.scales);
-    hipLaunchKernelGGL(scales_kernel, dim3(static_cast<unsigned>(a.n_wheads), static_cast<unsigned>(1 + a.W)), dim3(kThreads), 0, ctx->stream,
-                       static_cast<const bf16_raw*>(a.w1), static_cast<const bf16_raw*>(a.b1), static_cast<const bf16_raw*>(a.w2), scales, a.hidden, a.L);
+    const int n_operands = resident(a.hidden, a.W) ? 0 : blocks_of(a.hidden) * operands_of(words_for(a.W));
+    hipLaunchKernelGGL(scales_kernel, dim3(static_cast<unsigned>(a.n_wheads), static_cast<unsigned>(1 + a.W + (n_operands + kPerBlock - 1) / kPerBlock)), dim3(kThreads), 0,
+                       ctx->stream, static_cast<const bf16_raw*>(a.w1), static_cast<const bf16_raw*>(a.b1), static_cast<const bf16_raw*>(a.w2), scales,
+                       static_cast<uint4*>(a.operands), a.hidden, a.L);
     if (a.W <= 2) return launch_words<2>(ctx, a, scales, n_xheads, stage);
     if (a.W <= 4) return launch_words<4>(ctx, a, scales, n_xheads, stage);
     return launch_words<8>(ctx, a, scales, n_xheads, stage);

@@ -93,6 +93,7 @@ struct HashArgs {
     const void* pack_w1;   // packed copies for the single-vector kernel, or null
     const void* pack_out;
     void* scales;      // scratch of the first pass of bulk hashing (hash_screen.h), or null
+    void* operands;
     uint32_t* open;
     int64_t open_stride;
 };

@@ -40,6 +40,7 @@ struct Plan {
     size_t off_pack_out;   // output matrix of the hash (W2, or R of the linear hash) in that order
     size_t pack_w1_elems, pack_out_elems;   // elements per kv head; both 0 if the hash shape has no such copy
     size_t off_scales;     // [Hkv][1 + W][16 bytes] norms of the weights for the first pass of bulk hashing (hash_screen.h)
+    size_t off_operands;   // [Hkv][screen_operand_bytes] the weights in that pass's read order
     size_t off_open;       // [B*Hkv][ceil(Nmax / 32)] rows that pass left open, a bit each
     size_t off_audit;      // AuditRec of the bulk hash (SPOTLIGHT_OPT_BULK_HASH_AUDIT)
     size_t total_bytes;
@@ -70,6 +71,7 @@ __device__ __forceinline__ uint32_t wave_sum(uint32_t x)
 }
 #endif
 
+size_t screen_operand_bytes(int hidden, int W);          // of a weight head, in hash_screen.hip
 int make_plan(const spotlight_config* cfg, Plan* plan);  // SPOTLIGHT_OK or an error code; host only
 
 // What the audited bulk hash accumulates (device side), see spotlight_bulk_hash_audit_read.
@@ -162,6 +164,7 @@ struct HashLaunch {
     const void* pack_w1;      // packed copies of the weights (see launch_pack_weights), or null
     const void* pack_out;
     void* scales;             // scratch of the first pass of bulk hashing, or null: norms of the weights,
+    void* operands;           // the weights in its read order,
     uint32_t* open;           // and a bit for each row it leaves open, open_stride words per x-head
     int64_t open_stride;
 };

@@ -175,7 +175,7 @@ extern "C" int run_activation(const void* a, void* chain, void* fast, void* hi, 
 extern "C" int run_scales(const void* w1, const void* b1, const void* w2, void* out, int heads, int hidden, int L)
 {
     using hashdev::bf16_raw;
-    screen::scales_kernel<<<dim3(heads, 1 + L / 32), kThreads>>>((const bf16_raw*)w1, (const bf16_raw*)b1, (const bf16_raw*)w2, (char*)out, hidden, L);
+    screen::scales_kernel<<<dim3(heads, 1 + L / 32), kThreads>>>((const bf16_raw*)w1, (const bf16_raw*)b1, (const bf16_raw*)w2, (char*)out, nullptr, hidden, L);
     return hipDeviceSynchronize();
 }
 """
