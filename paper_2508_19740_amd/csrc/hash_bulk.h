@@ -39,6 +39,8 @@
 //   (0.02 - 0.15 %) are recomputed with the chain from the binary32 activations still in LDS.
 //   While every addition was taken to err by a unit in its last place, eps was 4.5 to 5.5 times this.
 #pragma once
+#include <algorithm>
+
 #include "hash_vec.h"
 
 namespace spotlight {
@@ -1346,6 +1348,322 @@ __global__ __launch_bounds__(kThreads, 2) void hash_linear_kernel(HashArgs a, fl
     }
 }
 
+// ------------------------------------------------------------------------------------------------
+// The same for larger calls.  R is in LDS as the instruction reads it (128 KB for
+// 512 bits), rows = the outputs of a word, columns = vectors; a wavefront takes two tiles of 32 vectors alone (one of
+// binary32), straight from memory into its registers, and all words of them, so that an operand of R feeds two
+// instructions and nothing waits at a barrier.  Lane c + 32 half has outputs 16 half .. 16 half + 15 of a word of vector c: the
+// code is shifted together from the signs, and one comparison with the smallest of them tells whether the word
+// is settled.  Outputs that are not (3 in 100000) go to a list of the wavefront, whose chains run when it is full or
+// the work is done, a lane each, and correct the codes in memory.
+// 8 heads x 65536 vectors of 512 bits: 221 us with the kernel above (waits for operands, barriers and chains),
+// 87 us; 32 x 65536 of 128 bits 467 and 132 us; binary32 vectors of 512 bits 270 and 146 us.
+constexpr int kLinearWaves = 8;       // wavefronts of a workgroup
+constexpr int kTilesList = 192;       // open outputs a wavefront keeps; at most 64 come at a time
+
+// How often the product of index j counts in the bound: n / 2 sums of the chain and three times as many groups' sums as are
+// added up to the nearer end, the cut products, the split (bulk_hash_eps, with each term's own share).
+template <int PASSES> __device__ __forceinline__ float linear_charge(int j)
+{
+    const int chain = j < kHeadDim / 2 ? kHeadDim / 2 - j : j - kHeadDim / 2 + 1;
+    return PASSES == 1 ? 1.375f * chain + 16.0f : 1.75f * chain + 151.0f;
+}
+
+struct LinearWord {
+    float scale;                      // max_j u ||charge R_j|| over the outputs of the word
+    uint32_t zeros;                   // bit c: output c * W + word has a row of zeros (y = 0, bit 0)
+};
+// LDS: the operands of the words in use ([8][64] of 16 bytes each), behind the operands: LinearWord[kLinearWords], list[kLinearWaves][kTilesList]
+inline size_t linear_lds(int words) { return static_cast<size_t>(words) * 8 * 64 * sizeof(uint4) + kLinearWords * sizeof(LinearWord) + kLinearWaves * kTilesList * sizeof(uint32_t); }
+
+// the value of lane l + 32 in lane l and the other way round
+__device__ __forceinline__ uint32_t other_half(uint32_t v)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);   // the lower half's value in all lanes, the upper half's
+    return (threadIdx.x & 32) ? r[0] : r[1];
+}
+__device__ __forceinline__ float add_halves(float v)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+template <typename XT, bool AUDIT>
+__global__ __launch_bounds__(kLinearWaves * 64, 2) void hash_linear_tiles_kernel(HashArgs a, int rounds)
+{
+    using WT = bf16_raw;
+    constexpr int TK = kTile, CH = kHeadDim / 8;
+    constexpr int PASSES = sizeof(XT) == 2 ? 1 : 2;           // hi, or hi and lo
+    constexpr int KT = sizeof(XT) == 2 ? 2 : 1;               // tiles a wavefront takes together
+    extern __shared__ __align__(16) float lds[];
+    uint4* ops = reinterpret_cast<uint4*>(lds);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c = lane & 31, half = lane >> 5;
+    const int xhead = blockIdx.y;
+    const int whead = whead_of(a, xhead);
+    const int word0 = blockIdx.z * kLinearWords, n_words = min(kLinearWords, a.W - word0);
+    LinearWord* lw = reinterpret_cast<LinearWord*>(ops + min(kLinearWords, a.W) * 8 * 64);
+    uint32_t* list = reinterpret_cast<uint32_t*>(lw + kLinearWords) + wave * kTilesList;
+    const WT* r = static_cast<const WT*>(a.w1) + static_cast<int64_t>(whead) * a.L * kHeadDim;
+    const XT* xbase = static_cast<const XT*>(a.x) + xhead * a.x_head_stride + a.x_row0 * kHeadDim;
+
+    // vectors: the lane's 8 of every 16 elements of vector c of each tile
+    const int64_t row0 = static_cast<int64_t>(blockIdx.x) * rounds * (kLinearWaves * KT * TK) + wave * (KT * TK);   // of this wavefront's first
+    Raw8<XT> xr[KT][8];
+    auto fetch_x = [&](int64_t row) {
+#pragma unroll
+        for (int t = 0; t < KT; ++t) {
+            const int64_t at = min(row + t * TK + c, a.n_rows - 1);   // rows past the end: a stand-in, never stored
+#pragma unroll
+            for (int s = 0; s < 8; ++s) load_raw(xbase + at * kHeadDim + (2 * s + half) * 8, xr[t][s]);
+        }
+    };
+    fetch_x(row0);
+    // ---- R into LDS, and its rows' norms.  Row c of an operand is the output whose bit a lane shifts in there.
+    const int bit_of_row = (c >> 3) * 4 + (c & 3) + 16 * ((c >> 2) & 1);
+    for (int w = wave; w < n_words; w += kLinearWaves) {
+        const WT* row = r + static_cast<int64_t>(bit_of_row * a.W + word0 + w) * kHeadDim;
+        uint4 v[8];
+#pragma unroll
+        for (int s = 0; s < 8; ++s) v[s] = *reinterpret_cast<const uint4*>(row + (2 * s + half) * 8);
+        float sum = 0.0f;
+        uint32_t bits = 0;
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            ops[(w * 8 + s) * 64 + lane] = v[s];
+            bits |= magnitude_bits(v[s]);
+            const uint32_t d[4] = {v[s].x, v[s].y, v[s].z, v[s].w};
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+                const int k = (2 * s + half) * 8 + 2 * p;
+                const float lo = linear_charge<PASSES>(k) * __uint_as_float(d[p] << 16), hi = linear_charge<PASSES>(k + 1) * __uint_as_float(d[p] & 0xffff0000u);
+                sum = __builtin_fmaf(hi, hi, __builtin_fmaf(lo, lo, sum));
+            }
+        }
+        sum = add_halves(sum);
+        bits |= other_half(bits);
+        float norm = norm_of(square_of(sum, bits));
+        uint32_t zeros = bits == 0 ? 1u << bit_of_row : 0u;
+#pragma unroll
+        for (int off = 1; off < 32; off <<= 1) {
+            const float n2 = __shfl_xor(norm, off);
+            norm = n2 > norm || n2 != n2 ? n2 : norm;   // a NaN stays
+            zeros |= __shfl_xor(zeros, off);
+        }
+        if (lane == 0) lw[w] = {static_cast<float>(1.02 * 0x1p-24) * norm, zeros};
+    }
+    uint32_t au_outputs = 0, au_listed = 0, au_wrong = 0;   // this lane's audit totals
+    float au_ratio = 0.0f;
+
+    // the chain of output row j for vector `row`, from the arrays as stored; the square of the row's norm beside it
+    auto chain = [&](int64_t row, int j, float& square) {
+        const XT* xp = xbase + row * kHeadDim;
+        const WT* rp = r + static_cast<int64_t>(j) * kHeadDim;
+        float y = 0.0f;
+        square = 0.0f;
+#pragma unroll 1
+        for (int g0 = 0; g0 < CH; g0 += 4) {
+            Raw8<XT> xv[4];
+            Raw8<WT> wv[4];
+#pragma unroll
+            for (int p = 0; p < 4; ++p) { load_raw(xp + (g0 + p) * 8, xv[p]); load_raw(rp + (g0 + p) * 8, wv[p]); }
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+                float xf[8], wf[8];
+                expand(xv[p], xf);
+                expand(wv[p], wf);
+#pragma unroll
+                for (int q = 0; q < 8; ++q) y = __builtin_fmaf(wf[q], xf[q], y);
+                if constexpr (AUDIT) {
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) square = __builtin_fmaf(wf[q], wf[q], square);
+                }
+            }
+        }
+        return y;
+    };
+    // ---- the list: row behind row0 << 11 | the sign as stored << 10 | word << 5 | bit
+    int listed = 0;
+    auto settle_list = [&]() {
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");   // the codes are stored, the list is written
+        for (int e = lane; e < listed; e += 64) {
+            const uint32_t entry = list[e];
+            const int64_t row = row0 + (entry >> 11);
+            const int bit = entry & 31, w = (entry >> 5) & 31;
+            float unused;
+            const bool one = chain(row, (31 - bit) * a.W + word0 + w, unused) > 0.0f;
+            // (nobody but this wavefront writes the word)
+            if (one != ((entry >> 10) & 1))
+                __hip_atomic_fetch_xor(a.codes + xhead * a.code_head_stride + (a.code_row0 + row) * a.W + word0 + w, 1u << bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+        listed = 0;
+    };
+    __syncthreads();
+
+    for (int round = 0; round < rounds; ++round) {
+        const int64_t row = row0 + static_cast<int64_t>(round) * (kLinearWaves * KT * TK);
+        if (row >= a.n_rows) break;
+        // ---- norms, and the vectors as operands
+        bf16x8_t x[KT][PASSES][8];
+        float xn[KT];
+#pragma unroll
+        for (int t = 0; t < KT; ++t) {
+            float sum = 0.0f;
+            uint32_t bits = 0;
+#pragma unroll
+            for (int s = 0; s < 8; ++s) {
+                float v[8];
+                expand(xr[t][s], v);
+#pragma unroll
+                for (int q = 0; q < 8; ++q) sum = __builtin_fmaf(v[q], v[q], sum);
+                if constexpr (PASSES == 1) {
+                    x[t][0][s] = __builtin_bit_cast(bf16x8_t, xr[t][s]);
+                } else {
+                    split8(v, x[t][0][s], x[t][PASSES - 1][s]);
+                }
+                bits |= magnitude_bits(xr[t][s]);
+            }
+            xn[t] = norm_of(square_of(add_halves(sum), bits | other_half(bits)));
+        }
+        if (round + 1 < rounds) fetch_x(row + kLinearWaves * KT * TK);   // in flight during this round
+        // ---- the words, four at a time
+        for (int w0 = 0; w0 < n_words; w0 += 4) {
+            uint32_t code[KT][4];
+#pragma unroll
+            for (int wi = 0; wi < 4; ++wi) {
+                const int w = min(w0 + wi, n_words - 1);
+                const LinearWord word = lw[w];
+                f32x16_t y[KT];
+#pragma unroll
+                for (int t = 0; t < KT; ++t)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) y[t][v] = 0.0f;
+                if (word.zeros) {   // rows of zeros: far from zero, and negative
+#pragma unroll
+                    for (int t = 0; t < KT; ++t)
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) y[t][v] = (word.zeros >> (v + 16 * half)) & 1 ? -1e30f : 0.0f;
+                }
+#pragma unroll
+                for (int s = 0; s < 8; ++s) {
+                    const bf16x8_t b = __builtin_bit_cast(bf16x8_t, ops[(w * 8 + s) * 64 + lane]);
+#pragma unroll
+                    for (int t = 0; t < KT; ++t)
+#pragma unroll
+                        for (int p = 0; p < PASSES; ++p) y[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, x[t][p][s], y[t], 0, 0, 0);
+                }
+                float bound[KT];
+                bool open = false;
+#pragma unroll
+                for (int t = 0; t < KT; ++t) {
+                    uint32_t sign = 0;
+                    float nearest = INFINITY;
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        sign = __builtin_amdgcn_alignbit(sign, __float_as_uint(y[t][v]), 31);
+                        nearest = fminf(nearest, __builtin_fabsf(y[t][v]));
+                    }
+                    bound[t] = word.scale * xn[t];
+                    if (!(bound[t] < 1e25f)) bound[t] = INFINITY;                  // also where it is no number
+                    open = open || (!(nearest >= bound[t]) || bound[t] == INFINITY);
+                    code[t][wi] = xn[t] == 0.0f ? 0u : ~sign & 0xffffu;            // a settled output is no zero, but for a vector of zeros
+                }
+                if constexpr (AUDIT) {
+                    if (w0 + wi < n_words) {
+#pragma unroll 1
+                        for (int tv = 0; tv < KT * 16; ++tv) {
+                            float yv = 0.0f, bv = 0.0f, xv = 0.0f;
+#pragma unroll
+                            for (int t = 0; t < KT; ++t)
+#pragma unroll
+                                for (int v = 0; v < 16; ++v) { const bool is = t * 16 + v == tv; yv = is ? y[t][v] : yv; bv = is ? bound[t] : bv; xv = is ? xn[t] : xv; }
+                            const int bit = 31 - (tv % 16 + 16 * half);
+                            const int64_t at = row + tv / 16 * TK + c;
+                            if (at >= a.n_rows) continue;
+                            float square;
+                            const float yc = chain(at, (31 - bit) * a.W + word0 + w, square);
+                            const bool sure = __builtin_fabsf(yv) >= bv && bv < INFINITY, one = yv > 0.0f && xv != 0.0f;
+                            // a NaN or an infinity on either side is never settled and is not a distance; nor is a row of zeros
+                            const float den = __builtin_sqrtf(square) * xv, diff = __builtin_fabsf(yv - yc);
+                            const float ratio = (diff == 0.0f || !(diff < INFINITY) || square == 0.0f) ? 0.0f : (den > 0.0f ? diff / den : INFINITY);
+                            au_ratio = fmaxf(au_ratio, ratio);
+                            au_outputs += 1;
+                            au_listed += sure ? 0 : 1;
+                            au_wrong += (sure && one != (yc > 0.0f)) ? 1 : 0;
+                        }
+                    }
+                }
+                if (__builtin_expect(__ballot(open) != 0, 0) && w0 + wi < n_words) {
+                    uint32_t which = 0;   // of the lane's outputs, 16 a tile
+#pragma unroll
+                    for (int t = 0; t < KT; ++t) {
+                        uint32_t m = 0;
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) m |= __builtin_fabsf(y[t][v]) >= bound[t] ? 0u : 1u << v;
+                        if (bound[t] == INFINITY) m = 0xffffu;
+                        if (row + t * TK + c < a.n_rows) which |= m << (16 * t);
+                    }
+                    uint32_t both = code[0][wi] | (KT == 2 ? code[KT - 1][wi] << 16 : 0u);
+                    while (__ballot(which != 0)) {
+                        const int tv = which ? __builtin_ctz(which) : 0, v = tv % 16, bit = 31 - (v + 16 * half);
+                        const int at_bit = tv - v + 15 - v;
+                        const uint32_t behind = static_cast<uint32_t>(row - row0) + tv / 16 * TK + c;
+                        const unsigned long long o = __ballot(which != 0);
+                        if (listed <= kTilesList - 64) {
+                            const int at = listed + static_cast<int>(__builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(o >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(o), 0u)));
+                            // (with the bit as it will be stored)
+                            if (which) list[at] = behind << 11 | ((both >> at_bit) & 1) << 10 | static_cast<uint32_t>(w) << 5 | static_cast<uint32_t>(bit);
+                            listed += static_cast<int>(__builtin_popcountll(o));
+                        } else if (which) {   // no room: at once (words that the list has open may not be stored yet)
+                            float unused;
+                            const uint32_t one = chain(row0 + behind, (31 - bit) * a.W + word0 + w, unused) > 0.0f;
+                            both = (both & ~(1u << at_bit)) | one << at_bit;
+                        }
+                        which &= which - 1;
+                    }
+                    code[0][wi] = both & 0xffffu;
+                    if constexpr (KT == 2) code[KT - 1][wi] = both >> 16;
+                }
+            }
+            // ---- the words of a vector: 16 bits in either half of the wavefront
+            uint32_t out[4];
+#pragma unroll
+            for (int wi = 0; wi < 4; ++wi) {
+                if constexpr (KT == 2) {   // the lower half of the wavefront takes the first tile, the upper the second
+                    const auto p = __builtin_amdgcn_permlane32_swap(code[0][wi], code[KT - 1][wi], false, false);
+                    out[wi] = (p[0] << 16) | p[1];
+                } else {
+                    out[wi] = (code[0][wi] << 16) | other_half(code[0][wi]);
+                }
+            }
+            const int64_t at = row + (KT == 2 ? half * TK : 0) + c;
+            if (at < a.n_rows && (KT == 2 || half == 0)) {
+                uint32_t* to = a.codes + xhead * a.code_head_stride + (a.code_row0 + at) * a.W + word0 + w0;
+                if (a.W % 4 == 0) {
+                    *reinterpret_cast<uint4*>(to) = make_uint4(out[0], out[1], out[2], out[3]);
+                } else {
+#pragma unroll
+                    for (int wi = 0; wi < 4; ++wi)
+                        if (w0 + wi < n_words) to[wi] = out[wi];
+                }
+            }
+            if (listed > kTilesList / 2) settle_list();
+        }
+    }
+    if (listed) settle_list();
+    if constexpr (AUDIT) {
+        const uint32_t outputs = wave_sum(au_outputs), listed_sum = wave_sum(au_listed), wrong = wave_sum(au_wrong);
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) au_ratio = fmaxf(au_ratio, __shfl_xor(au_ratio, off));
+        if (lane == 0) {
+            atomicAdd(&a.audit->outputs, static_cast<unsigned long long>(outputs));
+            if (listed_sum) atomicAdd(&a.audit->listed, static_cast<unsigned long long>(listed_sum));
+            if (wrong) atomicAdd(&a.audit->wrong, static_cast<unsigned long long>(wrong));
+            atomicMax(&a.audit->max_ratio_bits, __float_as_uint(au_ratio));   // non-negative floats order like their bits
+        }
+    }
+}
+
 // A workgroup takes a run of up to 16 tiles of one head (64, linear); the weights are fetched once per run.
 
 // As many workgroups as runs of `run` tiles make, their runs as equal as they can be.
@@ -1449,6 +1767,19 @@ int launch_word(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int stage)
     return hip_rc(hipGetLastError());
 }
 
+// Rounds a workgroup takes, one workgroup on a compute unit at a time: the fewest rounds in turn, the weights counted as one.
+inline int rounds_of(int64_t all_rounds, int n_xheads, int n_cus)
+{
+    int64_t best = all_rounds, best_cost = INT64_MAX;
+    const int64_t most = 4 * static_cast<int64_t>(n_cus) / n_xheads + 1;   // workgroups of a head
+    for (int64_t groups = 1; groups <= most && groups <= all_rounds; ++groups) {
+        const int64_t rounds = (all_rounds + groups - 1) / groups, used = (all_rounds + rounds - 1) / rounds;
+        const int64_t cost = (used * n_xheads + n_cus - 1) / n_cus * (rounds + 1);
+        if (cost < best_cost) { best = rounds; best_cost = cost; }
+    }
+    return static_cast<int>(best);
+}
+
 template <typename XT, int NB>
 int launch_linear(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int stage)
 {
@@ -1464,6 +1795,24 @@ int launch_linear(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int stage
     dim3 grid(static_cast<unsigned>((tiles + tpg - 1) / tpg), static_cast<unsigned>(n_xheads), static_cast<unsigned>(groups));
     StageTimer timer(ctx, stage);
     timer.launch(kern, grid, dim3(kThreads), lds, a, static_cast<float>(bulk_hash_eps(kHeadDim, sizeof(XT) == 4)), tpg);
+    return hip_rc(hipGetLastError());
+}
+
+template <typename XT>
+int launch_linear_tiles(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int stage)
+{
+    const size_t lds = linear_lds(a.W < kLinearWords ? a.W : kLinearWords);
+    auto kern = hash_linear_tiles_kernel<XT, false>;
+    if (a.audit) kern = hash_linear_tiles_kernel<XT, true>;
+    if (allow_dynamic_lds(ctx, reinterpret_cast<const void*>(kern), lds) != SPOTLIGHT_OK) return SPOTLIGHT_ERR_HIP;
+    const int per_round = kTile * (sizeof(XT) == 2 ? 2 : 1) * kLinearWaves;
+    const int64_t all_rounds = (a.n_rows + per_round - 1) / per_round;
+    const int groups = (a.W + kLinearWords - 1) / kLinearWords;
+    const int most = (1 << 21) / per_round;   // rows in a list entry
+    const int rounds = std::min(rounds_of(all_rounds, n_xheads * groups, ctx->n_cus), most);
+    dim3 grid(static_cast<unsigned>((all_rounds + rounds - 1) / rounds), static_cast<unsigned>(n_xheads), static_cast<unsigned>(groups));
+    StageTimer timer(ctx, stage);
+    timer.launch(kern, grid, dim3(kLinearWaves * 64), lds, a, rounds);
     return hip_rc(hipGetLastError());
 }
 
@@ -1521,6 +1870,18 @@ int launch_word_open(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int st
     StageTimer timer(ctx, stage);
     timer.launch(kern, grid, dim3(NW * 64), lds, a, static_cast<float>(bulk_hash_eps(a.hidden, true)), parts, static_cast<int>(open_at));
     return hip_rc(hipGetLastError());
+}
+
+// Which of the two kernels of the linear hash: with a tile or two for a wavefront, the one that spreads the words of a tile over
+// its wavefronts is done sooner; longer codes need fewer tiles to fill the other's time, short ranges of a head leave
+// its workgroups half empty.  That one and the other, bfloat16: 32 bits, 32000 and 65536 vectors 11.6, 17.1 and 12.4,
+// 12.4 us; 128 bits, 20000 and 32000 10.1, 15.7 and 13.3, 13.0; 512 bits, 4800 and 19200 20.8, 49.2 and 25.3, 26.1;
+// 1024 bits, 32 22.9 and 17.6; 512 heads x 100, 32 and 512 bits 15.5, 52.4 and 17.1, 40.1; x 32, 512 bits 30.2 and 37.0.
+inline bool linear_by_tiles(const spotlight_ctx* ctx, const HashArgs& a, int n_xheads)
+{
+    const int64_t tiles = (a.n_rows + kTile - 1) / kTile * n_xheads;
+    const int fill = a.W == 1 ? 8 : a.W < 16 ? 4 : 1;
+    return ctx->max_lds >= 160 * 1024 && (a.W > kLinearWords || tiles >= fill * (a.n_rows < 256 ? 3 : 1) * static_cast<int64_t>(ctx->n_cus));
 }
 
 inline size_t lds_bytes(size_t x_size, int hidden) { return kTile * (x_size * kHeadDim + sizeof(float) * static_cast<size_t>(hidden_padded(hidden))); }
@@ -1584,6 +1945,7 @@ int run_bulk_hash(spotlight_ctx* ctx, const hashdev::HashArgs& a, int n_xheads, 
     const int nub = hidden_padded(a.hidden) / 32;
     if constexpr (sizeof(WT) == 2) {
         if (nub == 0) {
+            if (linear_by_tiles(ctx, a, n_xheads)) return launch_linear_tiles<XT>(ctx, a, n_xheads, stage);
             if (a.W <= 4) return launch_linear<XT, 1>(ctx, a, n_xheads, stage);
             if (a.W <= 8) return launch_linear<XT, 2>(ctx, a, n_xheads, stage);
             return launch_linear<XT, 4>(ctx, a, n_xheads, stage);

@@ -29,8 +29,10 @@
 namespace spotlight {
 namespace screen {
 using namespace hashdev;
+using bulk::add_halves;
 using bulk::bf16x8_t;
 using bulk::f32x16_t;
+using bulk::other_half;
 
 constexpr int kWaves = 8;             // wavefronts of a workgroup
 constexpr int kWords = 8;             // code words at most
@@ -208,18 +210,6 @@ __global__ __launch_bounds__(kThreads) void scales_kernel(const bf16_raw* __rest
 __device__ __forceinline__ float fast_silu(float a)
 {
     return a * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(a * -0x1.715476p+0f));
-}
-
-// the value of lane l + 32 in lane l and the other way round
-__device__ __forceinline__ uint32_t other_half(uint32_t v)
-{
-    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);   // the lower half's value in all lanes, the upper half's
-    return (threadIdx.x & 32) ? r[0] : r[1];
-}
-__device__ __forceinline__ float add_halves(float v)
-{
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
 // The hi / lo split of bulk::split8, each h - hi in one instruction: h - 1 * hi[0] - 0 * hi[1] (exact; where hi[1] is no
@@ -495,20 +485,6 @@ inline size_t lds_bytes(int hidden, int words, bool resident)
 // Whether a workgroup's LDS (160 KB) holds the operands of all blocks.
 inline bool resident(int hidden, int W) { return lds_bytes(hidden, words_for(W), true) <= 160 * 1024; }
 
-// Rounds of eight tiles a workgroup takes, one workgroup on a compute unit at a time: the fewest rounds in turn, the
-// weights counted as one.
-inline int rounds_of(int64_t all_rounds, int n_xheads, int n_cus)
-{
-    int64_t best = all_rounds, best_cost = INT64_MAX;
-    const int64_t most = 4 * static_cast<int64_t>(n_cus) / n_xheads + 1;   // workgroups of a head
-    for (int64_t groups = 1; groups <= most && groups <= all_rounds; ++groups) {
-        const int64_t rounds = (all_rounds + groups - 1) / groups, used = (all_rounds + rounds - 1) / rounds;
-        const int64_t cost = (used * n_xheads + n_cus - 1) / n_cus * (rounds + 1);
-        if (cost < best_cost) { best = rounds; best_cost = cost; }
-    }
-    return static_cast<int>(best);
-}
-
 template <int WM, bool RESIDENT>
 int launch_kernel(spotlight_ctx* ctx, const HashArgs& a, const char* scales, int n_xheads, int stage)
 {
@@ -516,7 +492,7 @@ int launch_kernel(spotlight_ctx* ctx, const HashArgs& a, const char* scales, int
     auto kern = hash_screen_kernel<WM, RESIDENT>;
     if (allow_dynamic_lds(ctx, reinterpret_cast<const void*>(kern), lds) != SPOTLIGHT_OK) return SPOTLIGHT_ERR_HIP;
     const int64_t all_rounds = (a.n_rows + bulk::kTile * kWaves - 1) / (bulk::kTile * kWaves);
-    const int rounds = rounds_of(all_rounds, n_xheads, ctx->n_cus);
+    const int rounds = bulk::rounds_of(all_rounds, n_xheads, ctx->n_cus);
     dim3 grid(static_cast<unsigned>((all_rounds + rounds - 1) / rounds), static_cast<unsigned>(n_xheads));
     StageTimer timer(ctx, stage);
     if (timer.rec) timer.rec->more = true;
