@@ -1943,6 +1943,7 @@ int run_bulk_hash(spotlight_ctx* ctx, const hashdev::HashArgs& a, int n_xheads, 
     using namespace bulk;
     const size_t lds = lds_bytes(sizeof(XT), a.hidden);
     const int nub = hidden_padded(a.hidden) / 32;
+    const int64_t tiles = (a.n_rows + kTile - 1) / kTile * n_xheads;
     if constexpr (sizeof(WT) == 2) {
         if (nub == 0) {
             if (linear_by_tiles(ctx, a, n_xheads)) return launch_linear_tiles<XT>(ctx, a, n_xheads, stage);
@@ -1951,7 +1952,11 @@ int run_bulk_hash(spotlight_ctx* ctx, const hashdev::HashArgs& a, int n_xheads, 
             return launch_linear<XT, 4>(ctx, a, n_xheads, stage);
         }
         if (a.hidden % 16 == 0 && a.W <= 4 && nub <= 4) return launch_word<XT, 4, 1, 8>(ctx, a, n_xheads, stage);
-        if (a.hidden % 16 == 0 && a.W <= 4 && nub <= 8) return launch_word<XT, 4, 2, 16>(ctx, a, n_xheads, stage);
+        // Where no compute unit gets a second tile, a block of hidden units for each of eight wavefronts: the tile is done
+        // sooner, and no other workgroup would hide the waits of four.  One pass over 1 to 256 tiles, 128 -> 256 ->
+        // 128 23 and 18 us, 160 -> 64 15 - 18 and 13 - 15; 512 tiles 29 and 34.
+        if (a.hidden % 16 == 0 && a.W <= 4 && nub > 4 && nub <= 8)
+            return tiles <= ctx->n_cus ? launch_word<XT, 8, 1, 16>(ctx, a, n_xheads, stage) : launch_word<XT, 4, 2, 16>(ctx, a, n_xheads, stage);
         if (a.hidden % 16 == 0 && a.W <= 16 && nub <= 32) {
             if (nub <= 4) {
                 if (a.W <= 8) return launch_cert<XT, 4, 1, 2>(ctx, a, n_xheads, stage, lds);
@@ -1977,7 +1982,6 @@ int run_bulk_hash(spotlight_ctx* ctx, const hashdev::HashArgs& a, int n_xheads, 
     // the tile is done sooner (8 heads x 20 binary32 vectors, 128 -> 256 -> 256: 25.6 against 30.8 us; 128 bits:
     // 21.2 against 22.8; 8 x 65536, 256 bits: 1251 against 1276).  Otherwise the four hide each other's waits
     // better (4 x 4 x 10000, 32 bits: 276 against 304 us).
-    const int64_t tiles = (a.n_rows + kTile - 1) / kTile * n_xheads;
     if (nub > 4 && nub <= 8 && (a.W > 4 || tiles <= ctx->n_cus)) return launch<XT, WT, 8, 1, 0, false>(ctx, a, n_xheads, stage, lds);
     if (nub <= 8) return launch<XT, WT, 4, 2, 0, false>(ctx, a, n_xheads, stage, lds);
     if (nub <= 16) return launch<XT, WT, 8, 2, 0, false>(ctx, a, n_xheads, stage, lds);

@@ -186,3 +186,11 @@ def test_zeros_are_settled(bits, hidden, kv):
                                               (512, 0, "bf16", "bf16"), (128, 0, "f32", "bf16"), (256, 512, "f32", "bf16")])
 def test_extreme_values(bits, hidden, kv, w):
     _both(1, 2, 700, 0, 700, bits, hidden, kv, w, stress=True)
+
+
+@pytest.mark.parametrize("kv", ["bf16", "f32"])
+@pytest.mark.parametrize("bits,hidden", [(128, 256), (32, 144), (96, 192)])
+@pytest.mark.parametrize("B,rows", [(1, 9), (8, 17), (8, 32), (8, 33)])
+def test_up_to_a_tile_for_every_compute_unit(B, rows, bits, hidden, kv):
+    """Certified words with a block of hidden units for each of eight wavefronts, 256 tiles at most, and the step to four."""
+    _both(B, 32, rows, 2, rows + 4, bits, hidden, kv, "bf16")
