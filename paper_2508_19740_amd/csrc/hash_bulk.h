@@ -251,6 +251,22 @@ __global__ __launch_bounds__(kThreads) void row_norm_kernel(const bf16_raw* __re
 
 __host__ __device__ constexpr int hidden_padded(int hidden) { return (hidden + 31) / 32 * 32; }
 
+// The tiles of workgroup `id`, `parts` of them for every head: `longer` of a head's have run + 1 tiles, the others run (the
+// last what is left).  The longer ones come first, so that a compute unit that takes several workgroups gets one of
+// each kind before it gets a second longer one.
+struct Share {
+    int head;
+    int64_t tile;
+    int tiles;
+};
+__host__ __device__ inline Share share_of(unsigned id, unsigned parts, unsigned heads, int run, int longer)
+{
+    const unsigned long_ones = static_cast<unsigned>(longer) * heads;
+    if (id < long_ones) return {static_cast<int>(id / longer), static_cast<int64_t>(id % longer) * (run + 1), run + 1};
+    const unsigned rest = id - long_ones, others = parts - longer;
+    return {static_cast<int>(rest / others), static_cast<int64_t>(longer) * (run + 1) + static_cast<int64_t>(rest % others) * run, run};
+}
+
 // The rows that a first pass left open (hash_screen.h), compacted a span at a time, so that the kernels below hash
 // tiles of 32 of those alone: what does not fill a tile waits for the next span.  A segment of a head's rows is shared out
 // over `parts` workgroups, the same number of tiles of open rows each, as far as they divide: every one of them counts the
@@ -354,7 +370,7 @@ constexpr int min_waves(int NW, int NBW) { return NBW == 1 && NW >= 8 ? 4 : 2; }
 //        (distance in units of ||W2[j]|| ||h||, settled signs that disagree); totals go to a.audit.
 // OPEN:  only the rows a first pass left open, of the workgroup's range of tiles.
 template <typename XT, typename WT, int NW, int NUB, int NBW, bool AUDIT, bool OPEN = false>
-__global__ __launch_bounds__(NW * 64, min_waves(NW, NBW)) void hash_bulk_kernel(HashArgs a, float eps, int tiles_per_group, int open_at)
+__global__ __launch_bounds__(NW * 64, min_waves(NW, NBW)) void hash_bulk_kernel(HashArgs a, float eps, int run, int extra)
 {
     constexpr int TK = kTile, NT = NW * 64;
     constexpr bool CERT = NBW > 0;
@@ -365,7 +381,9 @@ __global__ __launch_bounds__(NW * 64, min_waves(NW, NBW)) void hash_bulk_kernel(
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c = lane & 31, half = lane >> 5;
-    const int xhead = blockIdx.y;
+    Share share{static_cast<int>(blockIdx.y), static_cast<int64_t>(blockIdx.x) * run, run};
+    if (!OPEN && extra != 0) share = share_of(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x, gridDim.y, run, extra);
+    const int xhead = share.head;
     const int whead = whead_of(a, xhead);
     const WT* w1 = static_cast<const WT*>(a.w1) + static_cast<int64_t>(whead) * (a.hidden > 0 ? a.hidden : a.L) * kHeadDim;
     const WT* b1 = static_cast<const WT*>(a.b1) + static_cast<int64_t>(whead) * a.hidden;
@@ -374,13 +392,13 @@ __global__ __launch_bounds__(NW * 64, min_waves(NW, NBW)) void hash_bulk_kernel(
     const int nub = hidden_padded(a.hidden) / 32;
 
     const int64_t n_tiles = (a.n_rows + TK - 1) / TK;
-    // OPEN: tiles_per_group workgroups share a segment of the rows
-    const int64_t first = OPEN ? static_cast<int64_t>(blockIdx.x / tiles_per_group) * (kOpenSegment / TK) : static_cast<int64_t>(blockIdx.x) * tiles_per_group;
-    int64_t tile0 = first, tile1 = min(n_tiles, first + (OPEN ? kOpenSegment / TK : tiles_per_group));
-    OpenWalk walk{*reinterpret_cast<OpenRows*>(reinterpret_cast<char*>(lds) + open_at), OPEN ? a.open + xhead * a.open_stride + first : nullptr,
+    // OPEN: `run` workgroups share a segment of the rows, their list is `extra` bytes into LDS
+    const int64_t first = OPEN ? static_cast<int64_t>(blockIdx.x / run) * (kOpenSegment / TK) : share.tile;
+    int64_t tile0 = first, tile1 = min(n_tiles, first + (OPEN ? kOpenSegment / TK : share.tiles));
+    OpenWalk walk{*reinterpret_cast<OpenRows*>(reinterpret_cast<char*>(lds) + (OPEN ? extra : 0)), OPEN ? a.open + xhead * a.open_stride + first : nullptr,
                   static_cast<int>(tile1 - tile0), 0, 0, 0, 0, 0};
     if constexpr (OPEN) {
-        if (!walk.begin(static_cast<int>(blockIdx.x % tiles_per_group), tiles_per_group, tid, NT)) return;
+        if (!walk.begin(static_cast<int>(blockIdx.x % run), run, tid, NT)) return;
         (void)walk.advance(wave, lane);
         tile0 = 0;
         tile1 = walk.tiles;
@@ -738,7 +756,7 @@ template <typename XT, int NUB> constexpr int kept_operands() { return sizeof(XT
 
 // NUB: blocks of 32 hidden units a wavefront owns; WREG: steps of 16 units of layer 2.
 template <typename XT, int NW, int NUB, int WREG, bool AUDIT, bool OPEN = false>
-__global__ __launch_bounds__(NW * 64, 2) void hash_cert_kernel(HashArgs a, float eps, int tiles_per_group, int open_at)
+__global__ __launch_bounds__(NW * 64, 2) void hash_cert_kernel(HashArgs a, float eps, int run, int extra)
 {
     using WT = bf16_raw;
     constexpr int TK = kTile, NT = NW * 64;
@@ -753,7 +771,9 @@ __global__ __launch_bounds__(NW * 64, 2) void hash_cert_kernel(HashArgs a, float
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = lane & 31, half = lane >> 5;
-    const int xhead = blockIdx.y;
+    Share share{static_cast<int>(blockIdx.y), static_cast<int64_t>(blockIdx.x) * run, run};
+    if (!OPEN && extra != 0) share = share_of(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x, gridDim.y, run, extra);
+    const int xhead = share.head;
     const int whead = whead_of(a, xhead);
     const WT* w1 = static_cast<const WT*>(a.w1) + static_cast<int64_t>(whead) * a.hidden * kHeadDim;
     const WT* b1 = static_cast<const WT*>(a.b1) + static_cast<int64_t>(whead) * a.hidden;
@@ -762,13 +782,13 @@ __global__ __launch_bounds__(NW * 64, 2) void hash_cert_kernel(HashArgs a, float
     const int n_ks = a.hidden / 16;                                  // hidden is a multiple of 16
 
     const int64_t n_tiles = (a.n_rows + TK - 1) / TK;
-    // OPEN: tiles_per_group workgroups share a segment of the rows
-    const int64_t first = OPEN ? static_cast<int64_t>(blockIdx.x / tiles_per_group) * (kOpenSegment / TK) : static_cast<int64_t>(blockIdx.x) * tiles_per_group;
-    int64_t tile0 = first, tile1 = min(n_tiles, first + (OPEN ? kOpenSegment / TK : tiles_per_group));
-    OpenWalk walk{*reinterpret_cast<OpenRows*>(reinterpret_cast<char*>(lds) + open_at), OPEN ? a.open + xhead * a.open_stride + first : nullptr,
+    // OPEN: `run` workgroups share a segment of the rows, their list is `extra` bytes into LDS
+    const int64_t first = OPEN ? static_cast<int64_t>(blockIdx.x / run) * (kOpenSegment / TK) : share.tile;
+    int64_t tile0 = first, tile1 = min(n_tiles, first + (OPEN ? kOpenSegment / TK : share.tiles));
+    OpenWalk walk{*reinterpret_cast<OpenRows*>(reinterpret_cast<char*>(lds) + (OPEN ? extra : 0)), OPEN ? a.open + xhead * a.open_stride + first : nullptr,
                   static_cast<int>(tile1 - tile0), 0, 0, 0, 0, 0};
     if constexpr (OPEN) {
-        if (!walk.begin(static_cast<int>(blockIdx.x % tiles_per_group), tiles_per_group, tid, NT)) return;
+        if (!walk.begin(static_cast<int>(blockIdx.x % run), run, tid, NT)) return;
         (void)walk.advance(wave, lane);
         tile0 = 0;
         tile1 = walk.tiles;
@@ -1715,6 +1735,29 @@ inline int whole_generations(int64_t tiles, int n_xheads, int n_cus, int per_cu)
     return even_runs(tiles, best);
 }
 
+// How the tiles of a head are shared out (share_of).
+struct Shares {
+    int parts, run, longer;
+};
+inline Shares equal_shares(int64_t tiles, int run) { return {static_cast<int>((tiles + run - 1) / run), run, 0}; }
+
+// Whole generations, or where a compute unit has fewer tiles then, one generation whose runs differ by a tile:
+// 4 heads x 313 tiles on 512 slots, runs of 3, six tiles on some compute units: 85.9 us; of 3 and 2, five: 78 us.
+inline Shares shares_of(int64_t tiles, int n_xheads, int n_cus, int per_cu)
+{
+    const Shares even = equal_shares(tiles, whole_generations(tiles, n_xheads, n_cus, per_cu));
+    const int64_t slots = static_cast<int64_t>(n_cus) * per_cu, parts = slots / n_xheads;
+    if (parts < 1 || parts >= tiles || tiles / parts >= 16) return even;
+    const int run = static_cast<int>(tiles / parts), longer = static_cast<int>(tiles % parts);
+    // tiles of a compute unit, three times, and its weights
+    const auto most = [&](int64_t groups) { return (groups + n_cus - 1) / n_cus; };
+    const int64_t groups = static_cast<int64_t>(even.parts) * n_xheads, last = groups % slots;
+    const int64_t cost_even = groups / slots * per_cu * (3 * even.run + 1) + most(last) * (3 * even.run + 1);
+    const int64_t longs = static_cast<int64_t>(longer) * n_xheads;
+    const int64_t cost = 3 * (static_cast<int64_t>(per_cu) * run + most(longs)) + per_cu;
+    return cost < cost_even ? Shares{static_cast<int>(parts), run, longer} : even;
+}
+
 template <typename XT, typename WT, int NW, int NUB, int NBW, bool AUDIT>
 int launch(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int stage, size_t lds)
 {
@@ -1726,17 +1769,17 @@ int launch(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int stage, size_
     // 1024 -> 512: 959 us with short runs, 994 with whole generations); narrow layers have little to fetch, and more
     // workgroups share a compute unit
     constexpr int kShort = NUB == 0 ? 4096 : NUB < 0 || (NUB == 1 && NW == 4) ? 1024 : 0;
-    const int tpg = kShort ? short_runs(tiles, n_xheads, kShort)
-                           : whole_generations(tiles, n_xheads, ctx->n_cus, resident(ctx, 4 * min_waves(NW, NBW) / NW, lds));
+    const Shares shares = kShort ? equal_shares(tiles, short_runs(tiles, n_xheads, kShort))
+                                 : shares_of(tiles, n_xheads, ctx->n_cus, resident(ctx, 4 * min_waves(NW, NBW) / NW, lds));
     if constexpr (NBW > 0) {
         constexpr int LPR = 16;
         const int n_out = a.n_wheads * a.L;
         hipLaunchKernelGGL(row_norm_kernel<LPR>, dim3(static_cast<unsigned>((n_out * LPR + kThreads - 1) / kThreads)), dim3(kThreads), 0,
                            ctx->stream, static_cast<const bf16_raw*>(a.w2), a.wnorm, n_out, a.hidden);   // microseconds: not timed
     }
-    dim3 grid(static_cast<unsigned>((tiles + tpg - 1) / tpg), static_cast<unsigned>(n_xheads));
+    dim3 grid(static_cast<unsigned>(shares.parts), static_cast<unsigned>(n_xheads));
     StageTimer timer(ctx, stage);
-    timer.launch(kern, grid, dim3(NW * 64), lds, a, static_cast<float>(bulk_hash_eps(a.hidden, true)), tpg, 0);
+    timer.launch(kern, grid, dim3(NW * 64), lds, a, static_cast<float>(bulk_hash_eps(a.hidden, true)), shares.run, shares.longer);
     return hip_rc(hipGetLastError());
 }
 
@@ -1760,10 +1803,10 @@ int launch_word(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int stage)
     const int64_t tiles = (a.n_rows + kTile - 1) / kTile;
     // narrow layers have less to fetch per run, and more workgroups share a compute unit (8 x 65536, 128 -> 128
     // -> 64: 257 us with at least 2048, 267 with 1024)
-    const int tpg = NUB == 1 ? short_runs(tiles, n_xheads, 2048) : whole_generations(tiles, n_xheads, ctx->n_cus, resident(ctx, 2, lds));
-    dim3 grid(static_cast<unsigned>((tiles + tpg - 1) / tpg), static_cast<unsigned>(n_xheads));
+    const Shares shares = NUB == 1 && NW == 4 ? equal_shares(tiles, short_runs(tiles, n_xheads, 2048)) : shares_of(tiles, n_xheads, ctx->n_cus, resident(ctx, 8 / NW, lds));
+    dim3 grid(static_cast<unsigned>(shares.parts), static_cast<unsigned>(n_xheads));
     StageTimer timer(ctx, stage);
-    timer.launch(kern, grid, dim3(NW * 64), lds, a, static_cast<float>(bulk_hash_eps(a.hidden, true)), tpg, 0);
+    timer.launch(kern, grid, dim3(NW * 64), lds, a, static_cast<float>(bulk_hash_eps(a.hidden, true)), shares.run, shares.longer);
     return hip_rc(hipGetLastError());
 }
 

@@ -41,6 +41,41 @@ int main()
 }
 """
 
+SHARES = r"""
+#include <stdio.h>
+#include <vector>
+#include "hash_bulk.h"
+using namespace spotlight;
+int main()
+{
+    const long some[] = {1, 2, 3, 5, 8, 9, 16, 17, 31, 63, 100, 127, 128, 129, 313, 625, 2047, 4097};
+    for (long tiles : some)
+        for (int heads : {1, 3, 4, 28, 32, 255, 256, 300, 512, 600})
+            for (int per_cu : {1, 2}) {
+                const bulk::Shares s = bulk::shares_of(tiles, heads, 256, per_cu);
+                std::vector<char> seen(tiles * heads, 0);
+                int before = 1 << 30, longest = 0, shortest = 1 << 30;
+                for (unsigned id = 0; id < static_cast<unsigned>(s.parts) * heads; ++id) {
+                    const bulk::Share w = bulk::share_of(id, s.parts, heads, s.run, s.longer);
+                    if (w.head < 0 || w.head >= heads || w.tiles > before || w.tile >= tiles) { printf("share %u of %ld x %d\n", id, tiles, heads); return 1; }
+                    before = w.tiles;
+                    longest = w.tiles > longest ? w.tiles : longest;
+                    shortest = w.tiles < shortest ? w.tiles : shortest;
+                    for (long t = w.tile; t < w.tile + w.tiles && t < tiles; ++t)
+                        if (seen[w.head * tiles + t]++) { printf("tile twice: %ld x %d, %ld\n", tiles, heads, t); return 1; }
+                }
+                for (char c : seen) if (c != 1) { printf("tile left out: %ld x %d\n", tiles, heads); return 1; }
+                if (longest > 17 || longest - shortest > 1 || (s.longer && s.parts * heads > 256 * per_cu)) { printf("runs: %ld x %d: %d %d %d\n", tiles, heads, s.parts, s.run, s.longer); return 1; }
+            }
+    // open rows: one generation where the segments allow it
+    for (long segments : {1, 2, 16, 56, 64, 300, 512, 4096}) {
+        const int parts = bulk::open_parts(segments, 512);
+        if (parts < 1 || parts > 64 || (segments <= 8 && parts != 64)) { printf("open %ld: %d\n", segments, parts); return 1; }
+    }
+    return 0;
+}
+"""
+
 ROUTES = r"""
 #include <stdio.h>
 #include <string.h>
@@ -79,6 +114,11 @@ def _program(tmp_path, text, name):
 
 def test_runs_are_even(tmp_path):
     run = subprocess.run([_program(tmp_path, RUNS, "runs")], capture_output=True, text=True)
+    assert run.returncode == 0, run.stdout
+
+
+def test_every_tile_belongs_to_one_workgroup(tmp_path):
+    run = subprocess.run([_program(tmp_path, SHARES, "shares")], capture_output=True, text=True)
     assert run.returncode == 0, run.stdout
 
 

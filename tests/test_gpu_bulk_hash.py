@@ -194,3 +194,9 @@ def test_extreme_values(bits, hidden, kv, w):
 def test_up_to_a_tile_for_every_compute_unit(B, rows, bits, hidden, kv):
     """Certified words with a block of hidden units for each of eight wavefronts, 256 tiles at most, and the step to four."""
     _both(B, 32, rows, 2, rows + 4, bits, hidden, kv, "bf16")
+
+
+@pytest.mark.parametrize("kv,w", [("f32", "f32"), ("bf16", "f32"), ("f32", "bf16"), ("bf16", "bf16")])
+@pytest.mark.parametrize("B,H,rows", [(1, 4, 10007), (1, 28, 700), (2, 150, 129)])
+def test_runs_that_differ_by_a_tile(B, H, rows, kv, w):
+    _both(B, H, rows, 0, rows, 128, 256, kv, w)
