@@ -1,5 +1,5 @@
 // Bulk hashing in two passes: hash_screen.h settles most keys, hash_bulk.h hashes the others with the chain.
-#include "hash_screen.h"
+#include "hash_open.h"
 
 namespace spotlight {
 using namespace hashdev;
@@ -16,6 +16,7 @@ int run_screened_hash(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int s
 {
     const int rc = screen::launch(ctx, a, n_xheads, stage);
     if (rc != SPOTLIGHT_OK) return rc;
+    if (!a.audit && screen::open_serves(a.hidden, a.W)) return screen::launch_open(ctx, a, n_xheads, stage);
     // audited: every row with the chain, which also counts what the first pass settled wrongly
     return a.audit ? run_bulk_hash<bf16_raw, bf16_raw>(ctx, a, n_xheads, stage) : run_open_hash(ctx, a, n_xheads, stage);
 }

@@ -58,7 +58,7 @@ def _check(K, ws, t0, rows, bits, hidden, n_oracle=40, b1_at=0, audit=False):
 
 
 @pytest.mark.parametrize("bits,hidden", [(32, 16), (64, 32), (96, 48), (128, 128), (160, 112), (256, 128), (64, 144), (128, 256), (192, 256),
-                                         (256, 400), (128, 512), (256, 512), (224, 528), (256, 1008), (32, 1024)])
+                                         (160, 288), (256, 400), (128, 512), (256, 512), (224, 528), (256, 1008), (32, 1024)])
 def test_every_instantiation(bits, hidden):
     """Weights of both layers in LDS or a block at a time, one to eight words, every kernel of the second pass."""
     g = torch.Generator().manual_seed(bits + hidden)
@@ -108,15 +108,16 @@ def test_extreme_values(bits, hidden):
     _check(K.bfloat16(), [t.bfloat16().contiguous() for t in ws], 0, rows, bits, hidden, n_oracle=610, b1_at=1)
 
 
+@pytest.mark.parametrize("bits,hidden", [(64, 64), (256, 512)])
 @pytest.mark.parametrize("share", [0.0, 0.5, 1.0])
-def test_rows_that_are_all_open(share):
+def test_rows_that_are_all_open(share, bits, hidden):
     """Two equal and opposite halves of a hidden layer make every output a sum that cancels: nothing is settled, and lists
-    of whole spans are full.  Scattered among settled rows, or all of them."""
+    of whole spans are full, those of a tile's chains too.  Scattered among settled rows, or all of them."""
     g = torch.Generator().manual_seed(3)
-    H, rows, bits, hidden = 2, 65600, 64, 64
+    H, rows, n = 2, 65600, hidden // 2
     ws = [t.float() for t in _weights(g, H, bits, hidden)]
-    ws[0][:, 32:], ws[1][:, 32:], ws[2][:, :, 32:] = ws[0][:, :32], ws[1][:, :32], -ws[2][:, :, :32]
-    ws[0][:, ::32], ws[1][:, ::32] = 0, 0
+    ws[0][:, n:], ws[1][:, n:], ws[2][:, :, n:] = ws[0][:, :n], ws[1][:, :n], -ws[2][:, :, :n]
+    ws[0][:, ::n], ws[1][:, ::n] = 0, 0
     ws[0][:, 0, 0] = 3.0                                 # the unit that tells the rows apart: a = 3 x_0
     K = torch.randn(1, H, rows, 128, generator=g)
     K[..., 0] = torch.where(torch.rand(1, H, rows, generator=g) < share, torch.tensor(0.0), torch.tensor(4.0))
