@@ -1872,7 +1872,7 @@ inline int open_parts(int64_t segments, int slots)
 {
     int best = 1;
     double best_cost = 1e30;
-    for (int parts = 1; parts <= 64; ++parts) {
+    for (int parts = 1; parts <= slots; ++parts) {
         const double cost = static_cast<double>((segments * parts + slots - 1) / slots) * (1.0 / parts + 0.03);
         if (cost < best_cost) { best = parts; best_cost = cost; }
     }

@@ -5,7 +5,7 @@
 // evaluates the whole network on v_mfma_f32_32x32x16_bf16 (products of bfloat16 vectors and weights are exact
 // there, only the sums round differently) with the hardware's exponential, and keeps a bound on the distance of
 // every output from the defined chain's.  A key all of whose outputs are further from zero than that bound has
-// its code; the others (about 8 % of random keys at 128 -> 256 -> 128) are marked in a bitmap, and the kernels of
+// its code; the others (9 % of random keys at 128 -> 256 -> 128) are marked in a bitmap, and the kernels of
 // hash_bulk.h hash those alone afterwards, with the chain.  The codes are the same bit for bit.
 //
 // The bound, in units of u = 2^-24.  One instruction adds its 16 products to c as two groups of eight,
@@ -512,14 +512,15 @@ inline bool serves(int hidden, int W) { return hidden > 0 && hidden % 16 == 0 &&
 
 // Whether two passes serve this job (bfloat16 vectors and weights): a network that the kernels of the second one take,
 // and enough tiles, since a workgroup of each pass fetches the weights and a tile of open rows is hashed by few wavefronts
-// of the chip.  One pass against two, 131072 vectors in all, 1 to 512 heads: 64 -> 32 62 - 64 and 30 - 33 us, 256 -> 128
-// 154 and 86 - 97 us, 512 -> 256 437 - 464 and 326 - 388 us; 65536: 39 and 26, 84 - 87 and 83 - 85, 230 - 240 and 282 -
-// 310 us; heads of 64 vectors fill half a round.
+// of the chip.  One pass against two, 8 and 64 heads, 32768, 65536 and 131072 vectors in all: 64 -> 32 21, 39, 63 and 28, 31,
+// 35 us; 256 -> 128 48, 80, 148 and 60, 68, 83; 256 -> 256 62, 109, 201 and 84, 87, 135; 512 -> 256 127, 224, 431 and 128,
+// 153, 243; 1024 -> 256 311, 594, 1156 and 288, 438, 800.  Heads of 128 vectors fill half a round: 512 of them, 256 -> 256
+// 108 against 132 us.
 inline bool applies(const spotlight_ctx* ctx, const HashArgs& a, int n_xheads)
 {
     if (!a.open || !a.wnorm || !serves(a.hidden, a.W) || ctx->max_lds < 160 * 1024) return false;
     const int64_t tiles = (a.n_rows + bulk::kTile - 1) / bulk::kTile * n_xheads;
-    return a.n_rows >= bulk::kTile * kWaves && tiles >= (a.hidden <= 128 ? 8 : 16) * static_cast<int64_t>(ctx->n_cus);
+    return a.n_rows >= bulk::kTile * kWaves && tiles >= 8 * static_cast<int64_t>(ctx->n_cus);
 }
 
 inline int launch(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int stage)

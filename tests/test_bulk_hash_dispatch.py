@@ -70,7 +70,7 @@ int main()
     // open rows: one generation where the segments allow it
     for (long segments : {1, 2, 16, 56, 64, 300, 512, 4096}) {
         const int parts = bulk::open_parts(segments, 512);
-        if (parts < 1 || parts > 64 || (segments <= 8 && parts != 64)) { printf("open %ld: %d\n", segments, parts); return 1; }
+        if (parts < 1 || parts > 512 || (segments <= 64 && (segments * parts > 512 || segments * (parts + 1) <= 512))) { printf("open %ld: %d\n", segments, parts); return 1; }
     }
     return 0;
 }
