@@ -112,8 +112,9 @@ size_t spotlight_workspace_bytes(const spotlight_config *cfg);
 
 /* Allocates the context and its device workspace on the current device.  *out is set only on
  * success.  The workspace holds the query codes, per-block distance histograms and candidate
- * lists (about one byte per (query head, token)), the partial attention results, and room for
- * one copy of the hash weights (spotlight_prepack_weights). */
+ * lists (about one byte per (query head, token)), the partial attention results, a bit per key and
+ * norms of the hash weights for bulk hashing (a second copy of bfloat16 weights that do not fit into
+ * LDS), and room for one copy of the hash weights (spotlight_prepack_weights). */
 int spotlight_create(spotlight_ctx **out, const spotlight_config *cfg);
 
 /* Waits for the stream, frees the workspace and the context.  NULL is accepted. */
@@ -156,7 +157,9 @@ int spotlight_prepack_weights(spotlight_ctx *ctx, const spotlight_hash_weights *
  * in increasing index order, so they do not depend on launch shape.  (A bulk call runs the chains on
  * the binary32 matrix instructions, which are such chains; the last layer of bfloat16 weights goes
  * through the bfloat16 instructions, and every output whose sign that result does not settle is
- * recomputed with the chain: same bits.  SPOTLIGHT_OPT_BULK_HASH_MATRIX_CORES = 0 keeps everything
+ * recomputed with the chain: same bits.  A large call with bfloat16 keys and weights first evaluates
+ * both layers on the bfloat16 instructions and hashes this way only the keys with an output whose sign
+ * that does not settle; until it has ended, the codes of those keys are not final.  SPOTLIGHT_OPT_BULK_HASH_MATRIX_CORES = 0 keeps everything
  * on the vector ALU.)
  *
  *   K      [B, Hkv, Nmax, d]  kv_dtype   read rows t0 .. t0+n_new-1 of every head
@@ -174,8 +177,8 @@ int spotlight_hash_keys(spotlight_ctx *ctx, const void *K, const spotlight_hash_
  * skipped):
  *   outputs    hash outputs (key x code bit) evaluated on the matrix cores
  *   listed     of those, outputs whose sign the error bound did not settle (recomputed on the chain)
- *   wrong      outputs the bound did settle whose sign differs from the chain's; the method relies
- *              on this being 0
+ *   wrong      outputs the bound (or the first pass of a large call) did settle whose sign differs
+ *              from the chain's; the method relies on this being 0
  *   max_ratio  largest |y_matrix - y_chain| / (||W2[j]|| ||h||) seen; the bound assumes it stays
  *              below eps = 1.01 2^-24 (0.875 h + 23 + 128), returned in *eps (the linear hash: R_j, x
  *              and d in place of W2[j], h and the hidden width, and no 128 for bfloat16 vectors)

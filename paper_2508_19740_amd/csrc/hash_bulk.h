@@ -730,10 +730,11 @@ __global__ __launch_bounds__(NW * 64, min_waves(NW, NBW)) void hash_bulk_kernel(
 // instead of each splitting all activations for its own word.  Wavefront w owns code word w: it
 // contracts it, takes the signs and recomputes what the bound does not settle itself, with the weights
 // it holds, so a tile costs two barriers.  Two workgroups per compute unit (LDS and registers).
-// Measured, 32 heads x 131072 vectors, 128 -> 256 -> 128: 4.28 ms (128 TFLOP/s), against 6.25 ms with
-// layer 1 on the vector ALU.  A tile takes 19.8 K cycles of a SIMD (counters): 8.2 K of binary32 and 1.0 K of
-// bfloat16 matrix instructions and 8.1 K of vector instructions (by count SiLU 4.0 K, recomputation 1.9 K,
-// unpacking 1.0 K), of which only the bfloat16 ones overlap with others.  Tried and slower: a list of open outputs shared by the workgroup, one
+// Measured in one pass, 32 heads x 131072 vectors, 128 -> 256 -> 128: 4.28 ms (128 TFLOP/s), against 6.25 ms with
+// layer 1 on the vector ALU (bfloat16 calls of that size take two passes now, hash_screen.h).  A tile took 19.8 K cycles
+// of a SIMD (counters, before the bound became four times smaller): 8.2 K of binary32 and 1.0 K of bfloat16 matrix instructions
+// and 8.1 K of vector instructions (by count SiLU 4.0 K, recomputation 1.9 K, unpacking 1.0 K), of which only the bfloat16
+// ones overlap with others.  Tried and slower: a list of open outputs shared by the workgroup, one
 // wavefront taking all of it (4.55 ms: fewer instructions, but everybody waits for its chain); the
 // kernel below with three or four wavefronts per SIMD (4.6 and 5.0 ms); the contraction split over the
 // hidden units with sums through LDS float atomics (14.7 ms: those take about 4 cycles a lane).
@@ -1106,7 +1107,7 @@ __global__ __launch_bounds__(NW * 64, 2) void hash_cert_kernel(HashArgs a, float
 // order, double-buffered with one barrier a tile.  What is left is the vector work of the signs (about
 // six instructions for 64 outputs) and waits: 65536 x 8 vectors of 512 bits went from 983 us on the vector ALU
 // (728 us on the binary32 matrix instruction) to 270 us; 39 % of the cycles issue vector instructions, 10 %
-// are matrix instructions.  With four words a wavefront 50 registers are spilled (66 with binary32 vectors); a
+// are matrix instructions (221 us with the smaller bound; calls of that size go to the next kernel now).  With four words a wavefront 50 registers are spilled (66 with binary32 vectors); a
 // recomputation that holds half as many operands spills 48 and is slower (284 us).
 constexpr int kLinearWords = 16;      // code words of a workgroup, four a wavefront
 constexpr int kLinearList = 256;      // open outputs of a wavefront and tile (of 32 x 128)
