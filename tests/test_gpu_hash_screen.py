@@ -139,6 +139,35 @@ def test_profile_counts_a_call_once():
         ctx.close()
 
 
+@pytest.mark.parametrize("bits,hidden", [(128, 256), (256, 512), (512, 0)])
+def test_in_a_hip_graph(bits, hidden):
+    """Both passes (and the linear hash) recorded once and replayed over other keys, with eager work between the replays."""
+    import paper_2508_19740_amd as sp
+    g = torch.Generator().manual_seed(bits)
+    ws = _weights(g, 8, bits, hidden) if hidden else [(0.1 * torch.randn(8, bits, 128, generator=g)).bfloat16()]
+    ws = [t.to(DEV) for t in ws] + ([] if hidden else [None, None])
+    keys = [torch.randn(1, 8, 16400, 128, generator=g).bfloat16().to(DEV) for _ in range(3)]
+    K = keys[0].clone()
+    codes, want = (torch.zeros(1, 8, 16400, bits // 32, dtype=torch.int32, device=DEV) for _ in range(2))
+    ctx = sp.Spotlight(1, 8, 8, bits, hidden, 16400, 1, kv_dtype=torch.bfloat16, weight_dtype=torch.bfloat16, device=DEV)
+    try:
+        ctx.hash_keys(K, *ws, 0, 16400, codes)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            ctx.hash_keys(K, *ws, 0, 16400, codes)
+        for k in (keys[1], keys[2], keys[0], keys[1]):
+            K.copy_(k)
+            codes.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            ctx.hash_keys(k, *ws, 0, 16400, want)
+            torch.cuda.synchronize()
+            assert torch.equal(codes, want)
+    finally:
+        ctx.close()
+
+
 # ------------------------------------------------------------------ what the bound takes for granted
 PROBE = r"""
 #include "hash_screen.h"
