@@ -117,21 +117,29 @@ __global__ __launch_bounds__(kThreads) void scales_kernel(const bf16_raw* __rest
     uint32_t any = 0;
     if (blockIdx.y == 0) {   // 16 lanes a row
         const bf16_raw* base = w1 + static_cast<int64_t>(whead) * hidden * kHeadDim;
-        for (int i0 = 0; i0 < hidden; i0 += kThreads / 16) {
-            const int i = i0 + tid / 16;
-            float s = 0.0f;
-            if (i < hidden) {
-                float v[8];
-                load8(base + static_cast<int64_t>(i) * kHeadDim + tid % 16 * 8, v);
+        float charge[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) charge[e] = first_layer_charge(tid % 16 * 8 + e);
+        constexpr int AHEAD = 8;   // rows on their way: 256 hidden units 9.2 us one at a time, 5.4 us
+        for (int i0 = tid / 16; i0 < hidden; i0 += AHEAD * (kThreads / 16)) {
+            Raw8<bf16_raw> raw[AHEAD];
+#pragma unroll
+            for (int p = 0; p < AHEAD; ++p) load_raw(base + static_cast<int64_t>(min(i0 + p * (kThreads / 16), hidden - 1)) * kHeadDim + tid % 16 * 8, raw[p]);
+#pragma unroll
+            for (int p = 0; p < AHEAD; ++p) {
+                float v[8], s = 0.0f;
+                expand(raw[p], v);
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
-                    const float t = first_layer_charge(tid % 16 * 8 + e) * v[e];
+                    const float t = charge[e] * v[e];
                     s = __builtin_fmaf(t, t, s);
                 }
+                s = bulk::add_across_16(s);             // (the lanes of a row agree on what follows)
+                if (i0 + p * (kThreads / 16) < hidden) {
+                    a += s;                             // 16 times, once in each lane of the row
+                    b = s > b || s != s ? s : b;
+                }
             }
-            s = bulk::add_across_16(s);
-            a += s;                                     // 16 times, once in each lane of the row
-            b = s > b || s != s ? s : b;
         }
         a *= 1.0f / 16.0f;
         for (int i = tid; i < hidden; i += kThreads) {
@@ -142,6 +150,7 @@ __global__ __launch_bounds__(kThreads) void scales_kernel(const bf16_raw* __rest
     } else {                 // 8 lanes a row
         const int word = blockIdx.y - 1, r = tid / 8;
         const bf16_raw* row = w2 + (static_cast<int64_t>(whead) * L + r * W + word) * hidden;
+#pragma unroll 4
         for (int g = tid % 8; g < hidden / 8; g += 8) {
             float v[8];
             load8(row + g * 8, v);
