@@ -277,25 +277,56 @@ constexpr int kOpenSegment = 65536;   // rows: offsets in 16 bits
 constexpr int kOpenSpan = 2048;       // rows: a word of the bitmap for each lane of a wavefront
 struct OpenRows {
     uint16_t row[kOpenSpan + kTile];  // in the segment
-    int count, left;                  // rows in the list, rows of the share not in the list yet
+    int count, left, tiles;           // rows in the list, rows of the share not in the list yet, whole tiles of the list
     int sums[16];
 };
+
+// The open rows of a segment that belong to a share, counted in the order of the rows.
+struct OpenShare { int from, to; };
+__host__ __device__ inline OpenShare open_share(int total, int part, int parts)
+{
+    const int all = (total + kTile - 1) / kTile;
+    const int from = static_cast<int>(static_cast<int64_t>(all) * part / parts) * kTile, to = static_cast<int>(static_cast<int64_t>(all) * (part + 1) / parts) * kTile;
+    return {from, to < total ? to : total};
+}
+
+// A word of the bitmap without what lies behind the segment's last row.
+__host__ __device__ inline uint32_t open_word(const uint32_t* open, int word, int n_rows)
+{
+    const int rows = n_rows - word * 32;
+    return rows <= 0 ? 0u : rows >= 32 ? open[word] : open[word] & ((1u << rows) - 1u);
+}
+
+// Puts a word's open rows into the list, the first at `at` behind the `rest` rows there; rows of the shares before have at < 0.
+__host__ __device__ inline void list_rows(uint16_t* list, uint32_t bits, int word, int rest, int at, int left)
+{
+    for (; bits != 0; bits &= bits - 1, ++at)
+        if (at >= 0 && at < left) list[rest + at] = static_cast<uint16_t>(word * 32 + __builtin_ctz(bits));
+}
+
+// Rows in the list and rows to come behind a span that ends at word `next` and had `found` rows of the share; whole tiles to hash
+// now.  Behind the last word nothing comes, whatever was counted in the beginning: the walk ends also where the bitmap has changed since (another
+// stream's call on the same context; its codes are undefined then, but it must not hang).
+struct OpenSpan { int count, left, tiles; };
+__host__ __device__ inline OpenSpan after_span(int rest, int found, int left, int next, int n_rows)
+{
+    const int added = found < 0 ? 0 : found < left ? found : left;
+    const int to_come = next * 32 < n_rows ? left - added : 0;
+    return {rest + added, to_come, to_come > 0 ? (rest + added) / kTile : (rest + added + kTile - 1) / kTile};
+}
 
 struct OpenWalk {
     OpenRows& list;
     const uint32_t* open;             // the segment's words of the bitmap
-    int n_words, next, skip;          // words of the segment, the next to be looked at, open rows there that belong to the shares before
+    int n_rows, next, skip;           // rows of the segment, the next word to be looked at, open rows there that belong to the shares before
     int count, left, tiles;           // as above; whole tiles of the list to be hashed now
 
     // Finds the share; false: it is empty.  Every thread of the workgroup calls it.
     __device__ __forceinline__ bool begin(int part, int parts, int tid, int n_threads)
     {
-        const int lane = tid & 63, wave = tid >> 6, per = (n_words + n_threads - 1) / n_threads;   // 64 words at most
+        const int lane = tid & 63, wave = tid >> 6, n_words = (n_rows + 31) / 32, per = (n_words + n_threads - 1) / n_threads;   // 64 words at most
         uint32_t mine = 0;
-        for (int i = 0; i < per; ++i) {
-            const int at = tid * per + i;
-            if (at < n_words) mine += static_cast<uint32_t>(__builtin_popcount(open[at]));
-        }
+        for (int i = 0; i < per; ++i) mine += static_cast<uint32_t>(__builtin_popcount(open_word(open, tid * per + i, n_rows)));
         const int upto = static_cast<int>(wave_inclusive_scan(mine));
         if (lane == 63) list.sums[wave] = upto;
         __syncthreads();
@@ -304,19 +335,17 @@ struct OpenWalk {
             before += w < wave ? list.sums[w] : 0;
             total += list.sums[w];
         }
-        const int all = (total + kTile - 1) / kTile;
-        const int from = static_cast<int>(static_cast<int64_t>(all) * part / parts) * kTile;
-        const int to = min(total, static_cast<int>(static_cast<int64_t>(all) * (part + 1) / parts) * kTile);
-        if (from >= to) return false;
-        if (before <= from && from < before + static_cast<int>(mine)) {
+        const OpenShare share = open_share(total, part, parts);
+        if (share.from >= share.to) return false;
+        if (before <= share.from && share.from < before + static_cast<int>(mine)) {
             list.count = tid * per;
-            list.left = from - before;
+            list.left = share.from - before;
         }
         __syncthreads();
-        next = list.count;
-        skip = list.left;
+        next = __builtin_amdgcn_readfirstlane(list.count);
+        skip = __builtin_amdgcn_readfirstlane(list.left);
         count = tiles = 0;
-        left = to - from;
+        left = __builtin_amdgcn_readfirstlane(share.to - share.from);
         return true;
     }
     // Fills the list up to the next tiles; false: there are none left.  Every thread of the workgroup calls it.
@@ -330,24 +359,24 @@ struct OpenWalk {
                 const uint16_t r = list.row[tiles * kTile + min(lane, kTile - 1)];
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
                 if (lane < rest) list.row[lane] = r;
-                uint32_t bits = next + lane < n_words ? open[next + lane] : 0u;
+                const uint32_t bits = open_word(open, next + lane, n_rows);
                 const int mine = __builtin_popcount(bits), upto = static_cast<int>(wave_inclusive_scan(static_cast<uint32_t>(mine)));
-                for (int at = upto - mine - skip; bits != 0; bits &= bits - 1, ++at)
-                    if (at >= 0 && at < left) list.row[rest + at] = static_cast<uint16_t>((next + lane) * 32 + __builtin_ctz(bits));
+                list_rows(list.row, bits, next + lane, rest, upto - mine - skip, left);
                 if (lane == 63) {
-                    const int added = min(left, upto - skip);
-                    list.count = rest + added;
-                    list.left = left - added;
+                    const OpenSpan s = after_span(rest, upto - skip, left, next + kOpenSpan / 32, n_rows);
+                    list.count = s.count;
+                    list.left = s.left;
+                    list.tiles = s.tiles;
                 }
             }
             __syncthreads();
-            count = list.count;
-            left = list.left;
+            count = __builtin_amdgcn_readfirstlane(list.count);
+            left = __builtin_amdgcn_readfirstlane(list.left);
+            tiles = __builtin_amdgcn_readfirstlane(list.tiles);
             next += kOpenSpan / 32;
             skip = 0;
-            tiles = left > 0 ? count / kTile : (count + kTile - 1) / kTile;
-        } while (tiles == 0);
-        return true;
+        } while (tiles == 0 && left > 0);
+        return tiles > 0;
     }
 };
 
@@ -396,10 +425,9 @@ __global__ __launch_bounds__(NW * 64, min_waves(NW, NBW)) void hash_bulk_kernel(
     const int64_t first = OPEN ? static_cast<int64_t>(blockIdx.x / run) * (kOpenSegment / TK) : share.tile;
     int64_t tile0 = first, tile1 = min(n_tiles, first + (OPEN ? kOpenSegment / TK : share.tiles));
     OpenWalk walk{*reinterpret_cast<OpenRows*>(reinterpret_cast<char*>(lds) + (OPEN ? extra : 0)), OPEN ? a.open + xhead * a.open_stride + first : nullptr,
-                  static_cast<int>(tile1 - tile0), 0, 0, 0, 0, 0};
+                  static_cast<int>(min(a.n_rows - first * TK, static_cast<int64_t>(kOpenSegment))), 0, 0, 0, 0, 0};
     if constexpr (OPEN) {
-        if (!walk.begin(static_cast<int>(blockIdx.x % run), run, tid, NT)) return;
-        (void)walk.advance(wave, lane);
+        if (!walk.begin(static_cast<int>(blockIdx.x % run), run, tid, NT) || !walk.advance(wave, lane)) return;
         tile0 = 0;
         tile1 = walk.tiles;
     }
@@ -671,10 +699,13 @@ __global__ __launch_bounds__(NW * 64, min_waves(NW, NBW)) void hash_bulk_kernel(
 #pragma unroll
                     for (int p = 0; p < PF; ++p) {
                         if (g0 + p < n8) {
-                            float wv[8];
+                            float wv[8], hv[8];
                             expand(raw[p], wv);
 #pragma unroll
-                            for (int q = 0; q < 8; ++q) y = __builtin_fmaf(wv[q], hs[((g0 + p) * 8 + q) * TK + t], y);
+                            for (int q = 0; q < 8; ++q) hv[q] = hs[((g0 + p) * 8 + q) * TK + t];
+                            if constexpr (OPEN) __builtin_amdgcn_sched_barrier(0);   // all on their way before the first is waited for
+#pragma unroll
+                            for (int q = 0; q < 8; ++q) y = __builtin_fmaf(wv[q], hv[q], y);
                         }
                     }
                 }
@@ -787,10 +818,9 @@ __global__ __launch_bounds__(NW * 64, 2) void hash_cert_kernel(HashArgs a, float
     const int64_t first = OPEN ? static_cast<int64_t>(blockIdx.x / run) * (kOpenSegment / TK) : share.tile;
     int64_t tile0 = first, tile1 = min(n_tiles, first + (OPEN ? kOpenSegment / TK : share.tiles));
     OpenWalk walk{*reinterpret_cast<OpenRows*>(reinterpret_cast<char*>(lds) + (OPEN ? extra : 0)), OPEN ? a.open + xhead * a.open_stride + first : nullptr,
-                  static_cast<int>(tile1 - tile0), 0, 0, 0, 0, 0};
+                  static_cast<int>(min(a.n_rows - first * TK, static_cast<int64_t>(kOpenSegment))), 0, 0, 0, 0, 0};
     if constexpr (OPEN) {
-        if (!walk.begin(static_cast<int>(blockIdx.x % run), run, tid, NT)) return;
-        (void)walk.advance(wave, lane);
+        if (!walk.begin(static_cast<int>(blockIdx.x % run), run, tid, NT) || !walk.advance(wave, lane)) return;
         tile0 = 0;
         tile1 = walk.tiles;
     }

@@ -49,12 +49,10 @@ __global__ __launch_bounds__(kOpenWaves * 64, 2) void hash_open_kernel(HashArgs 
     float* bias = reinterpret_cast<float*>(hilo + nub * 2 * 2 * 64);        // [blocks][32]
     OpenScratch& m = *reinterpret_cast<OpenScratch*>(bias + nub * 32);
 
-    const int64_t n_tiles = (a.n_rows + TK - 1) / TK;
     const int64_t first = static_cast<int64_t>(blockIdx.x / parts) * (bulk::kOpenSegment / TK);
     bulk::OpenWalk walk{*reinterpret_cast<bulk::OpenRows*>(reinterpret_cast<char*>(lds) + open_at), a.open + xhead * a.open_stride + first,
-                        static_cast<int>(min(n_tiles - first, static_cast<int64_t>(bulk::kOpenSegment / TK))), 0, 0, 0, 0, 0};
-    if (!walk.begin(static_cast<int>(blockIdx.x % parts), parts, tid, NT)) return;
-    (void)walk.advance(wave, lane);
+                        static_cast<int>(min(a.n_rows - first * TK, static_cast<int64_t>(bulk::kOpenSegment))), 0, 0, 0, 0, 0};
+    if (!walk.begin(static_cast<int>(blockIdx.x % parts), parts, tid, NT) || !walk.advance(wave, lane)) return;
 
     const bf16_raw* b1 = static_cast<const bf16_raw*>(a.b1) + static_cast<int64_t>(whead) * a.hidden;
     const bf16_raw* w2 = static_cast<const bf16_raw*>(a.w2) + static_cast<int64_t>(whead) * a.L * a.hidden;

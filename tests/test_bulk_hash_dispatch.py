@@ -76,6 +76,89 @@ int main()
 }
 """
 
+WALK = r"""
+#include <stdio.h>
+#include <stdlib.h>
+#include <vector>
+#include "hash_bulk.h"
+using namespace spotlight;
+using Bits = std::vector<uint32_t>;
+struct Seen { std::vector<int> rows; int advances = 0, fullest = 0; };
+// OpenWalk of one share, its lanes in turn; the bitmap is `counted` in the beginning and `met` afterwards.  False: out of range, or no end.
+static bool walk(const Bits& counted, const Bits& met, int n_rows, int part, int parts, Seen& seen)
+{
+    constexpr int kEntries = sizeof(bulk::OpenRows::row) / sizeof(uint16_t);
+    std::vector<uint16_t> list(kEntries + 64, 0xfffe);
+    const int n_words = (n_rows + 31) / 32;
+    int total = 0;
+    for (int w = 0; w < n_words; ++w) total += __builtin_popcount(bulk::open_word(counted.data(), w, n_rows));
+    const bulk::OpenShare share = bulk::open_share(total, part, parts);
+    if (share.from >= share.to) return true;
+    int next = 0, skip = share.from;
+    while (skip >= __builtin_popcount(bulk::open_word(counted.data(), next, n_rows))) skip -= __builtin_popcount(bulk::open_word(counted.data(), next++, n_rows));
+    int count = 0, tiles = 0, left = share.to - share.from;
+    while (left > 0) {
+        if (++seen.advances > n_words / 64 + 2) return false;
+        const int rest = count - tiles * bulk::kTile;
+        if (rest < 0 || rest >= bulk::kTile) return false;
+        for (int r = 0; r < rest; ++r) list[r] = list[tiles * bulk::kTile + r];
+        int upto = 0;
+        for (int lane = 0; lane < 64; ++lane) {
+            const uint32_t bits = bulk::open_word(met.data(), next + lane, n_rows);
+            bulk::list_rows(list.data(), bits, next + lane, rest, upto - skip, left);
+            upto += __builtin_popcount(bits);
+        }
+        const bulk::OpenSpan s = bulk::after_span(rest, upto - skip, left, next + 64, n_rows);
+        next += 64, skip = 0;
+        count = s.count, left = s.left, tiles = s.tiles;
+        if (count < 0 || count > kEntries || tiles * bulk::kTile > (count + 31) / 32 * 32 || (tiles == 0 && left == 0 && count > 0)) return false;
+        for (size_t e = kEntries; e < list.size(); ++e) if (list[e] != 0xfffe) return false;
+        seen.fullest = count > seen.fullest ? count : seen.fullest;
+        const int whole = left > 0 ? tiles * bulk::kTile : count;
+        for (int e = 0; e < whole; ++e) {
+            if (list[e] >= n_rows) return false;
+            seen.rows.push_back(list[e]);
+        }
+    }
+    return true;
+}
+static Bits random_bits(int words, int of_256) { Bits b(words, 0); for (auto& w : b) for (int i = 0; i < 32; ++i) w |= (rand() % 256 < of_256 ? 1u : 0u) << i; return b; }
+int main()
+{
+    int most = 0, fullest = 0;
+    for (int n_rows : {1, 31, 32, 33, 2047, 2048, 2049, 4700, 30001, 65536}) {
+        const int words = (n_rows + 31) / 32;
+        for (int parts : {1, 2, 7, 128, 512})
+            for (int of_256 : {0, 1, 24, 128, 255, 256}) {
+                const Bits open = random_bits(words, of_256);
+                std::vector<int> want, got;
+                for (int r = 0; r < n_rows; ++r) if (open[r / 32] >> (r % 32) & 1) want.push_back(r);
+                for (int part = 0; part < parts; ++part) {
+                    Seen seen;
+                    if (!walk(open, open, n_rows, part, parts, seen)) { printf("range: %d rows, part %d of %d, %d\n", n_rows, part, parts, of_256); return 1; }
+                    got.insert(got.end(), seen.rows.begin(), seen.rows.end());
+                    most = seen.advances > most ? seen.advances : most;
+                    fullest = seen.fullest > fullest ? seen.fullest : fullest;
+                    // a bitmap that changes after it has been counted: it ends, in range
+                    for (int met : {0, 3, 128, 256}) {
+                        Seen other;
+                        if (!walk(open, random_bits(words, met), n_rows, part, parts, other)) { printf("changed: %d rows, part %d of %d, %d then %d\n", n_rows, part, parts, of_256, met); return 1; }
+                    }
+                    if (parts > 7 && part > 9 && part < parts - 9) part += 50, got.clear(), want.clear();   // (a few of many shares)
+                }
+                if (got != want && parts <= 7) { printf("rows: %d, %d parts, %d\n", n_rows, parts, of_256); return 1; }
+            }
+    }
+    Bits open(2048, ~0u);     // one row short of a span: 31 rows wait in front of the next 2048
+    open[3] = 0xfffffffeu;
+    Seen seen;
+    if (!walk(open, open, 65536, 0, 1, seen) || seen.rows.size() != 65535) { printf("all open but one\n"); return 1; }
+    fullest = seen.fullest > fullest ? seen.fullest : fullest;
+    if (most < 32 || fullest != 2079) { printf("advances %d, list %d\n", most, fullest); return 1; }
+    return 0;
+}
+"""
+
 ROUTES = r"""
 #include <stdio.h>
 #include <string.h>
@@ -119,6 +202,13 @@ def test_runs_are_even(tmp_path):
 
 def test_every_tile_belongs_to_one_workgroup(tmp_path):
     run = subprocess.run([_program(tmp_path, SHARES, "shares")], capture_output=True, text=True)
+    assert run.returncode == 0, run.stdout
+
+
+def test_open_rows_are_walked_once_and_to_an_end(tmp_path):
+    """The second pass's walk over the rows left open: every row in one share and once, also over full lists with a partial tile in
+    front of them; and an end in range where another call on the same context has changed the bitmap meanwhile."""
+    run = subprocess.run([_program(tmp_path, WALK, "walk")], capture_output=True, text=True, timeout=100)
     assert run.returncode == 0, run.stdout
 
 
