@@ -1404,13 +1404,16 @@ __global__ __launch_bounds__(kThreads, 2) void hash_linear_kernel(HashArgs a, fl
 // 512 bits), rows = the outputs of a word, columns = vectors; a wavefront takes two tiles of 32 vectors alone (one of
 // binary32), straight from memory into its registers, and all words of them, so that an operand of R feeds two
 // instructions and nothing waits at a barrier.  Lane c + 32 half has outputs 16 half .. 16 half + 15 of a word of vector c: the
-// code is shifted together from the signs, and one comparison with the smallest of them tells whether the word
-// is settled.  Outputs that are not (3 in 100000) go to a list of the wavefront, whose chains run when it is full or
+// code is shifted together from the signs, and one comparison of the smallest of them with the word's largest bound tells
+// whether the word is settled (where the rows of a word are uneven and that does not, each output is held to the bound of its own
+// row: one row of 32 a hundred or a thousand times the others, 148 and 755 us without, 137 with; ten times 98 without, 111 with).  Outputs
+// that are not (3 in 100000) go to a list of the wavefront, whose chains run when it is full or
 // the work is done, a lane each, and correct the codes in memory.
 // 8 heads x 65536 vectors of 512 bits: 221 us with the kernel above (waits for operands, barriers and chains),
 // 87 us; 32 x 65536 of 128 bits 467 and 132 us; binary32 vectors of 512 bits 270 and 146 us.
 constexpr int kLinearWaves = 8;       // wavefronts of a workgroup
 constexpr int kTilesList = 192;       // open outputs a wavefront keeps; at most 64 come at a time
+constexpr float kUneven = 32.0f;      // rows of a word are uneven where one bound for all leaves more than this many times the outputs open
 
 // How often the product of index j counts in the bound: n / 2 sums of the chain and three times as many groups' sums as are
 // added up to the nearer end, the cut products, the split (bulk_hash_eps, with each term's own share).
@@ -1424,8 +1427,12 @@ struct LinearWord {
     float scale;                      // max_j u ||charge R_j|| over the outputs of the word
     uint32_t zeros;                   // bit c: output c * W + word has a row of zeros (y = 0, bit 0)
 };
-// LDS: the operands of the words in use ([8][64] of 16 bytes each), behind the operands: LinearWord[kLinearWords], list[kLinearWaves][kTilesList]
-inline size_t linear_lds(int words) { return static_cast<size_t>(words) * 8 * 64 * sizeof(uint4) + kLinearWords * sizeof(LinearWord) + kLinearWaves * kTilesList * sizeof(uint32_t); }
+// LDS: the operands of the words in use ([8][64] of 16 bytes each), behind the operands: LinearWord[kLinearWords], each row's u ||charge R_j||
+// ([kLinearWords][32] floats in the order of a word's bits) and whether they are uneven ([kLinearWords]), list[kLinearWaves][kTilesList]
+inline size_t linear_lds(int words)
+{
+    return static_cast<size_t>(words) * 8 * 64 * sizeof(uint4) + kLinearWords * (sizeof(LinearWord) + 33 * sizeof(float)) + kLinearWaves * kTilesList * sizeof(uint32_t);
+}
 
 // the value of lane l + 32 in lane l and the other way round
 __device__ __forceinline__ uint32_t other_half(uint32_t v)
@@ -1454,7 +1461,9 @@ __global__ __launch_bounds__(kLinearWaves * 64, 2) void hash_linear_tiles_kernel
     const int whead = whead_of(a, xhead);
     const int word0 = blockIdx.z * kLinearWords, n_words = min(kLinearWords, a.W - word0);
     LinearWord* lw = reinterpret_cast<LinearWord*>(ops + min(kLinearWords, a.W) * 8 * 64);
-    uint32_t* list = reinterpret_cast<uint32_t*>(lw + kLinearWords) + wave * kTilesList;
+    float* row_scale = reinterpret_cast<float*>(lw + kLinearWords);
+    uint32_t* uneven = reinterpret_cast<uint32_t*>(row_scale + kLinearWords * 32);
+    uint32_t* list = uneven + kLinearWords + wave * kTilesList;
     const WT* r = static_cast<const WT*>(a.w1) + static_cast<int64_t>(whead) * a.L * kHeadDim;
     const XT* xbase = static_cast<const XT*>(a.x) + xhead * a.x_head_stride + a.x_row0 * kHeadDim;
 
@@ -1494,14 +1503,19 @@ __global__ __launch_bounds__(kLinearWaves * 64, 2) void hash_linear_tiles_kernel
         sum = add_halves(sum);
         bits |= other_half(bits);
         float norm = norm_of(square_of(sum, bits));
+        const float own = norm;
         uint32_t zeros = bits == 0 ? 1u << bit_of_row : 0u;
+        if (half == 0) row_scale[w * 32 + bit_of_row] = static_cast<float>(1.02 * 0x1p-24) * norm;
 #pragma unroll
         for (int off = 1; off < 32; off <<= 1) {
             const float n2 = __shfl_xor(norm, off);
             norm = n2 > norm || n2 != n2 ? n2 : norm;   // a NaN stays
             zeros |= __shfl_xor(zeros, off);
         }
-        if (lane == 0) lw[w] = {static_cast<float>(1.02 * 0x1p-24) * norm, zeros};
+        float share = bits == 0 ? 0.0f : norm / own;   // how many times more outputs the largest bound leaves open than each row's own
+#pragma unroll
+        for (int off = 1; off < 32; off <<= 1) share += __shfl_xor(share, off);
+        if (lane == 0) { lw[w] = {static_cast<float>(1.02 * 0x1p-24) * norm, zeros}; uneven[w] = !(share <= 32.0f * kUneven); }   // also where one is no number
     }
     uint32_t au_outputs = 0, au_listed = 0, au_wrong = 0;   // this lane's audit totals
     float au_ratio = 0.0f;
@@ -1532,6 +1546,11 @@ __global__ __launch_bounds__(kLinearWaves * 64, 2) void hash_linear_tiles_kernel
             }
         }
         return y;
+    };
+    // whether an output is further from zero than the bound of its own row
+    auto sure_of = [&](float y, float scale, float norm) {
+        const float b = scale * norm;
+        return __builtin_fabsf(y) >= b && b < 1e25f;   // neither where it is no number
     };
     // ---- the list: row behind row0 << 11 | the sign as stored << 10 | word << 5 | bit
     int listed = 0;
@@ -1623,17 +1642,17 @@ __global__ __launch_bounds__(kLinearWaves * 64, 2) void hash_linear_tiles_kernel
                     if (w0 + wi < n_words) {
 #pragma unroll 1
                         for (int tv = 0; tv < KT * 16; ++tv) {
-                            float yv = 0.0f, bv = 0.0f, xv = 0.0f;
+                            float yv = 0.0f, xv = 0.0f;
 #pragma unroll
                             for (int t = 0; t < KT; ++t)
 #pragma unroll
-                                for (int v = 0; v < 16; ++v) { const bool is = t * 16 + v == tv; yv = is ? y[t][v] : yv; bv = is ? bound[t] : bv; xv = is ? xn[t] : xv; }
+                                for (int v = 0; v < 16; ++v) { const bool is = t * 16 + v == tv; yv = is ? y[t][v] : yv; xv = is ? xn[t] : xv; }
                             const int bit = 31 - (tv % 16 + 16 * half);
                             const int64_t at = row + tv / 16 * TK + c;
                             if (at >= a.n_rows) continue;
                             float square;
                             const float yc = chain(at, (31 - bit) * a.W + word0 + w, square);
-                            const bool sure = __builtin_fabsf(yv) >= bv && bv < INFINITY, one = yv > 0.0f && xv != 0.0f;
+                            const bool sure = sure_of(yv, uneven[w] ? row_scale[w * 32 + tv % 16 + 16 * half] : word.scale, xv), one = yv > 0.0f && xv != 0.0f;
                             // a NaN or an infinity on either side is never settled and is not a distance; nor is a row of zeros
                             const float den = __builtin_sqrtf(square) * xv, diff = __builtin_fabsf(yv - yc);
                             const float ratio = (diff == 0.0f || !(diff < INFINITY) || square == 0.0f) ? 0.0f : (den > 0.0f ? diff / den : INFINITY);
@@ -1645,6 +1664,7 @@ __global__ __launch_bounds__(kLinearWaves * 64, 2) void hash_linear_tiles_kernel
                     }
                 }
                 if (__builtin_expect(__ballot(open) != 0, 0) && w0 + wi < n_words) {
+                    const bool rows_differ = __builtin_amdgcn_readfirstlane(uneven[w]) != 0;
                     uint32_t which = 0;   // of the lane's outputs, 16 a tile
 #pragma unroll
                     for (int t = 0; t < KT; ++t) {
@@ -1652,6 +1672,11 @@ __global__ __launch_bounds__(kLinearWaves * 64, 2) void hash_linear_tiles_kernel
 #pragma unroll
                         for (int v = 0; v < 16; ++v) m |= __builtin_fabsf(y[t][v]) >= bound[t] ? 0u : 1u << v;
                         if (bound[t] == INFINITY) m = 0xffffu;
+                        if (rows_differ) {
+                            m = 0;
+#pragma unroll
+                            for (int v = 0; v < 16; ++v) m |= sure_of(y[t][v], row_scale[w * 32 + v + 16 * half], xn[t]) ? 0u : 1u << v;
+                        }
                         if (row + t * TK + c < a.n_rows) which |= m << (16 * t);
                     }
                     uint32_t both = code[0][wi] | (KT == 2 ? code[KT - 1][wi] << 16 : 0u);

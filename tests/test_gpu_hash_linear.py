@@ -105,3 +105,16 @@ def test_zeros_are_settled(kv):
     assert _check(zero, r, 0, rows, bits, audit=True)["listed"] == 0
     live = int(r[0].abs().sum(-1).count_nonzero())
     assert _check(K, r, 0, rows, bits, audit=True)["listed"] <= 2 * rows * live // 1000
+
+
+@pytest.mark.parametrize("kv,open_rows", [("bf16", 1.2e-4), ("f32", 4e-4)])
+@pytest.mark.parametrize("factor", [100.0, 1000.0, 1e-14])
+def test_rows_of_unequal_norm_have_bounds_of_their_own(factor, kv, open_rows):
+    """One row of every word far above the others, or below the norms that count: the other rows are settled as if it were not there
+    (equal rows leave 4e-5 of the outputs open, with binary32 vectors 1.3e-4), and of that one at most all outputs are open."""
+    rows, bits = 16400, 512
+    K, r = _inputs(1, 2, rows, bits, kv)
+    W = bits // 32
+    r[:, 5 * W:6 * W] = (r[:, 5 * W:6 * W].float() * factor).bfloat16()
+    own = 1 / 32 if factor < 1 else 0
+    assert _check(K, r, 0, rows, bits, audit=True)["listed"] <= (own + open_rows) * 2 * rows * bits
