@@ -21,11 +21,13 @@ constexpr int kOpenWaves = 8;         // each has two blocks of hidden units and
 
 __host__ __device__ constexpr int open_stride(int hidden) { return blocks_of(hidden) * 32 + 4; }   // words a key: b128 accesses of 8 lanes miss each other
 constexpr int kChains = 512;          // open outputs of a tile that go to its list
+// Wavefronts that run the chains of a tile's list of n.
+__host__ __device__ constexpr int chain_waves(int n) { return n <= 64 ? 1 : kOpenWaves; }
 struct OpenScratch {
     float part[kOpenWaves][bulk::kTile];   // sums of squares of the wavefronts' activations
     uint32_t codes[kOpenWaves][bulk::kTile];
     uint16_t list[kChains];                // key | word << 5 | output in the order of its bits << 8
-    uint32_t listed;
+    uint32_t listed[2];                    // of a tile and the next
 };
 inline size_t open_lds(int hidden)
 {
@@ -33,9 +35,11 @@ inline size_t open_lds(int hidden)
     return bulk::align16(sizeof(float) * (2 * bulk::XTile<bf16_raw>::kFloats + bulk::kTile * open_stride(hidden) + hp) + hp * bulk::kTile * 4 + sizeof(OpenScratch));
 }
 
+// WM: code words the first pass laid the operands out for.
+template <int WM>
 __global__ __launch_bounds__(kOpenWaves * 64, 2) void hash_open_kernel(HashArgs a, const char* __restrict__ scales, const uint4* __restrict__ operands, int parts, int open_at)
 {
-    constexpr int TK = bulk::kTile, NT = kOpenWaves * 64, NUB = 2, WM = 8, OPS = operands_of(WM);
+    constexpr int TK = bulk::kTile, NT = kOpenWaves * 64, NUB = 2, OPS = operands_of(WM);
     using bulk::XTile;
     extern __shared__ __align__(16) float lds[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -126,13 +130,14 @@ __global__ __launch_bounds__(kOpenWaves * 64, 2) void hash_open_kernel(HashArgs 
         const uint32_t bit = 1u << (31 - out);
         if (((m.codes[w][t] & bit) != 0) != (chain(out * W + w, t) > 0.0f)) atomicXor(&m.codes[w][t], bit);
     };
-    if (tid == 0) m.listed = 0;
+    if (tid < 2) m.listed[tid] = 0;
     fetch_x(0);
+    int turn = 0;                    // tiles so far
     bool more = true;
     while (more) {
         put_x(0);
         __syncthreads();
-        for (int tile = 0; tile < walk.tiles; ++tile) {
+        for (int tile = 0; tile < walk.tiles; ++tile, ++turn) {
             const int buf = tile & 1;
             if (tile + 1 < walk.tiles) fetch_x(tile + 1);   // in flight during layer 1
 
@@ -151,7 +156,8 @@ __global__ __launch_bounds__(kOpenWaves * 64, 2) void hash_open_kernel(HashArgs 
                 for (int s = 0; s < kHeadDim / 2; ++s)
                     h[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(ublk[i].step(s), XTile<bf16_raw>::step(xs + buf * XTile<bf16_raw>::kFloats, s, lane), h[i], 0, 0, 0);
             }
-            __syncthreads();   // the previous tile's activations are no longer needed
+            __syncthreads();   // the previous tile's activations are no longer needed, nor its number of chains
+            if (tid == 0) m.listed[~turn & 1] = 0;
             if (tile + 1 < walk.tiles) put_x(buf ^ 1);
             // layer 2's first weights, in flight meanwhile
             uint4 ahead[PF];
@@ -226,7 +232,7 @@ __global__ __launch_bounds__(kOpenWaves * 64, 2) void hash_open_kernel(HashArgs 
                 while (__ballot(which != 0)) {   // every lane's next open output, to the list; no room: at once
                     const unsigned long long o = __ballot(which != 0);
                     uint32_t at = 0;
-                    if (lane == 0) at = atomicAdd(&m.listed, static_cast<uint32_t>(__builtin_popcountll(o)));
+                    if (lane == 0) at = atomicAdd(&m.listed[turn & 1], static_cast<uint32_t>(__builtin_popcountll(o)));
                     at = __builtin_amdgcn_readfirstlane(at) + __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(o >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(o), 0u));
                     if (which) {
                         const int out = __builtin_ctz(which) + 16 * half;
@@ -237,15 +243,22 @@ __global__ __launch_bounds__(kOpenWaves * 64, 2) void hash_open_kernel(HashArgs 
                 }
             }
             __syncthreads();   // the tile's codes and list are complete
-            // ---- one wavefront runs the chains, a lane each, and stores the codes; the others are at the next tile's layer 1
-            if (wave == tile % kOpenWaves) {
-                const int n = min(static_cast<int>(m.listed), kChains);
-                for (int e = lane; e < n; e += 64) settle(m.list[e] & 31, (m.list[e] >> 5) & 7, m.list[e] >> 8);
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            // ---- one wavefront runs the chains, a lane each, and stores the codes; the others are at the next tile's layer 1.  More than
+            // a lane can have at once are shared by all: every key with 16 (4) open outputs, 8 x 32768, 2460 (1320) us by one wavefront, 1270 (1000) by all.
+            const int n = __builtin_amdgcn_readfirstlane(min(static_cast<int>(m.listed[turn & 1]), kChains));
+            const int sharers = chain_waves(n);
+            if (sharers > 1) {
+                for (int e = tid; e < n; e += NT) settle(m.list[e] & 31, (m.list[e] >> 5) & 7, m.list[e] >> 8);
+                __syncthreads();
+            }
+            if (wave == turn % kOpenWaves) {
+                if (sharers == 1) {
+                    for (int e = lane; e < n; e += 64) settle(m.list[e] & 31, (m.list[e] >> 5) & 7, m.list[e] >> 8);
+                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                }
                 const int rows = min(TK, walk.count - tile * TK);
                 for (int e = lane; e < rows * W; e += 64)
                     a.codes[xhead * a.code_head_stride + (a.code_row0 + row_of(tile * TK + e / W)) * W + e % W] = m.codes[e % W][e / W];
-                if (lane == 0) m.listed = 0;
             }
         }
         more = walk.advance(wave, lane);
@@ -259,12 +272,13 @@ inline bool open_serves(int hidden, int W) { return hidden > 256 && hidden <= 51
 inline int launch_open(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int stage)
 {
     const size_t open_at = open_lds(a.hidden), lds = open_at + sizeof(bulk::OpenRows);
-    if (allow_dynamic_lds(ctx, reinterpret_cast<const void*>(hash_open_kernel), lds) != SPOTLIGHT_OK) return SPOTLIGHT_ERR_HIP;
+    auto kern = hash_open_kernel<8>;
+    if (allow_dynamic_lds(ctx, reinterpret_cast<const void*>(kern), lds) != SPOTLIGHT_OK) return SPOTLIGHT_ERR_HIP;
     const int64_t segments = (a.n_rows + bulk::kOpenSegment - 1) / bulk::kOpenSegment;
     const int parts = bulk::open_parts(segments * n_xheads, ctx->n_cus);
     dim3 grid(static_cast<unsigned>(segments * parts), static_cast<unsigned>(n_xheads));
     StageTimer timer(ctx, stage);
-    timer.launch(hash_open_kernel, grid, dim3(kOpenWaves * 64), lds, a, static_cast<const char*>(a.scales), static_cast<const uint4*>(a.operands), parts, static_cast<int>(open_at));
+    timer.launch(kern, grid, dim3(kOpenWaves * 64), lds, a, static_cast<const char*>(a.scales), static_cast<const uint4*>(a.operands), parts, static_cast<int>(open_at));
     return hip_rc(hipGetLastError());
 }
 

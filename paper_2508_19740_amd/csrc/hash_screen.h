@@ -95,6 +95,8 @@ __device__ __forceinline__ uint4 operand(const bf16_raw* w1, const bf16_raw* w2,
 // What the first pass needs of the weights.  grid (weight heads, 1 + words + ...): block 0 the norms of the first layer, block
 // 1 + w those of code word w; the others lay out the operands for kernels that read them again for every eight tiles (from
 // the arrays as stored, a row per lane, each 16-byte load touches 64 cache lines).
+// AHEAD: rows of the first layer on their way (256 hidden units: 9.2 us one at a time, 5.4 us eight).
+template <int AHEAD>
 __global__ __launch_bounds__(kThreads) void scales_kernel(const bf16_raw* __restrict__ w1, const bf16_raw* __restrict__ b1,
                                                           const bf16_raw* __restrict__ w2, char* __restrict__ out,
                                                           uint4* __restrict__ operands, int hidden, int L)
@@ -120,7 +122,6 @@ __global__ __launch_bounds__(kThreads) void scales_kernel(const bf16_raw* __rest
         float charge[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) charge[e] = first_layer_charge(tid % 16 * 8 + e);
-        constexpr int AHEAD = 8;   // rows on their way: 256 hidden units 9.2 us one at a time, 5.4 us
         for (int i0 = tid / 16; i0 < hidden; i0 += AHEAD * (kThreads / 16)) {
             Raw8<bf16_raw> raw[AHEAD];
 #pragma unroll
@@ -536,7 +537,7 @@ inline int launch(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int stage
 {
     char* scales = static_cast<char*>(a.scales);
     const int n_operands = resident(a.hidden, a.W) ? 0 : blocks_of(a.hidden) * operands_of(words_for(a.W));
-    hipLaunchKernelGGL(scales_kernel, dim3(static_cast<unsigned>(a.n_wheads), static_cast<unsigned>(1 + a.W + (n_operands + kPerBlock - 1) / kPerBlock)), dim3(kThreads), 0,
+    hipLaunchKernelGGL(scales_kernel<8>, dim3(static_cast<unsigned>(a.n_wheads), static_cast<unsigned>(1 + a.W + (n_operands + kPerBlock - 1) / kPerBlock)), dim3(kThreads), 0,
                        ctx->stream, static_cast<const bf16_raw*>(a.w1), static_cast<const bf16_raw*>(a.b1), static_cast<const bf16_raw*>(a.w2), scales,
                        static_cast<uint4*>(a.operands), a.hidden, a.L);
     if (a.W <= 2) return launch_words<2>(ctx, a, scales, n_xheads, stage);

@@ -76,6 +76,20 @@ int main()
 }
 """
 
+CHAINS = r"""
+#include <stdio.h>
+#include "hash_open.h"
+using namespace spotlight;
+int main()
+{
+    for (int n = 0; n <= screen::kChains; ++n) {
+        const int lanes = 64 * screen::chain_waves(n);
+        if (n > lanes || lanes > 64 * screen::kOpenWaves) { printf("%d chains, %d lanes\n", n, lanes); return 1; }
+    }
+    return 0;
+}
+"""
+
 WALK = r"""
 #include <stdio.h>
 #include <stdlib.h>
@@ -202,6 +216,11 @@ def test_runs_are_even(tmp_path):
 
 def test_every_tile_belongs_to_one_workgroup(tmp_path):
     run = subprocess.run([_program(tmp_path, SHARES, "shares")], capture_output=True, text=True)
+    assert run.returncode == 0, run.stdout
+
+
+def test_no_lane_runs_two_chains_of_a_list(tmp_path):
+    run = subprocess.run([_program(tmp_path, CHAINS, "chains")], capture_output=True, text=True)
     assert run.returncode == 0, run.stdout
 
 

@@ -124,6 +124,18 @@ def test_rows_that_are_all_open(share, bits, hidden):
     _check(K.bfloat16(), [t.bfloat16().contiguous() for t in ws], 0, rows, bits, hidden)
 
 
+@pytest.mark.parametrize("n_open", [1, 2, 3, 15, 16, 17])
+def test_lists_of_every_length(n_open):
+    """The same of a few output rows, 288 to 512 hidden units and long codes: 32 to 544 outputs of a tile on its list of 512, run by one
+    wavefront or by all, the last with no room for some."""
+    g = torch.Generator().manual_seed(n_open)
+    bits, hidden, H, rows = 256, 512, 2, 33000
+    n = hidden // 2
+    ws = [t.float() for t in _weights(g, H, bits, hidden)]
+    ws[0][:, n:], ws[1][:, n:], ws[2][:, 7:7 + n_open, n:] = ws[0][:, :n], ws[1][:, :n], -ws[2][:, 7:7 + n_open, :n]
+    _check(torch.randn(1, H, rows, 128, generator=g).bfloat16(), [t.bfloat16().contiguous() for t in ws], 0, rows, bits, hidden)
+
+
 def test_profile_counts_a_call_once():
     import paper_2508_19740_amd as sp
     g = torch.Generator().manual_seed(1)
@@ -205,7 +217,7 @@ extern "C" int run_activation(const void* a, void* chain, void* fast, void* hi, 
 extern "C" int run_scales(const void* w1, const void* b1, const void* w2, void* out, int heads, int hidden, int L)
 {
     using hashdev::bf16_raw;
-    screen::scales_kernel<<<dim3(heads, 1 + L / 32), kThreads>>>((const bf16_raw*)w1, (const bf16_raw*)b1, (const bf16_raw*)w2, (char*)out, nullptr, hidden, L);
+    screen::scales_kernel<8><<<dim3(heads, 1 + L / 32), kThreads>>>((const bf16_raw*)w1, (const bf16_raw*)b1, (const bf16_raw*)w2, (char*)out, nullptr, hidden, L);
     return hipDeviceSynchronize();
 }
 """
