@@ -63,6 +63,7 @@ int make_plan(const spotlight_config* c, Plan* p)
     p->off_scales = off;    off = align_up(off + static_cast<size_t>(p->Hkv) * (1 + p->W) * 16, 256);
     p->off_operands = off;  off = align_up(off + (bf16 ? static_cast<size_t>(p->Hkv) * screen_operand_bytes(p->hidden, p->W) : 0), 256);
     p->off_open = off;      off = align_up(off + static_cast<size_t>(p->B) * p->Hkv * ((p->Nmax + 31) / 32) * 4, 256);
+    p->off_open_counts = off; off = align_up(off + static_cast<size_t>(p->B) * p->Hkv * ((p->Nmax + 65535) / 65536) * 128, 256);
     p->off_audit = off;     off = align_up(off + sizeof(AuditRec), 256);
     p->total_bytes = off;
     return SPOTLIGHT_OK;
@@ -276,6 +277,7 @@ static HashLaunch key_job(const spotlight_ctx* ctx, const void* K, const spotlig
     h.operands = h.wnorm ? ctx->workspace + p.off_operands : nullptr;
     h.open = h.wnorm ? reinterpret_cast<uint32_t*>(ctx->workspace + p.off_open) : nullptr;
     h.open_stride = (p.Nmax + 31) / 32;
+    h.open_counts = h.wnorm ? reinterpret_cast<uint32_t*>(ctx->workspace + p.off_open_counts) : nullptr;
     attach_packed(ctx, w, &h);
     return h;
 }
@@ -311,6 +313,7 @@ static HashLaunch query_job(const spotlight_ctx* ctx, const void* q, const spotl
     h.operands = nullptr;
     h.open = nullptr;
     h.open_stride = 0;
+    h.open_counts = nullptr;
     attach_packed(ctx, w, &h);
     return h;
 }

@@ -324,6 +324,7 @@ HashArgs make_hash_args(const HashLaunch& h)
     a.operands = h.operands;
     a.open = h.open;
     a.open_stride = h.open_stride;
+    a.open_counts = h.open_counts;
     return a;
 }
 

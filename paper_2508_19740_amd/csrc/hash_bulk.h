@@ -269,17 +269,92 @@ __host__ __device__ inline Share share_of(unsigned id, unsigned parts, unsigned 
 
 // The rows that a first pass left open (hash_screen.h), compacted a span at a time, so that the kernels below hash
 // tiles of 32 of those alone: what does not fill a tile waits for the next span.  A segment of a head's rows is shared out
-// over `parts` workgroups, the same number of tiles of open rows each, as far as they divide: every one of them counts the
+// over several workgroups, the same number of tiles of open rows each, as far as they divide: every one of them counts the
 // segment's rows first, a few words a thread.  (A range of rows for each, two for every slot of the chip, had a
 // tile that was not full in every range and waited for the ranges with the most: 32 heads x 131072, 128 -> 256 -> 128, 9 % open,
 // 557 us; this way 527.)
 constexpr int kOpenSegment = 65536;   // rows: offsets in 16 bits
+constexpr int kCountStride = 32;      // words between the counts of two segments: a cache line each
 constexpr int kOpenSpan = 2048;       // rows: a word of the bitmap for each lane of a wavefront
 struct OpenRows {
     uint16_t row[kOpenSpan + kTile];  // in the segment
     int count, left, tiles;           // rows in the list, rows of the share not in the list yet, whole tiles of the list
     int sums[16];
+    int job[4];                       // what the workgroup has: OpenJob, its segment for the tile
 };
+
+// Tiles of open rows a workgroup takes, the fewest with which `slots` of them have all `total` of the `segments` (fewer than slots);
+// parts_with(q): workgroups it takes with q tiles each.
+template <typename F>
+__host__ __device__ inline int open_quota(int total, int segments, int slots, F parts_with)
+{
+    int lo = (total + slots - 1) / slots, hi = (total - 1) / (slots - segments) + 1;   // segments' remainders: at most one each
+    while (lo < hi) {
+        const int mid = (lo + hi) / 2;
+        if (parts_with(mid) <= slots) hi = mid; else lo = mid + 1;
+    }
+    return hi;
+}
+
+// What a workgroup of the second pass has: share `part` of `parts` of a segment's open rows (parts 0: nothing).
+struct OpenJob {
+    int xhead, part, parts;
+    int64_t first;                    // the segment's first tile
+};
+constexpr int kOpenBalanced = 256;    // segments that a wavefront shares out; with more, or few slots for each, none runs on for long
+
+// Of `n` segments, `per_head` of every head, the one that workgroup blockIdx.x of gridDim.x has, and its share there.
+__device__ __forceinline__ void share_segments(OpenRows& list, const uint32_t* counts, int n, int per_head, int lane)
+{
+    constexpr int PL = kOpenBalanced / 64;
+    uint32_t tiles[PL], total = 0;
+#pragma unroll
+    for (int k = 0; k < PL; ++k) {
+        const int s = k * 64 + lane;
+        tiles[k] = s < n ? (counts[s * kCountStride] + kTile - 1) / kTile : 0u;
+        total += tiles[k];
+    }
+    total = wave_sum(total);
+    if (lane < 4) list.job[lane] = 0;
+    if (total == 0) return;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    auto parts_with = [&](int q) {
+        uint32_t parts = 0;
+#pragma unroll
+        for (int k = 0; k < PL; ++k) parts += (tiles[k] + q - 1) / static_cast<uint32_t>(q);
+        return static_cast<int>(wave_sum(parts));
+    };
+    const uint32_t q = open_quota(static_cast<int>(total), n, static_cast<int>(gridDim.x), parts_with);
+    uint32_t id = blockIdx.x;
+#pragma unroll
+    for (int k = 0; k < PL; ++k) {
+        const uint32_t parts = (tiles[k] + q - 1) / q, upto = wave_inclusive_scan(parts);
+        const bool here = upto - parts <= id && id < upto;
+        if (here) {   // one lane at most
+            const int s = k * 64 + lane;
+            list.job[0] = s / per_head;
+            list.job[1] = static_cast<int>(id - (upto - parts));
+            list.job[2] = static_cast<int>(parts);
+            list.job[3] = s % per_head;
+        }
+        const uint32_t before = __builtin_amdgcn_readlane(static_cast<int>(upto), 63);
+        if (id < before) return;
+        id -= before;
+    }
+}
+
+// run > 0: that many workgroups for every segment.  run < 0: the workgroups are shared out over the segments of -run heads by the rows that
+// the first pass counted there, so that a head with more of them does not run on when the others are done (8 heads x 65536, 128 -> 256 -> 128,
+// one output of one head open for all keys: 1475 us with as many for each, 488 us so; equal heads 227 and 235).  Every thread of the workgroup calls it.
+__device__ __forceinline__ OpenJob open_job(OpenRows& list, const HashArgs& a, int run, int wave, int lane)
+{
+    if (run > 0) return {static_cast<int>(blockIdx.y), static_cast<int>(blockIdx.x % run), run, static_cast<int64_t>(blockIdx.x / run) * (kOpenSegment / kTile)};
+    const int per_head = static_cast<int>((a.n_rows + kOpenSegment - 1) / kOpenSegment);
+    if (wave == 0) share_segments(list, a.open_counts, -run * per_head, per_head, lane);
+    __syncthreads();
+    const auto of = [&](int i) { return __builtin_amdgcn_readfirstlane(list.job[i]); };
+    return {of(0), of(1), of(2), static_cast<int64_t>(of(3)) * (kOpenSegment / kTile)};
+}
 
 // The open rows of a segment that belong to a share, counted in the order of the rows.
 struct OpenShare { int from, to; };
@@ -412,7 +487,12 @@ __global__ __launch_bounds__(NW * 64, min_waves(NW, NBW)) void hash_bulk_kernel(
     const int c = lane & 31, half = lane >> 5;
     Share share{static_cast<int>(blockIdx.y), static_cast<int64_t>(blockIdx.x) * run, run};
     if (!OPEN && extra != 0) share = share_of(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x, gridDim.y, run, extra);
-    const int xhead = share.head;
+    OpenJob job{};   // OPEN: in place of the share; its list is `extra` bytes into LDS
+    if constexpr (OPEN) {
+        job = open_job(*reinterpret_cast<OpenRows*>(reinterpret_cast<char*>(lds) + extra), a, run, wave, lane);
+        if (job.parts == 0) return;
+    }
+    const int xhead = OPEN ? job.xhead : share.head;
     const int whead = whead_of(a, xhead);
     const WT* w1 = static_cast<const WT*>(a.w1) + static_cast<int64_t>(whead) * (a.hidden > 0 ? a.hidden : a.L) * kHeadDim;
     const WT* b1 = static_cast<const WT*>(a.b1) + static_cast<int64_t>(whead) * a.hidden;
@@ -421,13 +501,12 @@ __global__ __launch_bounds__(NW * 64, min_waves(NW, NBW)) void hash_bulk_kernel(
     const int nub = hidden_padded(a.hidden) / 32;
 
     const int64_t n_tiles = (a.n_rows + TK - 1) / TK;
-    // OPEN: `run` workgroups share a segment of the rows, their list is `extra` bytes into LDS
-    const int64_t first = OPEN ? static_cast<int64_t>(blockIdx.x / run) * (kOpenSegment / TK) : share.tile;
+    const int64_t first = OPEN ? job.first : share.tile;
     int64_t tile0 = first, tile1 = min(n_tiles, first + (OPEN ? kOpenSegment / TK : share.tiles));
     OpenWalk walk{*reinterpret_cast<OpenRows*>(reinterpret_cast<char*>(lds) + (OPEN ? extra : 0)), OPEN ? a.open + xhead * a.open_stride + first : nullptr,
                   static_cast<int>(min(a.n_rows - first * TK, static_cast<int64_t>(kOpenSegment))), 0, 0, 0, 0, 0};
     if constexpr (OPEN) {
-        if (!walk.begin(static_cast<int>(blockIdx.x % run), run, tid, NT) || !walk.advance(wave, lane)) return;
+        if (!walk.begin(job.part, job.parts, tid, NT) || !walk.advance(wave, lane)) return;
         tile0 = 0;
         tile1 = walk.tiles;
     }
@@ -805,7 +884,12 @@ __global__ __launch_bounds__(NW * 64, 2) void hash_cert_kernel(HashArgs a, float
     const int c = lane & 31, half = lane >> 5;
     Share share{static_cast<int>(blockIdx.y), static_cast<int64_t>(blockIdx.x) * run, run};
     if (!OPEN && extra != 0) share = share_of(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x, gridDim.y, run, extra);
-    const int xhead = share.head;
+    OpenJob job{};   // OPEN: in place of the share; its list is `extra` bytes into LDS
+    if constexpr (OPEN) {
+        job = open_job(*reinterpret_cast<OpenRows*>(reinterpret_cast<char*>(lds) + extra), a, run, wave, lane);
+        if (job.parts == 0) return;
+    }
+    const int xhead = OPEN ? job.xhead : share.head;
     const int whead = whead_of(a, xhead);
     const WT* w1 = static_cast<const WT*>(a.w1) + static_cast<int64_t>(whead) * a.hidden * kHeadDim;
     const WT* b1 = static_cast<const WT*>(a.b1) + static_cast<int64_t>(whead) * a.hidden;
@@ -814,13 +898,12 @@ __global__ __launch_bounds__(NW * 64, 2) void hash_cert_kernel(HashArgs a, float
     const int n_ks = a.hidden / 16;                                  // hidden is a multiple of 16
 
     const int64_t n_tiles = (a.n_rows + TK - 1) / TK;
-    // OPEN: `run` workgroups share a segment of the rows, their list is `extra` bytes into LDS
-    const int64_t first = OPEN ? static_cast<int64_t>(blockIdx.x / run) * (kOpenSegment / TK) : share.tile;
+    const int64_t first = OPEN ? job.first : share.tile;
     int64_t tile0 = first, tile1 = min(n_tiles, first + (OPEN ? kOpenSegment / TK : share.tiles));
     OpenWalk walk{*reinterpret_cast<OpenRows*>(reinterpret_cast<char*>(lds) + (OPEN ? extra : 0)), OPEN ? a.open + xhead * a.open_stride + first : nullptr,
                   static_cast<int>(min(a.n_rows - first * TK, static_cast<int64_t>(kOpenSegment))), 0, 0, 0, 0, 0};
     if constexpr (OPEN) {
-        if (!walk.begin(static_cast<int>(blockIdx.x % run), run, tid, NT) || !walk.advance(wave, lane)) return;
+        if (!walk.begin(job.part, job.parts, tid, NT) || !walk.advance(wave, lane)) return;
         tile0 = 0;
         tile1 = walk.tiles;
     }
@@ -1935,6 +2018,20 @@ inline int open_parts(int64_t segments, int slots)
     return best;
 }
 
+// The grid of a second pass on a chip that holds `slots` of its workgroups, and its kernels' `run` (open_job).  By what is open where every
+// segment can have two workgroups and more.
+struct OpenGrid {
+    dim3 grid;
+    int run;
+};
+inline OpenGrid open_grid(const HashArgs& a, int n_xheads, int slots)
+{
+    const int64_t segments = (a.n_rows + kOpenSegment - 1) / kOpenSegment, all = segments * n_xheads;
+    if (all <= kOpenBalanced && 2 * all <= slots) return {dim3(static_cast<unsigned>(slots)), -n_xheads};
+    const int parts = open_parts(all, slots);
+    return {dim3(static_cast<unsigned>(segments * parts), static_cast<unsigned>(n_xheads)), parts};
+}
+
 inline size_t align16(size_t bytes) { return (bytes + 15) / 16 * 16; }
 
 template <int NW, int NUB, int NBW>
@@ -1944,15 +2041,13 @@ int launch_open(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int stage, 
     const size_t open_at = align16(work), lds = open_at + sizeof(OpenRows);
     auto kern = hash_bulk_kernel<T, T, NW, NUB, NBW, false, true>;
     if (allow_dynamic_lds(ctx, reinterpret_cast<const void*>(kern), lds) != SPOTLIGHT_OK) return SPOTLIGHT_ERR_HIP;
-    const int64_t segments = (a.n_rows + kOpenSegment - 1) / kOpenSegment;
-    const int parts = open_parts(segments * n_xheads, ctx->n_cus * resident(ctx, 4 * min_waves(NW, NBW) / NW, lds));
+    const OpenGrid g = open_grid(a, n_xheads, ctx->n_cus * resident(ctx, 4 * min_waves(NW, NBW) / NW, lds));
     constexpr int LPR = 16;
     const int n_out = a.n_wheads * a.L;
     hipLaunchKernelGGL(row_norm_kernel<LPR>, dim3(static_cast<unsigned>((n_out * LPR + kThreads - 1) / kThreads)), dim3(kThreads), 0,
                        ctx->stream, static_cast<const T*>(a.w2), a.wnorm, n_out, a.hidden);   // microseconds: not timed
-    dim3 grid(static_cast<unsigned>(segments * parts), static_cast<unsigned>(n_xheads));
     StageTimer timer(ctx, stage);
-    timer.launch(kern, grid, dim3(NW * 64), lds, a, static_cast<float>(bulk_hash_eps(a.hidden, true)), parts, static_cast<int>(open_at));
+    timer.launch(kern, g.grid, dim3(NW * 64), lds, a, static_cast<float>(bulk_hash_eps(a.hidden, true)), g.run, static_cast<int>(open_at));
     return hip_rc(hipGetLastError());
 }
 
@@ -1963,11 +2058,9 @@ int launch_word_open(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int st
     const size_t open_at = align16(word_lds<T, NW, NUB>(a)), lds = open_at + sizeof(OpenRows);
     auto kern = hash_cert_kernel<T, NW, NUB, WREG, false, true>;
     if (allow_dynamic_lds(ctx, reinterpret_cast<const void*>(kern), lds) != SPOTLIGHT_OK) return SPOTLIGHT_ERR_HIP;
-    const int64_t segments = (a.n_rows + kOpenSegment - 1) / kOpenSegment;
-    const int parts = open_parts(segments * n_xheads, ctx->n_cus * resident(ctx, 2, lds));
-    dim3 grid(static_cast<unsigned>(segments * parts), static_cast<unsigned>(n_xheads));
+    const OpenGrid g = open_grid(a, n_xheads, ctx->n_cus * resident(ctx, 2, lds));
     StageTimer timer(ctx, stage);
-    timer.launch(kern, grid, dim3(NW * 64), lds, a, static_cast<float>(bulk_hash_eps(a.hidden, true)), parts, static_cast<int>(open_at));
+    timer.launch(kern, g.grid, dim3(NW * 64), lds, a, static_cast<float>(bulk_hash_eps(a.hidden, true)), g.run, static_cast<int>(open_at));
     return hip_rc(hipGetLastError());
 }
 

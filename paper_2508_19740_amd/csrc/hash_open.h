@@ -37,14 +37,17 @@ inline size_t open_lds(int hidden)
 
 // WM: code words the first pass laid the operands out for.
 template <int WM>
-__global__ __launch_bounds__(kOpenWaves * 64, 2) void hash_open_kernel(HashArgs a, const char* __restrict__ scales, const uint4* __restrict__ operands, int parts, int open_at)
+__global__ __launch_bounds__(kOpenWaves * 64, 2) void hash_open_kernel(HashArgs a, const char* __restrict__ scales, const uint4* __restrict__ operands, int run, int open_at)
 {
     constexpr int TK = bulk::kTile, NT = kOpenWaves * 64, NUB = 2, OPS = operands_of(WM);
     using bulk::XTile;
     extern __shared__ __align__(16) float lds[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = lane & 31, half = lane >> 5;
-    const int xhead = blockIdx.y;
+    bulk::OpenRows& list = *reinterpret_cast<bulk::OpenRows*>(reinterpret_cast<char*>(lds) + open_at);
+    const bulk::OpenJob job = bulk::open_job(list, a, run, wave, lane);
+    if (job.parts == 0) return;
+    const int xhead = job.xhead;
     const int whead = whead_of(a, xhead);
     const int nub = blocks_of(a.hidden), stride = open_stride(a.hidden), W = a.W;
     float* xs = lds;                                                        // the x tile and the next one
@@ -53,10 +56,10 @@ __global__ __launch_bounds__(kOpenWaves * 64, 2) void hash_open_kernel(HashArgs 
     float* bias = reinterpret_cast<float*>(hilo + nub * 2 * 2 * 64);        // [blocks][32]
     OpenScratch& m = *reinterpret_cast<OpenScratch*>(bias + nub * 32);
 
-    const int64_t first = static_cast<int64_t>(blockIdx.x / parts) * (bulk::kOpenSegment / TK);
-    bulk::OpenWalk walk{*reinterpret_cast<bulk::OpenRows*>(reinterpret_cast<char*>(lds) + open_at), a.open + xhead * a.open_stride + first,
+    const int64_t first = job.first;
+    bulk::OpenWalk walk{list, a.open + xhead * a.open_stride + first,
                         static_cast<int>(min(a.n_rows - first * TK, static_cast<int64_t>(bulk::kOpenSegment))), 0, 0, 0, 0, 0};
-    if (!walk.begin(static_cast<int>(blockIdx.x % parts), parts, tid, NT) || !walk.advance(wave, lane)) return;
+    if (!walk.begin(job.part, job.parts, tid, NT) || !walk.advance(wave, lane)) return;
 
     const bf16_raw* b1 = static_cast<const bf16_raw*>(a.b1) + static_cast<int64_t>(whead) * a.hidden;
     const bf16_raw* w2 = static_cast<const bf16_raw*>(a.w2) + static_cast<int64_t>(whead) * a.L * a.hidden;
@@ -274,11 +277,9 @@ inline int launch_open(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int 
     const size_t open_at = open_lds(a.hidden), lds = open_at + sizeof(bulk::OpenRows);
     auto kern = hash_open_kernel<8>;
     if (allow_dynamic_lds(ctx, reinterpret_cast<const void*>(kern), lds) != SPOTLIGHT_OK) return SPOTLIGHT_ERR_HIP;
-    const int64_t segments = (a.n_rows + bulk::kOpenSegment - 1) / bulk::kOpenSegment;
-    const int parts = bulk::open_parts(segments * n_xheads, ctx->n_cus);
-    dim3 grid(static_cast<unsigned>(segments * parts), static_cast<unsigned>(n_xheads));
+    const bulk::OpenGrid g = bulk::open_grid(a, n_xheads, ctx->n_cus);
     StageTimer timer(ctx, stage);
-    timer.launch(kern, grid, dim3(kOpenWaves * 64), lds, a, static_cast<const char*>(a.scales), static_cast<const uint4*>(a.operands), parts, static_cast<int>(open_at));
+    timer.launch(kern, g.grid, dim3(kOpenWaves * 64), lds, a, static_cast<const char*>(a.scales), static_cast<const uint4*>(a.operands), g.run, static_cast<int>(open_at));
     return hip_rc(hipGetLastError());
 }
 

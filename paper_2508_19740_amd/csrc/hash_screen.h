@@ -36,6 +36,7 @@ using bulk::other_half;
 
 constexpr int kWaves = 8;             // wavefronts of a workgroup
 constexpr int kWords = 8;             // code words at most
+constexpr int kNear = 2;              // segments of open rows that a workgroup counts in LDS
 constexpr double kU = 0x1p-24;
 
 // How often the product of index j (0 ..) of a row's `n` counts in the bounds above.
@@ -93,17 +94,18 @@ __device__ __forceinline__ uint4 operand(const bf16_raw* w1, const bf16_raw* w2,
 }
 
 // What the first pass needs of the weights.  grid (weight heads, 1 + words + ...): block 0 the norms of the first layer, block
-// 1 + w those of code word w; the others lay out the operands for kernels that read them again for every eight tiles (from
+// 1 + w those of code word w (all clear the counts of open rows); the others lay out the operands for kernels that read them again for every eight tiles (from
 // the arrays as stored, a row per lane, each 16-byte load touches 64 cache lines).
 // AHEAD: rows of the first layer on their way (256 hidden units: 9.2 us one at a time, 5.4 us eight).
 template <int AHEAD>
 __global__ __launch_bounds__(kThreads) void scales_kernel(const bf16_raw* __restrict__ w1, const bf16_raw* __restrict__ b1,
                                                           const bf16_raw* __restrict__ w2, char* __restrict__ out,
-                                                          uint4* __restrict__ operands, int hidden, int L)
+                                                          uint4* __restrict__ operands, uint32_t* __restrict__ counts, int n_counts, int hidden, int L)
 {
     __shared__ float sums[kThreads / 64][3];
     __shared__ uint32_t bits[kThreads / 64];
     const int W = L / 32, whead = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    for (int i = (blockIdx.y * gridDim.x + blockIdx.x) * kThreads + tid; i < n_counts; i += gridDim.x * gridDim.y * kThreads) counts[i * bulk::kCountStride] = 0;
     if (static_cast<int>(blockIdx.y) > W) {
         const int words = words_for(W), per = operands_of(words), n = blocks_of(hidden) * per;
         w1 += static_cast<int64_t>(whead) * hidden * kHeadDim;
@@ -271,6 +273,18 @@ __global__ __launch_bounds__(kWaves * 64, 2) void hash_screen_kernel(HashArgs a,
 
     const bf16_raw* xbase = static_cast<const bf16_raw*>(a.x) + xhead * a.x_head_stride + a.x_row0 * kHeadDim;
     const int64_t n_tiles = (a.n_rows + TK - 1) / TK, tile0 = static_cast<int64_t>(blockIdx.x) * rounds * kWaves;
+    const int64_t segments = (a.n_rows + bulk::kOpenSegment - 1) / bulk::kOpenSegment;
+    // open rows: each wavefront counts its own, the workgroup adds those of the first segments up in LDS and then to the segments' counts
+    // (an addition in memory for every tile: 8 heads x 65536, 128 -> 256 -> 128, both passes, 334 us; so 235)
+    uint32_t* opened = reinterpret_cast<uint32_t*>(ops + (RESIDENT ? nub : 2) * OPS * 64);
+    const int seg0 = static_cast<int>(tile0 / (bulk::kOpenSegment / TK));
+    int seg = seg0, n_opened = 0;
+    if (tid < kNear) opened[tid] = 0;
+    auto count_opened = [&]() {
+        if (lane != 0 || n_opened == 0) return;
+        if (seg - seg0 < kNear) atomicAdd(opened + (seg - seg0), static_cast<uint32_t>(n_opened));
+        else atomicAdd(a.open_counts + (xhead * segments + seg) * bulk::kCountStride, static_cast<uint32_t>(n_opened));
+    };
     uint4 x[8];
     auto fetch_x = [&](int64_t tile) {
         const int64_t row = min(tile * TK + c, a.n_rows - 1);   // rows past the end: a stand-in, never stored
@@ -440,6 +454,13 @@ __global__ __launch_bounds__(kWaves * 64, 2) void hash_screen_kernel(HashArgs a,
                 if (w < W) to[w] = code[w];
         }
         if (lane == 0 && tile < n_tiles) a.open[xhead * a.open_stride + tile] = marked;
+        const int s = static_cast<int>(tile / (bulk::kOpenSegment / TK));
+        if (s != seg) {
+            count_opened();
+            seg = s;
+            n_opened = 0;
+        }
+        n_opened += __builtin_popcount(marked);
     };
 
     // operands of a step: layer 1 of the block behind `ub`, layer 2 of `ub`
@@ -484,12 +505,15 @@ __global__ __launch_bounds__(kWaves * 64, 2) void hash_screen_kernel(HashArgs a,
         ca = ca_next;
         next_step();
     }
+    count_opened();
+    __syncthreads();
+    if (tid < kNear && opened[tid] != 0) atomicAdd(a.open_counts + (xhead * segments + seg0 + tid) * bulk::kCountStride, opened[tid]);
 }
 
 inline size_t lds_bytes(int hidden, int words, bool resident)
 {
     const size_t nub = blocks_of(hidden);
-    return nub * 32 * sizeof(float) + (resident ? nub : 2) * operands_of(words) * 64 * sizeof(uint4);
+    return nub * 32 * sizeof(float) + (resident ? nub : 2) * operands_of(words) * 64 * sizeof(uint4) + kNear * sizeof(uint32_t);
 }
 
 // Whether a workgroup's LDS (160 KB) holds the operands of all blocks.
@@ -539,7 +563,7 @@ inline int launch(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int stage
     const int n_operands = resident(a.hidden, a.W) ? 0 : blocks_of(a.hidden) * operands_of(words_for(a.W));
     hipLaunchKernelGGL(scales_kernel<8>, dim3(static_cast<unsigned>(a.n_wheads), static_cast<unsigned>(1 + a.W + (n_operands + kPerBlock - 1) / kPerBlock)), dim3(kThreads), 0,
                        ctx->stream, static_cast<const bf16_raw*>(a.w1), static_cast<const bf16_raw*>(a.b1), static_cast<const bf16_raw*>(a.w2), scales,
-                       static_cast<uint4*>(a.operands), a.hidden, a.L);
+                       static_cast<uint4*>(a.operands), a.open_counts, static_cast<int>((a.n_rows + bulk::kOpenSegment - 1) / bulk::kOpenSegment * n_xheads), a.hidden, a.L);
     if (a.W <= 2) return launch_words<2>(ctx, a, scales, n_xheads, stage);
     if (a.W <= 4) return launch_words<4>(ctx, a, scales, n_xheads, stage);
     return launch_words<8>(ctx, a, scales, n_xheads, stage);

@@ -96,6 +96,7 @@ struct HashArgs {
     void* operands;
     uint32_t* open;
     int64_t open_stride;
+    uint32_t* open_counts;
 };
 
 __device__ __forceinline__ int whead_of(const HashArgs& a, int xhead) { return (xhead % a.heads_per_batch) / a.group; }

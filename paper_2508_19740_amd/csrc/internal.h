@@ -42,6 +42,7 @@ struct Plan {
     size_t off_scales;     // [Hkv][1 + W][16 bytes] norms of the weights for the first pass of bulk hashing (hash_screen.h)
     size_t off_operands;   // [Hkv][screen_operand_bytes] the weights in that pass's read order
     size_t off_open;       // [B*Hkv][ceil(Nmax / 32)] rows that pass left open, a bit each
+    size_t off_open_counts; // [B*Hkv][ceil(Nmax / 65536)][128 bytes] how many of each segment of a head's rows
     size_t off_audit;      // AuditRec of the bulk hash (SPOTLIGHT_OPT_BULK_HASH_AUDIT)
     size_t total_bytes;
 };
@@ -167,6 +168,7 @@ struct HashLaunch {
     void* operands;           // the weights in its read order,
     uint32_t* open;           // and a bit for each row it leaves open, open_stride words per x-head
     int64_t open_stride;
+    uint32_t* open_counts;    // the number of them in every segment of rows
 };
 int launch_hash(spotlight_ctx* ctx, const HashLaunch& a, int stage);
 // Elements per weight head of the packed copies the single-vector hash kernel can read (0: none).

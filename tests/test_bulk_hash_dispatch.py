@@ -90,6 +90,30 @@ int main()
 }
 """
 
+QUOTA = r"""
+#include <stdio.h>
+#include <stdlib.h>
+#include <vector>
+#include "hash_bulk.h"
+using namespace spotlight;
+int main()
+{
+    for (int slots : {256, 512, 768})
+        for (int n : {1, 2, 3, 8, 56, 64, 100, 128, slots / 2})
+            for (int kind = 0; kind < 6; ++kind) {
+                std::vector<int> tiles(n);
+                for (int s = 0; s < n; ++s) tiles[s] = kind == 0 ? 2048 : kind == 1 ? rand() % 2049 : kind == 2 ? (s == n / 2 ? 2048 : 1) : kind == 3 ? (s == 0) : kind == 4 ? 190 + rand() % 9 : (s % 3 ? 0 : 577);
+                int total = 0;
+                for (int t : tiles) total += t;
+                if (total == 0) continue;
+                auto parts_with = [&](int q) { int p = 0; for (int t : tiles) p += (t + q - 1) / q; return p; };
+                const int q = bulk::open_quota(total, n, slots, parts_with);
+                if (q < 1 || parts_with(q) > slots || (q > 1 && parts_with(q - 1) <= slots)) { printf("%d segments, %d slots, kind %d: %d\n", n, slots, kind, q); return 1; }
+            }
+    return 0;
+}
+"""
+
 WALK = r"""
 #include <stdio.h>
 #include <stdlib.h>
@@ -216,6 +240,12 @@ def test_runs_are_even(tmp_path):
 
 def test_every_tile_belongs_to_one_workgroup(tmp_path):
     run = subprocess.run([_program(tmp_path, SHARES, "shares")], capture_output=True, text=True)
+    assert run.returncode == 0, run.stdout
+
+
+def test_open_rows_are_shared_out_over_the_heads(tmp_path):
+    """As few tiles for a workgroup as the chip's workgroups allow, whichever heads the open rows are in."""
+    run = subprocess.run([_program(tmp_path, QUOTA, "quota")], capture_output=True, text=True)
     assert run.returncode == 0, run.stdout
 
 

@@ -124,6 +124,20 @@ def test_rows_that_are_all_open(share, bits, hidden):
     _check(K.bfloat16(), [t.bfloat16().contiguous() for t in ws], 0, rows, bits, hidden)
 
 
+@pytest.mark.parametrize("bits,hidden", [(64, 64), (256, 64), (256, 512)])
+@pytest.mark.parametrize("B,H,rows", [(1, 9, 66000), (2, 33, 2100), (1, 200, 700), (1, 1, 70000)])
+def test_heads_with_more_open_rows_than_others(B, H, rows, bits, hidden):
+    """Every third head has an output that cancels for all keys, another third of them rows that nothing leaves open: the workgroups are
+    shared out over the heads by what is open (one workgroup a head where there are many)."""
+    g = torch.Generator().manual_seed(H)
+    ws, n = [t.float() for t in _weights(g, H, bits, hidden)], hidden // 2
+    ws[0][::3, n:], ws[1][::3, n:], ws[2][::3, 5, n:] = ws[0][::3, :n], ws[1][::3, :n], -ws[2][::3, 5, :n]
+    K = torch.randn(B, H, rows, 128, generator=g)
+    ws[1][1::3] = 0
+    K[:, 1::3] = 0
+    _check(K.bfloat16(), [t.bfloat16().contiguous() for t in ws], 0, rows, bits, hidden, n_oracle=8)
+
+
 @pytest.mark.parametrize("n_open", [1, 2, 3, 15, 16, 17])
 def test_lists_of_every_length(n_open):
     """The same of a few output rows, 288 to 512 hidden units and long codes: 32 to 544 outputs of a tile on its list of 512, run by one
@@ -217,7 +231,7 @@ extern "C" int run_activation(const void* a, void* chain, void* fast, void* hi, 
 extern "C" int run_scales(const void* w1, const void* b1, const void* w2, void* out, int heads, int hidden, int L)
 {
     using hashdev::bf16_raw;
-    screen::scales_kernel<8><<<dim3(heads, 1 + L / 32), kThreads>>>((const bf16_raw*)w1, (const bf16_raw*)b1, (const bf16_raw*)w2, (char*)out, nullptr, hidden, L);
+    screen::scales_kernel<8><<<dim3(heads, 1 + L / 32), kThreads>>>((const bf16_raw*)w1, (const bf16_raw*)b1, (const bf16_raw*)w2, (char*)out, nullptr, nullptr, 0, hidden, L);
     return hipDeviceSynchronize();
 }
 """
