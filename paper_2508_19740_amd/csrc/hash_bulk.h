@@ -296,6 +296,9 @@ __host__ __device__ inline int open_quota(int total, int segments, int slots, F 
     return hi;
 }
 
+// Workgroups of a segment, where `all` would do with q tiles each: the others of the chip's `slots` are spread over the segments.
+__host__ __device__ inline uint32_t open_workgroups(uint32_t tiles, uint32_t q, uint32_t all, uint32_t slots) { return (tiles + q - 1) / q * slots / all; }
+
 // What a workgroup of the second pass has: share `part` of `parts` of a segment's open rows (parts 0: nothing).
 struct OpenJob {
     int xhead, part, parts;
@@ -321,14 +324,16 @@ __device__ __forceinline__ void share_segments(OpenRows& list, const uint32_t* c
     auto parts_with = [&](int q) {
         uint32_t parts = 0;
 #pragma unroll
-        for (int k = 0; k < PL; ++k) parts += (tiles[k] + q - 1) / static_cast<uint32_t>(q);
+        for (int k = 0; k < PL; ++k)
+            if (k * 64 < n) parts += (tiles[k] + q - 1) / static_cast<uint32_t>(q);
         return static_cast<int>(wave_sum(parts));
     };
     const uint32_t q = open_quota(static_cast<int>(total), n, static_cast<int>(gridDim.x), parts_with);
+    const uint32_t all = static_cast<uint32_t>(parts_with(static_cast<int>(q)));
     uint32_t id = blockIdx.x;
 #pragma unroll
     for (int k = 0; k < PL; ++k) {
-        const uint32_t parts = (tiles[k] + q - 1) / q, upto = wave_inclusive_scan(parts);
+        const uint32_t parts = open_workgroups(tiles[k], q, all, gridDim.x), upto = wave_inclusive_scan(parts);
         const bool here = upto - parts <= id && id < upto;
         if (here) {   // one lane at most
             const int s = k * 64 + lane;

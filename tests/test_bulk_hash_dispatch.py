@@ -109,6 +109,13 @@ int main()
                 auto parts_with = [&](int q) { int p = 0; for (int t : tiles) p += (t + q - 1) / q; return p; };
                 const int q = bulk::open_quota(total, n, slots, parts_with);
                 if (q < 1 || parts_with(q) > slots || (q > 1 && parts_with(q - 1) <= slots)) { printf("%d segments, %d slots, kind %d: %d\n", n, slots, kind, q); return 1; }
+                unsigned used = 0;
+                for (int t : tiles) {
+                    const unsigned w = bulk::open_workgroups(t, q, parts_with(q), slots);
+                    used += w;
+                    if ((t == 0) != (w == 0) || static_cast<unsigned>(t) > w * q) { printf("%d segments, %d slots, kind %d: %d tiles, %u\n", n, slots, kind, t, w); return 1; }
+                }
+                if (used > static_cast<unsigned>(slots)) { printf("%d segments, %d slots, kind %d: %u workgroups\n", n, slots, kind, used); return 1; }
             }
     return 0;
 }
