@@ -60,7 +60,7 @@ int make_plan(const spotlight_config* c, Plan* p)
     const size_t welem = p->w_dtype == SPOTLIGHT_BF16 ? 2 : 4;
     p->off_pack_w1 = off;   off = align_up(off + static_cast<size_t>(p->Hkv) * p->pack_w1_elems * welem, 256);
     p->off_pack_out = off;  off = align_up(off + static_cast<size_t>(p->Hkv) * p->pack_out_elems * welem, 256);
-    p->off_scales = off;    off = align_up(off + static_cast<size_t>(p->Hkv) * (1 + p->W) * 16, 256);
+    p->off_scales = off;    off = align_up(off + screen_scale_bytes(p->Hkv, p->W), 256);
     p->off_operands = off;  off = align_up(off + (bf16 ? static_cast<size_t>(p->Hkv) * screen_operand_bytes(p->hidden, p->W) : 0), 256);
     p->off_open = off;      off = align_up(off + static_cast<size_t>(p->B) * p->Hkv * ((p->Nmax + 31) / 32) * 4, 256);
     p->off_open_counts = off; off = align_up(off + static_cast<size_t>(p->B) * p->Hkv * ((p->Nmax + 65535) / 65536) * 128, 256);

@@ -68,6 +68,8 @@ __global__ __launch_bounds__(kOpenWaves * 64, 2) void hash_open_kernel(HashArgs 
     const int word = min(wave, W - 1);                               // wavefronts without one have layer 1 only
     const float scale = ws[word].s2;
     const uint32_t zeros = ws[word].zeros;
+    const bool uneven = ws[word].uneven != 0;
+    const RowScale* rows_of_word = row_scales(scales, a.n_wheads, whead, W) + word * 32 + 16 * half;
     const int n_mine = max(0, min(NUB, nub - wave * NUB));           // blocks of this wavefront
 
     bulk::UnitBlock<bf16_raw> ublk[NUB];                             // layer 1: the operands of the 64 steps
@@ -228,6 +230,15 @@ __global__ __launch_bounds__(kOpenWaves * 64, 2) void hash_open_kernel(HashArgs 
                     which |= __builtin_fabsf(y[v]) >= bound ? 0u : 1u << v;
                 }
                 if (bound == INFINITY) which = 0xffffu;
+                if (uneven) {   // each output and the bound of its own row
+                    which = 0;
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        const float b = 1.002f * (rows_of_word[v].s2 * hn);
+                        which |= __builtin_fabsf(y[v]) >= b && b < 1e25f ? 0u : 1u << v;
+                        if (v % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
                 if (tile * TK + c >= walk.count) which = 0;   // a stand-in
                 uint32_t code = ~sign & 0xffffu;
                 code = (code << 16) | other_half(code);

@@ -63,11 +63,25 @@ struct WordScale {
     float s2;         // max_j u ||s W2_j|| over the outputs of the word
     float w2;         // max_j ||W2_j||
     uint32_t zeros;   // bit c: output c * W + word has a row of zeros (y = 0, bit 0)
-    uint32_t pad;
+    uint32_t uneven;  // its rows' bounds differ: kUneven
+};
+struct RowScale {     // the same of each output, in the order of the word's bits
+    float s2, w2;
 };
 static_assert(sizeof(LayerScale) == 16 && sizeof(WordScale) == 16, "one record is 16 bytes");
 
 constexpr float kSlack = 1e-12f;
+// Rows of a word are uneven where its largest bound is in the mean more than this many times a row's own.  Equal rows stay with one
+// comparison (a threshold for every output: 64 more vector instructions a tile, 9.4 -> 8.7 % open, no gain).  One row of 32 three and ten times the others, 8 heads x
+// 65536, 128 -> 256 -> 128: 284 and 463 us with one bound, 238 with one for each.
+constexpr float kUneven = 1.5f;
+
+// Scales of all weight heads: [heads][1 + W] records, [heads][W][32] RowScale.
+__host__ __device__ inline size_t scale_bytes(int heads, int W) { return static_cast<size_t>(heads) * ((1 + W) * 16 + W * 32 * sizeof(RowScale)); }
+__device__ __forceinline__ const RowScale* row_scales(const char* scales, int heads, int whead, int W)
+{
+    return reinterpret_cast<const RowScale*>(scales + static_cast<int64_t>(heads) * (1 + W) * 16) + static_cast<int64_t>(whead) * W * 32;
+}
 
 // Blocks of 32 hidden units; at least two, so that the kernel below always has a next one.
 __host__ __device__ inline int blocks_of(int hidden) { return hidden > 32 ? (hidden + 31) / 32 : 2; }
@@ -171,8 +185,14 @@ __global__ __launch_bounds__(kThreads) void scales_kernel(const bf16_raw* __rest
             b += __shfl_xor(b, off);
             any |= __shfl_xor(any, off);
         }
+        const float own = 1.001f * __builtin_sqrtf(b) + kSlack;
+        if (tid % 8 == 0)
+            const_cast<RowScale*>(row_scales(out, gridDim.x, whead, W))[word * 32 + r] = {static_cast<float>(1.001 * kU) * (__builtin_sqrtf(a) + static_cast<float>(hidden) * kSlack), own};
+        c = any ? 1.0f / own : 0.0f;
+#pragma unroll
+        for (int off = 8; off < 64; off <<= 1) c += __shfl_xor(c, off);
     }
-    // over the workgroup: sums of a and c and the largest b (layer 1), the largest a and b (a word); a NaN stays
+    // over the workgroup: sums of a and c and the largest b (layer 1), the largest a and b and the sum of c (a word); a NaN stays
 #pragma unroll
     for (int off = 8; off < 64; off <<= 1) {
         const float a2 = __shfl_xor(a, off), b2 = __shfl_xor(b, off);
@@ -213,7 +233,7 @@ __global__ __launch_bounds__(kThreads) void scales_kernel(const bf16_raw* __rest
         s.s2 = static_cast<float>(1.001 * kU) * (__builtin_sqrtf(a) + static_cast<float>(hidden) * kSlack);
         s.w2 = 1.001f * __builtin_sqrtf(b) + kSlack;
         s.zeros = any;
-        s.pad = 0;
+        s.uneven = !(s.w2 * c <= kUneven * static_cast<float>(32 - __builtin_popcount(any)));   // also where one is no number
         reinterpret_cast<WordScale*>(rec)[blockIdx.y] = s;
     }
 }
@@ -274,9 +294,11 @@ __global__ __launch_bounds__(kWaves * 64, 2) void hash_screen_kernel(HashArgs a,
     const bf16_raw* xbase = static_cast<const bf16_raw*>(a.x) + xhead * a.x_head_stride + a.x_row0 * kHeadDim;
     const int64_t n_tiles = (a.n_rows + TK - 1) / TK, tile0 = static_cast<int64_t>(blockIdx.x) * rounds * kWaves;
     const int64_t segments = (a.n_rows + bulk::kOpenSegment - 1) / bulk::kOpenSegment;
+    RowScale* rows = reinterpret_cast<RowScale*>(ops + (RESIDENT ? nub : 2) * OPS * 64);   // [W][32]
+    for (int i = tid; i < W * 32; i += NT) rows[i] = row_scales(scales, a.n_wheads, whead, W)[i];
     // open rows: each wavefront counts its own, the workgroup adds those of the first segments up in LDS and then to the segments' counts
     // (an addition in memory for every tile: 8 heads x 65536, 128 -> 256 -> 128, both passes, 334 us; so 235)
-    uint32_t* opened = reinterpret_cast<uint32_t*>(ops + (RESIDENT ? nub : 2) * OPS * 64);
+    uint32_t* opened = reinterpret_cast<uint32_t*>(rows + W * 32);
     const int seg0 = static_cast<int>(tile0 / (bulk::kOpenSegment / TK));
     int seg = seg0, n_opened = 0;
     if (tid < kNear) opened[tid] = 0;
@@ -434,7 +456,20 @@ __global__ __launch_bounds__(kWaves * 64, 2) void hash_screen_kernel(HashArgs a,
                 nearest = fminf(nearest, __builtin_fabsf(y[w][v]));
             }
             const float bound = 1.002f * (ws[w].s2 * (hn + dh) + ws[w].w2 * dh);
-            sure = sure && nearest >= bound && bound < 1e25f;
+            bool far = nearest >= bound && bound < 1e25f;
+            if (ws[w].uneven) {   // each output and the bound of its own row
+                if (__ballot(!far)) {
+                    const RowScale* rs = rows + w * 32 + 16 * half;
+                    far = true;
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        const float b = 1.002f * (rs[v].s2 * (hn + dh) + rs[v].w2 * dh);
+                        far = far && __builtin_fabsf(y[w][v]) >= b && b < 1e25f;
+                        if (v % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // (registers)
+                    }
+                }
+            }
+            sure = sure && far;
             code[w] = ~s & 0xffffu;   // a settled output is no zero
         }
         uint32_t open = sure || nothing ? 0u : 1u;
@@ -510,19 +545,19 @@ __global__ __launch_bounds__(kWaves * 64, 2) void hash_screen_kernel(HashArgs a,
     if (tid < kNear && opened[tid] != 0) atomicAdd(a.open_counts + (xhead * segments + seg0 + tid) * bulk::kCountStride, opened[tid]);
 }
 
-inline size_t lds_bytes(int hidden, int words, bool resident)
+inline size_t lds_bytes(int hidden, int W, bool resident)
 {
-    const size_t nub = blocks_of(hidden);
-    return nub * 32 * sizeof(float) + (resident ? nub : 2) * operands_of(words) * 64 * sizeof(uint4) + kNear * sizeof(uint32_t);
+    const size_t nub = blocks_of(hidden), words = words_for(W);
+    return nub * 32 * sizeof(float) + (resident ? nub : 2) * operands_of(static_cast<int>(words)) * 64 * sizeof(uint4) + W * 32 * sizeof(RowScale) + kNear * sizeof(uint32_t);
 }
 
 // Whether a workgroup's LDS (160 KB) holds the operands of all blocks.
-inline bool resident(int hidden, int W) { return lds_bytes(hidden, words_for(W), true) <= 160 * 1024; }
+inline bool resident(int hidden, int W) { return lds_bytes(hidden, W, true) <= 160 * 1024; }
 
 template <int WM, bool RESIDENT>
 int launch_kernel(spotlight_ctx* ctx, const HashArgs& a, const char* scales, int n_xheads, int stage)
 {
-    const size_t lds = lds_bytes(a.hidden, WM, RESIDENT);
+    const size_t lds = lds_bytes(a.hidden, a.W, RESIDENT);
     auto kern = hash_screen_kernel<WM, RESIDENT>;
     if (allow_dynamic_lds(ctx, reinterpret_cast<const void*>(kern), lds) != SPOTLIGHT_OK) return SPOTLIGHT_ERR_HIP;
     const int64_t all_rounds = (a.n_rows + bulk::kTile * kWaves - 1) / (bulk::kTile * kWaves);

@@ -10,6 +10,8 @@ size_t screen_operand_bytes(int hidden, int W)
     return screen::serves(hidden, W) && !screen::resident(hidden, W) ? static_cast<size_t>(screen::blocks_of(hidden)) * screen::operands_of(screen::words_for(W)) * 64 * sizeof(uint4) : 0;
 }
 
+size_t screen_scale_bytes(int heads, int W) { return screen::scale_bytes(heads, W); }
+
 bool screened_hash_applies(const spotlight_ctx* ctx, const HashArgs& a, int n_xheads) { return screen::applies(ctx, a, n_xheads); }
 
 int run_screened_hash(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int stage)

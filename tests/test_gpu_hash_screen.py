@@ -124,6 +124,22 @@ def test_rows_that_are_all_open(share, bits, hidden):
     _check(K.bfloat16(), [t.bfloat16().contiguous() for t in ws], 0, rows, bits, hidden)
 
 
+@pytest.mark.parametrize("bits,hidden", [(64, 64), (96, 256), (256, 128), (160, 288), (256, 512), (256, 1008)])
+def test_output_rows_of_unequal_norm(bits, hidden):
+    """Bounds of each output's own where a word's rows differ: by any factor, by 1e4 once a word, by rows of zeros and of next to
+    nothing; equal rows in one head, one word uneven in another."""
+    g = torch.Generator().manual_seed(bits + hidden)
+    H, rows, W = 8, 16400, bits // 32
+    ws = [t.float() for t in _weights(g, H, bits, hidden)]
+    ws[2][1] *= torch.exp(1.5 * torch.randn(bits, 1, generator=g))
+    ws[2][2, 4 * W:5 * W] *= 1e4
+    ws[2][3, 7 * W:30 * W] = 0
+    ws[2][4, ::3] = torch.ldexp(ws[2][4, ::3], torch.tensor(-60))
+    ws[2][5, W + W // 2] *= 30
+    ws[2][6, 2 * W, 5], ws[2][6, 3 * W, 6] = float("inf"), float("nan")
+    _check(torch.randn(1, H, rows, 128, generator=g).bfloat16(), [t.bfloat16().contiguous() for t in ws], 0, rows, bits, hidden)
+
+
 @pytest.mark.parametrize("bits,hidden", [(64, 64), (256, 64), (256, 512)])
 @pytest.mark.parametrize("B,H,rows", [(1, 9, 66000), (2, 33, 2100), (1, 200, 700), (1, 1, 70000)])
 def test_heads_with_more_open_rows_than_others(B, H, rows, bits, hidden):
@@ -301,10 +317,11 @@ def test_scales(probe, heads, bits, hidden):
     ws = _weights(g, heads, bits, hidden)
     ws[2][:, 3] = 0
     ws[1][0] = 0
-    out = torch.zeros(heads, 1 + bits // 32, 4, dtype=torch.float32, device=DEV)
+    W = bits // 32
+    flat = torch.zeros(heads * ((1 + W) * 4 + W * 64), dtype=torch.float32, device=DEV)   # records, then two norms of every output
     wd = [t.to(DEV) for t in ws]
-    assert probe.run_scales(*(_p(t) for t in wd), _p(out), heads, hidden, bits) == 0
-    out = out.cpu()
+    assert probe.run_scales(*(_p(t) for t in wd), _p(flat), heads, hidden, bits) == 0
+    out, each = flat[:heads * (1 + W) * 4].view(heads, 1 + W, 4).cpu(), flat[heads * (1 + W) * 4:].view(heads, W, 32, 2).double().cpu()
     w1, b1, w2 = (t.double() for t in ws)
     k = torch.arange(128) % 32     # partial sums charged to a product, and its part in the groups' (recounted here)
     t1 = torch.zeros(128, dtype=torch.float64)
@@ -333,3 +350,25 @@ def test_scales(probe, heads, bits, hidden):
     for word in range(bits // 32):
         mask = sum(1 << c for c in range(32) if rows[word, c] == 3)
         assert (zeros[:, word] == mask).all()
+    for e, want in ((0, U * (s2 * w2).square().sum(2).sqrt()[:, rows]), (1, w2.square().sum(2).sqrt()[:, rows])):
+        assert (each[..., e] >= want).all() and (each[..., e] <= (1.003 + 2.2 * (e == 0) / hidden) * want + 1e-11).all(), e
+    assert (out[:, 1:, 3].view(torch.int32) == 0).all()           # rows of much the same norm
+
+
+def test_rows_of_unequal_norm_are_marked(probe):
+    """Uneven: the largest norm more than 1.5 times a row's in the mean, rows of zeros left out."""
+    heads, bits, hidden = 6, 64, 48
+    g = torch.Generator().manual_seed(4)
+    ws = _weights(g, heads, bits, hidden)
+    w2 = torch.ones(heads, bits, hidden)
+    w2[1, 6] = 1.45                                               # output 6: word 0
+    w2[2, 7] = 1.6                                                # output 7: word 1
+    w2[3, 2:] = 0
+    w2[4, 8] = 1e-20
+    w2[5, 9, 0] = float("nan")
+    ws[2] = w2.bfloat16()
+    flat = torch.zeros(heads * (3 * 4 + 2 * 64), dtype=torch.float32, device=DEV)
+    wd = [t.to(DEV) for t in ws]
+    assert probe.run_scales(*(_p(t) for t in wd), _p(flat), heads, hidden, bits) == 0
+    uneven = flat[:heads * 12].view(heads, 3, 4)[:, 1:, 3].contiguous().view(torch.int32)
+    assert uneven.tolist() == [[0, 0], [0, 0], [0, 1], [0, 0], [1, 0], [0, 1]]
