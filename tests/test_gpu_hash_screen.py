@@ -297,6 +297,66 @@ def test_rounding_of_the_matrix_instruction(probe, spread, low_bits):
         assert (err <= bound).all(), (err / bound).max()
 
 
+def _product(probe, A, B, C):
+    ad, bd, cd = A.bfloat16().to(DEV), B.bfloat16().to(DEV), C.float().to(DEV)
+    D = torch.empty_like(cd)
+    assert probe.run_product(_p(ad), _p(bd), _p(cd), _p(D), len(A)) == 0
+    return D.cpu().double()
+
+
+@pytest.mark.parametrize("apart", [-20, -8, -1, 0, 1, 8, 20])
+@pytest.mark.parametrize("spread", [0, 3, 8])
+def test_rounding_with_both_groups_filled(probe, spread, apart):
+    """The second group adds to the first's rounded sum: r1 of c + products 0 .. 7, r of r1 + products 8 .. 15, each within
+    u (10 max|p| + 2 |addend| + |result|).  Magnitudes of the groups apart by 2^apart; c takes the first group's sum away, or both; the
+    second group takes the first's away, as it is and but for one product."""
+    g = np.random.default_rng(spread + 100 * (apart + 50))
+    n = 640
+
+    def values(shape, s):
+        m = (128 + g.integers(0, 128, shape)) / 128.0
+        return torch.tensor(g.choice([-1.0, 1.0], shape) * m * np.exp2(g.integers(-s, s + 1, shape).astype(np.float64)), dtype=torch.float64)
+
+    A, B = values((n, 32, 16), spread), values((n, 32, 16), spread)
+    A[:, :, 8:] *= 2.0 ** apart
+    C = values((n, 32, 32), 2 * spread) * torch.tensor(g.random((n, 32, 32)) + 0.5) * torch.tensor(np.exp2(g.choice([0, apart], (n, 32, 32)).astype(np.float64)))
+    A[4 * n // 8:, :, 8:] = -A[4 * n // 8:, :, :8]             # the second group takes the first's sum away (with c in between)
+    B[4 * n // 8:, :, 8:] = B[4 * n // 8:, :, :8]
+    A[6 * n // 8:, :, 15] *= 2.0 ** apart
+    products = lambda lo: torch.matmul(A[:, :, lo:lo + 8], B[:, :, lo:lo + 8].transpose(1, 2))
+    biggest = lambda lo: (A[:, :, lo:lo + 8].abs().unsqueeze(2) * B[:, :, lo:lo + 8].abs().unsqueeze(1)).amax(-1)
+    s1, s2 = products(0), products(8)
+    C[: n // 8] = 0
+    C[n // 8: 2 * n // 8] = -s1[n // 8: 2 * n // 8] * (1 + 1e-6)
+    C[2 * n // 8: 3 * n // 8] = -(s1 + s2)[2 * n // 8: 3 * n // 8] * (1 + 1e-6)
+    C[5 * n // 8: 6 * n // 8] = 0
+    C[6 * n // 8: 7 * n // 8] = -s1[6 * n // 8: 7 * n // 8]
+    C = C.float().double()
+    D = _product(probe, A, B, C)
+    first = (C + s1).abs()
+    err1 = U * (10 * biggest(0) + 2 * C.abs() + 1.001 * first)
+    err, bound = (D - (C + s1 + s2)).abs(), 1.001 * (err1 + U * (10 * biggest(8) + 2 * (first + err1) + D.abs()))
+    print(f"[error / bound] spread {spread}, apart {apart}: {(err / bound).max():.3f}")
+    assert (err <= bound).all(), (err / bound).max()
+
+
+def test_order_of_the_matrix_instruction(probe):
+    """Products 0 .. 7 come first, and their sum with c is rounded before 8 .. 15 come: where one of the first takes c away
+    exactly, the others lose nothing to it."""
+    g = np.random.default_rng(1)
+    n = 8 * 40
+    A, B = (torch.tensor(g.choice([-1.0, 1.0], (n, 32, 16)) * (128 + g.integers(0, 128, (n, 32, 16))) / 128.0) for _ in range(2))
+    A[:, :, :8] = 0
+    for k in range(8):
+        A[k::8, :, k], B[k::8, :, k] = 2.0 ** 20, 2.0 ** 10
+    C = torch.full((n, 32, 32), -2.0 ** 30, dtype=torch.float64)
+    s2 = torch.matmul(A[:, :, 8:], B[:, :, 8:].transpose(1, 2))
+    biggest = (A[:, :, 8:].abs().unsqueeze(2) * B[:, :, 8:].abs().unsqueeze(1)).amax(-1)
+    D = _product(probe, A, B, C)
+    err, bound = (D - s2).abs(), U * (10 * biggest + D.abs())
+    assert (err <= bound).all(), (err / bound).max()
+
+
 def test_activations(probe):
     """Both evaluations of SiLU within 12 u |h| + 2 u |a| of each other; hi + lo within 128 u |h| of the activation."""
     g = torch.Generator().manual_seed(5)
