@@ -111,17 +111,30 @@ def test_extreme_values(bits, hidden):
 @pytest.mark.parametrize("bits,hidden", [(64, 64), (256, 512)])
 @pytest.mark.parametrize("share", [0.0, 0.5, 1.0])
 def test_rows_that_are_all_open(share, bits, hidden):
-    """Two equal and opposite halves of a hidden layer make every output a sum that cancels: nothing is settled, and lists
-    of whole spans are full, those of a tile's chains too.  Scattered among settled rows, or all of them."""
+    """Two equal and opposite halves of a hidden layer make every output a sum that cancels: nothing is settled, and the lists of a
+    tile's chains are full.  Scattered among settled rows, or all of them; many workgroups share them (a list holds 512 or 1024 rows)."""
+    _check_open_rows(2, 65600, share, bits, hidden)
+
+
+@pytest.mark.parametrize("bits,hidden", [(64, 64), (96, 256), (160, 64), (256, 128), (256, 512), (32, 1024)])
+@pytest.mark.parametrize("share", [0.5, 0.999])
+def test_lists_of_open_rows_that_are_full(share, bits, hidden):
+    """A workgroup for every head (whole generations of them) has more rows than a list of 2048 holds: it is filled three times, with
+    part of a tile in front the second and third time.  Every kernel of the second pass."""
+    _check_open_rows(1024, 4133, share, bits, hidden)
+
+
+def _check_open_rows(H, rows, share, bits, hidden):
     g = torch.Generator().manual_seed(3)
-    H, rows, n = 2, 65600, hidden // 2
-    ws = [t.float() for t in _weights(g, H, bits, hidden)]
+    n, some = hidden // 2, min(H, 8)
+    ws = [t.float() for t in _weights(g, some, bits, hidden)]
     ws[0][:, n:], ws[1][:, n:], ws[2][:, :, n:] = ws[0][:, :n], ws[1][:, :n], -ws[2][:, :, :n]
     ws[0][:, ::n], ws[1][:, ::n] = 0, 0
     ws[0][:, 0, 0] = 3.0                                 # the unit that tells the rows apart: a = 3 x_0
-    K = torch.randn(1, H, rows, 128, generator=g)
-    K[..., 0] = torch.where(torch.rand(1, H, rows, generator=g) < share, torch.tensor(0.0), torch.tensor(4.0))
-    _check(K.bfloat16(), [t.bfloat16().contiguous() for t in ws], 0, rows, bits, hidden)
+    K = torch.randn(1, some, rows, 128, generator=g)
+    K[..., 0] = torch.where(torch.rand(1, some, rows, generator=g) < share, torch.tensor(0.0), torch.tensor(4.0))
+    again = lambda t, dim: t.bfloat16().repeat_interleave(H // some, dim).contiguous()
+    _check(again(K, 1), [again(t, 0) for t in ws], 0, rows, bits, hidden, n_oracle=40 if H == some else 2)
 
 
 @pytest.mark.parametrize("bits,hidden", [(64, 64), (96, 256), (256, 128), (160, 288), (256, 512), (256, 1008)])
