@@ -36,8 +36,8 @@ inline size_t open_lds(int hidden)
 }
 
 // WM: code words the first pass laid the operands out for.
-template <int WM>
-__global__ __launch_bounds__(kOpenWaves * 64, 2) void hash_open_kernel(HashArgs a, const char* __restrict__ scales, const uint4* __restrict__ operands, int run, int open_at)
+template <int WM, typename Record>
+__global__ __launch_bounds__(kOpenWaves * 64, 2) void hash_open_kernel(HashArgs a, const char* __restrict__ scales, const uint4* __restrict__ operands, int run, int open_at, Record record)
 {
     constexpr int TK = bulk::kTile, NT = kOpenWaves * 64, NUB = 2, OPS = operands_of(WM);
     using bulk::XTile;
@@ -223,6 +223,8 @@ __global__ __launch_bounds__(kOpenWaves * 64, 2) void hash_open_kernel(HashArgs 
                 // ---- signs, and which outputs are too close to zero to trust
                 float bound = 1.002f * (scale * hn);
                 if (!(bound < 1e25f)) bound = INFINITY;   // also where it is no number
+                auto own_bound = [&](int v) { return 1.002f * (rows_of_word[v].s2 * hn); };
+                if (tile * TK + c < walk.count) record(xhead, row_of(tile * TK + c), wave, half, y, [&](int v) { return uneven ? own_bound(v) : bound; });
                 uint32_t sign = 0, which = 0;
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
@@ -234,7 +236,7 @@ __global__ __launch_bounds__(kOpenWaves * 64, 2) void hash_open_kernel(HashArgs 
                     which = 0;
 #pragma unroll
                     for (int v = 0; v < 16; ++v) {
-                        const float b = 1.002f * (rows_of_word[v].s2 * hn);
+                        const float b = own_bound(v);
                         which |= __builtin_fabsf(y[v]) >= b && b < 1e25f ? 0u : 1u << v;
                         if (v % 4 == 3) __builtin_amdgcn_sched_barrier(0);
                     }
@@ -283,14 +285,15 @@ __global__ __launch_bounds__(kOpenWaves * 64, 2) void hash_open_kernel(HashArgs 
 // Whether this kernel serves the second pass of a network.
 inline bool open_serves(int hidden, int W) { return hidden > 256 && hidden <= 512 && words_for(W) == 8 && !resident(hidden, W); }
 
-inline int launch_open(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int stage)
+template <typename Record = NoRecord>
+int launch_open(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int stage, Record record = {})
 {
     const size_t open_at = open_lds(a.hidden), lds = open_at + sizeof(bulk::OpenRows);
-    auto kern = hash_open_kernel<8>;
+    auto kern = hash_open_kernel<8, Record>;
     if (allow_dynamic_lds(ctx, reinterpret_cast<const void*>(kern), lds) != SPOTLIGHT_OK) return SPOTLIGHT_ERR_HIP;
     const bulk::OpenGrid g = bulk::open_grid(a, n_xheads, ctx->n_cus);
     StageTimer timer(ctx, stage);
-    timer.launch(kern, g.grid, dim3(kOpenWaves * 64), lds, a, static_cast<const char*>(a.scales), static_cast<const uint4*>(a.operands), g.run, static_cast<int>(open_at));
+    timer.launch(kern, g.grid, dim3(kOpenWaves * 64), lds, a, static_cast<const char*>(a.scales), static_cast<const uint4*>(a.operands), g.run, static_cast<int>(open_at), record);
     return hip_rc(hipGetLastError());
 }
 

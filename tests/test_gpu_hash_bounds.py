@@ -1,0 +1,156 @@
+"""The bounds that settle signs in bulk hashing of two passes, as its kernels evaluate them, against real distances: every output
+of hash_screen_kernel and of hash_open_kernel from the chain's (a plain kernel here, whose signs are the oracle's codes)."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+import torch
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+DEV = "cuda:0"
+
+PROBE = r"""
+#include <string.h>
+#include "hash_open.h"
+using namespace spotlight;
+using hashdev::bf16_raw;
+// what the library has in other files
+int spotlight::allow_dynamic_lds(spotlight_ctx* ctx, const void* kernel, size_t)
+{
+    return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, ctx->max_lds) == hipSuccess ? SPOTLIGHT_OK : SPOTLIGHT_ERR_HIP;
+}
+spotlight::StageTimer::StageTimer(spotlight_ctx* c, int) : ctx(c), rec(nullptr) {}
+// [head][row][output in the order of the code's words and bits]
+struct Record {
+    float* y;
+    float* bound;
+    int64_t rows;
+    int words;
+    template <typename Bound>
+    __device__ void operator()(int xhead, int64_t row, int word, int half, const bulk::f32x16_t& out, Bound bound_of) const
+    {
+        const int64_t at = ((xhead * rows + row) * words + word) * 32 + 16 * half;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) { y[at + v] = out[v]; bound[at + v] = bound_of(v); }
+    }
+};
+// the chain: a workgroup hashes a vector
+__global__ void chain(const bf16_raw* x, const bf16_raw* w1, const bf16_raw* b1, const bf16_raw* w2, float* y, int64_t rows, int hidden, int L)
+{
+    __shared__ float h[1024];
+    const int64_t row = blockIdx.x, head = blockIdx.y;
+    const bf16_raw* xr = x + (head * rows + row) * 128;
+    for (int i = threadIdx.x; i < hidden; i += blockDim.x) {
+        float a = hashdev::load1(b1 + head * hidden + i);
+        for (int k = 0; k < 128; ++k) a = __builtin_fmaf(hashdev::load1(w1 + (head * hidden + i) * 128 + k), hashdev::load1(xr + k), a);
+        h[i] = hashdev::silu(a);
+    }
+    __syncthreads();
+    for (int o = threadIdx.x; o < L; o += blockDim.x) {
+        const int j = o % 32 * (L / 32) + o / 32;
+        float s = 0.0f;
+        for (int i = 0; i < hidden; ++i) s = __builtin_fmaf(hashdev::load1(w2 + (head * L + j) * hidden + i), h[i], s);
+        y[(head * rows + row) * L + o] = s;
+    }
+}
+extern "C" int64_t scratch(int heads, int64_t rows, int hidden, int bits, int what)
+{
+    return what == 0 ? screen::scale_bytes(heads, bits / 32) : what == 1 ? (int64_t)heads * screen::blocks_of(hidden) * screen::operands_of(screen::words_for(bits / 32)) * 1024
+                     : heads * ((rows + 31) / 32) * 4 + 128;
+}
+extern "C" int run(const void* x, const void* w1, const void* b1, const void* w2, void* scales, void* operands, void* open, void* counts, void* codes, float* y_chain,
+                   float* y1, float* bound1, float* y2, float* bound2, int heads, int64_t rows, int hidden, int bits, int n_cus)
+{
+    static spotlight_ctx ctx;
+    memset(&ctx, 0, sizeof(ctx));
+    ctx.n_cus = n_cus;
+    ctx.max_lds = 160 * 1024;
+    hashdev::HashArgs a;
+    memset(&a, 0, sizeof(a));
+    a.x = x; a.x_head_stride = rows * 128; a.n_rows = rows; a.heads_per_batch = heads; a.group = 1; a.n_wheads = heads;
+    a.w1 = w1; a.b1 = b1; a.w2 = w2; a.hidden = hidden; a.L = bits; a.W = bits / 32;
+    a.codes = (uint32_t*)codes; a.code_head_stride = rows * a.W;
+    a.scales = scales; a.operands = operands; a.open = (uint32_t*)open; a.open_stride = (rows + 31) / 32; a.open_counts = (uint32_t*)counts;
+    if (!screen::serves(hidden, a.W) || hidden > 1024) return -1;
+    chain<<<dim3((unsigned)rows, heads), 256>>>((const bf16_raw*)x, (const bf16_raw*)w1, (const bf16_raw*)b1, (const bf16_raw*)w2, y_chain, rows, hidden, bits);
+    if (screen::launch(&ctx, a, heads, 0, Record{y1, bound1, rows, a.W}) != SPOTLIGHT_OK) return -2;
+    if (y2 && screen::open_serves(hidden, a.W) && screen::launch_open(&ctx, a, heads, 0, Record{y2, bound2, rows, a.W}) != SPOTLIGHT_OK) return -3;
+    return hipDeviceSynchronize();
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def probe(tmp_path_factory):
+    from paper_2508_19740_amd import build
+    tmp = tmp_path_factory.mktemp("bounds")
+    src, lib = tmp / "bounds.hip", tmp / "bounds.so"
+    src.write_text(PROBE)
+    subprocess.run(["/opt/rocm/bin/hipcc", *build.FLAGS, "-shared", "-I", os.path.join(ROOT, "include"), "-I", build.CSRC, "-o", str(lib), str(src)],
+                   check=True, capture_output=True)
+    lib = ctypes.CDLL(str(lib))
+    lib.scratch.restype = ctypes.c_int64
+    return lib
+
+
+def _inputs(kind, bits, hidden, H, rows):
+    g = torch.Generator().manual_seed(bits + hidden)
+    ws = [0.05 * torch.randn(H, *s, generator=g) for s in ((hidden, 128), (hidden,), (bits, hidden))]
+    K = torch.randn(1, H, rows, 128, generator=g)
+    if kind == "cone":
+        K += 2.0 * torch.randn(1, H, 1, 128, generator=g).sign()
+    if kind == "exponents":
+        K = torch.ldexp(K, torch.randint(-12, 13, K.shape, generator=g))
+        ws = [torch.ldexp(w, torch.randint(-8, 9, w.shape, generator=g)) for w in ws]
+    if kind == "bias":
+        ws[1] *= 2000
+    if kind == "cancels":         # activations come in pairs whose outputs take each other away
+        n = hidden // 2
+        ws[0][:, n:], ws[1][:, n:], ws[2][:, :, n:] = ws[0][:, :n], ws[1][:, :n], -ws[2][:, :, :n]
+    if kind == "small":
+        K *= 1e-4
+    if kind == "uneven":
+        ws[2] *= torch.exp(2.0 * torch.randn(H, bits, 1, generator=g))
+    return K.bfloat16(), [w.bfloat16() for w in ws]
+
+
+@pytest.mark.parametrize("kind", ["random", "cone", "exponents", "bias", "cancels", "small", "uneven"])
+@pytest.mark.parametrize("bits,hidden", [(64, 64), (128, 256), (256, 512), (224, 272), (64, 1024)])
+def test_no_output_is_further_from_the_chain_than_its_bound(probe, bits, hidden, kind):
+    H, rows = 2, 4100
+    K, ws = _inputs(kind, bits, hidden, H, rows)
+    Kd, wd = K.to(DEV), [w.to(DEV) for w in ws]
+    scales, operands, open_ = (torch.zeros(probe.scratch(H, ctypes.c_int64(rows), hidden, bits, what) // 4, dtype=torch.int32, device=DEV) for what in range(3))
+    counts, codes = torch.zeros(H * 32, dtype=torch.int32, device=DEV), torch.zeros(H, rows, bits // 32, dtype=torch.int32, device=DEV)
+    y, y1, b1, y2, b2 = (torch.full((H, rows, bits), float("nan"), device=DEV) for _ in range(5))
+    p = [ctypes.c_void_p(t.data_ptr()) for t in (Kd, *wd, scales, operands, open_, counts, codes, y, y1, b1, y2, b2)]
+    assert probe.run(*p, H, ctypes.c_int64(rows), hidden, bits, torch.cuda.get_device_properties(0).multi_processor_count) == 0
+    assert not torch.isnan(y).any()
+    # the chain here is the oracle's
+    ref = torch.zeros(1, H, rows, bits // 32, dtype=torch.int32)
+    oracle.hash_keys(K, *ws, bits, 0, 40, ref)
+    weight = (1 << torch.arange(31, -1, -1, device=DEV, dtype=torch.int64))
+    mine = ((y[:, :40].view(H, 40, -1, 32) > 0).long() * weight).sum(-1)
+    assert torch.equal(mine.cpu(), ref[0, :, :40].long() & 0xffffffff)
+
+    def check(name, got, bound, keys):
+        settles = keys & (bound < 1e25) & (got > -1e29)      # (rows of zeros start from -1e30)
+        assert settles.any()
+        ratio = ((got.double() - y.double()).abs() / bound.double())[settles]
+        print(f"[distance / bound] {name} 128 -> {hidden} -> {bits}, {kind}: largest {ratio.max():.4f}")
+        assert ratio.max() < 0.5, (name, ratio.max())        # 0.14 at most measured: a bound a few times smaller would not do
+        assert ((got > 0) == (y > 0))[settles & (got.abs() >= bound)].all()
+    every = torch.ones_like(y, dtype=torch.bool)
+    assert not torch.isnan(y1).any()
+    check("first pass", y1, b1, every)
+    if 256 < hidden <= 512 and bits >= 160:
+        words = open_[:H * ((rows + 31) // 32)].view(H, -1)
+        is_open = ((words.unsqueeze(-1) >> torch.arange(32, device=DEV)) & 1).bool().view(H, -1)[:, :rows]
+        assert torch.equal(~torch.isnan(y2[..., 0]), is_open)
+        assert torch.equal(counts.view(H, 32)[:, 0], is_open.sum(1, dtype=torch.int32))
+        check("second pass", y2, b2, is_open.unsqueeze(-1) & every)
