@@ -2063,7 +2063,9 @@ int launch_word_open(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int st
     const size_t open_at = align16(word_lds<T, NW, NUB>(a)), lds = open_at + sizeof(OpenRows);
     auto kern = hash_cert_kernel<T, NW, NUB, WREG, false, true>;
     if (allow_dynamic_lds(ctx, reinterpret_cast<const void*>(kern), lds) != SPOTLIGHT_OK) return SPOTLIGHT_ERR_HIP;
-    const OpenGrid g = open_grid(a, n_xheads, ctx->n_cus * resident(ctx, 2, lds));
+    // narrow layers leave room for a third workgroup: 8 heads x 65536 keys, all open, 128 -> 64 -> 64 646 us with two, 470 with three, 128 -> 128 -> 64 940 and
+    // 770; random keys 20 and 19, 32 and 27
+    const OpenGrid g = open_grid(a, n_xheads, ctx->n_cus * resident(ctx, NUB == 1 ? 3 : 2, lds));
     StageTimer timer(ctx, stage);
     timer.launch(kern, g.grid, dim3(NW * 64), lds, a, static_cast<float>(bulk_hash_eps(a.hidden, true)), g.run, static_cast<int>(open_at));
     return hip_rc(hipGetLastError());
