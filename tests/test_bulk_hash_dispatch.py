@@ -113,7 +113,7 @@ int main()
                 for (int t : tiles) {
                     const unsigned w = bulk::open_workgroups(t, q, parts_with(q), slots);
                     used += w;
-                    if ((t == 0) != (w == 0) || static_cast<unsigned>(t) > w * q) { printf("%d segments, %d slots, kind %d: %d tiles, %u\n", n, slots, kind, t, w); return 1; }
+                    if ((t == 0) != (w == 0) || static_cast<unsigned>(t) > w * q || w > static_cast<unsigned>(t)) { printf("%d segments, %d slots, kind %d: %d tiles, %u\n", n, slots, kind, t, w); return 1; }
                 }
                 if (used > static_cast<unsigned>(slots)) { printf("%d segments, %d slots, kind %d: %u workgroups\n", n, slots, kind, used); return 1; }
             }
@@ -251,7 +251,7 @@ def test_every_tile_belongs_to_one_workgroup(tmp_path):
 
 
 def test_open_rows_are_shared_out_over_the_heads(tmp_path):
-    """As few tiles for a workgroup as the chip's workgroups allow, whichever heads the open rows are in."""
+    """As few tiles for a workgroup as the chip's workgroups allow, whichever heads the open rows are in, and none for no tile."""
     run = subprocess.run([_program(tmp_path, QUOTA, "quota")], capture_output=True, text=True)
     assert run.returncode == 0, run.stdout
 
