@@ -301,9 +301,8 @@ __global__ __launch_bounds__(kWaves * 64, 2) void hash_screen_kernel(HashArgs a,
 
     const bf16_raw* xbase = static_cast<const bf16_raw*>(a.x) + xhead * a.x_head_stride + a.x_row0 * kHeadDim;
     const int64_t n_tiles = (a.n_rows + TK - 1) / TK, tile0 = static_cast<int64_t>(blockIdx.x) * rounds * kWaves;
-    const int64_t segments = (a.n_rows + bulk::kOpenSegment - 1) / bulk::kOpenSegment;
+    const int64_t segments = bulk::segments_of(a);
     RowScale* rows = reinterpret_cast<RowScale*>(ops + (RESIDENT ? nub : 2) * OPS * 64);   // [W][32]
-    for (int i = tid; i < W * 32; i += NT) rows[i] = row_scales(scales, a.n_wheads, whead, W)[i];
     // open rows: each wavefront counts its own, the workgroup adds those of the first segments up in LDS and then to the segments' counts
     // (an addition in memory for every tile: 8 heads x 65536, 128 -> 256 -> 128, both passes, 334 us; so 235)
     uint32_t* opened = reinterpret_cast<uint32_t*>(rows + W * 32);
@@ -355,6 +354,10 @@ __global__ __launch_bounds__(kWaves * 64, 2) void hash_screen_kernel(HashArgs a,
         bring(nub - 1, 1);   // layer 1 of block 0
         bring(0, 0);
     }
+    static_assert(kWords * 32 <= NT, "one record a thread");
+    uint32_t uneven = 0;
+    for (int w = 0; w < W; ++w) uneven |= ws[w].uneven;
+    if (uneven && tid < W * 32) rows[tid] = row_scales(scales, a.n_wheads, whead, W)[tid];
     const float t1 = ls->t1, t1_max = ls->t1_max, bn = ls->b1;
     const bool no_bias = ls->no_bias != 0;
     arrive();
@@ -608,7 +611,7 @@ int launch(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int stage, Recor
     const int n_operands = resident(a.hidden, a.W) ? 0 : blocks_of(a.hidden) * operands_of(words_for(a.W));
     hipLaunchKernelGGL(scales_kernel<8>, dim3(static_cast<unsigned>(a.n_wheads), static_cast<unsigned>(1 + a.W + (n_operands + kPerBlock - 1) / kPerBlock)), dim3(kThreads), 0,
                        ctx->stream, static_cast<const bf16_raw*>(a.w1), static_cast<const bf16_raw*>(a.b1), static_cast<const bf16_raw*>(a.w2), scales,
-                       static_cast<uint4*>(a.operands), a.open_counts, static_cast<int>((a.n_rows + bulk::kOpenSegment - 1) / bulk::kOpenSegment * n_xheads), a.hidden, a.L);
+                       static_cast<uint4*>(a.operands), a.open_counts, static_cast<int>(bulk::segments_of(a) * n_xheads), a.hidden, a.L);
     if (a.W <= 2) return launch_words<2>(ctx, a, scales, n_xheads, stage, record);
     if (a.W <= 4) return launch_words<4>(ctx, a, scales, n_xheads, stage, record);
     return launch_words<8>(ctx, a, scales, n_xheads, stage, record);
