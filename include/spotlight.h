@@ -276,10 +276,10 @@ int spotlight_decode_step_noalloc(const spotlight_config *cfg, const void *q, co
  * stamped when the kernel starts and when it ends.  spotlight_profile_read waits for the stream,
  * adds the elapsed times of the launches recorded since the last read to the per-stage totals and
  * returns the totals for `stage` (milliseconds, number of launches; an ATTEND launch that has whole heads
- * adds one to MERGE as well, so that both stages count the calls).  Do not capture into a HIP
- * graph while it is enabled.  spotlight_profile_enable(ctx, 0) stops recording
- * and clears the totals.  At most 8192 launches are recorded between two reads; later ones are
- * not timed.
+ * adds one to MERGE as well, so that both stages count the calls, and a bulk hash of several launches
+ * counts as one, with the time of all of them).  Do not capture into a HIP graph while it is enabled.
+ * spotlight_profile_enable(ctx, 0) stops recording and clears the totals.  At most 8192 launches are
+ * recorded between two reads; later ones are not timed.
  */
 int spotlight_profile_enable(spotlight_ctx *ctx, int on);
 int spotlight_profile_read(spotlight_ctx *ctx, int stage, double *total_ms, int64_t *launches);

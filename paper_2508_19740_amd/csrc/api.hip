@@ -69,7 +69,7 @@ int make_plan(const spotlight_config* c, Plan* p)
     return SPOTLIGHT_OK;
 }
 
-StageTimer::StageTimer(spotlight_ctx* c, int stage) : ctx(c), rec(nullptr)
+StageTimer::StageTimer(spotlight_ctx* c, int stage, bool more) : ctx(c), rec(nullptr)
 {
     if (!c->profiling || c->n_rec >= kMaxProfile) return;
     ProfileRec* r = &c->recs[c->n_rec];
@@ -80,7 +80,7 @@ StageTimer::StageTimer(spotlight_ctx* c, int stage) : ctx(c), rec(nullptr)
     }
     r->stage = stage;
     r->whole = false;
-    r->more = false;
+    r->more = more;
     rec = r;
 }
 

@@ -1909,6 +1909,15 @@ inline Shares shares_of(int64_t tiles, int n_xheads, int n_cus, int per_cu)
     return cost < cost_even ? Shares{static_cast<int>(parts), run, longer} : even;
 }
 
+inline int launch_row_norms(spotlight_ctx* ctx, const HashArgs& a, int stage)
+{
+    constexpr int LPR = 16;
+    const int n_out = a.n_wheads * a.L;
+    StageTimer timer(ctx, stage, true);
+    timer.launch(row_norm_kernel<LPR>, dim3(static_cast<unsigned>((n_out * LPR + kThreads - 1) / kThreads)), dim3(kThreads), 0, static_cast<const bf16_raw*>(a.w2), a.wnorm, n_out, a.hidden);
+    return hip_rc(hipGetLastError());
+}
+
 template <typename XT, typename WT, int NW, int NUB, int NBW, bool AUDIT>
 int launch(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int stage, size_t lds)
 {
@@ -1923,10 +1932,7 @@ int launch(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int stage, size_
     const Shares shares = kShort ? equal_shares(tiles, short_runs(tiles, n_xheads, kShort))
                                  : shares_of(tiles, n_xheads, ctx->n_cus, resident(ctx, 4 * min_waves(NW, NBW) / NW, lds));
     if constexpr (NBW > 0) {
-        constexpr int LPR = 16;
-        const int n_out = a.n_wheads * a.L;
-        hipLaunchKernelGGL(row_norm_kernel<LPR>, dim3(static_cast<unsigned>((n_out * LPR + kThreads - 1) / kThreads)), dim3(kThreads), 0,
-                           ctx->stream, static_cast<const bf16_raw*>(a.w2), a.wnorm, n_out, a.hidden);   // microseconds: not timed
+        if (const int rc = launch_row_norms(ctx, a, stage)) return rc;
     }
     dim3 grid(static_cast<unsigned>(shares.parts), static_cast<unsigned>(n_xheads));
     StageTimer timer(ctx, stage);
@@ -2054,10 +2060,7 @@ int launch_open(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int stage, 
     auto kern = hash_bulk_kernel<T, T, NW, NUB, NBW, false, true>;
     if (allow_dynamic_lds(ctx, reinterpret_cast<const void*>(kern), lds) != SPOTLIGHT_OK) return SPOTLIGHT_ERR_HIP;
     const OpenGrid g = open_grid(a, n_xheads, ctx->n_cus * resident(ctx, 4 * min_waves(NW, NBW) / NW, lds));
-    constexpr int LPR = 16;
-    const int n_out = a.n_wheads * a.L;
-    hipLaunchKernelGGL(row_norm_kernel<LPR>, dim3(static_cast<unsigned>((n_out * LPR + kThreads - 1) / kThreads)), dim3(kThreads), 0,
-                       ctx->stream, static_cast<const T*>(a.w2), a.wnorm, n_out, a.hidden);   // microseconds: not timed
+    if (const int rc = launch_row_norms(ctx, a, stage)) return rc;
     StageTimer timer(ctx, stage);
     timer.launch(kern, g.grid, dim3(NW * 64), lds, a, static_cast<float>(bulk_hash_eps(a.hidden, true)), g.run, static_cast<int>(open_at));
     return hip_rc(hipGetLastError());

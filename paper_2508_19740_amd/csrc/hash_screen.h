@@ -575,8 +575,7 @@ int launch_kernel(spotlight_ctx* ctx, const HashArgs& a, const char* scales, int
     const int64_t all_rounds = (a.n_rows + bulk::kTile * kWaves - 1) / (bulk::kTile * kWaves);
     const int rounds = bulk::rounds_of(all_rounds, n_xheads, ctx->n_cus);
     dim3 grid(static_cast<unsigned>((all_rounds + rounds - 1) / rounds), static_cast<unsigned>(n_xheads));
-    StageTimer timer(ctx, stage);
-    if (timer.rec) timer.rec->more = true;
+    StageTimer timer(ctx, stage, true);
     timer.launch(kern, grid, dim3(kWaves * 64), lds, a, scales, static_cast<const uint4*>(a.operands), rounds, record);
     return hip_rc(hipGetLastError());
 }
@@ -609,9 +608,11 @@ int launch(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int stage, Recor
 {
     char* scales = static_cast<char*>(a.scales);
     const int n_operands = resident(a.hidden, a.W) ? 0 : blocks_of(a.hidden) * operands_of(words_for(a.W));
-    hipLaunchKernelGGL(scales_kernel<8>, dim3(static_cast<unsigned>(a.n_wheads), static_cast<unsigned>(1 + a.W + (n_operands + kPerBlock - 1) / kPerBlock)), dim3(kThreads), 0,
-                       ctx->stream, static_cast<const bf16_raw*>(a.w1), static_cast<const bf16_raw*>(a.b1), static_cast<const bf16_raw*>(a.w2), scales,
-                       static_cast<uint4*>(a.operands), a.open_counts, static_cast<int>(bulk::segments_of(a) * n_xheads), a.hidden, a.L);
+    StageTimer timer(ctx, stage, true);
+    timer.launch(scales_kernel<8>, dim3(static_cast<unsigned>(a.n_wheads), static_cast<unsigned>(1 + a.W + (n_operands + kPerBlock - 1) / kPerBlock)), dim3(kThreads), 0,
+                 static_cast<const bf16_raw*>(a.w1), static_cast<const bf16_raw*>(a.b1), static_cast<const bf16_raw*>(a.w2), scales,
+                 static_cast<uint4*>(a.operands), a.open_counts, static_cast<int>(bulk::segments_of(a) * n_xheads), a.hidden, a.L);
+    if (hipGetLastError() != hipSuccess) return SPOTLIGHT_ERR_HIP;
     if (a.W <= 2) return launch_words<2>(ctx, a, scales, n_xheads, stage, record);
     if (a.W <= 4) return launch_words<4>(ctx, a, scales, n_xheads, stage, record);
     return launch_words<8>(ctx, a, scales, n_xheads, stage, record);

@@ -88,7 +88,7 @@ struct AuditRec {
 struct ProfileRec {
     int stage;
     bool whole;   // an attend launch that leaves nothing to merge
-    bool more;    // a call's first launch of two: its time counts, the call is counted with the second
+    bool more;    // not a call's last launch of several: its time counts, the call is counted with the last
     hipEvent_t start, stop;
 };
 
@@ -126,7 +126,7 @@ namespace spotlight {
 struct StageTimer {
     spotlight_ctx* ctx;
     ProfileRec* rec;
-    StageTimer(spotlight_ctx* c, int stage);
+    StageTimer(spotlight_ctx* c, int stage, bool more = false);
 #if defined(__HIPCC__)
     template <typename F, typename... Args>
     void launch(F kernel, const dim3& grid, const dim3& block, size_t lds, Args... args)

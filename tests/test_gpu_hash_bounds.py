@@ -24,7 +24,7 @@ int spotlight::allow_dynamic_lds(spotlight_ctx* ctx, const void* kernel, size_t)
 {
     return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, ctx->max_lds) == hipSuccess ? SPOTLIGHT_OK : SPOTLIGHT_ERR_HIP;
 }
-spotlight::StageTimer::StageTimer(spotlight_ctx* c, int) : ctx(c), rec(nullptr) {}
+spotlight::StageTimer::StageTimer(spotlight_ctx* c, int, bool) : ctx(c), rec(nullptr) {}
 // [head][row][output in the order of the code's words and bits]
 struct Record {
     float* y;

@@ -194,6 +194,36 @@ def test_profile_counts_a_call_once():
         ctx.close()
 
 
+def test_profile_times_every_launch_of_a_call():
+    """512 weight heads that are used for 256 keys each: what a call does with the weights first is a good part of it.  The times of its
+    launches sum to the call's but for the gaps between them."""
+    import paper_2508_19740_amd as sp
+    g = torch.Generator().manual_seed(1)
+    H, rows, bits, hidden = 512, 256, 32, 1024
+    K, ws = torch.randn(1, H, rows, 128, generator=g).bfloat16().to(DEV), [t.to(DEV) for t in _weights(g, H, bits, hidden)]
+    codes = torch.zeros(1, H, rows, 1, dtype=torch.int32, device=DEV)
+    ctx = sp.Spotlight(1, H, H, bits, hidden, rows, 1, kv_dtype=torch.bfloat16, weight_dtype=torch.bfloat16, device=DEV)
+    try:
+        def whole():
+            start, stop = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            for _ in range(10):
+                ctx.hash_keys(K, *ws, 0, rows, codes)
+            stop.record()
+            torch.cuda.synchronize()
+            return start.elapsed_time(stop) / 10
+        whole()
+        call = min(whole() for _ in range(3))
+        ctx.profile_enable(True)
+        for _ in range(10):
+            ctx.hash_keys(K, *ws, 0, rows, codes)
+        ms, n = ctx.profile_read()["hash_keys"]
+        print(f"[profile] call {call * 1e3:.1f} us, its launches {ms / n * 1e3:.1f}")
+        assert n == 10 and ms / n > 0.9 * call
+    finally:
+        ctx.close()
+
+
 @pytest.mark.parametrize("bits,hidden", [(128, 256), (256, 512), (512, 0)])
 def test_in_a_hip_graph(bits, hidden):
     """Both passes (and the linear hash) recorded once and replayed over other keys, with eager work between the replays."""
