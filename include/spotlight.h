@@ -258,8 +258,8 @@ int spotlight_decode_step(spotlight_ctx *ctx, const void *q, const void *K, cons
  * Arguments, layouts, results and argument errors are those of spotlight_decode_step (cfg->max_topk
  * bounds k as it does for a context); the hash weights are read as stored (no packed copy).
  *
- * Limit: the workspace of the shape (spotlight_workspace_bytes without the room for the packed
- * weights: about 1 KiB per (query head, block of 4096 tokens of max_tokens) x 4 + 516 B per
+ * Limit: the step's part of the workspace of the shape (spotlight_workspace_bytes without the room for
+ * packed weights and for bulk hashing: about 1 KiB per (query head, block of 4096 tokens of max_tokens) x 4 + 516 B per
  * (query head, 32 of max_topk)) must fit the buffer, else SPOTLIGHT_ERR_TOO_LARGE and nothing is
  * launched.  Batch 1, 32 heads, 524288 tokens, top-k 10486 needs 24.4 MB and fits.
  * All calls on one GPU share the one buffer: calls that overlap in time on the same GPU (two

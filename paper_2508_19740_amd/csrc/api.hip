@@ -56,14 +56,17 @@ int make_plan(const spotlight_config* c, Plan* p)
     p->off_part_acc = off;  off = align_up(off + BH * p->max_splits * static_cast<size_t>(kHeadDim) * 4, 256);
     p->off_wnorm = off;     off = align_up(off + static_cast<size_t>(p->Hkv) * p->L * 4, 256);
     pack_sizes(p->hidden, p->L, &p->pack_w1_elems, &p->pack_out_elems);
-    const bool bf16 = p->w_dtype == SPOTLIGHT_BF16 && p->kv_dtype == SPOTLIGHT_BF16;
     const size_t welem = p->w_dtype == SPOTLIGHT_BF16 ? 2 : 4;
     p->off_pack_w1 = off;   off = align_up(off + static_cast<size_t>(p->Hkv) * p->pack_w1_elems * welem, 256);
     p->off_pack_out = off;  off = align_up(off + static_cast<size_t>(p->Hkv) * p->pack_out_elems * welem, 256);
-    p->off_scales = off;    off = align_up(off + screen_scale_bytes(p->Hkv, p->W), 256);
-    p->off_operands = off;  off = align_up(off + (bf16 ? static_cast<size_t>(p->Hkv) * screen_operand_bytes(p->hidden, p->W) : 0), 256);
-    p->off_open = off;      off = align_up(off + static_cast<size_t>(p->B) * p->Hkv * ((p->Nmax + 31) / 32) * 4, 256);
-    p->off_open_counts = off; off = align_up(off + static_cast<size_t>(p->B) * p->Hkv * ((p->Nmax + 65535) / 65536) * 128, 256);
+    // bulk hashing in two passes, where the configuration has it
+    const bool two = p->w_dtype == SPOTLIGHT_BF16 && p->kv_dtype == SPOTLIGHT_BF16 && screen_serves(p->hidden, p->W);
+    const size_t kheads = two ? static_cast<size_t>(p->B) * p->Hkv : 0, wheads = two ? static_cast<size_t>(p->Hkv) : 0;
+    p->two_passes = two;
+    p->off_scales = off;    off = align_up(off + screen_scale_bytes(static_cast<int>(wheads), p->W), 256);
+    p->off_operands = off;  off = align_up(off + wheads * screen_operand_bytes(p->hidden, p->W), 256);
+    p->off_open = off;      off = align_up(off + kheads * ((p->Nmax + 31) / 32) * 4, 256);
+    p->off_open_counts = off; off = align_up(off + kheads * ((p->Nmax + 65535) / 65536) * 128, 256);
     p->off_audit = off;     off = align_up(off + sizeof(AuditRec), 256);
     p->total_bytes = off;
     return SPOTLIGHT_OK;
@@ -273,11 +276,12 @@ static HashLaunch key_job(const spotlight_ctx* ctx, const void* K, const spotlig
     h.zero_words = 0;
     h.wnorm = ctx->opt[SPOTLIGHT_OPT_BULK_HASH_MATRIX_CORES] ? reinterpret_cast<float*>(ctx->workspace + p.off_wnorm) : nullptr;
     h.audit = ctx->opt[SPOTLIGHT_OPT_BULK_HASH_AUDIT] ? reinterpret_cast<AuditRec*>(ctx->workspace + p.off_audit) : nullptr;
-    h.scales = h.wnorm ? ctx->workspace + p.off_scales : nullptr;
-    h.operands = h.wnorm ? ctx->workspace + p.off_operands : nullptr;
-    h.open = h.wnorm ? reinterpret_cast<uint32_t*>(ctx->workspace + p.off_open) : nullptr;
+    const bool two = h.wnorm && p.two_passes;
+    h.scales = two ? ctx->workspace + p.off_scales : nullptr;
+    h.operands = two ? ctx->workspace + p.off_operands : nullptr;
+    h.open = two ? reinterpret_cast<uint32_t*>(ctx->workspace + p.off_open) : nullptr;
     h.open_stride = (p.Nmax + 31) / 32;
-    h.open_counts = h.wnorm ? reinterpret_cast<uint32_t*>(ctx->workspace + p.off_open_counts) : nullptr;
+    h.open_counts = two ? reinterpret_cast<uint32_t*>(ctx->workspace + p.off_open_counts) : nullptr;
     attach_packed(ctx, w, &h);
     return h;
 }

@@ -5,6 +5,8 @@ namespace spotlight {
 using namespace hashdev;
 extern template int run_bulk_hash<bf16_raw, bf16_raw>(spotlight_ctx*, const HashArgs&, int, int);
 
+bool screen_serves(int hidden, int W) { return screen::serves(hidden, W); }
+
 size_t screen_operand_bytes(int hidden, int W)
 {
     return screen::serves(hidden, W) && !screen::resident(hidden, W) ? static_cast<size_t>(screen::blocks_of(hidden)) * screen::operands_of(screen::words_for(W)) * 64 * sizeof(uint4) : 0;

@@ -39,6 +39,7 @@ struct Plan {
     size_t off_pack_w1;    // first hash layer in the single-vector kernel's read order (pack_w1_elems per kv head)
     size_t off_pack_out;   // output matrix of the hash (W2, or R of the linear hash) in that order
     size_t pack_w1_elems, pack_out_elems;   // elements per kv head; both 0 if the hash shape has no such copy
+    bool two_passes;       // bulk hashing may take two passes; the next four areas are empty otherwise
     size_t off_scales;     // [screen_scale_bytes] norms of the weights for the first pass of bulk hashing (hash_screen.h)
     size_t off_operands;   // [Hkv][screen_operand_bytes] the weights in that pass's read order
     size_t off_open;       // [B*Hkv][ceil(Nmax / 32)] rows that pass left open, a bit each
@@ -72,7 +73,8 @@ __device__ __forceinline__ uint32_t wave_sum(uint32_t x)
 }
 #endif
 
-size_t screen_operand_bytes(int hidden, int W);          // of a weight head, in hash_screen.hip
+bool screen_serves(int hidden, int W);                   // whether the first pass takes such a network, in hash_screen.hip
+size_t screen_operand_bytes(int hidden, int W);          // of a weight head
 size_t screen_scale_bytes(int heads, int W);
 int make_plan(const spotlight_config* cfg, Plan* plan);  // SPOTLIGHT_OK or an error code; host only
 

@@ -88,6 +88,22 @@ def test_workspace_grows_with_the_problem():
     assert more_weights <= wide - small <= more_weights + (1 << 20)
 
 
+def test_workspace_has_room_for_two_passes_where_they_run():
+    """Norms, a bitmap of the keys and its counts: bfloat16 keys and weights, up to 256 bits behind 16 to 1024 hidden units."""
+    tokens = 1 << 20
+    bitmap = 32 * tokens // 8
+
+    def extra(kv=torch.bfloat16, w=torch.bfloat16, **kw):
+        f32 = sp.make_config(1, 32, 32, kw.get("bits", 128), kw.get("hidden", 256), tokens, 128, kv_dtype=torch.float32, weight_dtype=w)
+        own = sp.make_config(1, 32, 32, kw.get("bits", 128), kw.get("hidden", 256), tokens, 128, kv_dtype=kv, weight_dtype=w)
+        return sp.workspace_bytes(own) - sp.workspace_bytes(f32)
+    assert bitmap <= extra() <= bitmap + (1 << 20)
+    assert bitmap <= extra(bits=256, hidden=512) <= bitmap + (16 << 20)
+    for kw in (dict(w=torch.float32), dict(hidden=0), dict(bits=288), dict(hidden=1152), dict(hidden=264), dict(bits=512, hidden=0)):
+        assert extra(**kw) == 0, kw
+
+
+
 def test_null_arguments_are_rejected_without_a_gpu():
     bad = sp.ERR_INVALID_ARG
     lib = sp.lib
