@@ -1234,7 +1234,7 @@ __global__ __launch_bounds__(NW * 64, 2) void hash_cert_kernel(HashArgs a, float
 // (728 us on the binary32 matrix instruction) to 270 us; 39 % of the cycles issue vector instructions, 10 %
 // are matrix instructions (221 us with the smaller bound; calls of that size go to the next kernel now).  With four words a wavefront 50 registers are spilled (66 with binary32 vectors); a
 // recomputation that holds half as many operands spills 48 and is slower (284 us).
-constexpr int kLinearWords = 16;      // code words of a workgroup, four a wavefront
+constexpr int kLinearWords = 16;      // code words of a workgroup, four a wavefront here (longer codes have the next kernel)
 constexpr int kLinearList = 256;      // open outputs of a wavefront and tile (of 32 x 128)
 constexpr int kLinearStage = 256;     // rows of R on their way into registers at a time
 
@@ -1261,12 +1261,12 @@ __global__ __launch_bounds__(kThreads, 2) void hash_linear_kernel(HashArgs a, fl
     const int c = lane & 31, half = lane >> 5;
     const int xhead = blockIdx.y;
     const int whead = whead_of(a, xhead);
-    const int word0 = blockIdx.z * kLinearWords, n_words = min(kLinearWords, a.W - word0);
+    const int n_words = a.W;
     const WT* r = static_cast<const WT*>(a.w1) + static_cast<int64_t>(whead) * a.L * kHeadDim;
     const XT* xbase = static_cast<const XT*>(a.x) + xhead * a.x_head_stride + a.x_row0 * kHeadDim;
 
     // ---- R into registers by way of LDS (whole cache lines), kLinearStage rows at a time: word
-    // word0 + wave + 4 nb, the lane's output, 16 k a step and 8 of them per lane
+    // wave + 4 nb, the lane's output, 16 k a step and 8 of them per lane
     uint4 wreg[NB][8];
     for (int j0 = 0; j0 < a.L; j0 += kLinearStage) {
         const uint4* from = reinterpret_cast<const uint4*>(r + static_cast<int64_t>(j0) * kHeadDim);
@@ -1285,7 +1285,7 @@ __global__ __launch_bounds__(kThreads, 2) void hash_linear_kernel(HashArgs a, fl
         __syncthreads();
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
-            const int j = (31 - c) * a.W + word0 + min(wave + 4 * nb, n_words - 1) - j0;
+            const int j = (31 - c) * a.W + min(wave + 4 * nb, n_words - 1) - j0;
             if (j >= 0 && j < rows) {
 #pragma unroll
                 for (int ks = 0; ks < 8; ++ks) wreg[nb][ks] = reinterpret_cast<const uint4*>(lds)[j * (CH + 1) + 2 * ks + half];
@@ -1386,7 +1386,7 @@ __global__ __launch_bounds__(kThreads, 2) void hash_linear_kernel(HashArgs a, fl
         }
         s += __shfl_xor(s, 32);
         if (rare(s == 0.0f))   // a row of zeros, or did its squares underflow?
-            s = square_of(s, magnitude_bits(r + static_cast<int64_t>((31 - c) * a.W + word0 + min(wave + 4 * nb, n_words - 1)) * kHeadDim, kHeadDim));
+            s = square_of(s, magnitude_bits(r + static_cast<int64_t>((31 - c) * a.W + min(wave + 4 * nb, n_words - 1)) * kHeadDim, kHeadDim));
         tcol[nb] = eps * norm_of(s);
     }
     put_x(0);
@@ -1430,7 +1430,7 @@ __global__ __launch_bounds__(kThreads, 2) void hash_linear_kernel(HashArgs a, fl
                     float yv = 0.0f, hv = 0.0f;
 #pragma unroll
                     for (int e = 0; e < 16; ++e) { yv = e == v ? y[e] : yv; hv = e == v ? hn[e] : hv; }
-                    const float yc = chain(r0 + t, (31 - c) * a.W + word0 + w);
+                    const float yc = chain(r0 + t, (31 - c) * a.W + w);
                     const bool sure = settled(yv, tcol[nb], hv);
                     const float den = tcol[nb] / eps * hv, diff = __builtin_fabsf(yv - yc);
                     // a NaN or an infinity on either side is never settled and is not a distance
@@ -1472,13 +1472,13 @@ __global__ __launch_bounds__(kThreads, 2) void hash_linear_kernel(HashArgs a, fl
                 const int entry = all ? static_cast<int>(e) : m.list[wave][e];
                 const int t = entry & 31, col = (entry >> 5) & 31, w = wave + 4 * (entry >> 10);
                 if (t >= rows || w >= n_words) continue;
-                const float yc = chain(r0 + t, (31 - col) * a.W + word0 + w);
+                const float yc = chain(r0 + t, (31 - col) * a.W + w);
                 const uint32_t bit = 1u << col;
                 if (((m.codes[buf][t][w] & bit) != 0) != (yc > 0.0f)) atomicXor(&m.codes[buf][t][w], bit);
             }
         }
         __syncthreads();   // the tile's codes are final, the next tile's vectors are there
-        uint32_t* cbase = a.codes + xhead * a.code_head_stride + (a.code_row0 + r0) * a.W + word0;
+        uint32_t* cbase = a.codes + xhead * a.code_head_stride + (a.code_row0 + r0) * a.W;
         for (int e = tid; e < rows * n_words; e += NT) cbase[static_cast<int64_t>(e / n_words) * a.W + e % n_words] = m.codes[buf][e / n_words][e % n_words];
     }
     if constexpr (AUDIT) {
@@ -1505,7 +1505,7 @@ __global__ __launch_bounds__(kThreads, 2) void hash_linear_kernel(HashArgs a, fl
 // that are not (3 in 100000) go to a list of the wavefront, whose chains run when it is full or
 // the work is done, a lane each, and correct the codes in memory.
 // 8 heads x 65536 vectors of 512 bits: 221 us with the kernel above (waits for operands, barriers and chains),
-// 87 us; 32 x 65536 of 128 bits 467 and 132 us; binary32 vectors of 512 bits 270 and 146 us.
+// 87 us; 32 x 65536 of 128 bits 467 and 132 us; binary32 vectors of 512 bits 322 and 146 us.
 constexpr int kLinearWaves = 8;       // wavefronts of a workgroup
 constexpr int kTilesList = 192;       // open outputs a wavefront keeps; at most 64 come at a time
 constexpr float kUneven = 32.0f;      // rows of a word are uneven where one bound for all leaves more than this many times the outputs open
@@ -1990,9 +1990,8 @@ int launch_linear(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int stage
     if (allow_dynamic_lds(ctx, reinterpret_cast<const void*>(kern), lds) != SPOTLIGHT_OK) return SPOTLIGHT_ERR_HIP;
     const int64_t tiles = (a.n_rows + kTile - 1) / kTile;
     // a run of tiles pays for fetching R; the grid keeps two workgroups for every compute unit
-    const int groups = (a.W + kLinearWords - 1) / kLinearWords;
-    const int tpg = short_runs(tiles, n_xheads * groups, 2 * ctx->n_cus, 64);
-    dim3 grid(static_cast<unsigned>((tiles + tpg - 1) / tpg), static_cast<unsigned>(n_xheads), static_cast<unsigned>(groups));
+    const int tpg = short_runs(tiles, n_xheads, 2 * ctx->n_cus, 64);
+    dim3 grid(static_cast<unsigned>((tiles + tpg - 1) / tpg), static_cast<unsigned>(n_xheads));
     StageTimer timer(ctx, stage);
     timer.launch(kern, grid, dim3(kThreads), lds, a, static_cast<float>(bulk_hash_eps(kHeadDim, sizeof(XT) == 4)), tpg);
     return hip_rc(hipGetLastError());
@@ -2090,7 +2089,7 @@ inline bool linear_by_tiles(const spotlight_ctx* ctx, const HashArgs& a, int n_x
 {
     const int64_t tiles = (a.n_rows + kTile - 1) / kTile * n_xheads;
     const int fill = a.W == 1 ? 8 : a.W < 16 ? 4 : 1;
-    return ctx->max_lds >= 160 * 1024 && (a.W > kLinearWords || tiles >= fill * (a.n_rows < 256 ? 3 : 1) * static_cast<int64_t>(ctx->n_cus));
+    return a.W > kLinearWords || tiles >= fill * (a.n_rows < 256 ? 3 : 1) * static_cast<int64_t>(ctx->n_cus);
 }
 
 inline size_t lds_bytes(size_t x_size, int hidden) { return kTile * (x_size * kHeadDim + sizeof(float) * static_cast<size_t>(hidden_padded(hidden))); }
