@@ -228,6 +228,37 @@ int main(int argc, char** argv)
 }
 """
 
+TWO_PASSES = r"""
+#include <stdio.h>
+#include <string.h>
+#include "hash_open.h"
+using namespace spotlight;
+int main()
+{
+    int heads, rows, bits, hidden;
+    while (scanf("%d %d %d %d", &heads, &rows, &bits, &hidden) == 4) {
+        spotlight_ctx ctx;
+        memset(&ctx, 0, sizeof(ctx));
+        ctx.n_cus = 256;
+        ctx.max_lds = 160 * 1024;
+        hashdev::HashArgs a;
+        memset(&a, 0, sizeof(a));
+        float scratch;
+        uint32_t open;
+        a.wnorm = &scratch;
+        a.open = &open;
+        a.n_rows = rows; a.hidden = hidden; a.L = bits; a.W = bits / 32;
+        const bool two = screen::applies(&ctx, a, heads);
+        printf("%d %d %d\n", two, two && screen::resident(hidden, a.W), two && screen::open_serves(hidden, a.W));
+        a.open = nullptr;
+        if (screen::applies(&ctx, a, heads)) printf("without room for a bitmap\n");
+        a.open = &open, a.wnorm = nullptr;
+        if (screen::applies(&ctx, a, heads)) printf("with the matrix cores switched off\n");
+    }
+    return 0;
+}
+"""
+
 
 def _program(tmp_path, text, name):
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -289,4 +320,30 @@ def test_routes(tmp_path):
     text = "\n".join(f"{h} {r} {b} {n} 2 {w}" for h, r, b, n, w in routes)
     run = subprocess.run([_program(tmp_path, ROUTES, "routes")], input=text, capture_output=True, text=True, check=True)
     got = dict(zip(routes, map(int, run.stdout.split())))
+    assert got == routes
+
+
+def test_routes_of_two_passes(tmp_path):
+    """(heads, rows, bits, hidden) of bfloat16 vectors and weights -> whether two passes take the call, whether the first holds all weights in
+    LDS, whether hash_open_kernel is the second: the shapes of the GPU tests, whose kernels these decide, and both sides of every line."""
+    routes = {
+        # every kernel of either pass
+        (8, 16400, 32, 16): "1 1 0", (8, 16400, 64, 32): "1 1 0", (8, 16400, 96, 48): "1 1 0", (8, 16400, 128, 128): "1 1 0", (8, 16400, 160, 112): "1 1 0",
+        (8, 16400, 256, 128): "1 1 0", (8, 16400, 64, 144): "1 1 0", (8, 16400, 128, 256): "1 1 0", (8, 16400, 192, 256): "1 0 0", (8, 16400, 160, 288): "1 0 1",
+        (8, 16400, 256, 400): "1 0 1", (8, 16400, 128, 512): "1 0 0", (8, 16400, 256, 512): "1 0 1", (8, 16400, 224, 528): "1 0 0", (8, 16400, 256, 1008): "1 0 0",
+        (8, 16400, 32, 1024): "1 0 0", (8, 16400, 96, 80): "1 1 0", (8, 16384, 160, 272): "1 0 1", (8, 16384, 160, 256): "1 0 0", (8, 16384, 128, 288): "1 1 0", (8, 16384, 128, 304): "1 0 0",
+        # grids of other shapes
+        (1, 131073, 64, 64): "1 1 0", (3, 43700, 64, 64): "1 1 0", (512, 256, 64, 64): "1 1 0", (512, 257, 64, 64): "1 1 0", (300, 511, 64, 64): "1 1 0",
+        (300, 513, 64, 64): "1 1 0", (28, 4703, 64, 64): "1 1 0", (2, 65600, 64, 64): "1 1 0", (2, 65600, 256, 512): "1 0 1", (2, 33000, 256, 512): "1 0 1",
+        (9, 66000, 256, 64): "1 1 0", (66, 2100, 64, 64): "1 1 0", (200, 700, 256, 512): "1 0 1", (1, 70000, 64, 64): "1 1 0", (1024, 4133, 32, 1024): "1 0 0",
+        (1024, 4133, 256, 512): "1 0 1", (512, 256, 32, 1024): "1 0 0",
+        # eight tiles for every compute unit, a round of a workgroup
+        (1, 65505, 64, 64): "1 1 0", (1, 65504, 64, 64): "0 0 0", (512, 255, 64, 64): "0 0 0", (255, 256, 64, 64): "0 0 0", (256, 256, 64, 64): "1 1 0",
+        # networks
+        (8, 16400, 288, 256): "0 0 0", (8, 16400, 128, 264): "0 0 0", (8, 16400, 128, 1040): "0 0 0", (8, 16400, 512, 0): "0 0 0", (8, 16400, 32, 8): "0 0 0",
+    }
+    text = "\n".join(" ".join(map(str, r)) for r in routes)
+    run = subprocess.run([_program(tmp_path, TWO_PASSES, "two_passes")], input=text, capture_output=True, text=True, check=True)
+    got = dict(zip(routes, run.stdout.strip().split("\n")))
+    assert len(run.stdout.strip().split("\n")) == len(routes), run.stdout
     assert got == routes
