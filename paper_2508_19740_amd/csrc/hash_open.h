@@ -1,8 +1,9 @@
-// Bulk hashing, second pass, for hidden layers of 288 to 512 units: the keys that the first pass (hash_screen.h) left open.
+// Bulk hashing, second pass, for hidden layers of 272 to 512 units and codes of 160 to 256 bits: the keys that the first pass
+// (hash_screen.h) left open.
 //
 // The same work as hash_cert_kernel: layer 1 with the chain on the binary32 matrix instruction, layer 2 on the
 // bfloat16 one with the bound, what that leaves open with the chain.  Eight wavefronts, one workgroup on a compute unit
-// (its LDS holds the activations three times, as there: 145 KB).  The weights of layer 1 stay in registers, those of layer 2
+// (its LDS holds the activations three times, as there: 154 KB at 512 units).  The weights of layer 1 stay in registers, those of layer 2
 // come from the first pass's copy, in operand order, eight steps ahead: hash_bulk_kernel, which this replaces, read
 // them a row per lane a step ahead, split all activations in every wavefront, and waited two thirds of its time.
 // Rows = the outputs of a word and columns = keys, as in the first pass, so that a lane has the signs of one key.  Half of the
