@@ -455,7 +455,8 @@ __global__ __launch_bounds__(kWaves * 64, 2) void hash_screen_kernel(HashArgs a,
         const float dh = u * ((slope < steepest ? slope : steepest) * xn + 1.1f * sums + 12.0f * hn + 2.0f * an);
         auto own_bound = [&](int w, int v) { const RowScale& r = rows[w * 32 + 16 * half + v]; return 1.002f * (r.s2 * (hn + dh) + r.w2 * dh); };
         // signs, and the distance of the nearest output from zero
-        uint32_t code[WM], near = 0;   // bit w: word w is not settled by its own bound
+        uint32_t code[WM];
+        bool sure = true;
 #pragma unroll
         for (int w = 0; w < WM; ++w) {
             if (w >= W) continue;
@@ -467,26 +468,25 @@ __global__ __launch_bounds__(kWaves * 64, 2) void hash_screen_kernel(HashArgs a,
                 nearest = fminf(nearest, __builtin_fabsf(y[w][v]));
             }
             const float bound = 1.002f * (ws[w].s2 * (hn + dh) + ws[w].w2 * dh);
-            near |= nearest >= bound && bound < 1e25f ? 0u : 1u << w;
+            sure = sure && nearest >= bound && bound < 1e25f;
             code[w] = ~s & 0xffffu;   // a settled output is no zero
             if (tile * TK + c < a.n_rows) record(xhead, tile * TK + c, w, half, y[w], [&](int v) { return ws[w].uneven ? own_bound(w, v) : bound; });
         }
-        if (uneven) {   // each output and the bound of its own row (behind all words: a branch in each, 8 heads x 131072, 128 -> 512 -> 256, 787 us, so 762;
-                        // 32 x 131072, 128 -> 256 -> 128, 926 and 914)
+        // each output and the bound of its own row (behind all words: a branch in each, 8 heads x 131072, 128 -> 512 -> 256, 787 us, so 762;
+        // 32 x 131072, 128 -> 256 -> 128, 926 and 914)
+        if (uneven && __ballot(!sure)) {
+            sure = true;
 #pragma unroll
             for (int w = 0; w < WM; ++w) {
-                if (w >= W || !ws[w].uneven || !__ballot((near >> w) & 1)) continue;
-                bool far = true;
+                if (w >= W) continue;
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
                     const float b = own_bound(w, v);
-                    far = far && __builtin_fabsf(y[w][v]) >= b && b < 1e25f;
+                    sure = sure && __builtin_fabsf(y[w][v]) >= b && b < 1e25f;
                     if (v % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // (registers)
                 }
-                near = far ? near & ~(1u << w) : near | 1u << w;
             }
         }
-        const bool sure = near == 0;
         uint32_t open = sure || nothing ? 0u : 1u;
         open |= other_half(open);
         const bool mine = half == 0 && tile * TK + c < a.n_rows;
