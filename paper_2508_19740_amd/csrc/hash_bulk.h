@@ -313,6 +313,15 @@ struct OpenJob {
 };
 constexpr int kOpenBalanced = 256;    // segments that a wavefront shares out; with more, or few slots for each, none runs on for long
 
+// Whether the first pass counts them and the second shares them out.  Counts take 3 to 5 us; small calls of narrow layers are over before an uneven share
+// costs that.  Without and with: 100 heads x 700, 128 -> 64 -> 32 29.5 and 31.6 us, 40 x 1800, 128 -> 16 -> 32 27 and 31; 64 x 1024, 128 -> 256 -> 128 65.5 and 61.5,
+// one head open for all keys 215 and 91; 8 x 8192, 128 -> 128 -> 64 35.7 and 34.9; 28 x 4703, 128 -> 64 -> 64 38.2 and 37.4, one head 160 and 48.
+inline bool counts_open_rows(const HashArgs& a, int n_xheads, int n_cus)
+{
+    const int64_t tiles = (a.n_rows + kTile - 1) / kTile * n_xheads;
+    return segments_of(a) * n_xheads <= kOpenBalanced && tiles * a.hidden > 800 * static_cast<int64_t>(n_cus);
+}
+
 // Of `n` segments, `per_head` of every head, the one that workgroup blockIdx.x of gridDim.x has, and its share there.
 __device__ __forceinline__ void share_segments(OpenRows& list, const uint32_t* counts, int n, int per_head, int lane)
 {
@@ -2044,7 +2053,7 @@ struct OpenGrid {
 inline OpenGrid open_grid(const HashArgs& a, int n_xheads, int slots)
 {
     const int64_t segments = segments_of(a), all = segments * n_xheads;
-    if (all <= kOpenBalanced && 2 * all <= slots) return {dim3(static_cast<unsigned>(slots)), -n_xheads};
+    if (a.open_counts && 2 * all <= slots) return {dim3(static_cast<unsigned>(slots)), -n_xheads};
     const int parts = open_parts(all, slots);
     return {dim3(static_cast<unsigned>(segments * parts), static_cast<unsigned>(n_xheads)), parts};
 }
@@ -2073,8 +2082,8 @@ int launch_word_open(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int st
     auto kern = hash_cert_kernel<T, NW, NUB, WREG, false, true>;
     if (allow_dynamic_lds(ctx, reinterpret_cast<const void*>(kern), lds) != SPOTLIGHT_OK) return SPOTLIGHT_ERR_HIP;
     // narrow layers leave room for a third workgroup: 8 heads x 65536 keys, all open, 128 -> 64 -> 64 646 us with two, 470 with three, 128 -> 128 -> 64 940 and
-    // 770; random keys 20 and 19, 32 and 27
-    const OpenGrid g = open_grid(a, n_xheads, ctx->n_cus * resident(ctx, NUB == 1 ? 3 : 2, lds));
+    // 770; random keys 20 and 19, 32 and 27.  More segments than are shared out by their open rows have few tiles each: 512 heads x 257, 128 -> 64 -> 32, the call 39 and 47
+    const OpenGrid g = open_grid(a, n_xheads, ctx->n_cus * resident(ctx, NUB == 1 && a.open_counts ? 3 : 2, lds));
     StageTimer timer(ctx, stage);
     timer.launch(kern, g.grid, dim3(NW * 64), lds, a, static_cast<float>(bulk_hash_eps(a.hidden, true)), g.run, static_cast<int>(open_at));
     return hip_rc(hipGetLastError());

@@ -310,7 +310,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void hash_screen_kernel(HashArgs a,
     int seg = seg0, n_opened = 0;
     if (tid < kNear) opened[tid] = 0;
     auto count_opened = [&]() {
-        if (lane != 0 || n_opened == 0) return;
+        if (lane != 0 || n_opened == 0 || !a.open_counts) return;
         if (seg - seg0 < kNear) atomicAdd(opened + (seg - seg0), static_cast<uint32_t>(n_opened));
         else atomicAdd(a.open_counts + (xhead * segments + seg) * bulk::kCountStride, static_cast<uint32_t>(n_opened));
     };
@@ -356,7 +356,8 @@ __global__ __launch_bounds__(kWaves * 64, 2) void hash_screen_kernel(HashArgs a,
     }
     static_assert(kWords * 32 <= NT, "one record a thread");
     uint32_t uneven = 0;
-    for (int w = 0; w < W; ++w) uneven |= ws[w].uneven;
+#pragma unroll
+    for (int w = 0; w < WM; ++w) uneven |= ws[min(w, W - 1)].uneven;
     if (uneven && tid < W * 32) rows[tid] = row_scales(scales, a.n_wheads, whead, W)[tid];
     const float t1 = ls->t1, t1_max = ls->t1_max, bn = ls->b1;
     const bool no_bias = ls->no_bias != 0;
@@ -555,6 +556,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void hash_screen_kernel(HashArgs a,
         ca = ca_next;
         next_step();
     }
+    if (!a.open_counts) return;
     count_opened();
     __syncthreads();
     if (tid < kNear && opened[tid] != 0) atomicAdd(a.open_counts + (xhead * segments + seg0 + tid) * bulk::kCountStride, opened[tid]);
@@ -614,7 +616,7 @@ int launch(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int stage, Recor
     StageTimer timer(ctx, stage, true);
     timer.launch(scales_kernel<8>, dim3(static_cast<unsigned>(a.n_wheads), static_cast<unsigned>(1 + a.W + (n_operands + kPerBlock - 1) / kPerBlock)), dim3(kThreads), 0,
                  static_cast<const bf16_raw*>(a.w1), static_cast<const bf16_raw*>(a.b1), static_cast<const bf16_raw*>(a.w2), scales,
-                 static_cast<uint4*>(a.operands), a.open_counts, static_cast<int>(bulk::segments_of(a) * n_xheads), a.hidden, a.L);
+                 static_cast<uint4*>(a.operands), a.open_counts, a.open_counts ? static_cast<int>(bulk::segments_of(a) * n_xheads) : 0, a.hidden, a.L);
     if (hipGetLastError() != hipSuccess) return SPOTLIGHT_ERR_HIP;
     if (a.W <= 2) return launch_words<2>(ctx, a, scales, n_xheads, stage, record);
     if (a.W <= 4) return launch_words<4>(ctx, a, scales, n_xheads, stage, record);

@@ -16,8 +16,10 @@ size_t screen_scale_bytes(int heads, int W) { return screen::scale_bytes(heads, 
 
 bool screened_hash_applies(const spotlight_ctx* ctx, const HashArgs& a, int n_xheads) { return screen::applies(ctx, a, n_xheads); }
 
-int run_screened_hash(spotlight_ctx* ctx, const HashArgs& a, int n_xheads, int stage)
+int run_screened_hash(spotlight_ctx* ctx, const HashArgs& job, int n_xheads, int stage)
 {
+    HashArgs a = job;
+    if (!bulk::counts_open_rows(a, n_xheads, ctx->n_cus)) a.open_counts = nullptr;
     const int rc = screen::launch(ctx, a, n_xheads, stage);
     if (rc != SPOTLIGHT_OK) return rc;
     if (!a.audit && screen::open_serves(a.hidden, a.W)) return screen::launch_open(ctx, a, n_xheads, stage);

@@ -249,6 +249,13 @@ int main()
         a.open = &open;
         a.n_rows = rows; a.hidden = hidden; a.L = bits; a.W = bits / 32;
         const bool two = screen::applies(&ctx, a, heads);
+        uint32_t counts;
+        a.open_counts = two && bulk::counts_open_rows(a, heads, ctx.n_cus) ? &counts : nullptr;
+        for (int slots : {256, 512, 768}) {     // shared out by count, or the same number of workgroups for every segment
+            const bulk::OpenGrid g = bulk::open_grid(a, heads, slots);
+            const long segments = (rows + 65535) / 65536;
+            if (a.open_counts && 2 * segments * heads <= slots ? g.run != -heads || (int)g.grid.x != slots : g.run < 1 || g.grid.x != segments * g.run || (int)g.grid.y != heads) { printf("grid\n"); return 1; }
+        }
         printf("%d %d %d\n", two, two && screen::resident(hidden, a.W), two && screen::open_serves(hidden, a.W));
         a.open = nullptr;
         if (screen::applies(&ctx, a, heads)) printf("without room for a bitmap\n");
