@@ -303,7 +303,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void hash_screen_kernel(HashArgs a,
     const int64_t n_tiles = (a.n_rows + TK - 1) / TK, tile0 = static_cast<int64_t>(blockIdx.x) * rounds * kWaves;
     const int64_t segments = bulk::segments_of(a);
     RowScale* rows = reinterpret_cast<RowScale*>(ops + (RESIDENT ? nub : 2) * OPS * 64);   // [W][32]
-    // open rows: each wavefront counts its own, the workgroup adds those of the first segments up in LDS and then to the segments' counts
+    // open rows, where the second pass is shared out by them: each wavefront counts its own, the workgroup adds those of the first segments up in LDS and then to the segments' counts
     // (an addition in memory for every tile: 8 heads x 65536, 128 -> 256 -> 128, both passes, 334 us; so 235)
     uint32_t* opened = reinterpret_cast<uint32_t*>(rows + W * 32);
     const int seg0 = static_cast<int>(tile0 / (bulk::kOpenSegment / TK));
@@ -605,7 +605,17 @@ inline bool applies(const spotlight_ctx* ctx, const HashArgs& a, int n_xheads)
 {
     if (!a.open || !a.wnorm || !serves(a.hidden, a.W) || ctx->max_lds < 160 * 1024) return false;
     const int64_t tiles = (a.n_rows + bulk::kTile - 1) / bulk::kTile * n_xheads;
-    return a.n_rows >= bulk::kTile * kWaves && tiles >= 8 * static_cast<int64_t>(ctx->n_cus);
+    if (a.n_rows < bulk::kTile * kWaves || tiles < 8 * static_cast<int64_t>(ctx->n_cus)) return false;
+    if (a.W <= 4 || resident(a.hidden, a.W)) return true;
+    // Codes of more than 128 bits whose weights do not fit into LDS gain least, so they need rounds of the first pass that are filled: by the heads, and by
+    // the tiles of a head.  256 -> 256, one pass and two: 300 heads x 257 174 and 240 us, 257 x 288 164 and 227, 256 x 300 145 and 162, 300 x 384 228 and
+    // 252; 200 x 352 152 and 137, 257 x 511 269 and 244.  512 -> 256: 300 x 257 377 and 433, 257 x 288 354 and 482; 300 x 384 492 and 473, 228 x 257 311 and 264.
+    const int64_t all_rounds = (a.n_rows + bulk::kTile * kWaves - 1) / (bulk::kTile * kWaves);
+    const int rounds = bulk::rounds_of(all_rounds, n_xheads, ctx->n_cus);
+    const int64_t groups = (all_rounds + rounds - 1) / rounds * n_xheads;
+    const int64_t room = (groups + ctx->n_cus - 1) / ctx->n_cus * rounds * ctx->n_cus * kWaves;   // tiles there would be time for
+    if (a.hidden > 256) return 20 * tiles >= 7 * room;
+    return 2 * tiles >= room && 3 * tiles >= 2 * all_rounds * kWaves * n_xheads;
 }
 
 template <typename Record = NoRecord>

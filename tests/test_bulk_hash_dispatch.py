@@ -346,6 +346,10 @@ def test_routes_of_two_passes(tmp_path):
         (1024, 4133, 256, 512): "1 0 1", (512, 256, 32, 1024): "1 0 0",
         # eight tiles for every compute unit, a round of a workgroup
         (1, 65505, 64, 64): "1 1 0", (1, 65504, 64, 64): "0 0 0", (512, 255, 64, 64): "0 0 0", (255, 256, 64, 64): "0 0 0", (256, 256, 64, 64): "1 1 0",
+        # long codes, weights not in LDS: rounds of the first pass that are half empty
+        (300, 257, 256, 256): "0 0 0", (257, 288, 256, 256): "0 0 0", (256, 300, 256, 256): "0 0 0", (300, 384, 256, 256): "0 0 0", (200, 352, 256, 256): "1 0 0",
+        (257, 511, 256, 256): "1 0 0", (300, 257, 256, 512): "0 0 0", (300, 384, 256, 512): "1 0 1", (228, 257, 256, 512): "1 0 1", (300, 257, 160, 1024): "0 0 0",
+        (300, 257, 128, 256): "1 1 0", (300, 257, 128, 512): "1 0 0", (300, 257, 256, 128): "1 1 0",
         # networks
         (8, 16400, 288, 256): "0 0 0", (8, 16400, 128, 264): "0 0 0", (8, 16400, 128, 1040): "0 0 0", (8, 16400, 512, 0): "0 0 0", (8, 16400, 32, 8): "0 0 0",
     }
